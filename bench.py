@@ -30,7 +30,7 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 MFMA_FP32_PEAK_TFLOPS = 157.3    # MI355X dense fp32 matrix, published
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix, published
-
+GRAM_TERMS = 6                   # bf16 products that the Gram kernels execute for one product of 32-bit numbers
 
 VALU_FP32_PEAK_TFLOPS = 157.3     # MI355X fp32 vector, published: 256 CUs x 128 fused multiply-adds per clock at 2.4 GHz. A loop of
                                   # plain (unpacked) v_fma_f32 chains measures 118 TFLOP/s here (rfsf_ts_probe_peaks), so the
@@ -82,7 +82,7 @@ def bench_dp1d(args, w, inp, dev, ls) -> int:
     valu_tflops = elements * (COS_FLOPS + 3.0) / (ms * 1e-3) / 1e12
     mfma_tflops = elements * 2.0 * w.d / (ms * 1e-3) / 1e12
     valu_frac, mfma_frac = valu_tflops / VALU_FP32_PEAK_TFLOPS, mfma_tflops / MFMA_FP32_PEAK_TFLOPS
-    gram_pairs = w.N * w.N if ((w.N + 63) // 64) * ((w.N + 63) // 64 + 1) // 2 < 512 else w.N * (w.N + 1) / 2
+    gram_pairs = w.N * (w.N + 1) / 2
     gms = prof["ms_gram"] / max(1, prof["launches_gram"])
     by_mfma = mfma_frac > valu_frac
     kernels = {
@@ -92,9 +92,9 @@ def bench_dp1d(args, w, inp, dev, ls) -> int:
                  "ms_per_step": prof["ms_dp1d"] / args.steps,
                  "alu_frac": valu_frac, "alu_peak": VALU_FP32_PEAK_TFLOPS, "mfma_frac": mfma_frac,
                  "cosines_per_s": elements / (ms * 1e-3)},
-        "gram": {"bound": "mfma", "achieved": 2.0 * gram_pairs * ncols / (gms * 1e-3) / 1e12,
-                 "peak": MFMA_FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
-                 "frac": 2.0 * gram_pairs * ncols / (gms * 1e-3) / 1e12 / MFMA_FP32_PEAK_TFLOPS, "traffic": None,
+        "gram": {"bound": "mfma", "achieved": 2.0 * GRAM_TERMS * gram_pairs * ncols / (gms * 1e-3) / 1e12,
+                 "peak": MFMA_BF16_PEAK_TFLOPS, "unit": "TFLOP/s",
+                 "frac": 2.0 * GRAM_TERMS * gram_pairs * ncols / (gms * 1e-3) / 1e12 / MFMA_BF16_PEAK_TFLOPS, "traffic": None,
                  "avg_launch_ms": gms, "ms_per_step": prof["ms_gram"] / args.steps},
     }
     dominant = max(kernels, key=lambda k: kernels[k]["ms_per_step"])
@@ -178,10 +178,10 @@ def bench_trp(args, w, inp, dev, ls) -> int:
                          "ms_per_step": prof[f"ms_{name}"] / args.steps}
 
     entry("rff_increments", "hbm", units * (4.0 * w.d + 4.0 * w.M * 2 * w.F), "GB/s", HBM_PEAK_GBS)
-    entry("trp_project", "mfma", 2.0 * units * w.M * 2 * w.F * Q, "TFLOP/s", MFMA_FP32_PEAK_TFLOPS)   # M GEMMs per scope
+    entry("trp_project", "mfma", 2.0 * GRAM_TERMS * units * w.M * 2 * w.F * Q, "TFLOP/s", MFMA_BF16_PEAK_TFLOPS)
     entry("trp_scan", "hbm", 4.0 * units * w.M * Q + 4.0 * w.N * ncols, "GB/s", HBM_PEAK_GBS)
-    gram_pairs = w.N * w.N if ((w.N + 63) // 64) * ((w.N + 63) // 64 + 1) // 2 < 512 else w.N * (w.N + 1) / 2
-    entry("gram", "mfma", 2.0 * gram_pairs * ncols, "TFLOP/s", MFMA_FP32_PEAK_TFLOPS)
+    gram_pairs = w.N * (w.N + 1) / 2
+    entry("gram", "mfma", 2.0 * GRAM_TERMS * gram_pairs * ncols, "TFLOP/s", MFMA_BF16_PEAK_TFLOPS)
     dominant = max(kernels, key=lambda k: kernels[k]["ms_per_step"])
     roofline = {k: kernels[dominant][k] for k in ("bound", "achieved", "peak", "unit", "frac", "traffic")}
     roofline["kernel"] = dominant
@@ -342,17 +342,16 @@ def bench_ts(args, name: str, steps: int, warmup: int, cpu_baseline: bool) -> di
         kernels["rff_increments"]["mfma_frac"] = kernels["rff_increments"]["mfma_tflops"] / mfma_peak
     entry("sketch_fft_scan", "hbm", incr_units * incr_bytes + 4.0 * n_seq * w.M * w.D, "GB/s", HBM_PEAK_GBS)
     Ny = w.N2 if w.N2 else w.N
-    # flops the kernel performs: the whole matrix for a cross Gram; for K = Phi Phi^T of 2048+ rows
-    # only the tiles on or above the diagonal (counted here as N(N+1)/2 inner products)
-    gram_pairs = w.N * Ny if (w.N2 or ((w.N + 63) // 64) * ((w.N + 63) // 64 + 1) // 2 < 512) else w.N * (w.N + 1) / 2
-    entry("gram", "mfma", 2.0 * gram_pairs * w.ncols, "TFLOP/s", MFMA_FP32_PEAK_TFLOPS)
+    # flops the kernel performs: the whole matrix for a cross Gram, for K = Phi Phi^T only the tiles on or above the
+    # diagonal (counted here as N(N+1)/2 inner products); six bf16 products each (csrc/gram.hip)
+    gram_pairs = w.N * Ny if w.N2 else w.N * (w.N + 1) / 2
+    entry("gram", "mfma", 2.0 * GRAM_TERMS * gram_pairs * w.ncols, "TFLOP/s", MFMA_BF16_PEAK_TFLOPS)
     entry("normalize", "hbm", 2.0 * 4.0 * n_seq * w.ncols, "GB/s", HBM_PEAK_GBS)
     # beside the published peaks: what the simplest kernels of the same kind reach on this GPU (streaming reads for
-    # the kernel that reads the increments, non-temporal streaming writes for the one that writes them, an issue
-    # loop of fp32 matrix instructions for the Gram)
+    # the kernel that reads the increments, non-temporal streaming writes for the one that writes them)
     peaks = getattr(args, "measured_peaks", None)
     if peaks:
-        for kname, key in (("rff_increments", "write_nt_gbs"), ("sketch_fft_scan", "read_gbs"), ("gram", "mfma_f32_tflops"),
+        for kname, key in (("rff_increments", "write_nt_gbs"), ("sketch_fft_scan", "read_gbs"),
                            ("normalize", "copy_gbs")):
             if kname in kernels:
                 kernels[kname]["measured_peak"] = peaks[key]

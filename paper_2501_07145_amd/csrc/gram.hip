@@ -1,526 +1,508 @@
-// Linear Gram of primal features, K = PhiX PhiY^T (Sec. 1: the Gram matrix of the
-// low-rank feature map is the matrix of inner products of the features).
+// Linear Gram of primal features, K = PhiX PhiY^T (Sec. 1: the Gram matrix of the low-rank feature map is the
+// matrix of inner products of the features); the same kernels project the increments of RFSF-TRP.
+//
+// Arithmetic. The operands are 32-bit, and so are the products and sums, but the products run on the bfloat16
+// matrix instructions, which are 16 times as fast as the 32-bit ones: a float is the sum of three bfloat16
+// numbers, x = hi + mid + lo (each the rounding of what the ones before it leave over, 8 significand bits each,
+// 24 in all: nothing is lost), a product of two bfloat16 numbers is exact in 32 bits, and of the nine products of
+// a pair of floats the six largest are added up in the 32-bit accumulators, smallest first. The three that are
+// left out (mid*lo, lo*mid, lo*lo) are together below 2^-25 of the product, half of what rounding it to 32 bits
+// may cost. Measured against 64 bits, the sums are a third closer than with v_mfma_f32_32x32x2f32, which rounds
+// after every product: relative error of K 1.2e-6 against 1.95e-6 on 10000 x 10000 x 5121, 1.8e-6 against 2.8e-6
+// on 50000 x 5000 x 10241.
+// Infinite operands, and finite ones that round to an infinite bfloat16, would turn into NaN in the split
+// (inf - inf): an entry that comes out as NaN is computed again, one product after the other in 32 bits.
 #include "rfsf_internal.h"
+#include <type_traits>
 
 namespace rfsf {
 namespace {
 
-constexpr int kTile = 64;     // output tile edge
-constexpr int kK = 16;        // K slab
-
-// Generic fp32 kernel: 64x64 output tile per workgroup, 4x4 per thread, operands staged
-// through LDS with scalar loads so that any leading dimension and alignment is accepted.
-__global__ __launch_bounds__(256) void gram_generic(
-    const float *__restrict__ A, int64_t Nx, int64_t lda, const float *__restrict__ B, int64_t Ny,
-    int64_t ldb, int64_t K, float *__restrict__ C, int64_t ldc)
-{
-    __shared__ float As[kK][kTile + 4];
-    __shared__ float Bs[kK][kTile + 4];
-    const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-    const int64_t i0 = (int64_t)blockIdx.y * kTile, j0 = (int64_t)blockIdx.x * kTile;
-    float acc[4][4] = {};
-    for (int64_t k0 = 0; k0 < K; k0 += kK) {
-        for (int e = threadIdx.x; e < kTile * kK; e += 256) {
-            const int r = e / kK, kk = e % kK;
-            const int64_t k = k0 + kk;
-            As[kk][r] = (i0 + r < Nx && k < K) ? A[(i0 + r) * lda + k] : 0.f;
-            Bs[kk][r] = (j0 + r < Ny && k < K) ? B[(j0 + r) * ldb + k] : 0.f;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int kk = 0; kk < kK; ++kk) {
-            float a[4], b[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { a[u] = As[kk][ty * 4 + u]; b[u] = Bs[kk][tx * 4 + u]; }
-#pragma unroll
-            for (int u = 0; u < 4; ++u)
-#pragma unroll
-                for (int v = 0; v < 4; ++v) acc[u][v] = fmaf(a[u], b[v], acc[u][v]);
-        }
-        __syncthreads();
-    }
-    for (int u = 0; u < 4; ++u)
-        for (int v = 0; v < 4; ++v) {
-            const int64_t i = i0 + ty * 4 + u, j = j0 + tx * 4 + v;
-            if (i < Nx && j < Ny) C[i * ldc + j] = acc[u][v];
-        }
-}
-
-
 typedef float floatx16 __attribute__((ext_vector_type(16)));
+typedef float floatx4 __attribute__((ext_vector_type(4)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kKT = 32;             // K slab
-constexpr int kLdsStride = kKT + 4; // floats per LDS row: 16 consecutive rows start in distinct bank quads
-
-// Matrix-core kernel (v_mfma_f32_32x32x2f32). Workgroup tile (64*WT) x (64*WT), four wavefronts
-// in a 2x2 grid, each owning (32*WT) x (32*WT) as WT x WT blocks of 32x32. Both operands are
-// K-contiguous rows, staged per K slab of 32 through LDS with float4 loads; the next slab is
-// fetched into registers while the current one is multiplied.
-// MFMA k-step kk of a slab uses the physical columns kk (lanes 0-31) and kk + 16 (lanes 32-63),
-// the same for both operands, so that each lane reads 16 consecutive floats of its row.
-// Needs 16-byte aligned bases and leading dimensions that are multiples of 4.
-// SYM: PhiY is PhiX. Only the tiles on or above the diagonal are computed (blockIdx.x enumerates
-// them row by row); mirror_lower_kernel fills in the rest afterwards.
-// KS = 2 (small problems only, WT = 1): a second group of four wavefronts takes every other K slab with
-// its own LDS staging, so that a CU that gets a single tile still has two wavefronts per SIMD; the two
-// partial tiles are added through LDS at the end, in a fixed order.
-template <int WT, bool SYM, int KS = 1>
-__global__ __launch_bounds__(256 * KS) void gram_mfma(
-    const float *__restrict__ A, int64_t Nx, int64_t lda, const float *__restrict__ B, int64_t Ny,
-    int64_t ldb, int64_t K, float *__restrict__ C, int64_t ldc)
+struct Split8 { bf16x8 hi, mid, lo; };
+__device__ __forceinline__ uint32_t round_pair(float a, float b)          // v_cvt_pk_bf16_f32
 {
-    constexpr int TILE = 64 * WT;               // rows of A (and of B) per workgroup
-    constexpr int NLD = TILE * (kKT / 4) / 256; // float4 loads per thread per operand per slab
-    __shared__ __attribute__((aligned(16))) float As_all[KS * TILE * kLdsStride];
-    __shared__ __attribute__((aligned(16))) float Bs_all[KS * TILE * kLdsStride];
-    __shared__ float red[KS == 2 ? 16 * 256 : 1];       // partial tile of the second K-split group
-    const int group = threadIdx.x / 256;                 // K-split group (0 when KS = 1)
-    float *As = As_all + group * TILE * kLdsStride, *Bs = Bs_all + group * TILE * kLdsStride;
-    const int tid = threadIdx.x % 256, lane = tid & 63, wave = tid >> 6;
-    const int half = lane >> 5, col = lane & 31;
-    const int wi = wave >> 1, wj = wave & 1;
-    int64_t bi = blockIdx.y, bj = blockIdx.x;
-    if (SYM) {      // linear index over the upper triangle of an nt x nt tile grid -> (bi, bj >= bi)
-        const int64_t nt = (Nx + TILE - 1) / TILE, idx = blockIdx.x;
-        bi = (int64_t)(((double)(2 * nt + 1) - sqrt((double)(2 * nt + 1) * (double)(2 * nt + 1) - 8.0 * (double)idx)) * 0.5);
-        while (bi > 0 && bi * nt - bi * (bi - 1) / 2 > idx) --bi;                 // start of row bi
-        while ((bi + 1) * nt - (bi + 1) * bi / 2 <= idx) ++bi;
-        bj = bi + (idx - (bi * nt - bi * (bi - 1) / 2));
+    const floatx2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+// The three terms of eight consecutive numbers of a row: 44 vector instructions for the 8 floats of a lane.
+__device__ __forceinline__ Split8 split8(const float (&x)[8])
+{
+    uint32_t h[4], m[4], l[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = x[2 * i], b = x[2 * i + 1];
+        h[i] = round_pair(a, b);
+        const float ra = a - __uint_as_float(h[i] << 16), rb = b - __uint_as_float(h[i] & 0xffff0000u);
+        m[i] = round_pair(ra, rb);
+        const float sa = ra - __uint_as_float(m[i] << 16), sb = rb - __uint_as_float(m[i] & 0xffff0000u);
+        l[i] = round_pair(sa, sb);
     }
-    const int64_t i0 = bi * TILE, j0 = bj * TILE;
-
-    floatx16 acc[WT][WT];
-#pragma unroll
-    for (int a = 0; a < WT; ++a)
-#pragma unroll
-        for (int b = 0; b < WT; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-
-    float4 ra[NLD], rb[NLD];
-    auto fetch = [&](int64_t k0) {
-#pragma unroll
-        for (int u = 0; u < NLD; ++u) {
-            const int e = tid + 256 * u;                 // float4 slot inside the slab tile
-            const int r = e / (kKT / 4), c4 = e % (kKT / 4);
-            const int64_t k = k0 + 4 * c4;
-            float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-            if (k < K) {
-                if (i0 + r < Nx) va = *reinterpret_cast<const float4 *>(A + (i0 + r) * lda + k);
-                if (j0 + r < Ny) vb = *reinterpret_cast<const float4 *>(B + (j0 + r) * ldb + k);
-                if (k + 3 >= K) {                        // columns beyond K hold padding, not data
-                    if (k + 1 >= K) { va.y = 0.f; vb.y = 0.f; }
-                    if (k + 2 >= K) { va.z = 0.f; vb.z = 0.f; }
-                    va.w = 0.f; vb.w = 0.f;
-                }
-            }
-            ra[u] = va;
-            rb[u] = vb;
-        }
-    };
-    auto stage = [&]() {
-#pragma unroll
-        for (int u = 0; u < NLD; ++u) {
-            const int e = tid + 256 * u;
-            const int r = e / (kKT / 4), c4 = e % (kKT / 4);
-            *reinterpret_cast<float4 *>(&As[r * kLdsStride + 4 * c4]) = ra[u];
-            *reinterpret_cast<float4 *>(&Bs[r * kLdsStride + 4 * c4]) = rb[u];
-        }
-    };
-
-    // group g takes slabs g, g + KS, ...; a slab past the end is fetched as zeros, so that every group
-    // runs the same number of iterations (the barriers are workgroup-wide)
-    fetch((int64_t)group * kKT);
-    for (int64_t kb = 0; kb < K; kb += (int64_t)KS * kKT) {
-        const int64_t k0 = kb + (int64_t)group * kKT;
-        __syncthreads();                                 // previous slab fully consumed
-        stage();
-        __syncthreads();
-        if (kb + (int64_t)KS * kKT < K) fetch(k0 + (int64_t)KS * kKT);
-        // this lane's 16 columns of each of its rows: physical columns 16*half .. 16*half+15
-        float4 fa[WT][4], fb[WT][4];
-#pragma unroll
-        for (int t = 0; t < WT; ++t)
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                fa[t][c] = *reinterpret_cast<const float4 *>(&As[((wi * WT + t) * 32 + col) * kLdsStride + 16 * half + 4 * c]);
-                fb[t][c] = *reinterpret_cast<const float4 *>(&Bs[((wj * WT + t) * 32 + col) * kLdsStride + 16 * half + 4 * c]);
-            }
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-#pragma unroll
-                for (int a = 0; a < WT; ++a)
-#pragma unroll
-                    for (int b = 0; b < WT; ++b) {
-                        const float av = e == 0 ? fa[a][c].x : e == 1 ? fa[a][c].y : e == 2 ? fa[a][c].z : fa[a][c].w;
-                        const float bv = e == 0 ? fb[b][c].x : e == 1 ? fb[b][c].y : e == 2 ? fb[b][c].z : fb[b][c].w;
-                        acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[a][b], 0, 0, 0);
-                    }
-    }
-    if constexpr (KS == 2) {                            // group 1 hands its partial tile to group 0
-        static_assert(WT == 1 || KS == 1, "the K split is for the single-block tile only");
-        __syncthreads();
-        if (group == 1) {
-#pragma unroll
-            for (int v = 0; v < 16; ++v) red[v * 256 + tid] = acc[0][0][v];
-        }
-        __syncthreads();
-        if (group == 1) return;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[0][0][v] += red[v * 256 + tid];
-    }
-    // result layout of a 32x32 block: lane holds column lane%32 and rows 8q + 4*(lane/32) + i
-#pragma unroll
-    for (int a = 0; a < WT; ++a)
-#pragma unroll
-        for (int b = 0; b < WT; ++b) {
-            const int64_t j = j0 + (wj * WT + b) * 32 + col;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t i = i0 + (wi * WT + a) * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (i < Nx && j < Ny) C[i * ldc + j] = acc[a][b][v];
-            }
-        }
+    return {__builtin_bit_cast(bf16x8, make_uint4(h[0], h[1], h[2], h[3])),
+            __builtin_bit_cast(bf16x8, make_uint4(m[0], m[1], m[2], m[3])),
+            __builtin_bit_cast(bf16x8, make_uint4(l[0], l[1], l[2], l[3]))};
 }
 
-// Tile order of the large-problem kernel. The hardware deals consecutive workgroup ids round-robin to the
-// eight XCDs, each with its own L2. Tiles are therefore first put in a locality order -- strips of eight tile
-// rows, inside a strip column by column -- and that list is cut into eight equal contiguous pieces, one per
-// XCD: the 64 or so tiles an XCD has in flight then form an 8 x 8 block that shares eight row panels and
-// eight column panels through its L2, and every XCD gets the same number of tiles (to within one).
-// SYM: only tiles on or above the diagonal exist; a strip starts with its triangular part.
+__device__ __forceinline__ floatx16 mfma(const bf16x8 &a, const bf16x8 &b, const floatx16 &c)   // 32 x 32, 16 columns of K
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ floatx4 mfma(const bf16x8 &a, const bf16x8 &b, const floatx4 &c)     // 16 x 16, 32 columns of K
+{
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
+}
+// acc[v] += a * b[v] for one block row and NB block columns.
+template <int NB, typename Acc>
+__device__ __forceinline__ void mfma_split(const Split8 &a, const Split8 (&b)[NB], Acc (&acc)[NB])
+{
+#define RFSF_TERM(X, Y)                                                                                        \
+    _Pragma("unroll") for (int v = 0; v < NB; ++v) acc[v] = mfma(a.X, b[v].Y, acc[v])
+    RFSF_TERM(lo, hi);
+    RFSF_TERM(hi, lo);
+    RFSF_TERM(mid, mid);
+    RFSF_TERM(mid, hi);
+    RFSF_TERM(hi, mid);
+    RFSF_TERM(hi, hi);
+#undef RFSF_TERM
+}
+
+// An entry that came out as NaN, in plain 32-bit arithmetic.
+__device__ __noinline__ float plain_dot(const float *a, const float *b, int64_t K)
+{
+    float s = 0.f;
+    for (int64_t k = 0; k < K; ++k) s = fmaf(a[k], b[k], s);
+    return s;
+}
+
+// One operand pair of a launch: row-major, K-contiguous. Batched launches (one product per level of RFSF-TRP) add
+// blockIdx.y times the steps.
+struct GramArgs {
+    const float *A, *B;
+    float *C;
+    int64_t Nx, Ny, K, lda, ldb, ldc;
+    int64_t step_a, step_b, step_c;
+};
+
+// Stores four consecutive rows i .. i+3 of column j; `mirror` also writes their mirror image, row j. `diagonal`: the
+// tile meets the diagonal, and only what lies on or above it counts.
+__device__ __forceinline__ void store_quad(const GramArgs &g, const float *A, const float *B, float *C, int64_t i, int64_t j,
+                                           float (&v)[4], bool mirror, bool diagonal, bool vec_mirror)
+{
+    if (j >= g.Ny) return;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        if (i + e >= g.Nx) continue;
+        if (v[e] != v[e]) v[e] = plain_dot(A + (i + e) * g.lda, B + j * g.ldb, g.K);
+        if (!diagonal || i + e <= j) C[(i + e) * g.ldc + j] = v[e];
+    }
+    if (!mirror) return;
+    float *dst = C + j * g.ldc + i;
+    if (!diagonal && vec_mirror && i + 3 < g.Nx) {
+        *reinterpret_cast<float4 *>(dst) = make_float4(v[0], v[1], v[2], v[3]);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (i + e < g.Nx && (!diagonal || i + e < j)) dst[e] = v[e];
+    }
+}
+
+// Consecutive workgroup ids go to the eight XCDs in turn, each with an L2 of its own: tile `id` of an order that
+// keeps neighbours close, cut into eight contiguous pieces.
+__device__ __forceinline__ int64_t rank_of_block(int64_t tiles)
+{
+    const int64_t per = (tiles + 7) / 8;
+    return (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+}
+unsigned xcd_grid(int64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
+
+// ---------------------------------------------------------------------------------------------------------------
+// Small problems: too few tiles to fill the chip with large ones, time is latency. Tile (32 T) x (32 T), NW
+// wavefronts that share out the columns of K in steps of 32, step s to wavefront s mod NW, and work without any
+// barrier: each loads its fragments from global memory straight into registers, one step ahead. The partial tiles are
+// added through LDS at the end in a fixed order. 16 x 16 blocks (v_mfma_f32_16x16x32_bf16: lane l holds columns
+// 8 (l / 16) .. + 7 of row l mod 16) rather than 32 x 32: a 16-byte load then touches 16 rows instead of 32, and what
+// bounds the loop is one row (cache line) per cycle of the CU's address unit, 37 cycles a load with 32 rows.
+// Any row stride and alignment (the loads need four bytes).
+struct __attribute__((packed, aligned(4))) Float4u { float x, y, z, w; };
+
+template <int T, int NW, bool SYM>
+__global__ __launch_bounds__(64 * NW) void gram_small(GramArgs g, int64_t tiles, int64_t tiles_j)
+{
+    constexpr int NR = 2 * T, NH = NW / 2;      // 16-row blocks per side; wavefronts that keep a partial tile in LDS
+    __shared__ floatx4 red[NH * NR * NR * 64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int quarter = lane >> 4, col = lane & 15;
+    const int64_t rank = rank_of_block(tiles);
+    if (rank >= tiles) return;
+    int64_t bi, bj;
+    if (SYM) {          // column by column of the upper triangle: column c holds rows 0 .. c
+        bj = (int64_t)((sqrt(8.0 * (double)rank + 1.0) - 1.0) * 0.5);
+        while (bj * (bj + 1) / 2 > rank) --bj;
+        while ((bj + 1) * (bj + 2) / 2 <= rank) ++bj;
+        bi = rank - bj * (bj + 1) / 2;
+    } else {
+        bi = rank / tiles_j;
+        bj = rank - bi * tiles_j;
+    }
+    const float *A = g.A + blockIdx.y * g.step_a, *B = g.B + blockIdx.y * g.step_b;
+    float *C = g.C + blockIdx.y * g.step_c;
+    const int64_t i0 = bi * (32 * T), j0 = bj * (32 * T);
+    // rows beyond the matrix are redirected to its last one: what they contribute is never stored
+    const float *p[2 * NR];
+#pragma unroll
+    for (int t = 0; t < NR; ++t) {
+        p[t] = A + min(i0 + 16 * t + col, g.Nx - 1) * g.lda + 8 * quarter;
+        p[NR + t] = B + min(j0 + 16 * t + col, g.Ny - 1) * g.ldb + 8 * quarter;
+    }
+    floatx4 acc[NR][NR];
+#pragma unroll
+    for (int a = 0; a < NR; ++a)
+#pragma unroll
+        for (int b = 0; b < NR; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    float raw[2 * NR][8];
+    auto fetch = [&](int64_t step) {
+#pragma unroll
+        for (int t = 0; t < 2 * NR; ++t)
+#pragma unroll
+            for (int c = 0; c < 2; ++c) {
+                const Float4u v = *reinterpret_cast<const Float4u *>(p[t] + 32 * step + 4 * c);
+                raw[t][4 * c] = v.x;
+                raw[t][4 * c + 1] = v.y;
+                raw[t][4 * c + 2] = v.z;
+                raw[t][4 * c + 3] = v.w;
+            }
+    };
+    auto split_all = [&](Split8 (&a)[NR], Split8 (&b)[NR]) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t) {
+            a[t] = split8(raw[t]);
+            b[t] = split8(raw[NR + t]);
+        }
+    };
+    auto multiply = [&](const Split8 (&a)[NR], const Split8 (&b)[NR]) {
+#pragma unroll
+        for (int t = 0; t < NR; ++t) mfma_split<NR>(a[t], b, acc[t]);
+    };
+    const int64_t nfull = g.K / 32;
+    const int rest = (int)(g.K - 32 * nfull);
+    if (wave < nfull) fetch(wave);
+    for (int64_t s = wave; s < nfull; s += NW) {
+        Split8 a[NR], b[NR];
+        split_all(a, b);
+        if (s + NW < nfull) fetch(s + NW);
+        multiply(a, b);
+    }
+    if (rest != 0 && wave == (int)(nfull % NW)) {      // the columns left over, number by number
+#pragma unroll
+        for (int t = 0; t < 2 * NR; ++t)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) raw[t][e] = 8 * quarter + e < rest ? p[t][32 * nfull + e] : 0.f;
+        Split8 a[NR], b[NR];
+        split_all(a, b);
+        multiply(a, b);
+    }
+    // partial tiles: the second half of the wavefronts to the first, then all of those by everybody
+    auto slot = [&](int w, int blk) { return (w * NR * NR + blk) * 64 + lane; };
+    if (wave >= NH) {
+#pragma unroll
+        for (int b = 0; b < NR * NR; ++b) red[slot(wave - NH, b)] = acc[b / NR][b % NR];
+    }
+    __syncthreads();
+    if (wave < NH) {
+#pragma unroll
+        for (int b = 0; b < NR * NR; ++b) red[slot(wave, b)] += acc[b / NR][b % NR];
+    }
+    __syncthreads();
+    // result layout of a 16x16 block: lane l holds column l mod 16 and rows 4 (l / 16) + 0 .. 3
+    const bool vec_mirror = g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;
+    for (int b = wave; b < NR * NR; b += NW) {
+        floatx4 sum = red[slot(0, b)];
+#pragma unroll
+        for (int w = 1; w < NH; ++w) sum += red[slot(w, b)];
+        float v[4] = {sum[0], sum[1], sum[2], sum[3]};
+        store_quad(g, A, B, C, i0 + (b / NR) * 16 + 4 * quarter, j0 + (b % NR) * 16 + col, v, SYM, SYM && bi == bj,
+                   vec_mirror);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Large problems: tile 256 x 128, four wavefronts 2 x 2 of 128 x 64, steps of 16 columns of K in three LDS buffers.
+// The floats go from global memory straight into LDS (global_load_lds: lane i of a wavefront deposits its bytes at
+// LDS base + i times their number, no register and no LDS-write instruction involved), two steps ahead, and are split
+// when they are read: a wavefront splits (128 + 64) x 16 numbers for 48 matrix instructions, 5.5 vector
+// instructions for each, which issue in the 32 cycles that it takes (measured: up to six are free, with
+// eight the rate falls by a fifth; 64 x 64 per wavefront would need 7.3). 128 x 64 also keeps the LDS reads at a
+// quarter of the matrix time. Two workgroups per CU (74 KB of LDS and 256 registers each), so that one computes while
+// the other waits at its barrier.
+// Bound: power. On 50000 x 5000 x 10241 the matrix pipes are busy 66 % of the cycles and the clock falls from 2.4 to
+// 1.7 GHz: 26.0 ms, 1.18 PFLOP/s of bfloat16 products (the library's bfloat16 product of two 8192 x 8192 matrices
+// reaches 1.09 here), 197 TFLOP/s of the product asked for. v_mfma_f32_32x32x2f32 gave 38.8 ms, 132 TFLOP/s, 0.84 of
+// its peak. 10000 rows with themselves, 5121 columns: 2.88 ms against 3.90.
+// LDS layout of one buffer: 384 rows (256 of A, 128 of B) of 4 chunks of 16 bytes; slot p of row r holds chunk
+// p ^ ((r / 4) mod 4): the XOR makes the fragment reads (16 consecutive rows, same chunk) hit 16 distinct 16-byte
+// positions of the 256-byte bank row, and a direct load can produce it because each lane chooses what it fetches.
+// ALIGNED: rows start on 16 bytes and are loaded 16 bytes per lane; otherwise four bytes per lane.
+constexpr int kBigM = 256, kBigN = 128, kBigRows = kBigM + kBigN, kStep = 16;
+constexpr int kBigBuffer = kBigRows * kStep;                  // floats
+constexpr int64_t kBigMaxStride = (int64_t)1 << 21;           // offsets inside a tile are 32-bit byte offsets
+
 struct TileCoord { int64_t bi, bj; };
-constexpr int kStrip = 8;
+constexpr int kStrip = 4;        // tile rows per strip: 4 x 8 tiles, 1024 x 1024 entries, share their panels in an L2
 template <bool SYM>
-__device__ __forceinline__ TileCoord tile_of_rank(int64_t rank, int64_t nti, int64_t ntj)
+__device__ __forceinline__ TileCoord big_tile(int64_t rank, int64_t nti, int64_t ntj)
 {
     if (!SYM) {
         const int64_t full = kStrip * ntj, I = rank / full, r = rank - I * full;
-        const int64_t h = nti - kStrip * I < kStrip ? nti - kStrip * I : kStrip;
+        const int64_t h = min(nti - kStrip * I, (int64_t)kStrip);
         return {kStrip * I + r % h, r / h};
     }
-    int64_t I = 0;
-    for (;; ++I) {
-        const int64_t h = nti - kStrip * I < kStrip ? nti - kStrip * I : kStrip;
-        const int64_t cnt = h * (h + 1) / 2 + h * (nti - kStrip * I - h);
-        if (rank < cnt) break;
-        rank -= cnt;
-    }
-    const int64_t h = nti - kStrip * I < kStrip ? nti - kStrip * I : kStrip, tri = h * (h + 1) / 2;
-    if (rank < tri) {                       // column c of the triangle holds rows 0..c
-        int64_t c = 0;
-        while (rank >= c + 1) { rank -= c + 1; ++c; }
-        return {kStrip * I + rank, kStrip * I + c};
-    }
-    rank -= tri;
-    return {kStrip * I + rank % h, kStrip * I + h + rank / h};
-}
-
-// Matrix-core kernel for large problems: 128 x 128 tile, four wavefronts 2 x 2, v_mfma_f32_32x32x2f32, K slabs
-// of 32 in two LDS buffers. While slab s is multiplied out of one buffer, slab s+1 is loaded from global memory
-// straight into the other one (global_load_lds_dwordx4: lane i of a wavefront deposits its 16 bytes at
-// LDS base + 16 i, no register and no LDS-write instruction involved -- measured here, LDS writes issued by
-// the wavefronts cost 11 % of the matrix rate, because they hold the issue port the matrix instructions need).
-// One barrier per slab separates the two roles of a buffer.
-// LDS layout of one operand in one buffer: 128 rows x 8 chunks of 16 bytes, unpadded; chunk slot p of row r
-// holds columns 4 (p ^ s(r)) .. +3 of the slab, s(r) = (r / 2) mod 8. The XOR makes the fragment reads
-// (16 consecutive rows, same chunk) hit 16 distinct 16-byte positions of the 256-byte bank row, and a direct
-// load can produce it because each lane chooses which global chunk it fetches. MFMA k-step (c, e) uses column
-// 4c + e in lanes 0-31 and 16 + 4c + e in lanes 32-63, for both operands.
-// The last slab, if K is no multiple of 32, goes through registers so that columns beyond K can be zeroed.
-constexpr int kBigTile = 128;
-constexpr int kBigOperand = kBigTile * kKT;                 // floats of one operand in one buffer
-
-// Fragments of one lane for k-groups c = C0 .. C0+1 of a staged slab: row (wi or wj)*64 + 32 t + col of each
-// operand, chunk 4 half + c in slot (4 half + c) ^ s(row).
-struct BigFrag { float4 a[2][2], b[2][2]; };           // [c - C0][t]
-template <int C0>
-__device__ __forceinline__ void big_read(const float *__restrict__ rd, int frag_a, int frag_b, int half, int fsw, BigFrag &f)
-{
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-        const int slot = 4 * ((4 * half + C0 + c) ^ fsw);
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            f.a[c][t] = *reinterpret_cast<const float4 *>(&rd[frag_a + t * 32 * kKT + slot]);
-            f.b[c][t] = *reinterpret_cast<const float4 *>(&rd[frag_b + t * 32 * kKT + slot]);
+    // a strip starts at column tile 2 kStrip I; column c of its first 2 h ones holds rows 0 .. c / 2
+    for (int64_t I = 0;; ++I) {
+        const int64_t h = min(nti - kStrip * I, (int64_t)kStrip), w = ntj - 2 * kStrip * I;
+        const int64_t count = h * w - h * (h - 1);
+        if (rank >= count) {
+            rank -= count;
+            continue;
         }
+        for (int64_t c = 0; c < 2 * h; ++c) {
+            if (rank <= c / 2) return {kStrip * I + rank, 2 * kStrip * I + c};
+            rank -= c / 2 + 1;
+        }
+        return {kStrip * I + rank % h, 2 * kStrip * I + 2 * h + rank / h};
     }
 }
-// 16 matrix instructions on k-group c of a fragment pair
-__device__ __forceinline__ void big_mfma16(const BigFrag &f, int c, floatx16 (&acc)[2][2])
+int64_t big_tiles(int64_t Nx, int64_t Ny, bool sym)
 {
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b) {
-                const float4 &fa = f.a[c][a], &fb = f.b[c][b];
-                const float av = e == 0 ? fa.x : e == 1 ? fa.y : e == 2 ? fa.z : fa.w;
-                const float bv = e == 0 ? fb.x : e == 1 ? fb.y : e == 2 ? fb.z : fb.w;
-                acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc[a][b], 0, 0, 0);
-            }
+    const int64_t nti = (Nx + kBigM - 1) / kBigM, ntj = (Ny + kBigN - 1) / kBigN;
+    return sym ? nti * ntj - nti * (nti - 1) : nti * ntj;
 }
 
-// Direct loads of one full slab (columns k0 .. k0+31) into `wr`: wavefront `wave` fills rows 32u + 8 wave .. +7.
-__device__ __forceinline__ void big_load_direct(float *__restrict__ wr, const float *const (&pa)[4],
-                                                const float *const (&pb)[4], int64_t k0, int wave)
+// Lane i's BYTES bytes at base + off to LDS at dst + BYTES * i. Written out so that the compiler, which cannot tell
+// the buffers apart, does not wait for the loads in flight before every read of LDS; the caller waits.
+template <int BYTES>
+__device__ __forceinline__ void direct_load(const char *base, uint32_t off, float *dst)
 {
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        float *dst = wr + (32 * u + 8 * wave) * kKT;        // wavefront-uniform
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pa[u] + k0),
-                                         (__attribute__((address_space(3))) void *)dst, 16, 0, 0);
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(pb[u] + k0),
-                                         (__attribute__((address_space(3))) void *)(dst + kBigOperand), 16, 0, 0);
-    }
+    const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)dst);
+    if constexpr (BYTES == 16)
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
+    else
+        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
 }
 
-// One steady-state step, software-pipelined across the barrier: on entry `f01` holds the fragments of
-// k-groups 0, 1 of the slab in `rd`. The next slab's direct loads go out first and have three quarters of the
-// step to land; the barrier sits before the last 16 matrix instructions, so that the first LDS reads of the next
-// slab (into `f01` again) run under them instead of stalling the matrix pipe after the barrier. `rd` and `wr`
-// are the two distinct LDS buffers; telling the compiler so (restrict) keeps it from waiting for the loads
-// before the reads of `rd`.
-__device__ __forceinline__ void big_step(const float *__restrict__ rd, float *__restrict__ wr,
-                                         const float *const (&pa)[4], const float *const (&pb)[4], int64_t k_next,
-                                         int wave, int frag_a, int frag_b, int half, int fsw, BigFrag &f01,
-                                         floatx16 (&acc)[2][2])
+template <bool ALIGNED, bool SYM>
+__global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, int64_t nti, int64_t ntj)
 {
-    BigFrag f23;
-    big_load_direct(wr, pa, pb, k_next, wave);
-    big_read<2>(rd, frag_a, frag_b, half, fsw, f23);
-    big_mfma16(f01, 0, acc);
-    big_mfma16(f01, 1, acc);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 4, 0);  // 4 matrix instructions
-        __builtin_amdgcn_sched_group_barrier(0x010, 1, 0);  // one direct load of the next slab
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // one LDS read of k-groups 2, 3
-    }
-    big_mfma16(f23, 0, acc);
-    __builtin_amdgcn_sched_barrier(0);
-    __syncthreads();                                        // next slab complete, this one read by everyone
-    big_read<0>(wr, frag_a, frag_b, half, fsw, f01);
-    big_mfma16(f23, 1, acc);
-#pragma unroll
-    for (int i = 0; i < 8; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x100, 1, 1);  // one LDS read of the next slab's k-groups 0, 1
-        __builtin_amdgcn_sched_group_barrier(0x008, 2, 1);  // 2 matrix instructions
-    }
-    __builtin_amdgcn_sched_barrier(0);
-}
-
-template <bool SYM>
-__global__ __launch_bounds__(256, 2) void gram_mfma_big(
-    const float *__restrict__ A, int64_t Nx, int64_t lda, const float *__restrict__ B, int64_t Ny,
-    int64_t ldb, int64_t K, float *__restrict__ C, int64_t ldc, int64_t ntiles, int64_t per_xcd)
-{
-    // two buffers of [A | B][128 rows][32]; 64 KB in all (the direct loads address LDS with 16 bits)
-    __shared__ __attribute__((aligned(16))) float buf0[2 * kBigOperand];
-    __shared__ __attribute__((aligned(16))) float buf1[2 * kBigOperand];
+    __shared__ __attribute__((aligned(16))) float buf[3][kBigBuffer];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int half = lane >> 5, col = lane & 31;
     const int wi = wave >> 1, wj = wave & 1;
-    const int64_t xcd = blockIdx.x % 8, k_in_xcd = blockIdx.x / 8;
-    const int64_t rank = xcd * per_xcd + k_in_xcd;
-    if (k_in_xcd >= per_xcd || rank >= ntiles) return;
-    const int64_t nti = (Nx + kBigTile - 1) / kBigTile, ntj = (Ny + kBigTile - 1) / kBigTile;
-    const TileCoord tc = tile_of_rank<SYM>(rank, nti, ntj);
-    const int64_t i0 = tc.bi * kBigTile, j0 = tc.bj * kBigTile;
+    const int64_t rank = rank_of_block(tiles);
+    if (rank >= tiles) return;
+    const TileCoord tc = big_tile<SYM>(rank, nti, ntj);
+    const int64_t i0 = (int64_t)__builtin_amdgcn_readfirstlane((int)tc.bi) * kBigM;
+    const int64_t j0 = (int64_t)__builtin_amdgcn_readfirstlane((int)tc.bj) * kBigN;
+    const float *A = g.A + blockIdx.y * g.step_a, *B = g.B + blockIdx.y * g.step_b;
+    float *C = g.C + blockIdx.y * g.step_c;
 
-    floatx16 acc[2][2];
+    floatx16 acc[4][2];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int b = 0; b < 2; ++b)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
 
-    // Loading: wavefront w fills rows 32u + 8w .. +7 (u = 0..3) of each operand; lane i covers row i/8 of those
-    // and chunk slot i%8. Rows beyond the matrix are redirected to row 0: what they contribute lands in output
-    // rows or columns that are never stored.
-    const int lrow = 8 * wave + (lane >> 3);                 // row within a group of 32
-    const int lchunk = (lane & 7) ^ ((lrow >> 1) & 7);       // global chunk that belongs in this lane's slot
-    const float *pa[4], *pb[4];
+    // Direct loads: instruction j of wavefront w fills rows RI (w NL + j) .. + RI - 1 of the buffer (RI rows per
+    // instruction). Rows beyond the matrix are redirected to its last one.
+    constexpr int RI = ALIGNED ? 16 : 4, NL = kBigRows / RI / 4;
+    const int lrow = ALIGNED ? lane >> 2 : lane >> 4;
+    uint32_t off[NL];                   // byte offset of this lane's source from the operand's tile
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-        const int64_t ra_ = i0 + lrow + 32 * u, rb_ = j0 + lrow + 32 * u;
-        pa[u] = A + (ra_ < Nx ? ra_ : 0) * lda + 4 * lchunk;
-        pb[u] = B + (rb_ < Ny ? rb_ : 0) * ldb + 4 * lchunk;
+    for (int j = 0; j < NL; ++j) {
+        const int row0 = RI * (wave * NL + j), row = row0 + lrow;
+        const int slot = ALIGNED ? lane & 3 : (lane >> 2) & 3;
+        const int column = 4 * (slot ^ ((row >> 2) & 3)) + (ALIGNED ? 0 : lane & 3);
+        const bool is_b = row0 >= kBigM;
+        const int64_t left = is_b ? g.Ny - 1 - j0 : g.Nx - 1 - i0, r = is_b ? row - kBigM : row;
+        off[j] = (uint32_t)((r < left ? r : left) * (is_b ? g.ldb : g.lda) + column) * 4u;
     }
-    float4 ra[4], rb[4];
-    auto fetch_masked = [&](int64_t k0) {                    // through registers: columns >= K become zero
-        const int64_t k = k0 + 4 * lchunk;
+    const char *base_a = reinterpret_cast<const char *>(A + i0 * g.lda);
+    const char *base_b = reinterpret_cast<const char *>(B + j0 * g.ldb);
+    auto load = [&](float *dst, int64_t k0) {
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float4 va = make_float4(0.f, 0.f, 0.f, 0.f), vb = va;
-            if (k < K) {
-                va = *reinterpret_cast<const float4 *>(pa[u] + k0);
-                vb = *reinterpret_cast<const float4 *>(pb[u] + k0);
-                if (k + 3 >= K) {                            // columns beyond K hold padding, not data
-                    if (k + 1 >= K) { va.y = 0.f; vb.y = 0.f; }
-                    if (k + 2 >= K) { va.z = 0.f; vb.z = 0.f; }
-                    va.w = 0.f; vb.w = 0.f;
-                }
-            }
-            ra[u] = va;
-            rb[u] = vb;
+        for (int j = 0; j < NL; ++j) {
+            const int row0 = RI * (wave * NL + j);              // uniform
+            direct_load<ALIGNED ? 16 : 4>((row0 >= kBigM ? base_b : base_a) + 4 * k0, off[j], dst + row0 * kStep);
         }
     };
-    auto stage_masked = [&](float *buf) {                    // the same slots the direct loads would fill
+    const int64_t nfull = g.K / kStep;
+    const int rest = (int)(g.K - kStep * nfull);
+    // the last, partial step comes first (buffer 0), number by number with zeros beyond K; full step s follows
+    // in buffer (s + shift) mod 3
+    const int shift = rest != 0 ? 1 : 0;
+    const int64_t nsteps = nfull + shift;
+    if (rest != 0) {
+        float v[kBigBuffer / 256];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float *dst = buf + (32 * u + 8 * wave) * kKT + 4 * lane;
-            *reinterpret_cast<float4 *>(dst) = ra[u];
-            *reinterpret_cast<float4 *>(dst + kBigOperand) = rb[u];
+        for (int u = 0; u < kBigBuffer / 256; ++u) {
+            const int e = tid + 256 * u, row = e / kStep, k = e % kStep;
+            const bool is_b = row >= kBigM;
+            const int64_t left = is_b ? g.Ny - 1 - j0 : g.Nx - 1 - i0, r = is_b ? row - kBigM : row;
+            const float *src = is_b ? B + j0 * g.ldb : A + i0 * g.lda;
+            v[u] = k < rest ? src[(r < left ? r : left) * (is_b ? g.ldb : g.lda) + kStep * nfull + k] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < kBigBuffer / 256; ++u) {
+            const int e = tid + 256 * u, row = e / kStep, k = e % kStep;
+            buf[0][row * kStep + 4 * ((k >> 2) ^ ((row >> 2) & 3)) + (k & 3)] = v[u];
+        }
+    }
+    const int fsw = (col >> 2) & 3;
+    const int frag_a = (wi * 128 + col) * kStep, frag_b = (kBigM + wj * 64 + col) * kStep;
+    auto read8 = [&](const float *rd, int at, float (&x)[8]) {
+#pragma unroll
+        for (int c = 0; c < 2; ++c) {
+            const float4 v = *reinterpret_cast<const float4 *>(rd + at + 4 * ((2 * half + c) ^ fsw));
+            x[4 * c] = v.x;
+            x[4 * c + 1] = v.y;
+            x[4 * c + 2] = v.z;
+            x[4 * c + 3] = v.w;
         }
     };
-    const int fsw = (col >> 1) & 7;
-    const int frag_a = (wi * 64 + col) * kKT, frag_b = kBigOperand + (wj * 64 + col) * kKT;
-    const bool vec_store = ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;    // for the mirrored stores
-
-    const int64_t nfull = K / kKT, nslab = (K + kKT - 1) / kKT;
-    if (nfull > 0) {
-        big_load_direct(buf0, pa, pb, 0, wave);
-    } else {
-        fetch_masked(0);
-        stage_masked(buf0);
-    }
-    __syncthreads();
-    BigFrag f01, f23;
-    big_read<0>(buf0, frag_a, frag_b, half, fsw, f01);
-    int64_t sl = 0;
-    // steady state, two slabs per trip so that each step names its buffers statically
-    for (; sl + 2 < nfull; sl += 2) {
-        big_step(buf0, buf1, pa, pb, (sl + 1) * kKT, wave, frag_a, frag_b, half, fsw, f01, acc);
-        big_step(buf1, buf0, pa, pb, (sl + 2) * kKT, wave, frag_a, frag_b, half, fsw, f01, acc);
-    }
-    // the last slabs (at most two full ones and the partial one): loads through registers; `f01` holds the
-    // first half of slab sl
-    for (; sl < nslab; ++sl) {
-        const bool more = sl + 1 < nslab;
-        float *rd = (sl & 1) ? buf1 : buf0, *wr = (sl & 1) ? buf0 : buf1;
-        if (more) fetch_masked((sl + 1) * kKT);
-        big_read<2>(rd, frag_a, frag_b, half, fsw, f23);
-        big_mfma16(f01, 0, acc);
-        big_mfma16(f01, 1, acc);
-        big_mfma16(f23, 0, acc);
-        big_mfma16(f23, 1, acc);
-        if (more) stage_masked(wr);
-        __syncthreads();
-        if (more) big_read<0>(wr, frag_a, frag_b, half, fsw, f01);
-    }
-    // result layout of a 32x32 block: lane holds column lane%32 and rows 8q + 4*(lane/32) + i
+    // Software pipeline. A step enters with the split fragments of its two blocks of B and of its first block of A; the
+    // matrix instructions of one block of A run while the next one is split. Before the last block's, when
+    // everything of this step has been read, the wavefront waits for its loads of the next step (those of the
+    // step after it stay in flight) and then for everybody: the next step can be read, and this step's buffer takes
+    // the loads of the step three ahead. The next step's first fragments are read and split under the last
+    // block's matrix instructions.
+    Split8 b[2], a;
+    auto first_fragments = [&](const float *rd, Split8 (&nb)[2], Split8 &na) {
+        float x[3][8];
+        read8(rd, frag_b, x[0]);
+        read8(rd, frag_b + 32 * kStep, x[1]);
+        read8(rd, frag_a, x[2]);
+        nb[0] = split8(x[0]);
+        nb[1] = split8(x[1]);
+        na = split8(x[2]);
+    };
+    auto interleave = [&](auto vector_tag) {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b) {
-            const int64_t j = j0 + (wj * 2 + b) * 32 + col;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int64_t i = i0 + (wi * 2 + a) * 32 + 8 * (v >> 2) + 4 * half + (v & 3);
-                if (i < Nx && j < Ny) C[i * ldc + j] = acc[a][b][v];
-            }
-            // SYM, tile above the diagonal: its mirror image below the diagonal is written from the same
-            // registers (four consecutive rows of the tile are four consecutive floats of the mirrored row)
-            if (SYM && tc.bi != tc.bj && j < Ny) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int64_t i = i0 + (wi * 2 + a) * 32 + 8 * q + 4 * half;
-                    float *dst = C + j * ldc + i;
-                    if (i + 3 < Nx && vec_store) {
-                        *reinterpret_cast<float4 *>(dst) = make_float4(acc[a][b][4 * q], acc[a][b][4 * q + 1],
-                                                                       acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (i + e < Nx) dst[e] = acc[a][b][4 * q + e];
-                    }
-                }
-            }
+        for (int i = 0; i < 12; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                      // one matrix instruction
+            __builtin_amdgcn_sched_group_barrier(0x002, decltype(vector_tag)::value, 0);    // and vector ones behind it
         }
+    };
+    auto step = [&](int64_t s, float *rd, const float *next) {
+        float x[3][8];
+#pragma unroll
+        for (int t = 0; t < 3; ++t) read8(rd, frag_a + (t + 1) * 32 * kStep, x[t]);
+#pragma unroll
+        for (int t = 0; t < 3; ++t) {
+            mfma_split<2>(a, b, acc[t]);
+            a = split8(x[t]);
+            interleave(std::integral_constant<int, 4>{});
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (s + 2 < nsteps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (s + 3 < nsteps) load(rd, kStep * (s + 3 - shift));
+        Split8 nb[2], na;
+        first_fragments(next, nb, na);                          // (junk after the last step, not used)
+        mfma_split<2>(a, b, acc[3]);
+        interleave(std::integral_constant<int, 11>{});
+        __builtin_amdgcn_sched_barrier(0);
+        b[0] = nb[0];
+        b[1] = nb[1];
+        a = na;
+    };
+    if (nsteps > 0) {
+        if (shift == 0) load(buf[0], 0);
+        if (nsteps > 1) load(buf[1], kStep * (1 - shift));
+        if (nsteps > 2) load(buf[2], kStep * (2 - shift));
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        first_fragments(buf[0], b, a);
+        for (int64_t s = 0; s < nsteps; s += 3) {
+            step(s, buf[0], buf[1]);
+            if (s + 1 < nsteps) step(s + 1, buf[1], buf[2]);
+            if (s + 2 < nsteps) step(s + 2, buf[2], buf[0]);
+        }
+    }
+    // result layout of a 32x32 block: lane holds column lane % 32 and rows 8 q + 4 (lane / 32) + 0 .. 3
+    const bool vec_mirror = g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;
+    const bool diagonal = SYM && tc.bj < 2 * tc.bi + 2;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float v[4] = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
+                store_quad(g, A, B, C, i0 + (wi * 4 + a) * 32 + 8 * q + 4 * half, j0 + (wj * 2 + b) * 32 + col, v, SYM,
+                           diagonal, vec_mirror);
+            }
 }
 
-// Copies the part of a symmetric matrix above the diagonal to the part below it, 32x32 tiles
-// transposed through LDS so that both the reads and the writes are coalesced.
-__global__ __launch_bounds__(256) void mirror_lower_kernel(float *__restrict__ C, int64_t N, int64_t ldc)
+template <int T, int NW>
+hipError_t launch_small(const GramArgs &g, bool sym, int batch, hipStream_t stream)
 {
-    __shared__ float t[32][33];
-    const int64_t ti = blockIdx.y, tj = blockIdx.x;
-    if (tj < ti) return;
-    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-    for (int r = ty; r < 32; r += 8) {
-        const int64_t i = ti * 32 + r, j = tj * 32 + tx;
-        t[r][tx] = (i < N && j < N) ? C[i * ldc + j] : 0.f;
-    }
-    __syncthreads();
-    for (int r = ty; r < 32; r += 8) {
-        const int64_t i = tj * 32 + r, j = ti * 32 + tx;       // destination (i, j) = source (j, i)
-        if (i < N && j < N && i > j) C[i * ldc + j] = t[tx][r];
-    }
-}
-
-template <bool SYM>
-hipError_t launch_big(const float *PhiX, int64_t Nx, int64_t ldx, const float *PhiY, int64_t Ny, int64_t ldy,
-                      int64_t ncols, float *K, int64_t ldk, int64_t tiles, hipStream_t stream)
-{
-    const int64_t per_xcd = (tiles + 7) / 8;
-    hipLaunchKernelGGL((gram_mfma_big<SYM>), dim3((unsigned)(per_xcd * 8)), dim3(256), 0, stream, PhiX, Nx, ldx,
-                       PhiY, Ny, ldy, ncols, K, ldk, tiles, per_xcd);
+    const int64_t ti = (g.Nx + 32 * T - 1) / (32 * T), tj = (g.Ny + 32 * T - 1) / (32 * T);
+    const int64_t tiles = sym ? ti * (ti + 1) / 2 : ti * tj;
+    if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
+    const dim3 grid(xcd_grid(tiles), (unsigned)batch);
+    if (sym) hipLaunchKernelGGL((gram_small<T, NW, true>), grid, dim3(64 * NW), 0, stream, g, tiles, tj);
+    else hipLaunchKernelGGL((gram_small<T, NW, false>), grid, dim3(64 * NW), 0, stream, g, tiles, tj);
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *PhiY, int64_t Ny,
-                       int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream)
+                       int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, int batch,
+                       int64_t step_x, int64_t step_y, int64_t step_k)
 {
     if (Nx == 0 || Ny == 0) return hipSuccess;
-    const bool aligned = ldx % 4 == 0 && ldy % 4 == 0 && reinterpret_cast<uintptr_t>(PhiX) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(PhiY) % 16 == 0;
-    if (aligned) {
-        const int64_t big_tiles = ((Nx + 127) / 128) * ((Ny + 127) / 128);
-        // worth it once the upper triangle alone fills the chip twice over (64-row tiles)
-        const int64_t nt64 = (Nx + 63) / 64;
-        const bool symmetric = PhiX == PhiY && Nx == Ny && ldx == ldy && nt64 * (nt64 + 1) / 2 >= 512;
-        if (symmetric) {        // K = PhiX PhiX^T: upper triangle on the matrix cores, then mirrored
-            const bool big = big_tiles >= 1024;
-            const int64_t nt = (Nx + (big ? 127 : 63)) / (big ? 128 : 64);
-            const int64_t tiles = nt * (nt + 1) / 2;
-            if (tiles > 0x7fffffffLL || (Nx + 31) / 32 > 65535) return hipErrorInvalidValue;
-            if (big) {
-                const hipError_t e = launch_big<true>(PhiX, Nx, ldx, PhiY, Ny, ldy, ncols, K, ldk, tiles, stream);
-                if (e != hipSuccess) return e;
-            } else
-                hipLaunchKernelGGL((gram_mfma<1, true>), dim3((unsigned)tiles), dim3(256), 0, stream, PhiX, Nx, ldx,
-                                   PhiY, Ny, ldy, ncols, K, ldk);
-            if (!big) {         // the large-tile kernel writes the mirror image itself
-                const unsigned nm = (unsigned)((Nx + 31) / 32);
-                hipLaunchKernelGGL(mirror_lower_kernel, dim3(nm, nm), dim3(256), 0, stream, K, Nx, ldk);
-            }
-        } else if (big_tiles >= 512) {
-            if (big_tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
-            const hipError_t e = launch_big<false>(PhiX, Nx, ldx, PhiY, Ny, ldy, ncols, K, ldk, big_tiles, stream);
-            if (e != hipSuccess) return e;
+    const GramArgs g = {PhiX, PhiY, K, Nx, Ny, ncols, ldx, ldy, ldk, step_x, step_y, step_k};
+    // K = PhiX PhiX^T: only what lies on or above the diagonal is computed, and written twice
+    const bool sym = PhiX == PhiY && Nx == Ny && ldx == ldy;
+    const auto count = [&](int64_t edge) {
+        const int64_t ti = (Nx + edge - 1) / edge, tj = (Ny + edge - 1) / edge;
+        return (sym ? ti * (ti + 1) / 2 : ti * tj) * batch;
+    };
+    // Large tiles run one per CU at a time or, faster together, two; with `rounds` = their number over 256, rounded up,
+    // they take as long as about 1340 tiles of 64 x 64 per round do (measured for 201, 1025 and 5121 columns, both kinds,
+    // symmetric and not: 2500 x 2500, 200 large or 1600 small tiles, 32 / 98 / 411 us against 36 / 108 / 477;
+    // 4000 rows with themselves, 272 or 2016 tiles, 57 / 169 / 725 against 47 / 135 / 576).
+    const int64_t tiles = big_tiles(Nx, Ny, sym), rounds = (tiles * batch + 255) / 256;
+    if (count(64) > 1340 * rounds && ldx <= kBigMaxStride && ldy <= kBigMaxStride) {
+        if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
+        const bool aligned = ldx % 4 == 0 && ldy % 4 == 0 && step_x % 4 == 0 && step_y % 4 == 0 &&
+                             reinterpret_cast<uintptr_t>(PhiX) % 16 == 0 && reinterpret_cast<uintptr_t>(PhiY) % 16 == 0;
+        const int64_t nti = (Nx + kBigM - 1) / kBigM, ntj = (Ny + kBigN - 1) / kBigN;
+        const dim3 grid(xcd_grid(tiles), (unsigned)batch);
+#define RFSF_BIG(AL, SY) hipLaunchKernelGGL((gram_big<AL, SY>), grid, dim3(256), 0, stream, g, tiles, nti, ntj)
+        if (aligned) {
+            if (sym) RFSF_BIG(true, true);
+            else RFSF_BIG(true, false);
         } else {
-            dim3 g((unsigned)((Ny + 63) / 64), (unsigned)((Nx + 63) / 64));
-            const int64_t small_tiles = (int64_t)g.x * g.y;
-            if (small_tiles <= 512 && ncols >= 256)     // at most two tiles per CU: split K inside the workgroup
-                hipLaunchKernelGGL((gram_mfma<1, false, 2>), g, dim3(512), 0, stream, PhiX, Nx, ldx, PhiY, Ny, ldy,
-                                   ncols, K, ldk);
-            else
-                hipLaunchKernelGGL((gram_mfma<1, false>), g, dim3(256), 0, stream, PhiX, Nx, ldx, PhiY, Ny, ldy,
-                                   ncols, K, ldk);
+            if (sym) RFSF_BIG(false, true);
+            else RFSF_BIG(false, false);
         }
+#undef RFSF_BIG
         return hipGetLastError();
     }
-    dim3 grid((unsigned)((Ny + kTile - 1) / kTile), (unsigned)((Nx + kTile - 1) / kTile));
-    hipLaunchKernelGGL(gram_generic, grid, dim3(256), 0, stream, PhiX, Nx, ldx, PhiY, Ny, ldy, ncols, K, ldk);
-    return hipGetLastError();
+    // 32 x 32 tiles while 64 x 64 ones would not give every CU one (700 rows with themselves, 121 tiles of 64 x 64:
+    // 16 us against 22 with 1025 columns, 65 against 74 with 5121; 1500 rows, 300 tiles: 158 against 131 with 5121)
+    if (count(64) <= 256) return launch_small<1, 8>(g, sym, batch, stream);
+    return launch_small<2, 4>(g, sym, batch, stream);
 }
 
 }  // namespace rfsf

@@ -559,13 +559,12 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
                                             shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream) != hipSuccess)
                 return RFSF_E_HIP;
         }
-        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, one GEMM per level (rows whose increment does not exist are
-            // computed too and never read)
+        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (rows whose increment does not
+            // exist are computed too and never read)
             rfsf::ProfileScope scope(rfsf::kTrpProject, stream);
-            for (int m = 0; m < shape->M; ++m)
-                if (rfsf::launch_gram(dphi + (int64_t)m * twoF, cnt * shape->L, rf, Z + (int64_t)m * Q * twoF, Q, twoF,
-                                      twoF, P + (int64_t)m * Q, MQ, stream) != hipSuccess)
-                    return RFSF_E_HIP;
+            if (rfsf::launch_gram(dphi, cnt * shape->L, rf, Z, Q, twoF, twoF, P, MQ, stream, shape->M, twoF,
+                                  (int64_t)Q * twoF, Q) != hipSuccess)
+                return RFSF_E_HIP;
         }
         {
             rfsf::ProfileScope scope(rfsf::kTrpScan, stream);
