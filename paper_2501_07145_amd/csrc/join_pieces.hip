@@ -8,10 +8,11 @@
 // by how many indices fall into x, so per bin
 //     A^{(1..m)}(x y) = A^{(1..m)}(y) + A^{(1..m)}(x) + sum_{j=1}^{m-1} A^{(1..j)}(x) A^{(j+1..m)}(y),
 // where A^{(a..b)} is the accumulator of the recurrence run with the sketches of positions a .. b. The sketch
-// kernel is therefore launched on every piece once per first position a = 1 .. M (levels a .. M of the
-// increment rows, accumulators written out instead of features), this kernel folds the pieces of a sequence
-// together from left to right, bin by bin, and a last launch of the sketch kernel turns the joined accumulators
-// into features.
+// kernel therefore produces the accumulators of every range of positions for every piece -- in one launch
+// (join_chain_kernel), or, for transforms of 4096 and 8192 points, whose threads own too many bins for that, in one
+// launch per first position a = 1 .. M (levels a .. M of the increment rows; join_pieces_kernel) --, the pieces of a
+// sequence are folded together from left to right, bin by bin, and a last launch of the sketch kernel turns the
+// joined accumulators into features.
 #include "rfsf_internal.h"
 
 namespace rfsf {
@@ -63,7 +64,74 @@ __global__ __launch_bounds__(256) void join_pieces_kernel(PieceRows src, int64_t
     for (int m = 0; m < M; ++m) joined[(n * M + m) * bins + f] = A[m];
 }
 
+// Pieces that carry the accumulators of all ranges of positions (TimeCut): one thread per (sequence, bin) folds the
+// pieces from left to right and leaves the sums in the place of the first piece's levels (ranges from position 1 on);
+// only that thread touches the pieces' numbers of its bin. The chain is what bounds it: the numbers of the next
+// kAhead pieces are in flight while one is folded in. (Joining groups of pieces first and the groups afterwards
+// shortens the chain, but multiplies large pieces with each other, whose products cancel: on 1398 points of one
+// channel and eight levels the error of the top level rose past 1e-4. Left to right every factor but one is short.)
+template <int M>
+__global__ __launch_bounds__(64) void join_chain_kernel(float2 *spectra, int64_t n_seq, int pieces, int bins,
+                                                        int64_t seq_stride, int64_t piece_stride)
+{
+    constexpr int Q = M * (M + 1) / 2, kAhead = Q <= 15 ? 4 : 3;
+    const int64_t g = (int64_t)blockIdx.x * 64 + threadIdx.x;
+    const int64_t n = g / bins;
+    if (n >= n_seq) return;
+    float2 *first = spectra + n * seq_stride + (g - n * bins);
+    auto at = [](int a, int l) { return a * M - a * (a - 1) / 2 + l - a; };
+    float2 A[M], B[kAhead][Q];
+#pragma unroll
+    for (int m = 0; m < M; ++m) A[m] = first[(int64_t)m * bins];
+    auto fetch = [&](int slot, int s) {
+        const float2 *src = first + s * piece_stride;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) B[slot][q] = src[(int64_t)q * bins];
+    };
+#pragma unroll
+    for (int i = 0; i < kAhead; ++i)
+        if (1 + i < pieces) fetch(i, 1 + i);
+    for (int s0 = 1; s0 < pieces; s0 += kAhead) {
+#pragma unroll
+        for (int i = 0; i < kAhead; ++i) {
+            if (s0 + i < pieces) {
+#pragma unroll
+                for (int l = M - 1; l >= 0; --l) {            // descending: the lower levels are still the old ones
+                    float2 acc = make_float2(A[l].x + B[i][at(0, l)].x, A[l].y + B[i][at(0, l)].y);
+#pragma unroll
+                    for (int j = 1; j <= l; ++j) acc = cmadd(A[j - 1], B[i][at(j, l)], acc);
+                    A[l] = acc;
+                }
+                if (s0 + i + kAhead < pieces) fetch(i, s0 + i + kAhead);
+            }
+        }
+    }
+#pragma unroll
+    for (int m = 0; m < M; ++m) first[(int64_t)m * bins] = A[m];
+}
+
 }  // namespace
+
+hipError_t launch_join_chain(float2 *spectra, int64_t n_seq, int pieces, int M, int bins, int64_t seq_stride,
+                             int64_t piece_stride, hipStream_t stream)
+{
+    if (n_seq == 0) return hipSuccess;
+    if (pieces < 1 || bins < 1) return hipErrorInvalidValue;
+    const int64_t blocks = (n_seq * bins + 63) / 64;
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    switch (M) {
+#define RFSF_JOIN_CASE(LEVELS)                                                                                        \
+        case LEVELS:                                                                                                  \
+            hipLaunchKernelGGL(join_chain_kernel<LEVELS>, dim3((unsigned)blocks), dim3(64), 0, stream, spectra, n_seq, \
+                               pieces, bins, seq_stride, piece_stride);                                               \
+            break;
+        RFSF_JOIN_CASE(1) RFSF_JOIN_CASE(2) RFSF_JOIN_CASE(3) RFSF_JOIN_CASE(4) RFSF_JOIN_CASE(5) RFSF_JOIN_CASE(6)
+        RFSF_JOIN_CASE(7) RFSF_JOIN_CASE(8)
+#undef RFSF_JOIN_CASE
+        default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
 
 hipError_t launch_join_pieces(const PieceRows &pieces_of_start, int64_t n_seq, int pieces, int M, int bins,
                               float2 *joined, hipStream_t stream)

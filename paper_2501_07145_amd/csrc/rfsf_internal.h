@@ -8,18 +8,22 @@
 namespace rfsf {
 
 // A launch of the tuned sketch kernels may cut every sequence into `pieces` pieces of `pairs` pairs of time
-// steps each (workgroup v then owns piece v % pieces of sequence v / pieces and row v of its output), and may
-// run only the first levels of increment rows that hold `row_levels` levels (the pointers to the increments
-// and the tables are then advanced to the first level to run). `mode` 1: instead of the features, the
-// accumulators of the recurrence (levels x bins 0 .. D/2 of the transform, complex) are written to row v of
-// `spectra`; `mode` 2: no time step is run, the accumulators are read from `spectra` and turned into
-// features (the final transforms).
+// steps each (workgroup v then owns piece v % pieces of sequence v / pieces). `mode` 1: instead of the features, the
+// accumulators of the recurrence (sets of bins 0 .. D/2 of the transform, complex) of piece p of sequence n are
+// written at spectra + n * seq_stride + p * piece_stride (float2); `mode` 2: no time step is run, accumulators are
+// read from there and turned into features (the final transforms).
+// Transforms up to 2048 points: the sets are those of all M(M+1)/2 ranges of tensor positions (a <= l, ordered by a),
+// mode 2 joins `join` pieces per sequence, and a null `spectra` stands for the increments' own place.
+// Transforms of 4096 and 8192 points: the sets are the levels of the launch, which may be the last ones of increment
+// rows that hold `row_levels` levels (the pointers to the increments and the tables are then advanced to the first
+// level to run); mode 2 reads joined accumulators.
 struct TimeCut {
     int pieces, row_levels;
     int64_t pairs;
     float2 *spectra;
-    int mode;
-    static TimeCut whole(int64_t L, int M) { return {1, M, (L + 1) / 2, nullptr, 0}; }
+    int mode, join;
+    int64_t seq_stride, piece_stride;
+    static TimeCut whole(int64_t L, int M) { return {1, M, (L + 1) / 2, nullptr, 0, 1, 0, 0}; }
 };
 constexpr int kMaxCutLevels = 8;                       // the tuned kernels run at most eight levels
 struct PieceRows { const float2 *rows[kMaxCutLevels]; };
@@ -58,9 +62,16 @@ hipError_t launch_sketch_fft_scan(const float *dphi, const int32_t *hash, const 
 // to `joined`.
 hipError_t launch_join_pieces(const PieceRows &pieces_of_start, int64_t n_seq, int pieces, int M, int bins,
                               float2 *joined, hipStream_t stream);
+// Joins the pieces of every sequence (all M(M+1)/2 ranges of tensor positions, layout of TimeCut) and leaves the M
+// levels of the whole sequence in the place of the first piece's.
+hipError_t launch_join_chain(float2 *spectra, int64_t n_seq, int pieces, int M, int bins, int64_t seq_stride,
+                             int64_t piece_stride, hipStream_t stream);
 hipError_t launch_pack_tables(const int32_t *hash, const float *sign, int M, int F, int D, int Dout,
                               uint32_t *table, hipStream_t stream);
 bool sketch_fft_scan_is_tuned(int M, int F, int D);
+// The tuned kernel of the shape can hold the accumulators of all ranges of tensor positions (transforms up to 2048).
+bool sketch_fft_scan_joint(int M, int F, int D);
+int sketch_fft_scan_pairs_per_iteration(int D);            // pairs of steps a wavefront transforms at a time
 bool sketch_fft_scan_fits(int M, int F, int D, int order);  // false: neither kernel can run it (LDS need above a CU's)
 size_t sketch_fft_scan_table_bytes(int M, int F, int D);   // 0 when the generic kernel runs
 size_t sketch_fft_scan_lds_bytes(int M, int F, int D);

@@ -108,6 +108,43 @@ TimeCutPlan time_cut_plan(const rfsf_ts_shape *s)
     const int64_t pairs = (all_pairs + want - 1) / want;
     return {(int)((all_pairs + pairs - 1) / pairs), pairs};
 }
+
+// The cut that a launch makes. Shapes that time_cut_plan leaves whole but whose batch does not fill the chip with
+// one workgroup per sequence -- more than 64 sequences, or sequences too short for M + 1 pieces of 32 pairs -- are
+// split as well where one launch produces all ranges of positions (sketch_fft_scan_joint): the transforms are then
+// not repeated, so a few iterations of a workgroup per piece are enough to gain. The pieces' accumulators take the place of
+// their increments, so these splits need no workspace of their own; a piece has to be long enough for that.
+// A function of the shape alone, like the plan.
+constexpr int64_t kSplitSequences = 256, kSplitWorkgroups = 512;
+constexpr int kSplitIterations = 2;
+constexpr int kJoinInPlace = 8;     // more pieces are joined by a kernel of its own, which keeps several in flight
+struct SketchCut { int pieces; int64_t pairs; bool joint, in_place; };
+SketchCut sketch_cut(const rfsf_ts_shape *s)
+{
+    const TimeCutPlan plan = time_cut_plan(s);
+    const int P = transform_length(s->M, s->F, s->D);
+    const bool joint = rfsf::sketch_fft_scan_joint(s->M, s->F, P);
+    if (plan.pieces > 1) return {plan.pieces, plan.pairs, joint, false};
+    const SketchCut whole = {1, plan.pairs, false, false};
+    if (!joint || s->N < 1 || s->N > kSplitSequences || s->L < 3) return whole;
+    const int64_t slots = (s->L + 1) / 2, all_pairs = s->L / 2;
+    const int64_t floats_per_pair = (int64_t)s->M * 4 * s->F;
+    const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
+    const int fpw = rfsf::sketch_fft_scan_pairs_per_iteration(P);
+    int64_t least = (needed + floats_per_pair - 1) / floats_per_pair;                   // pairs a piece needs for them
+    if (least < kSplitIterations * fpw) least = kSplitIterations * fpw;
+    int64_t want = kSplitWorkgroups / s->N;
+    if (want > all_pairs / least) want = all_pairs / least;
+    if (want > 32) want = 32;
+    for (; want >= 2; --want) {
+        int64_t pairs = (all_pairs + want - 1) / want;
+        pairs = (pairs + fpw - 1) / fpw * fpw;                                          // whole iterations of the kernel
+        const int64_t pieces = (all_pairs + pairs - 1) / pairs;
+        const int64_t last = slots - (pieces - 1) * pairs;                              // pair slots of the last piece
+        if (pieces >= 2 && last * floats_per_pair >= needed) return {(int)pieces, pairs, true, true};
+    }
+    return whole;
+}
 // floats of one sequence's pieces: per piece and first position a the accumulators of levels a+1 .. M (bins
 // 0 .. P/2 of the transform, complex), plus the joined accumulators of the sequence
 size_t piece_floats(const rfsf_ts_shape *s, int pieces)
@@ -294,7 +331,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
     }
 
     const float inv_ls = 1.0f / lengthscale;
-    const TimeCutPlan plan = time_cut_plan(shape);
+    const SketchCut plan = sketch_cut(shape);
     // the tuned consumer takes the increments in the pair layout with the signs applied, the generic one in
     // the row layout without
     const float *producer_sign = rfsf::sketch_fft_scan_is_tuned(shape->M, shape->F, P) ? sign : nullptr;
@@ -318,9 +355,39 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
                                              out + n0 * shape->ld_out, shape->ld_out, state, stream,
                                              rfsf::TimeCut::whole(shape->L, shape->M)) != hipSuccess)
                 return RFSF_E_HIP;
+        } else if (plan.joint) {
+            // sequences cut in time: the accumulators of all ranges of tensor positions of every piece, the join (of many
+            // pieces by a launch of its own) and the final transforms (timed as one launch of the sketch kernel class)
+            rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
+            const int order = shape->order < 2 ? 1 : shape->order, bins = P / 2 + 1;
+            rfsf::TimeCut cut = {plan.pieces, shape->M, plan.pairs, nullptr, 1, plan.pieces, 0, 0};
+            if (plan.in_place) {
+                cut.piece_stride = plan.pairs * (int64_t)shape->M * 2 * shape->F;          // float2 per pair: M * 2F
+                cut.seq_stride = (shape->L + 1) / 2 * (int64_t)shape->M * 2 * shape->F;
+            } else {
+                cut.spectra = reinterpret_cast<float2 *>(state);
+                cut.piece_stride = (int64_t)shape->M * (shape->M + 1) / 2 * bins;
+                cut.seq_stride = plan.pieces * cut.piece_stride;
+            }
+            if (rfsf::launch_sketch_fft_scan(dphi, hash, sign, table, cnt, shape->L, chunk_lengths, shape->M, shape->F, P,
+                                             shape->D, order, out + n0 * shape->ld_out, shape->ld_out, nullptr, stream,
+                                             cut) != hipSuccess)
+                return RFSF_E_HIP;
+            if (plan.pieces > kJoinInPlace) {
+                if (rfsf::launch_join_chain(cut.spectra ? cut.spectra : reinterpret_cast<float2 *>(dphi), cnt, plan.pieces,
+                                            shape->M, bins, cut.seq_stride, cut.piece_stride, stream) != hipSuccess)
+                    return RFSF_E_HIP;
+                cut.join = 1;
+            }
+            cut.pieces = 1;
+            cut.mode = 2;
+            if (rfsf::launch_sketch_fft_scan(dphi, hash, sign, table, cnt, shape->L, chunk_lengths, shape->M, shape->F, P,
+                                             shape->D, order, out + n0 * shape->ld_out, shape->ld_out, nullptr, stream,
+                                             cut) != hipSuccess)
+                return RFSF_E_HIP;
         } else {
-            // sequences cut in time: the accumulators of levels a+1 .. M of every piece for a = 0 .. M-1, the join,
-            // and the final transforms of the joined accumulators (timed as one launch of the sketch kernel class)
+            // the same with one launch per first position: the accumulators of levels a+1 .. M of every piece for
+            // a = 0 .. M-1, the join, and the final transforms of the joined accumulators (timed as one launch of the sketch kernel class)
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
             rfsf::PieceRows rows = {};
             const int order = shape->order < 2 ? 1 : shape->order;
@@ -333,7 +400,8 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
                 if (rfsf::launch_sketch_fft_scan(dphi + (size_t)a * 4 * shape->F, hash, sign, table + (size_t)a * level_words,
                                                  cnt, shape->L, chunk_lengths, levels, shape->F, P, shape->D, order,
                                                  out + n0 * shape->ld_out, shape->ld_out, nullptr, stream,
-                                                 rfsf::TimeCut{plan.pieces, shape->M, plan.pairs, next, 1}) != hipSuccess)
+                                                 rfsf::TimeCut{plan.pieces, shape->M, plan.pairs, next, 1, 1,
+                                                               (int64_t)plan.pieces * levels * (int64_t)bins, levels * (int64_t)bins}) != hipSuccess)
                     return RFSF_E_HIP;
                 next += (size_t)cnt * plan.pieces * levels * bins;
             }
@@ -341,7 +409,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
                 return RFSF_E_HIP;
             if (rfsf::launch_sketch_fft_scan(dphi, hash, sign, table, cnt, shape->L, chunk_lengths, shape->M, shape->F, P,
                                              shape->D, order, out + n0 * shape->ld_out, shape->ld_out, nullptr, stream,
-                                             rfsf::TimeCut{1, shape->M, (shape->L + 1) / 2, next, 2}) != hipSuccess)
+                                             rfsf::TimeCut{1, shape->M, (shape->L + 1) / 2, next, 2, 1, shape->M * (int64_t)bins, 0}) != hipSuccess)
                 return RFSF_E_HIP;
         }
     }

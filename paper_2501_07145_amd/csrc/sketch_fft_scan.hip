@@ -302,6 +302,14 @@ bool sketch_fft_scan_is_tuned(int M, int F, int D)
     return sketch_fft_scan_lds_bytes(M, F, D) <= kLdsPerCu;
 }
 
+bool sketch_fft_scan_joint(int M, int F, int D) { return !wide_shape(D) && sketch_fft_scan_is_tuned(M, F, D); }
+
+int sketch_fft_scan_pairs_per_iteration(int D)
+{
+    TunedGeometry g;
+    return tuned_geometry(D, &g) ? g.FPW : 1;
+}
+
 bool sketch_fft_scan_fits(int M, int F, int D, int order)
 {
     return sketch_fft_scan_is_tuned(M, F, D) || order <= 2;

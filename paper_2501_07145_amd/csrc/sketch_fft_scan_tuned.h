@@ -565,16 +565,40 @@ __device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool se
 // Wavefronts per SIMD the register budget of the kernel is set for: the plan's, except that workgroups of 5 or 6
 // wavefronts with 6 to 12 transforms per wavefront (D = 100, 128, 200) get 96 registers: their workgroups then
 // find room on a CU more often (see transforms_in_flight; measured +8-15 %).
-template <int LOG2D, int M>
+//
+// The kernel for sequences cut in time (JOINT) holds M(M+1)/2 accumulators per bin instead of M. Four wavefronts per
+// SIMD (128 registers) cost it a few dozen spills of accumulators, which are touched once per iteration; from
+// kJointRegs registers of accumulators on, or with values carried from iteration to iteration, it gets the budget of two.
+constexpr int kJointRegs = 44;
+constexpr int accumulators(int M, bool JOINT) { return JOINT ? M * (M + 1) / 2 : M; }
+template <int LOG2D, int M, int NTR, bool JOINT>
 constexpr int kernel_min_waves()
 {
     using P = Plan<LOG2D>;
+    constexpr int BPT = (P::D / 2 + 64 * NTR - 1) / (64 * NTR);
+    if (JOINT) return P::kMinWaves <= 2 || NTR != M || 2 * BPT * accumulators(M, JOINT) > kJointRegs ? 2 : P::kMinWaves;
     return (P::FPW > 4 && P::FPW < 16 && (M == 5 || M == 6)) ? 5 : P::kMinWaves;
 }
+// JOINT: transforms in flight as above where the values carried from one iteration to the next (one set per first
+// position) fit the registers.
+constexpr int joint_transforms_in_flight(int M, int LOG2D, int order)
+{
+    return order == 1 && (LOG2D != 2048 || M <= 4) ? transforms_in_flight(M, LOG2D) : M;
+}
 
-template <int LOG2D, int M, int ORDER, int NTR>
+// Index of the accumulator of tensor positions a+1 .. l+1 (0-based a <= l) among those of a bin; a = 0 first.
+__host__ __device__ constexpr int acc_index(int M, int a, int l) { return a * M - a * (a - 1) / 2 + l - a; }
+
+// JOINT: the workgroup owns one piece of a sequence cut in time (TimeCut::mode 1) and runs the recurrence for
+// every first tensor position at once: per bin A^{(a..l)} += A^{(a..l-1)}(before the step) C_l for all a <= l. The
+// transforms, which are most of the work, are thus done once per step and level however many first positions
+// need them (one launch per first position, as before, did (M+1)/2 times as many: paper's longest run,
+// 10 x 1e5 steps, see csrc/join_pieces.hip for the figures). In mode 2 the same kernel joins a sequence's pieces and runs the final
+// transforms.
+template <int LOG2D, int M, int ORDER, int NTR, bool JOINT>
 __global__ __launch_bounds__(64 * NTR)
-    __attribute__((amdgpu_waves_per_eu(kernel_min_waves<LOG2D, M>(), kernel_min_waves<LOG2D, M>() > 4 ? 8 : 4))) void sketch_fft_scan_kernel(
+    __attribute__((amdgpu_waves_per_eu(kernel_min_waves<LOG2D, M, NTR, JOINT>(),
+                                       kernel_min_waves<LOG2D, M, NTR, JOINT>() > 4 ? 8 : 4))) void sketch_fft_scan_kernel(
     const float *__restrict__ dphi, const uint32_t *__restrict__ table, int64_t L,
     const int64_t *__restrict__ lengths, int F, int Dout, float *__restrict__ out, int64_t ld_out, TimeCut cut)
 {
@@ -593,7 +617,8 @@ __global__ __launch_bounds__(64 * NTR)
     // Phase 3 is compiled separately for iterations in which every item exists and has both time steps (no
     // per-item conditions and selects) when a wavefront has at most two transforms per iteration; with more the
     // extra copy costs registers.
-    constexpr bool kSplitFull = P::FPW <= 2;
+    constexpr bool kSplitFull = P::FPW <= 2 && !JOINT;
+    constexpr int kAcc = accumulators(M, JOINT), kStarts = JOINT ? M : 1;
     extern __shared__ float2 lds[];                    // [NTR][FPW][PS] slots, then the twiddle table
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wv = wave;                                     // transform of the workgroup
@@ -611,18 +636,19 @@ __global__ __launch_bounds__(64 * NTR)
     char *my_slot_bytes = reinterpret_cast<char *>(my_slot);
     // the workgroup's row of out, its sequence and its piece of that sequence (one piece: the whole sequence)
     const int64_t row_id = blockIdx.x;
-    const int64_t n = cut.pieces == 1 ? row_id : row_id / cut.pieces, piece = row_id - n * cut.pieces;
+    const int64_t n = JOINT ? row_id / cut.pieces : row_id, piece = row_id - n * cut.pieces;
     // this sequence's own number of points (variable-length batch: X is padded to L points, the steps beyond a
     // sequence's length do not exist); out-of-range entries are clamped, they are never used as addresses
     const int64_t Ln = lengths ? (lengths[n] < 1 ? 1 : (lengths[n] > L ? L : lengths[n])) : L;
     // the piece's own steps: 2 * cut.pairs of them from its first one on, fewer (or none) at the sequence's end
-    const int64_t steps_left = Ln - 1 - 2 * piece * cut.pairs;
-    const int64_t T = cut.mode == 2 || steps_left < 0 ? 0 : (steps_left < 2 * cut.pairs ? steps_left : 2 * cut.pairs);
+    const int64_t steps_left = JOINT ? Ln - 1 - 2 * piece * cut.pairs : 0;
+    const int64_t T = !JOINT ? Ln - 1
+                      : cut.mode == 2 || steps_left < 0 ? 0 : (steps_left < 2 * cut.pairs ? steps_left : 2 * cut.pairs);
     const int64_t pairs = (T + 1) / 2;
     // pair p of level l: 2F float2 at seq + l * 2 * twoF + p * pf (pair layout of the producing kernel, Lp / 2
     // pair slots per sequence with Lp = L rounded up to even)
-    const int64_t pf = (int64_t)cut.row_levels * 2 * twoF;
-    const float *seq = dphi + (n * ((L + 1) / 2) + piece * cut.pairs) * pf;
+    const int64_t pf = (int64_t)M * 2 * twoF;
+    const float *seq = dphi + (n * ((L + 1) / 2) + (JOINT ? piece * cut.pairs : 0)) * pf;
     const TableLayout tl = table_layout(D, P::GF, twoF);
     const int nload = staged(twoF) / 128;                    // direct loads per pair, 128 coordinates each
     // one level per wavefront for good: its increments, table and number of fold rounds
@@ -635,23 +661,51 @@ __global__ __launch_bounds__(64 * NTR)
     if (lg == 0) my_slot[ZS] = make_float2(0.f, 0.f);
     __syncthreads();
 
-    float2 A[BPT][M];
+    float2 A[BPT][kAcc];
 #pragma unroll
     for (int b = 0; b < BPT; ++b)
 #pragma unroll
-        for (int l = 0; l < M; ++l) A[b][l] = make_float2(0.f, 0.f);
-    // accumulators kept outside the kernel (sequences cut in time): M levels of bins 0 .. D/2 per row
-    float2 *spectra_row = cut.mode != 0 ? cut.spectra + row_id * (int64_t)(M * (D / 2 + 1)) : nullptr;
-    if (cut.mode == 2) {
-#pragma unroll
-        for (int b = 0; b < BPT; ++b) {
-            const int f = tid + NT * b;
-            if (f < NB) {
+        for (int l = 0; l < kAcc; ++l) A[b][l] = make_float2(0.f, 0.f);
+    // accumulators of a piece outside the kernel: kAcc times bins 0 .. D/2. Without a buffer of their own they take
+    // the place of the piece's increments (which the host has checked to be large enough, and which this workgroup
+    // alone reads: what other workgroups' direct loads pick up beyond their last coordinate is never used).
+    float2 *spectra_row = JOINT ? (cut.spectra ? cut.spectra : reinterpret_cast<float2 *>(const_cast<float *>(dphi))) +
+                                      n * cut.seq_stride + piece * cut.piece_stride
+                                : nullptr;
+    if constexpr (JOINT) {
+        if (cut.mode == 2) {                                 // join the pieces of the sequence, left to right
+            for (int b = 0; b < BPT; ++b) {
+                const int f = tid + NT * b;
+                if (f >= NB) continue;
+                const bool pk = kPack && f == 0;
+                float2 J[M], B[kAcc];
 #pragma unroll
                 for (int l = 0; l < M; ++l) {
-                    const float2 *sp = spectra_row + l * (D / 2 + 1);
-                    A[b][l] = kPack && f == 0 ? make_float2(sp[0].x, sp[D / 2].x) : sp[f];
+                    J[l] = spectra_row[l * (D / 2 + 1) + f];
+                    if (pk) J[l].y = spectra_row[l * (D / 2 + 1) + D / 2].x;
                 }
+                for (int s = 1; s < cut.join; ++s) {
+                    const float2 *sp = spectra_row + s * cut.piece_stride + f;
+#pragma unroll
+                    for (int q = 0; q < kAcc; ++q) B[q] = sp[q * (D / 2 + 1)];
+                    if (pk) {
+#pragma unroll
+                        for (int q = 0; q < kAcc; ++q) B[q].y = sp[q * (D / 2 + 1) + D / 2].x;
+                    }
+#pragma unroll
+                    for (int l = M - 1; l >= 0; --l) {       // descending: the lower levels are still the old ones
+                        float2 acc = make_float2(J[l].x + B[acc_index(M, 0, l)].x, J[l].y + B[acc_index(M, 0, l)].y);
+#pragma unroll
+                        for (int j = 1; j <= l; ++j) acc = cfmaf_pk(J[j - 1], B[acc_index(M, j, l)], acc, pk);
+                        J[l] = acc;
+                    }
+                }
+#pragma unroll
+                for (int bb = 0; bb < BPT; ++bb)             // (no run-time index into the register array)
+                    if (bb == b) {
+#pragma unroll
+                        for (int l = 0; l < M; ++l) A[bb][l] = J[l];
+                    }
             }
         }
     }
@@ -701,7 +755,7 @@ __global__ __launch_bounds__(64 * NTR)
     // first item of the iteration (the one of wavefront 0; streaming only)
     int lvl_first = 0;
     int64_t pair0_first = 0;
-    LevelCarry<ORDER> carry[kStream ? P::FPW : 1][kStream ? BPT : 1];
+    LevelCarry<ORDER> carry[kStream ? P::FPW : 1][kStream ? BPT : 1][kStarts];
 
     __builtin_amdgcn_s_setprio(1);
     if (kEarly && pair0 < pairs) stage_direct(lvl, pair0);
@@ -797,7 +851,7 @@ __global__ __launch_bounds__(64 * NTR)
 
         // one (pair, level) of one bin: separation of the two steps and A_LL += ... for both
         auto update_bin = [&](auto level_tag, auto packed_tag, auto full_tag, int s, int b, int j, int64_t pair0_j,
-                              LevelCarry<ORDER> &c) {
+                              LevelCarry<ORDER> (&c)[kStarts]) {
             constexpr int LL = decltype(level_tag)::value;
             constexpr bool PK = kPack && decltype(packed_tag)::value != 0;   // this wavefront holds the thread of bins 0 and D/2
             constexpr bool FULL = decltype(full_tag)::value != 0;      // every item of the iteration has both steps
@@ -813,7 +867,11 @@ __global__ __launch_bounds__(64 * NTR)
                 z = Z[P::pad(f)];
                 zc = Z[kPack ? P::pad(f > 0 ? D - f : D / 2) : P::pad(f > 0 ? D - f : 0)];
             }
-            level_step<ORDER, LL, PK>(z, zc, pk, second_step, A[b][LL], c);
+            // every first tensor position up to this level (JOINT; the whole sequence needs the first one only)
+            level_loop<JOINT ? LL + 1 : 1>([&](auto start_tag) {
+                constexpr int a = decltype(start_tag)::value;
+                level_step<ORDER, LL - a, PK>(z, zc, pk, second_step, A[b][acc_index(M, a, LL)], c[a]);
+            });
         };
         // The whole of phase 3, compiled four times: for the wavefront of the packed thread and for the others,
         // and for iterations whose items all exist and have both time steps (all but the last one or two of a
@@ -849,7 +907,7 @@ __global__ __launch_bounds__(64 * NTR)
 #pragma unroll
                     for (int b = 0; b < BPT; ++b) {
                         if (NT * BPT == NB || tid_here + NT * b < NB) {
-                            LevelCarry<ORDER> c;
+                            LevelCarry<ORDER> c[kStarts];
                             level_loop<M>([&](auto level_tag) {
                                 update_bin(level_tag, packed_tag, full_tag, s, b, decltype(level_tag)::value, pair0_now, c);
                             });
@@ -873,13 +931,13 @@ __global__ __launch_bounds__(64 * NTR)
     }
     if (kEarly) __syncthreads();
 
-    if (cut.mode == 1) {                                     // a piece of a sequence: its accumulators are the result
+    if (JOINT && cut.mode == 1) {                            // a piece of a sequence: its accumulators are the result
 #pragma unroll
         for (int b = 0; b < BPT; ++b) {
             const int f = tid + NT * b;
             if (f < NB) {
 #pragma unroll
-                for (int l = 0; l < M; ++l) {
+                for (int l = 0; l < kAcc; ++l) {
                     float2 *sp = spectra_row + l * (D / 2 + 1);
                     const float2 y = A[b][l];
                     if (kPack && f == 0) {                   // bins 0 and D/2, both real

@@ -84,7 +84,7 @@ __global__ __launch_bounds__(64 * (1 << LOG2S) * NTR) __attribute__((amdgpu_wave
 #pragma unroll
         for (int l = 0; l < M; ++l) A[b][l] = make_float2(0.f, 0.f);
     // accumulators kept outside the kernel (sequences cut in time): M levels of bins 0 .. DF/2 per row
-    float2 *spectra_row = cut.mode != 0 ? cut.spectra + row_id * (int64_t)(M * (DF / 2 + 1)) : nullptr;
+    float2 *spectra_row = cut.mode != 0 ? cut.spectra + n * cut.seq_stride + piece * cut.piece_stride : nullptr;
     if (cut.mode == 2) {
 #pragma unroll
         for (int b = 0; b < BPT; ++b) {

@@ -1,0 +1,57 @@
+"""Batches that leave the chip idle with one workgroup per sequence are split in time even where rfsf_ts_time_cut
+reports no cut (sequences too short for its pieces, or 65 .. 256 of them); the pieces' accumulators take the place of
+their increments. The sizes sit at the edges of the rule: two pieces, last pieces of one iteration, accumulators that
+barely fit their piece, one level, the largest batch that is split and the first that is not."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_07145_amd as rfsf
+from tests.parity import FP32_BLOCK_TOL, block_errors
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(seed, N, L, d, M, F, D):
+    rng = np.random.default_rng(seed)
+    X = np.cumsum(rng.standard_normal((N, L, d)) * 0.2, axis=1).astype(np.float32)
+    W = rng.standard_normal((M, d, F)).astype(np.float32)
+    hash_ = rng.integers(0, D, size=(M, 2 * F)).astype(np.int32)
+    sign = (2.0 * rng.integers(0, 2, size=(M, 2 * F)) - 1.0).astype(np.float32)
+    return X, W, hash_, sign
+
+
+@pytest.mark.parametrize("N,L,d,M,F,D,order", [
+    (70, 131, 3, 5, 50, 100, 1),       # two pieces of the exact 100-point transform, even number of steps
+    (100, 250, 3, 5, 50, 100, 1),
+    (1, 100, 8, 4, 128, 256, 1),       # one sequence, six pieces
+    (1, 2100, 3, 8, 64, 128, 1),       # eight levels
+    (5, 200, 4, 3, 30, 64, 1),
+    (3, 300, 4, 1, 30, 64, 1),         # one level: the pieces' sums are added up
+    (3, 41, 2, 8, 300, 1024, 1),       # pieces as short as their accumulators allow
+    (2, 30, 2, 5, 256, 1024, 1),       # items dealt to eight wavefronts
+    (2, 41, 2, 6, 250, 1000, 1),
+    (4, 90, 5, 3, 250, 500, 1),
+    (4, 90, 5, 5, 250, 500, 1),
+    (2, 33, 3, 4, 300, 300, 1),        # linear route in 2048 points
+    (1, 24, 3, 5, 600, 2048, 1),
+    (256, 70, 2, 2, 64, 128, 1),       # the largest batch that is split
+    (257, 70, 2, 2, 64, 128, 1),       # the smallest that is not
+    (1, 3, 2, 3, 64, 64, 1),           # a single pair
+    (3, 131, 3, 4, 50, 100, 2),
+    (2, 50, 3, 5, 300, 1024, 2),
+    (2, 131, 3, 3, 50, 200, 3),
+    (1, 40, 3, 4, 200, 512, 3),
+])
+def test_split_batches_match_the_oracle(oracle, N, L, d, M, F, D, order):
+    X, W, hash_, sign = _case(N + L + D, N, L, d, M, F, D)
+    rng = np.random.default_rng(L)
+    for lengths in (None, np.where(rng.random(N) < 0.4, L, rng.integers(1, L + 1, size=N)).astype(np.int64)):
+        got = rfsf.rfsf_ts_features(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(hash_).cuda(),
+                                    torch.from_numpy(sign).cuda(), 1.5, D, order=order,
+                                    lengths=None if lengths is None else torch.from_numpy(lengths).cuda()).cpu().numpy()
+        want = oracle.features_ragged(X, np.full(N, L, dtype=np.int64) if lengths is None else lengths, W, hash_, sign,
+                                      1.5, D, order=order)
+        err = block_errors(got, want, M, D)
+        print(f"N={N} L={L} M={M} F={F} D={D} order {order}: block errors {err}")
+        assert np.all(err <= FP32_BLOCK_TOL)
