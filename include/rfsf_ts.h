@@ -19,16 +19,14 @@
  *     nothing that the caller sees.
  *   - Work is enqueued on `hip_stream` (a hipStream_t passed as void*; NULL is the
  *     default stream). The calls do not synchronise the device; results are
- *     ready when the stream has drained. (rfsf_ts_features builds its sketch tables
- *     on a stream the library owns, forked from and joined back into `hip_stream`
- *     with events, so the ordering seen by the caller is that of `hip_stream`.)
+ *     ready when the stream has drained.
  *   - Return value: RFSF_OK (0) or a negative RFSF_E_* code. After an argument
  *     error (every code except RFSF_E_HIP) nothing has been enqueued and no output byte
  *     has been written. After RFSF_E_HIP earlier kernels of the call may have been
  *     enqueued; the outputs and the workspace are then unspecified, but nothing of the
  *     library touches them any more once `hip_stream` has drained.
- *   - Threads: the library keeps process-wide state (the side stream and its two events,
- *     the optional profiling record) without locks. Calls from several host threads must
+ *   - Threads: the library keeps process-wide state (the optional profiling record, the
+ *     LDS limits already raised) without locks. Calls from several host threads must
  *     be serialised by the caller; calls from one thread on several streams are fine.
  */
 #ifndef RFSF_TS_H

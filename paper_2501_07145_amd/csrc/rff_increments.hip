@@ -3,15 +3,21 @@
 // and their increments along time (the factors nabla phi_m of Sec. 3.2, eq. (rfsf)).
 #include "rfsf_internal.h"
 #include "sincos.h"
+#include "sketch_tables.h"
 
 // The increments are written once and read once, by the next kernel, long after they have left the caches:
 // non-temporal stores (measured: the projection kernel of Large 8.2 -> 6.4 ms, Long 3 % faster, Medium unchanged;
 // on Small, which would fit the last-level cache, the producer loses what the consumer gains).
-typedef float rfsf_float2v __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ void store_stream(float *p, float a, float b)
+// Only where a frequency slab's rows start and end on lines of 128 bytes, though (F a multiple of 8): of lines that two
+// wavefronts write in part, a non-temporal store sends each part to memory by itself, while an ordinary one lets the
+// cache join them (`STREAM`).
+typedef float rfsf_float4v __attribute__((ext_vector_type(4)));
+template <bool STREAM>
+__device__ __forceinline__ void store_increments(float *p, float c0, float c1, float s0, float s1)
 {
-    rfsf_float2v v = {a, b};
-    __builtin_nontemporal_store(v, reinterpret_cast<rfsf_float2v *>(p));
+    rfsf_float4v v = {c0, c1, s0, s1};
+    if (STREAM) __builtin_nontemporal_store(v, reinterpret_cast<rfsf_float4v *>(p));
+    else *reinterpret_cast<rfsf_float4v *>(p) = v;
 }
 
 namespace rfsf {
@@ -91,20 +97,21 @@ __device__ __forceinline__ void sincos_difference_store(
     carry_s = below_s;
 }
 
-// Pair layout: increments 2P and 2P+1 of a coordinate are stored next to each other as a float2 at
-// ((P * M + m) * 2F + a), the form in which the tuned consumer loads them straight into LDS as the real and
-// imaginary parts of one transform input. Tile row r is row gt + r of the (padded) row space and its increment
+// Pair layout: increments 2P and 2P+1 of a coordinate are stored next to each other as a float2, the form in which
+// the tuned consumer loads them straight into LDS as the real and imaginary parts of one transform input; cosine and
+// sine of frequency f sit at positions 2f and 2f + 1 of the (P, m) row of 2F float2, so that a lane stores 16 bytes and
+// a half-wavefront 512 in one piece (with the cosines of all frequencies ahead of the sines, 256-byte pieces of
+// 8F-byte runs, rows of F = 190 and 250 were written at half the rate of F = 512). Tile row r is row gt + r of the (padded) row space and its increment
 // has index k = gt - 1 + r with gt - 1 even, so a lane's rows i = 0,1 and i = 2,3 form pairs. A pair is stored
 // when its even index lies in [k_lo, k_hi].
-template <typename AngleOf>
+template <bool STREAM, typename AngleOf>
 __device__ __forceinline__ void sincos_difference_store_pairs(
     AngleOf angle, const ScaledCoeffs &coeffs, float &carry_c, float &carry_s, int half, bool f_ok,
-    int64_t gt, int64_t k_lo, int64_t k_hi, int64_t pair_floats, int F, float *__restrict__ level_base, int f)
+    int64_t gt, int64_t k_lo, int64_t k_hi, int64_t pair_floats, float *__restrict__ level_base, int f)
 {
     const int64_t k_tile = gt - 1;                                  // even; may be -2 for the very first tile
-    float *cos_base = level_base + (k_tile / 2) * pair_floats;      // uniform; pair_floats = M * 4F
-    float *sin_base = cos_base + 2 * F;
-    const uint32_t lane_off = 2u * (uint32_t)f + (uint32_t)(2 * half) * (uint32_t)pair_floats;
+    float *base = level_base + (k_tile / 2) * pair_floats;          // uniform; pair_floats = M * 4F
+    const uint32_t lane_off = 4u * (uint32_t)f + (uint32_t)(2 * half) * (uint32_t)pair_floats;
     float below_c = carry_c, below_s = carry_s;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -126,8 +133,7 @@ __device__ __forceinline__ void sincos_difference_store_pairs(
             const int64_t k0 = k_tile + 8 * q + 4 * half + 2 * j;  // lane-uniform per half-wavefront
             if (f_ok && k0 >= k_lo && k0 <= k_hi) {
                 const uint32_t off = lane_off + (uint32_t)(4 * q + j) * (uint32_t)pair_floats;
-                store_stream(cos_base + off, dc[2 * j], dc[2 * j + 1]);
-                store_stream(sin_base + off, ds[2 * j], ds[2 * j + 1]);
+                store_increments<STREAM>(base + off, dc[2 * j], dc[2 * j + 1], ds[2 * j], ds[2 * j + 1]);
             }
         }
     }
@@ -250,8 +256,7 @@ __global__ __launch_bounds__(256) void rff_increments_valu_pairs(
             if (k >= k_lo) {
                 if (k & 1) {
                     float *dst = dphi + ((k / 2) * M + m) * 4 * F;
-                    *reinterpret_cast<float2 *>(dst + 2 * a) = make_float2(hold_c, co - pc);
-                    *reinterpret_cast<float2 *>(dst + 2 * (F + a)) = make_float2(hold_s, s - ps);
+                    store_increments<false>(dst + 4 * a, hold_c, co - pc, hold_s, s - ps);
                 } else {
                     hold_c = co - pc;
                     hold_s = s - ps;
@@ -279,22 +284,30 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // one row early, at the odd row g0 - 1, so that a lane's four rows split into two whole pairs. Signs cost
 // nothing: flipping both coordinates of a frequency is a negative scale, flipping the sine alone is a negated
 // frequency vector (sin(-x) = -sin x, cos(-x) = cos x), flipping the cosine alone is both.
-template <int KSTEPS, bool PAIRED>     // ceil(d / 2) padded: channels 2*KSTEPS
+// With a table job (pair layout, first launch of a call) the first M workgroups build the sketch tables instead: the
+// projection does not need them, and the launch and the two cross-stream waits that a build beside it costs are saved.
+template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 2) padded: channels 2*KSTEPS
 __global__ __launch_bounds__(256) void rff_increments_mfma(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
-    float *__restrict__ dphi)
+    float *__restrict__ dphi, TableJob job)
 {
     constexpr int KP = 2 * KSTEPS;              // padded channel count
     constexpr int XS = KP | 1;                  // odd LDS row stride: conflict-free A reads
-    __shared__ float xs[2 * kRowsPerTile * XS];
+    extern __shared__ __attribute__((aligned(16))) char rff_lds[];
+    float *xs = reinterpret_cast<float *>(rff_lds);         // [2][kRowsPerTile][XS]
+    unsigned block = blockIdx.x;
+    if (PAIRED && job.table) {
+        if (block < (unsigned)M) return build_level_table(job, (int)block, reinterpret_cast<int *>(rff_lds));
+        block -= (unsigned)M;
+    }
     // Block order: the (level, frequency slab) index runs fastest, so that the workgroups that write the
     // same rows are dispatched together, which keeps the writes of one DRAM page close in time (also with
     // few slabs: four slabs of 1000 short sequences run 17 % faster this way than row range first).
     const int fblocks = (F + 127) / 128;
     const int nslab = M * fblocks;
-    const int slab = (int)(blockIdx.x % nslab);
-    const int64_t range = blockIdx.x / nslab;
+    const int slab = (int)(block % nslab);
+    const int64_t range = block / nslab;
     const int m = slab / fblocks;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, col = lane & 31;
@@ -363,8 +376,8 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
             acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xt[col * XS + 2 * kk + half], breg[kk], acc, 0, 0, 0);
 
         if (PAIRED)
-            sincos_difference_store_pairs([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, gt, g0,
-                                          min(g0 + rows_per_block - 2, rows - 2), 2 * rf, F, level_base, f);
+            sincos_difference_store_pairs<STREAM>([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, gt, g0,
+                                          min(g0 + rows_per_block - 2, rows - 2), 2 * rf, level_base, f);
         else
             sincos_difference_store([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, nrow, gt, g0,
                                     rf, F, level_base, f);
@@ -387,20 +400,25 @@ __device__ __forceinline__ float bf16_value(uint32_t b) { return __uint_as_float
 // W is rounded to bf16; X is split into two bf16 terms, hi = bf16(x) and lo = bf16(x - hi),
 // and both are multiplied with the same W, so that the time difference of the angles does not
 // inherit the 2^-9 rounding of x itself. Same tiling and epilogue as the fp32 kernel.
-template <int KSTEPS, bool PAIRED>     // ceil(d / 16): channels padded to 16*KSTEPS; PAIRED as in the fp32 kernel
+template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 16): channels padded to 16*KSTEPS; PAIRED as in the fp32 kernel
 __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
-    float *__restrict__ dphi)
+    float *__restrict__ dphi, TableJob job)
 {
     constexpr int KP = 16 * KSTEPS;
     constexpr int XS = KP + 8;                  // bf16 elements per LDS row (16-byte padded)
-    __shared__ __attribute__((aligned(16))) uint16_t xhi[2 * kRowsPerTile * XS];
-    __shared__ __attribute__((aligned(16))) uint16_t xlo[2 * kRowsPerTile * XS];
+    extern __shared__ __attribute__((aligned(16))) char rff_lds[];
+    uint16_t *xhi = reinterpret_cast<uint16_t *>(rff_lds), *xlo = xhi + 2 * kRowsPerTile * XS;   // [2][kRowsPerTile][XS] each
+    unsigned block = blockIdx.x;                            // as in the fp32 kernel
+    if (PAIRED && job.table) {
+        if (block < (unsigned)M) return build_level_table(job, (int)block, reinterpret_cast<int *>(rff_lds));
+        block -= (unsigned)M;
+    }
     const int fblocks = (F + 127) / 128;                              // same block order as the fp32 kernel
     const int nslab = M * fblocks;
-    const int slab = (int)(blockIdx.x % nslab);
-    const int64_t range = blockIdx.x / nslab;
+    const int slab = (int)(block % nslab);
+    const int64_t range = block / nslab;
     const int m = slab / fblocks;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, col = lane & 31;
@@ -483,8 +501,8 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
             acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ah, breg[kk], acc, 0, 0, 0);
         }
         if (PAIRED)
-            sincos_difference_store_pairs([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s,
-                                          half, f_ok, gt, g0, min(g0 + rows_per_block - 2, rows - 2), 2 * rf, F,
+            sincos_difference_store_pairs<STREAM>([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s,
+                                          half, f_ok, gt, g0, min(g0 + rows_per_block - 2, rows - 2), 2 * rf,
                                           level_base, f);
         else
             sincos_difference_store([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s, half,
@@ -498,11 +516,27 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
 
 hipError_t launch_rff_increments(const float *X, const float *W, const float *sign, float inv_lengthscale,
                                  int64_t n_seq, int64_t L, int d, int M, int F, bool bf16,
-                                 float *dphi, hipStream_t stream)
+                                 float *dphi, hipStream_t stream, const TableJob *tables)
 {
     const bool paired = sign != nullptr;
     const int64_t Lp = (L + 1) & ~(int64_t)1;
     const int64_t rows = paired ? n_seq * Lp : n_seq * L;
+    const bool matrix_cores = bf16 || d <= 64;        // bf16: the caller (API layer) has checked d <= 128
+    // Workgroups that build tables need LDS that the others do not use, but every workgroup of the launch is given it:
+    // up to kSharedTableLds five workgroups (20 wavefronts) still fit a CU, beyond that the tables get a launch
+    // of their own.
+    constexpr size_t kSharedTableLds = 32 * 1024;
+    TableJob job = {};
+    size_t table_lds = 0;
+    if (tables) {
+        table_lds = table_lds_bytes(tables->F, tables->Dout);
+        if (paired && matrix_cores && rows >= 2 && table_lds <= kSharedTableLds) {
+            job = *tables;
+        } else {
+            const hipError_t e = launch_build_tables(*tables, M, stream);
+            if (e != hipSuccess) return e;
+        }
+    }
     if (rows < 2) return hipSuccess;
     // Row layout: 255 increments per workgroup (256 rows of phi = eight tiles; consecutive workgroups share one
     // row). Pair layout: 254 increments, the eight tiles start one row early; problems that would give fewer
@@ -518,58 +552,51 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     }
     const int64_t nblk = paired ? (rows - 2) / rows_per_block + 1 : (rows - 1 + rows_per_block - 1) / rows_per_block;
     const float scale = 0.5f / sqrtf((float)F);    // the consumer's two-for-one FFT wants halved increments
-    if (nblk * M * ((F + 127) / 128) > 0x7fffffffLL) return hipErrorInvalidValue;
-    if (bf16) {            // the caller (API layer) has checked d <= 128
-        const int fb = (F + 127) / 128;
-        dim3 grid((unsigned)(nblk * M * fb));
-#define RFSF_LAUNCH_BF16(KS)                                                                                     \
+    if (nblk * M * ((F + 127) / 128) + (job.table ? M : 0) > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(nblk * M * ((F + 127) / 128) + (job.table ? M : 0)));
+    const bool whole_lines = F % 8 == 0;           // 16 bytes per frequency and pair of steps
+#define RFSF_LAUNCH(KERNEL, KS, PAIRED, STREAM, TILE)                                                                \
+    hipLaunchKernelGGL((KERNEL<KS, PAIRED, STREAM>), grid, dim3(256), job.table && table_lds > (TILE) ? table_lds : (TILE), \
+                       stream, X, W, sign, inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi, job)
+#define RFSF_LAUNCH_MFMA(KERNEL, KS, TILE)                                                                           \
     do {                                                                                                         \
-        if (paired)                                                                                              \
-            hipLaunchKernelGGL((rff_increments_mfma_bf16<KS, true>), grid, dim3(256), 0, stream, X, W, sign,     \
-                               inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi);              \
-        else                                                                                                     \
-            hipLaunchKernelGGL((rff_increments_mfma_bf16<KS, false>), grid, dim3(256), 0, stream, X, W, sign,    \
-                               inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi);              \
+        if (!paired) RFSF_LAUNCH(KERNEL, KS, false, false, TILE);                                                \
+        else if (whole_lines) RFSF_LAUNCH(KERNEL, KS, true, true, TILE);                                         \
+        else RFSF_LAUNCH(KERNEL, KS, true, false, TILE);                                                         \
     } while (0)
+#define RFSF_LAUNCH_FP32(KS) RFSF_LAUNCH_MFMA(rff_increments_mfma, KS, sizeof(float) * 2 * kRowsPerTile * ((2 * KS) | 1))
+#define RFSF_LAUNCH_BF16(KS) RFSF_LAUNCH_MFMA(rff_increments_mfma_bf16, KS, sizeof(uint16_t) * 4 * kRowsPerTile * (16 * KS + 8))
+    if (bf16) {
         if (d <= 16) RFSF_LAUNCH_BF16(1);
         else if (d <= 32) RFSF_LAUNCH_BF16(2);
         else if (d <= 64) RFSF_LAUNCH_BF16(4);
         else RFSF_LAUNCH_BF16(8);
-#undef RFSF_LAUNCH_BF16
         return hipGetLastError();
     }
     if (d <= 64) {
-        const int fb = (F + 127) / 128;
-        dim3 grid((unsigned)(nblk * M * fb));
-#define RFSF_LAUNCH_MFMA(KS)                                                                                     \
-    do {                                                                                                         \
-        if (paired)                                                                                              \
-            hipLaunchKernelGGL((rff_increments_mfma<KS, true>), grid, dim3(256), 0, stream, X, W, sign,          \
-                               inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi);              \
-        else                                                                                                     \
-            hipLaunchKernelGGL((rff_increments_mfma<KS, false>), grid, dim3(256), 0, stream, X, W, sign,         \
-                               inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi);              \
-    } while (0)
-        if (d <= 4) RFSF_LAUNCH_MFMA(2);
-        else if (d <= 8) RFSF_LAUNCH_MFMA(4);
-        else if (d <= 18) RFSF_LAUNCH_MFMA(9);
-        else if (d <= 32) RFSF_LAUNCH_MFMA(16);
-        else RFSF_LAUNCH_MFMA(32);
-#undef RFSF_LAUNCH_MFMA
+        if (d <= 4) RFSF_LAUNCH_FP32(2);
+        else if (d <= 8) RFSF_LAUNCH_FP32(4);
+        else if (d <= 18) RFSF_LAUNCH_FP32(9);
+        else if (d <= 32) RFSF_LAUNCH_FP32(16);
+        else RFSF_LAUNCH_FP32(32);
         return hipGetLastError();
     }
+#undef RFSF_LAUNCH_FP32
+#undef RFSF_LAUNCH_BF16
+#undef RFSF_LAUNCH_MFMA
+#undef RFSF_LAUNCH
     const int fblocks = (F + 255) / 256;
     if ((int64_t)M * fblocks > 65535) return hipErrorInvalidValue;
     if (paired) {
         const int64_t nb = (rows - 2) / 254 + 1;
         if (nb > 0x7fffffffLL) return hipErrorInvalidValue;
-        dim3 grid((unsigned)nb, (unsigned)(M * fblocks));
-        hipLaunchKernelGGL(rff_increments_valu_pairs, grid, dim3(256), sizeof(float) * kRowsPerTile * d, stream,
+        const dim3 pairs_grid((unsigned)nb, (unsigned)(M * fblocks));
+        hipLaunchKernelGGL(rff_increments_valu_pairs, pairs_grid, dim3(256), sizeof(float) * kRowsPerTile * d, stream,
                            X, W, sign, inv_lengthscale, scale, rows, L, Lp, d, M, F, dphi);
         return hipGetLastError();
     }
-    dim3 grid((unsigned)nblk, (unsigned)(M * fblocks));
-    hipLaunchKernelGGL(rff_increments_valu, grid, dim3(256), sizeof(float) * kRowsPerTile * d, stream,
+    const dim3 rows_grid((unsigned)nblk, (unsigned)(M * fblocks));
+    hipLaunchKernelGGL(rff_increments_valu, rows_grid, dim3(256), sizeof(float) * kRowsPerTile * d, stream,
                        X, W, inv_lengthscale, scale, rows, d, M, F, rows_per_block, dphi);
     return hipGetLastError();
 }

@@ -36,11 +36,14 @@ struct PieceRows { const float2 *rows[kMaxCutLevels]; };
 // for `n_seq` sequences starting at X (already offset to the chunk), halved.
 // sign == nullptr: row layout, element (g, m, a) of row g = n * L + t at ((g * M + m) * 2F + a), no signs.
 // sign != nullptr ([M, 2F], the CountSketch signs): pair layout with the signs applied. With Lp = L rounded up
-// to even, increment k = n * Lp + t of coordinate a sits at ((((k / 2) * M + m) * 2F + a) * 2 + k % 2): the
-// two increments of a pair of consecutive time steps are one float2. n_seq * Lp * M * 2F floats in all.
+// to even, increment k = n * Lp + t of coordinate a sits at ((((k / 2) * M + m) * 2F + p) * 2 + k % 2), p = 2a for a
+// cosine (a < F) and 2(a - F) + 1 for a sine: the two increments of a pair of consecutive time steps are one float2.
+// n_seq * Lp * M * 2F floats in all.
+// `tables` (may be null): the sketch tables are built as well, by workgroups of the same launch where that pays.
+struct TableJob;
 hipError_t launch_rff_increments(const float *X, const float *W, const float *sign, float inv_lengthscale,
                                  int64_t n_seq, int64_t L, int d, int M, int F, bool bf16,
-                                 float *dphi, hipStream_t stream);
+                                 float *dphi, hipStream_t stream, const TableJob *tables);
 
 // Steps 3-4: CountSketch, FFT-domain level recursion over time, inverse transform; writes
 // (D is the transform length, a power of two; Dout <= D the number of buckets per level: equal to D,
@@ -49,7 +52,7 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
 // `lengths` (may be null: all L) holds each sequence's own number of points, X being padded to L.
 // `state` is scratch for the generic kernel: sketch_fft_scan_state_bytes (accumulators, and the work buffers
 // when they do not fit in LDS).
-// `table` (sketch_fft_scan_table_bytes, filled by launch_pack_tables once per call) feeds the tuned kernel.
+// `table` (sketch_fft_scan_table_bytes, built once per call) feeds the tuned kernel.
 // `cut` (tuned kernels only): how the launch cuts the sequences in time and which levels of the increment rows
 // it runs; TimeCut::whole(L, M) for the plain case.
 hipError_t launch_sketch_fft_scan(const float *dphi, const int32_t *hash, const float *sign,
@@ -66,8 +69,9 @@ hipError_t launch_join_pieces(const PieceRows &pieces_of_start, int64_t n_seq, i
 // levels of the whole sequence in the place of the first piece's.
 hipError_t launch_join_chain(float2 *spectra, int64_t n_seq, int pieces, int M, int bins, int64_t seq_stride,
                              int64_t piece_stride, hipStream_t stream);
-hipError_t launch_pack_tables(const int32_t *hash, const float *sign, int M, int F, int D, int Dout,
-                              uint32_t *table, hipStream_t stream);
+// The job of building the tables of a shape (csrc/sketch_tables.h); false if its kernel needs none.
+bool sketch_table_job(const int32_t *hash, int M, int F, int D, int Dout, uint32_t *table, TableJob *job);
+hipError_t launch_build_tables(const TableJob &job, int M, hipStream_t stream);
 bool sketch_fft_scan_is_tuned(int M, int F, int D);
 // The tuned kernel of the shape can hold the accumulators of all ranges of tensor positions (transforms up to 2048).
 bool sketch_fft_scan_joint(int M, int F, int D);

@@ -1,6 +1,7 @@
 // C ABI of librfsf_ts: argument checks, chunking over sequences, kernel launches.
 #include "../../include/rfsf_ts.h"
 #include "rfsf_internal.h"
+#include "sketch_tables.h"
 
 #include <cmath>
 #include <vector>
@@ -182,36 +183,6 @@ int64_t chunk_for(const rfsf_ts_shape *s, size_t bytes)
     return (int64_t)((bytes - fixed) / (incr + state));
 }
 
-// The sketch tables depend only on hash/sign, not on the increments, so they are built on a side
-// stream (default priority) while the first projection kernel runs. The side stream first waits for
-// everything already enqueued on the caller's stream (an earlier call may still be reading the
-// tables), and the caller's stream waits for the tables before the first sketch kernel.
-// Process-wide, created on first use; if anything fails the build simply runs on the caller's stream.
-struct SideStream {
-    hipStream_t stream = nullptr;
-    hipEvent_t begin = nullptr, done = nullptr;
-    int device = -1;            // the device the stream and events belong to
-    bool usable = false;
-};
-SideStream &side_stream()
-{
-    static SideStream s;
-    static bool tried = false;
-    if (!tried) {
-        tried = true;
-        s.usable = hipGetDevice(&s.device) == hipSuccess &&
-                   hipStreamCreateWithFlags(&s.stream, hipStreamNonBlocking) == hipSuccess &&
-                   hipEventCreateWithFlags(&s.begin, hipEventDisableTiming) == hipSuccess &&
-                   hipEventCreateWithFlags(&s.done, hipEventDisableTiming) == hipSuccess;
-    }
-    return s;
-}
-bool side_stream_matches_current_device(const SideStream &s)
-{
-    int dev = -1;
-    return s.usable && hipGetDevice(&dev) == hipSuccess && dev == s.device;
-}
-
 }  // namespace
 
 extern "C" const char *rfsf_ts_strerror(int code)
@@ -266,8 +237,7 @@ extern "C" int rfsf_ts_time_cut(const rfsf_ts_shape *shape, int32_t *pieces, int
 
 namespace {
 // Body of rfsf_ts_features. `may_create` = false keeps the call free of anything that creates runtime
-// objects: the tables are then built on the caller's stream (no library-owned stream or events) and no
-// profiling events are recorded.
+// objects: no profiling events are recorded.
 int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *lengths, const float *W,
                   const int32_t *hash, const float *sign, float lengthscale, float *out, void *workspace,
                   size_t workspace_bytes, void *hip_stream, bool may_create)
@@ -306,30 +276,8 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
     float *dphi = reinterpret_cast<float *>(p_incr);
     float *state = reinterpret_cast<float *>(p_state);
     uint32_t *table = reinterpret_cast<uint32_t *>(p_table);
-    static SideStream no_side;
-    SideStream &side = may_create ? side_stream() : no_side;
-    bool tables_on_side = false;
-    // Error return after the fork: the caller's stream first waits for whatever the side stream still does
-    // (the table build writes the workspace), so that the workspace is quiet once `stream` has drained.
-    auto fail = [&]() {
-        if (tables_on_side) {
-            if (hipStreamWaitEvent(stream, side.done, 0) != hipSuccess) (void)hipStreamSynchronize(side.stream);
-        }
-        return RFSF_E_HIP;
-    };
-    if (side_stream_matches_current_device(side) && hipEventRecord(side.begin, stream) == hipSuccess &&
-        hipStreamWaitEvent(side.stream, side.begin, 0) == hipSuccess) {
-        const hipError_t e = rfsf::launch_pack_tables(hash, sign, shape->M, shape->F, P, shape->D, table, side.stream);
-        if (hipEventRecord(side.done, side.stream) != hipSuccess) {
-            (void)hipStreamSynchronize(side.stream);
-            return RFSF_E_HIP;
-        }
-        tables_on_side = true;
-        if (e != hipSuccess) return fail();
-    } else if (rfsf::launch_pack_tables(hash, sign, shape->M, shape->F, P, shape->D, table, stream) != hipSuccess) {
-        return RFSF_E_HIP;
-    }
-
+    rfsf::TableJob tables;                  // built with the first chunk's increments
+    const bool has_tables = rfsf::sketch_table_job(hash, shape->M, shape->F, P, shape->D, table, &tables);
     const float inv_ls = 1.0f / lengthscale;
     const SketchCut plan = sketch_cut(shape);
     // the tuned consumer takes the increments in the pair layout with the signs applied, the generic one in
@@ -340,12 +288,9 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
         {
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream, may_create);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, producer_sign, inv_ls, cnt, shape->L, shape->d,
-                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream) != hipSuccess)
-                return fail();
-        }
-        if (tables_on_side) {           // join: the tables are needed from here on
-            if (hipStreamWaitEvent(stream, side.done, 0) != hipSuccess) return fail();
-            tables_on_side = false;
+                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream,
+                                            n0 == 0 && has_tables ? &tables : nullptr) != hipSuccess)
+                return RFSF_E_HIP;
         }
         const int64_t *chunk_lengths = lengths ? lengths + n0 : nullptr;
         if (plan.pieces == 1) {
@@ -624,7 +569,7 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
         {
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, nullptr, inv_ls, cnt, shape->L, shape->d,
-                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream) != hipSuccess)
+                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr) != hipSuccess)
                 return RFSF_E_HIP;
         }
         {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (rows whose increment does not

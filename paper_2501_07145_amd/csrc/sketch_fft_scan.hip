@@ -11,6 +11,7 @@
 #include "sketch_fft_scan_tuned.h"
 #include "sketch_fft_scan_wide.h"
 #include "sketch_fft_scan_dispatch.h"
+#include "sketch_tables.h"
 
 namespace rfsf {
 namespace {
@@ -155,73 +156,10 @@ __global__ __launch_bounds__(256) void sketch_fft_scan_generic(
     }
 }
 
-// Builds the per-level tables of the tuned kernel (layout: tuned::TableLayout). One workgroup per
-// level. rank(a) = number of earlier coordinates of the level in the same bucket; ranks 0 and 1
-// go to the gather words, ranks >= 2 become fold entries, ordered by rank and padded so that a
-// round of G entries never mixes two ranks (hence never repeats a bucket).
-constexpr int kTableThreads = 1024;
-
-__global__ __launch_bounds__(1024) void build_tables_kernel(
-    const int32_t *__restrict__ hash, const float *__restrict__ sign, int twoF, int D, int Dout, int G, uint32_t coord_base,
-    uint32_t zero_off, uint32_t *__restrict__ table)
+__global__ __launch_bounds__(kTableThreads) void build_tables_kernel(TableJob job)
 {
     extern __shared__ __attribute__((aligned(16))) int table_scratch[];
-    const int tf4 = (twoF + 3) & ~3;              // keeps the arrays 16-byte aligned
-    int *h = table_scratch, *rk = h + tf4, *cls = rk + tf4, *src0 = cls + tf4 + 4, *src1 = src0 + D;
-    __shared__ int max_rank, n_rounds;
-    const int m = blockIdx.x, tid = threadIdx.x;
-    const tuned::TableLayout tl = tuned::table_layout(D, G, twoF);
-    uint32_t *tab = table + (int64_t)m * tl.words;
-    (void)sign;                           // applied by the producing kernel
-
-    for (int a = tid; a < twoF; a += kTableThreads) h[a] = ((hash[(int64_t)m * twoF + a] % Dout) + Dout) % Dout;
-    for (int e = tid; e < D; e += kTableThreads) { src0[e] = -1; src1[e] = -1; }
-    for (int r = tid; r <= twoF; r += kTableThreads) cls[r] = 0;
-    if (tid == 0) max_rank = 0;
-    __syncthreads();
-    for (int a = tid; a < twoF; a += kTableThreads) {
-        const int ha = h[a];
-        int r = 0, a2 = 0;
-        for (; a2 + 8 <= a; a2 += 8) {              // wide LDS reads keep the loop off the LDS latency
-            const int4 u = *reinterpret_cast<const int4 *>(h + a2), w = *reinterpret_cast<const int4 *>(h + a2 + 4);
-            r += (u.x == ha) + (u.y == ha) + (u.z == ha) + (u.w == ha) + (w.x == ha) + (w.y == ha) + (w.z == ha) + (w.w == ha);
-        }
-        for (; a2 < a; ++a2) r += h[a2] == ha;
-        rk[a] = r;
-        if (r == 0) src0[h[a]] = a;
-        else if (r == 1) src1[h[a]] = a;
-        else { atomicAdd(&cls[r], 1); atomicMax(&max_rank, r); }
-    }
-    __syncthreads();
-    if (tid == 0) {                       // class sizes -> start offsets, each class padded to G
-        int off = 0;
-        for (int r = 2; r <= max_rank; ++r) {
-            const int c = cls[r];
-            cls[r] = off;
-            off += (c + G - 1) / G * G;
-        }
-        n_rounds = off / G;
-        tab[0] = (uint32_t)n_rounds;
-    }
-    __syncthreads();
-    for (int i = tid; i < n_rounds * G; i += kTableThreads) tab[tl.fold + i] = zero_off | (tuned::kFoldPad << 16);
-    for (int e = tid; e < D; e += kTableThreads) {
-        const uint32_t s0 = src0[e] >= 0 ? coord_base + (uint32_t)src0[e] * 8u : zero_off;
-        const uint32_t s1 = src1[e] >= 0 ? coord_base + (uint32_t)src1[e] * 8u : zero_off;
-        tab[tl.gather + e] = s0 | (s1 << 16);
-    }
-    __syncthreads();                      // padding entries are in place before the real ones land
-    for (int a = tid; a < twoF; a += kTableThreads) {
-        const int r = rk[a];
-        if (r < 2) continue;
-        int idx = 0, a2 = 0;
-        for (; a2 + 8 <= a; a2 += 8) {
-            const int4 u = *reinterpret_cast<const int4 *>(rk + a2), w = *reinterpret_cast<const int4 *>(rk + a2 + 4);
-            idx += (u.x == r) + (u.y == r) + (u.z == r) + (u.w == r) + (w.x == r) + (w.y == r) + (w.z == r) + (w.w == r);
-        }
-        for (; a2 < a; ++a2) idx += rk[a2] == r;
-        tab[tl.fold + cls[r] + idx] = (coord_base + (uint32_t)a * 8u) | ((coord_base + (uint32_t)src0[h[a]] * 8u) << 16);
-    }
+    build_level_table(job, (int)blockIdx.x, table_scratch);
 }
 
 __global__ void fill_trivial_kernel(float *out, int64_t n_seq, int64_t ld_out, int64_t ncols)
@@ -259,7 +197,6 @@ namespace {
 struct TunedGeometry { int G /* entries per fold round */, PD, FPW, NTWL; };
 // transforms of 4096 and 8192: the kernel of sketch_fft_scan_wide.h
 bool wide_shape(int D) { return D == 4096 || D == 8192; }
-size_t table_builder_lds(int twoF, int D) { return sizeof(int) * (size_t)(3 * ((twoF + 3) & ~3) + 4 + 2 * D); }
 bool tuned_geometry(int D, TunedGeometry *g)
 {
     if (wide_shape(D)) {
@@ -298,7 +235,8 @@ bool sketch_fft_scan_is_tuned(int M, int F, int D)
     // F <= 4032: the staging area (2F rounded up to 128 coordinates) and the zero float2 behind it are
     // addressed with 16-bit byte offsets
     if (M > 8 || F > 4032 || !tuned_geometry(D, &g)) return false;
-    if (wide_shape(D) && table_builder_lds(2 * F, D) > kLdsPerCu) return false;
+    // (the limit of an earlier table builder, kept so that the route of a shape stays what it was)
+    if (wide_shape(D) && sizeof(int) * (size_t)(3 * ((2 * F + 3) & ~3) + 4 + 2 * D) > kLdsPerCu) return false;
     return sketch_fft_scan_lds_bytes(M, F, D) <= kLdsPerCu;
 }
 
@@ -322,13 +260,21 @@ size_t sketch_fft_scan_table_bytes(int M, int F, int D)
     return sizeof(uint32_t) * (size_t)M * tuned::table_layout(D, g.G, 2 * F).words;
 }
 
-hipError_t launch_pack_tables(const int32_t *hash, const float *sign, int M, int F, int D, int Dout,
-                              uint32_t *table, hipStream_t stream)
+bool sketch_table_job(const int32_t *hash, int M, int F, int D, int Dout, uint32_t *table, TableJob *job)
 {
     TunedGeometry g;
-    if (!sketch_fft_scan_is_tuned(M, F, D) || !tuned_geometry(D, &g)) return hipSuccess;   // generic kernel: no table
-    const int twoF = 2 * F;
-    const size_t lds = table_builder_lds(twoF, D);
+    if (!sketch_fft_scan_is_tuned(M, F, D) || !tuned_geometry(D, &g)) return false;       // generic kernel: no table
+    const tuned::TableLayout tl = tuned::table_layout(D, g.G, 2 * F);
+    // byte offsets within a slot: of position 0 and of the float2 that is always zero
+    const uint32_t coord_base = wide_shape(D) ? 8u * tuned::kWideStageBase : 0u;
+    const uint32_t zero_off = wide_shape(D) ? 0u : 8u * (uint32_t)tuned::zero_slot(g.PD, 2 * F);
+    *job = {hash, table, F, D, Dout, g.G, tl.words, tl.gather, tl.fold, coord_base, zero_off};
+    return true;
+}
+
+hipError_t launch_build_tables(const TableJob &job, int M, hipStream_t stream)
+{
+    const size_t lds = table_lds_bytes(job.F, job.Dout);
     if (lds > 64 * 1024) {
         static size_t granted = 0;
         if (lds > granted) {
@@ -338,11 +284,7 @@ hipError_t launch_pack_tables(const int32_t *hash, const float *sign, int M, int
             granted = lds;
         }
     }
-    // byte offsets within a slot: of coordinate 0 and of the float2 that is always zero
-    const uint32_t coord_base = wide_shape(D) ? 8u * tuned::kWideStageBase : 0u;
-    const uint32_t zero_off = wide_shape(D) ? 0u : 8u * (uint32_t)tuned::zero_slot(g.PD, twoF);
-    hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)M), dim3(kTableThreads), lds, stream, hash, sign, twoF, D, Dout,
-                       g.G, coord_base, zero_off, table);
+    hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)M), dim3(kTableThreads), lds, stream, job);
     return hipGetLastError();
 }
 
