@@ -116,7 +116,9 @@ TimeCutPlan time_cut_plan(const rfsf_ts_shape *s)
 // not repeated, so a few iterations of a workgroup per piece are enough to gain. The pieces' accumulators take the place of
 // their increments, so these splits need no workspace of their own; a piece has to be long enough for that.
 // A function of the shape alone, like the plan.
-constexpr int64_t kSplitSequences = 256, kSplitWorkgroups = 512;
+// Two pieces of each of 150 sequences of 500 points (512 buckets, two workgroups per CU): 443 -> 354 us; of 200 sequences
+// where a CU holds one workgroup (500 buckets, five levels): 463 -> 491, hence as many pieces as CUs hold.
+constexpr int64_t kSplitSequences = 256, kCUs = 256;
 constexpr int kSplitIterations = 2;
 constexpr int kJoinInPlace = 8;     // more pieces are joined by a kernel of its own, which keeps several in flight
 struct SketchCut { int pieces; int64_t pairs; bool joint, in_place; };
@@ -134,7 +136,7 @@ SketchCut sketch_cut(const rfsf_ts_shape *s)
     const int fpw = rfsf::sketch_fft_scan_pairs_per_iteration(P);
     int64_t least = (needed + floats_per_pair - 1) / floats_per_pair;                   // pairs a piece needs for them
     if (least < kSplitIterations * fpw) least = kSplitIterations * fpw;
-    int64_t want = kSplitWorkgroups / s->N;
+    int64_t want = kCUs * rfsf::sketch_fft_scan_joint_per_cu(s->M, P) / s->N;
     if (want > all_pairs / least) want = all_pairs / least;
     if (want > 32) want = 32;
     for (; want >= 2; --want) {

@@ -242,6 +242,8 @@ bool sketch_fft_scan_is_tuned(int M, int F, int D)
 
 bool sketch_fft_scan_joint(int M, int F, int D) { return !wide_shape(D) && sketch_fft_scan_is_tuned(M, F, D); }
 
+int sketch_fft_scan_joint_per_cu(int M, int D) { return tuned::joint_workgroups_per_cu(M, D); }
+
 int sketch_fft_scan_pairs_per_iteration(int D)
 {
     TunedGeometry g;

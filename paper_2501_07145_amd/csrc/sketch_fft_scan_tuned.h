@@ -576,8 +576,17 @@ constexpr int kernel_min_waves()
 {
     using P = Plan<LOG2D>;
     constexpr int BPT = (P::D / 2 + 64 * NTR - 1) / (64 * NTR);
-    if (JOINT) return P::kMinWaves <= 2 || NTR != M || 2 * BPT * accumulators(M, JOINT) > kJointRegs ? 2 : P::kMinWaves;
-    return (P::FPW > 4 && P::FPW < 16 && (M == 5 || M == 6)) ? 5 : P::kMinWaves;
+    if (JOINT && (P::kMinWaves <= 2 || NTR != M || 2 * BPT * accumulators(M, JOINT) > kJointRegs)) return 2;
+    // (JOINT: 96 registers cost spills; D = 100 with five levels 139 -> 117 us all the same, on 1000 sequences of 100
+    // points, but D = 128 192 -> 223, with six levels 228 -> 308)
+    return P::FPW > 4 && P::FPW < 16 && (M == 5 || M == 6) && (!JOINT || (LOG2D == 100 && M == 5)) ? 5 : P::kMinWaves;
+}
+// Workgroups of the JOINT kernel that a CU holds: one where eight wavefronts, or five and more of the budget of two
+// wavefronts per SIMD, make up the workgroup; two otherwise (by LDS).
+constexpr int joint_workgroups_per_cu(int M, int D)
+{
+    const bool dealt = D == 1000 || D == 1024 || D == 500 || D == 512;
+    return D == 2048 || M >= 7 || (dealt && M >= 5) || ((D == 1000 || D == 1024) && M <= 3) ? 1 : 2;
 }
 // JOINT: transforms in flight as above where the values carried from one iteration to the next (one set per first
 // position) fit the registers.
@@ -585,6 +594,24 @@ constexpr int joint_transforms_in_flight(int M, int LOG2D, int order)
 {
     return order == 1 && (LOG2D != 2048 || M <= 4) ? transforms_in_flight(M, LOG2D) : M;
 }
+
+// Short transforms: a wavefront carries FPW = 4 .. 16 pairs of steps per iteration, while their D/2 + 1 bins occupy
+// a fraction of the workgroup's threads, which would take the pairs one after the other (D = 100, five levels: 51 of 320
+// threads, 12 pairs). The kernel for sequences cut in time therefore cuts its piece once more, into as many groups as
+// bins fit the threads: FPW / groups transforms of an iteration belong to each, and each has its own threads and
+// accumulators in phase 3. The groups are joined in LDS at the end (which has to hold all but the first's).
+constexpr int joint_groups(int M, int D, int FPW, int PD)
+{
+    const int NB = D / 2 + 1, Q = M * (M + 1) / 2;
+    for (int g = FPW; g > 1; --g)
+        if (FPW % g == 0 && g * NB <= 64 * M && (g - 1) * Q * NB <= M * FPW * slot_stride(PD, 2)) return g;
+    return 1;
+}
+// ... and from three groups on that is also the faster way for a whole sequence, for all that it advances
+// M(M+1)/2 accumulators instead of M. (1000 sequences of 100 points: D = 64 82 -> 67 us with four levels, D = 100
+// 65 -> 56 with three, 248 -> 225 with eight, D = 128 218 -> 192 with five; D = 200, whose bins fill more of the threads,
+// 209 -> 257 with five and 389 -> 402 with eight.)
+constexpr bool grouped(int M, int D, int FPW, int PD) { return D <= 128 && joint_groups(M, D, FPW, PD) >= 3; }
 
 // Index of the accumulator of tensor positions a+1 .. l+1 (0-based a <= l) among those of a bin; a = 0 first.
 __host__ __device__ constexpr int acc_index(int M, int a, int l) { return a * M - a * (a - 1) / 2 + l - a; }
@@ -614,6 +641,8 @@ __global__ __launch_bounds__(64 * NTR)
     constexpr int D = P::D, NT = 64 * NTR;
     constexpr bool kPack = (D / 2) % NT == 0;
     constexpr int NB = kPack ? D / 2 : D / 2 + 1, BPT = (NB + NT - 1) / NT;
+    constexpr int GR = JOINT && !kStream ? joint_groups(M, D, P::FPW, P::PD) : 1, SPG = P::FPW / GR;   // groups; transforms of each
+    static_assert(GR == 1 || (BPT == 1 && !kPack), "a thread of a group owns one bin");
     // Phase 3 is compiled separately for iterations in which every item exists and has both time steps (no
     // per-item conditions and selects) when a wavefront has at most two transforms per iteration; with more the
     // extra copy costs registers.
@@ -644,7 +673,14 @@ __global__ __launch_bounds__(64 * NTR)
     const int64_t steps_left = JOINT ? Ln - 1 - 2 * piece * cut.pairs : 0;
     const int64_t T = !JOINT ? Ln - 1
                       : cut.mode == 2 || steps_left < 0 ? 0 : (steps_left < 2 * cut.pairs ? steps_left : 2 * cut.pairs);
-    const int64_t pairs = (T + 1) / 2;
+    const int64_t all_pairs = (T + 1) / 2;
+    // pairs of a group (of the first ones; the last may have fewer or none): what the iterations run over
+    const int64_t pairs = GR > 1 ? (all_pairs + GR - 1) / GR : all_pairs;
+    const int64_t last_grp = GR > 1 && pairs > 0 ? (all_pairs - 1) / pairs : 0, last_in_grp = all_pairs - 1 - last_grp * pairs;
+    // this thread's group in phase 3, its bin (f = tid + NT * b where there is one group) and its group's steps
+    const int grp = GR > 1 ? tid / NB : 0, bin = GR > 1 ? tid - grp * NB : tid;
+    const int64_t T_left = GR > 1 ? T - 2 * grp * pairs : T;
+    const int64_t T_grp = GR > 1 ? (grp >= GR || T_left < 0 ? 0 : (T_left < 2 * pairs ? T_left : 2 * pairs)) : T;
     // pair p of level l: 2F float2 at seq + l * 2 * twoF + p * pf (pair layout of the producing kernel, Lp / 2
     // pair slots per sequence with Lp = L rounded up to even)
     const int64_t pf = (int64_t)M * 2 * twoF;
@@ -717,7 +753,8 @@ __global__ __launch_bounds__(64 * NTR)
     auto stage_direct = [&](int lvl, int64_t pair0) {
 #pragma unroll
         for (int s = 0; s < P::FPW; ++s) {
-            const int64_t p = pair0 + s < pairs ? pair0 + s : pairs - 1;
+            int64_t p = GR > 1 ? (s / SPG) * pairs + pair0 + s % SPG : pair0 + s;
+            if (p >= all_pairs) p = all_pairs - 1;
             const float *src = (kStream ? seq + (int64_t)lvl * 2 * twoF : seq_fixed) + p * pf + 4 * lane;
             float2 *dst = wave_lds + s * PS;
             for (int j = 0; j < nload; ++j)
@@ -732,7 +769,7 @@ __global__ __launch_bounds__(64 * NTR)
     // (Measured: 3-4 % on D = 1024 and 2048 with five levels; with 32 float2 -- D = 512, four levels -- it no
     // longer pays, and loading the next iteration's table words early as well costs more registers than it hides.)
     constexpr int ZREGS = P::FPW * BPT * NTR * 2;
-    constexpr bool kEarly = ZREGS <= (P::kMinWaves <= 2 ? 64 : 24);    // (a plan with twice the registers per wavefront affords more)
+    constexpr bool kEarly = GR == 1 && ZREGS <= (P::kMinWaves <= 2 ? 64 : 24);    // (a plan with twice the registers per wavefront affords more)
     uint32_t gw[P::R], fw[kFoldInRegs];
 
     // The item of this wavefront: level and first pair of its transform in the current iteration (a transform
@@ -749,7 +786,7 @@ __global__ __launch_bounds__(64 * NTR)
                 p0 += P::FPW;
             }
         } else {
-            p0 += P::FPW;
+            p0 += SPG;
         }
     };
     // first item of the iteration (the one of wavefront 0; streaming only)
@@ -778,10 +815,11 @@ __global__ __launch_bounds__(64 * NTR)
             // 1a. staging
             if (!kEarly) stage_direct(lvl, pair0);
             __builtin_amdgcn_s_waitcnt(0x0f70);                 // vmcnt(0): the direct loads have landed
-            if ((T & 1) && pair0 + P::FPW >= pairs) {
-                // odd number of increments, last pair: its second step does not exist; what the producer left in
-                // its place (the increment across the sequence boundary) is cleared so that it cannot touch the result
-                float2 *st = wave_lds + (int)(pairs - 1 - pair0) * PS;
+            // odd number of increments, last pair: its second step does not exist; what the producer left in
+            // its place (the increment across the sequence boundary) is cleared so that it cannot touch the result
+            const int64_t last = last_in_grp - pair0;
+            if ((T & 1) && last >= 0 && last < SPG) {
+                float2 *st = wave_lds + (int)(last_grp * SPG + last) * PS;
                 for (int a = lane; a < twoF; a += 64) st[a].y = 0.f;
             }
             transform_fence<P>();
@@ -916,10 +954,31 @@ __global__ __launch_bounds__(64 * NTR)
                 }
             }
         };
+        // groups: every thread advances its bin by its group's pairs (existence of pairs and steps is per lane)
+        auto phase3_groups = [&]() {
+#pragma unroll 1
+            for (int i = 0; i < SPG; ++i) {
+                const int64_t p = pair0_now + i;
+                if (2 * p >= T_grp) break;
+                const float2 *Z = lds + (size_t)(grp * SPG + i) * PS;
+                const int fi = P::pad(bin), fc = P::pad(bin > 0 ? D - bin : 0);
+                LevelCarry<ORDER> c[kStarts];
+                level_loop<M>([&](auto level_tag) {
+                    constexpr int LL = decltype(level_tag)::value;
+                    const float2 z = Z[(size_t)LL * P::FPW * PS + fi], zc = Z[(size_t)LL * P::FPW * PS + fc];
+                    level_loop<LL + 1>([&](auto start_tag) {
+                        constexpr int a = decltype(start_tag)::value;
+                        level_step<ORDER, LL - a, false>(z, zc, false, 2 * p + 1 < T_grp, A[0][acc_index(M, a, LL)], c[a]);
+                    });
+                });
+            }
+        };
         // full: the last pair of the last pair group that this iteration touches has a second step
         const int64_t last_pair0 = kStream ? pair0_first + ((lvl_first + NTR - 1) / M) * P::FPW : pair0_now;
         const bool full = 2 * (last_pair0 + P::FPW) - 1 < T;
-        if (kPack && wave == 0) {
+        if constexpr (GR > 1) {
+            if (grp < GR) phase3_groups();
+        } else if (kPack && wave == 0) {
             if (kSplitFull && full) phase3(LevelTag<1>{}, LevelTag<1>{});
             else phase3(LevelTag<1>{}, LevelTag<0>{});
         } else {
@@ -930,6 +989,39 @@ __global__ __launch_bounds__(64 * NTR)
         if (!kEarly) __syncthreads();
     }
     if (kEarly) __syncthreads();
+
+    if constexpr (GR > 1) {                                  // join the groups, left to right, in the threads of the first
+        if (cut.mode != 2) {
+            if (grp > 0 && grp < GR) {
+                float2 *dst = lds + (size_t)(grp - 1) * kAcc * NB + bin;
+#pragma unroll
+                for (int q = 0; q < kAcc; ++q) dst[q * NB] = A[0][q];
+            }
+            __syncthreads();
+            if (grp == 0) {
+#pragma unroll 1
+                for (int g = 1; g < GR; ++g) {
+                    const float2 *src = lds + (size_t)(g - 1) * kAcc * NB + bin;
+                    float2 B[kAcc];
+#pragma unroll
+                    for (int q = 0; q < kAcc; ++q) B[q] = src[q * NB];
+#pragma unroll
+                    for (int a = 0; a < M; ++a) {
+                        if (a > 0 && cut.mode == 0) break;   // the whole sequence: only ranges from position 1 on
+#pragma unroll
+                        for (int l = M - 1; l >= a; --l) {
+                            const float2 x = A[0][acc_index(M, a, l)], y = B[acc_index(M, a, l)];
+                            float2 acc = make_float2(x.x + y.x, x.y + y.y);
+#pragma unroll
+                            for (int j = a; j < l; ++j) acc = cfmaf(A[0][acc_index(M, a, j)], B[acc_index(M, j + 1, l)], acc);
+                            A[0][acc_index(M, a, l)] = acc;
+                        }
+                    }
+                }
+            }
+            __syncthreads();
+        }
+    }
 
     if (JOINT && cut.mode == 1) {                            // a piece of a sequence: its accumulators are the result
 #pragma unroll
