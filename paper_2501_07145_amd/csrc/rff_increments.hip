@@ -62,14 +62,14 @@ constexpr int kRowsPerTile = 32;
 template <typename AngleOf>
 __device__ __forceinline__ void sincos_difference_store(
     AngleOf angle, const ScaledCoeffs &coeffs, float &carry_c, float &carry_s, int half, bool f_ok, int nrow,
-    int64_t gt, int64_t g0, int64_t rf, int F, float *__restrict__ level_base, int f)
+    int64_t gt, int64_t g0, int64_t rf, int F, float *__restrict__ dphi, int cos_at)
 {
     // One store path for every tile: scalar base + 32-bit lane offset. The first row of a range has no
     // increment to store (it belongs to the previous range) and rows past the end of the range do not
     // exist; both cases are lane-uniform per row and folded into one predicate per store.
-    float *cos_base = level_base + (gt - 1) * rf;               // uniform (gt = g0: row -1 is never stored)
+    float *cos_base = dphi + (gt - 1) * rf;               // uniform (gt = g0: row -1 is never stored)
     float *sin_base = cos_base + F;
-    const uint32_t lane_off = (uint32_t)f + (uint32_t)(4 * half) * (uint32_t)rf;
+    const uint32_t lane_off = (uint32_t)cos_at + (uint32_t)(4 * half) * (uint32_t)rf;
     const int first = gt > g0 ? 0 : 1;                          // first tile row whose increment is ours
     float below_c = carry_c, below_s = carry_s;                 // lower half: partner's previous block
 #pragma unroll
@@ -107,11 +107,11 @@ __device__ __forceinline__ void sincos_difference_store(
 template <bool STREAM, typename AngleOf>
 __device__ __forceinline__ void sincos_difference_store_pairs(
     AngleOf angle, const ScaledCoeffs &coeffs, float &carry_c, float &carry_s, int half, bool f_ok,
-    int64_t gt, int64_t k_lo, int64_t k_hi, int64_t pair_floats, float *__restrict__ level_base, int f)
+    int64_t gt, int64_t k_lo, int64_t k_hi, int64_t pair_floats, float *__restrict__ dphi, int column)
 {
     const int64_t k_tile = gt - 1;                                  // even; may be -2 for the very first tile
-    float *base = level_base + (k_tile / 2) * pair_floats;          // uniform; pair_floats = M * 4F
-    const uint32_t lane_off = 4u * (uint32_t)f + (uint32_t)(2 * half) * (uint32_t)pair_floats;
+    float *base = dphi + (k_tile / 2) * pair_floats;                // uniform; pair_floats = M * 4F
+    const uint32_t lane_off = 4u * (uint32_t)column + (uint32_t)(2 * half) * (uint32_t)pair_floats;
     float below_c = carry_c, below_s = carry_s;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -272,8 +272,10 @@ __global__ __launch_bounds__(256) void rff_increments_valu_pairs(
 
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-// Matrix-core kernel (fp32 operands). A workgroup of four wavefronts owns 128 frequencies of
-// one level and a range of flattened rows; wavefront w owns frequencies 32w..32w+31. Per tile
+// Matrix-core kernel (fp32 operands). A workgroup of four wavefronts owns 128 of the M * F columns (level, frequency)
+// and a range of flattened rows; wavefront w owns columns 32w..32w+31. A slab may span levels (one level per slab left
+// 78 of 128 lanes without a frequency at F = 50, 66 of 256 at F = 190), and in the pair layout the columns
+// are the order in memory, so that what neighbouring wavefronts store is contiguous. Per tile
 // of 32 rows, theta[32 rows x 32 freq] = X_tile[32 x d] * W[d x 32] is accumulated with
 // v_mfma_f32_32x32x2f32 (A = rows x channels from LDS, B = channels x frequencies held in
 // registers for the whole row range). In the result a lane holds one frequency (lane % 32)
@@ -304,15 +306,14 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
     // Block order: the (level, frequency slab) index runs fastest, so that the workgroups that write the
     // same rows are dispatched together, which keeps the writes of one DRAM page close in time (also with
     // few slabs: four slabs of 1000 short sequences run 17 % faster this way than row range first).
-    const int fblocks = (F + 127) / 128;
-    const int nslab = M * fblocks;
+    const int nslab = (M * F + 127) / 128;
     const int slab = (int)(block % nslab);
     const int64_t range = block / nslab;
-    const int m = slab / fblocks;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, col = lane & 31;
-    const int f = (slab % fblocks) * 128 + wave * 32 + col;           // this lane's frequency
-    const bool f_ok = f < F;
+    const int column = slab * 128 + wave * 32 + col;                  // this lane's column: level m, frequency f
+    const bool f_ok = column < M * F;
+    const int m = f_ok ? column / F : 0, f = f_ok ? column - m * F : 0;
     const int64_t g0 = range * rows_per_block;
     // last row whose phi we need (PAIRED: row `rows` does not exist and is redirected)
     const int64_t g1 = PAIRED ? min(rows, g0 + rows_per_block) : min(rows - 1, g0 + rows_per_block);
@@ -332,7 +333,6 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
         breg[kk] = (f_ok && k < d) ? W[((int64_t)m * d + k) * F + f] * wscale : 0.f;
     }
     float carry_c = 0.f, carry_s = 0.f;         // row 31 of the previous tile (lower half-wavefront)
-    float *level_base = dphi + (int64_t)m * (PAIRED ? 4 : 2) * F;     // uniform; the lane's frequency is added per store
     const ScaledCoeffs coeffs = scaled_coeffs(flip_c ? -scale : scale);
     const int64_t first_row = PAIRED ? g0 - 1 : g0;                    // row of tile row 0 of the first tile
     const PaddedRowBase row_base = PAIRED ? padded_row_base(first_row, rows, Lp) : PaddedRowBase{0, 0, 0};
@@ -377,10 +377,10 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
 
         if (PAIRED)
             sincos_difference_store_pairs<STREAM>([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, gt, g0,
-                                          min(g0 + rows_per_block - 2, rows - 2), 2 * rf, level_base, f);
+                                          min(g0 + rows_per_block - 2, rows - 2), 2 * rf, dphi, column);
         else
             sincos_difference_store([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, nrow, gt, g0,
-                                    rf, F, level_base, f);
+                                    rf, F, dphi, m * 2 * F + f);
         if (more) put_tile(xs + (cur ^ 1) * (kRowsPerTile * XS));
         __syncthreads();
     }
@@ -415,15 +415,14 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
         if (block < (unsigned)M) return build_level_table(job, (int)block, reinterpret_cast<int *>(rff_lds));
         block -= (unsigned)M;
     }
-    const int fblocks = (F + 127) / 128;                              // same block order as the fp32 kernel
-    const int nslab = M * fblocks;
+    const int nslab = (M * F + 127) / 128;                            // same block order as the fp32 kernel
     const int slab = (int)(block % nslab);
     const int64_t range = block / nslab;
-    const int m = slab / fblocks;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int half = lane >> 5, col = lane & 31;
-    const int f = (slab % fblocks) * 128 + wave * 32 + col;
-    const bool f_ok = f < F;
+    const int column = slab * 128 + wave * 32 + col;
+    const bool f_ok = column < M * F;
+    const int m = f_ok ? column / F : 0, f = f_ok ? column - m * F : 0;
     const int64_t g0 = range * rows_per_block;
     const int64_t g1 = PAIRED ? min(rows, g0 + rows_per_block) : min(rows - 1, g0 + rows_per_block);
     const int64_t rf = (int64_t)M * 2 * F;
@@ -449,7 +448,6 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
         breg[kk] = __builtin_bit_cast(bf16x8, make_uint4(w[0], w[1], w[2], w[3]));
     }
     float carry_c = 0.f, carry_s = 0.f;
-    float *level_base = dphi + (int64_t)m * (PAIRED ? 4 : 2) * F;     // uniform; the lane's frequency is added per store
     const ScaledCoeffs coeffs = scaled_coeffs(flip_c ? -scale : scale);
     const int64_t first_row = PAIRED ? g0 - 1 : g0;
     const PaddedRowBase row_base = PAIRED ? padded_row_base(first_row, rows, Lp) : PaddedRowBase{0, 0, 0};
@@ -503,10 +501,10 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
         if (PAIRED)
             sincos_difference_store_pairs<STREAM>([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s,
                                           half, f_ok, gt, g0, min(g0 + rows_per_block - 2, rows - 2), 2 * rf,
-                                          level_base, f);
+                                          dphi, column);
         else
             sincos_difference_store([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s, half,
-                                    f_ok, nrow, gt, g0, rf, F, level_base, f);
+                                    f_ok, nrow, gt, g0, rf, F, dphi, m * 2 * F + f);
         if (more) put_tile(cur ^ 1);
         __syncthreads();
     }
@@ -544,16 +542,18 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     // (two) tiles instead (1000 sequences of 100 points: 0.095 -> 0.080 ms; large problems are faster with
     // eight, except that 126 increments measured 7 % faster on 10000 x 200 x 17 -- and 11 % slower on
     // 2000 x 2000 x 32 and 50000 x 64 x 64).
+    const int64_t slabs = ((int64_t)M * F + 127) / 128;
     int64_t rows_per_block = paired ? 254 : 255;
     if (paired) {
-        const int64_t wgs = ((rows - 2) / 254 + 1) * M * ((F + 127) / 128);
+        const int64_t wgs = ((rows - 2) / 254 + 1) * slabs;
         if (wgs < 2048) rows_per_block = 62;
         else if (wgs < 4096) rows_per_block = 126;
     }
     const int64_t nblk = paired ? (rows - 2) / rows_per_block + 1 : (rows - 1 + rows_per_block - 1) / rows_per_block;
     const float scale = 0.5f / sqrtf((float)F);    // the consumer's two-for-one FFT wants halved increments
-    if (nblk * M * ((F + 127) / 128) + (job.table ? M : 0) > 0x7fffffffLL) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(nblk * M * ((F + 127) / 128) + (job.table ? M : 0)));
+    const int64_t blocks = nblk * slabs + (job.table ? M : 0);
+    if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)blocks);
     const bool whole_lines = F % 8 == 0;           // 16 bytes per frequency and pair of steps
 #define RFSF_LAUNCH(KERNEL, KS, PAIRED, STREAM, TILE)                                                                \
     hipLaunchKernelGGL((KERNEL<KS, PAIRED, STREAM>), grid, dim3(256), job.table && table_lds > (TILE) ? table_lds : (TILE), \
