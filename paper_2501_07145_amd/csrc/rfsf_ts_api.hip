@@ -119,8 +119,10 @@ TimeCutPlan time_cut_plan(const rfsf_ts_shape *s)
 // Two pieces of each of 150 sequences of 500 points (512 buckets, two workgroups per CU): 443 -> 354 us; of 200 sequences
 // where a CU holds one workgroup (500 buckets, five levels): 463 -> 491, hence as many pieces as CUs hold.
 constexpr int64_t kSplitSequences = 256, kCUs = 256;
-constexpr int kSplitIterations = 2;
-constexpr int kJoinInPlace = 8;     // more pieces are joined by a kernel of its own, which keeps several in flight
+// An iteration of a workgroup alone on its CU takes about 3 us, a piece in the join 0.3: with p pairs in all and pieces of
+// i iterations, 3 i + 0.3 p / (i * pairs per iteration) is least at i^2 = p / (10 * pairs per iteration).
+constexpr int64_t kSplitPieces = 64, kJoinsPerIteration = 10;
+constexpr int kJoinInPlace = 16;    // more pieces are joined by a kernel of its own, which keeps several in flight
 struct SketchCut { int pieces; int64_t pairs; bool joint, in_place; };
 SketchCut sketch_cut(const rfsf_ts_shape *s)
 {
@@ -134,17 +136,17 @@ SketchCut sketch_cut(const rfsf_ts_shape *s)
     const int64_t floats_per_pair = (int64_t)s->M * 4 * s->F;
     const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
     const int fpw = rfsf::sketch_fft_scan_pairs_per_iteration(P);
-    int64_t least = (needed + floats_per_pair - 1) / floats_per_pair;                   // pairs a piece needs for them
-    if (least < kSplitIterations * fpw) least = kSplitIterations * fpw;
-    int64_t want = kCUs * rfsf::sketch_fft_scan_joint_per_cu(s->M, P) / s->N;
-    if (want > all_pairs / least) want = all_pairs / least;
-    if (want > 32) want = 32;
-    for (; want >= 2; --want) {
-        int64_t pairs = (all_pairs + want - 1) / want;
-        pairs = (pairs + fpw - 1) / fpw * fpw;                                          // whole iterations of the kernel
-        const int64_t pieces = (all_pairs + pairs - 1) / pairs;
-        const int64_t last = slots - (pieces - 1) * pairs;                              // pair slots of the last piece
-        if (pieces >= 2 && last * floats_per_pair >= needed) return {(int)pieces, pairs, true, true};
+    int64_t most = kCUs * rfsf::sketch_fft_scan_joint_per_cu(s->M, P) / s->N;           // pieces that fill the chip
+    if (most > kSplitPieces) most = kSplitPieces;
+    // iterations of the kernel per piece: the fewest that keep to `most`, and no fewer than balance the join
+    int64_t its = (all_pairs + most * fpw - 1) / (most > 0 ? most * fpw : 1);
+    while (its * its * kJoinsPerIteration * fpw < all_pairs) ++its;
+    for (; most >= 2; ++its) {
+        const int64_t pairs = its * fpw, pieces = (all_pairs + pairs - 1) / pairs;
+        if (pieces < 2) break;
+        // every piece, the last one too, has to hold its accumulators
+        if (pairs * floats_per_pair >= needed && (slots - (pieces - 1) * pairs) * floats_per_pair >= needed)
+            return {(int)pieces, pairs, true, true};
     }
     return whole;
 }

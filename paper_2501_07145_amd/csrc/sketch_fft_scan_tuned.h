@@ -308,12 +308,24 @@ struct WaveFft {
     int rbase;
     const float2 *twl;      // LDS twiddle table of the radix-16 passes, entry ((set*(r-1) + t-1)*G + lg)
 
-    __device__ __forceinline__ void init(int lg, float2 *twl_table)
+    // `roots`: D float2 of LDS that are free until the caller's next use of them. The register twiddles are picked out of
+    // a table of the D-th roots of unity: computed where they are needed, D = 64 and 128 have 12 and 14 inlined sine-cosine
+    // codes per lane, fetched and run once by every workgroup. Ends with a workgroup barrier.
+    __device__ __forceinline__ void init(int lg, float2 *twl_table, float2 *roots)
     {
         rbase = P::pad(lg);
         twl = twl_table + lg;
-        init_pass<0>(lg);
+        if constexpr (P::tw_off(P::NP) > 0) {
+            for (int i = threadIdx.x; i < P::D; i += blockDim.x) {
+                float s, c;
+                sincospif(-2.0f * (float)i / (float)P::D, &s, &c);
+                roots[i] = make_float2(c, s);
+            }
+        }
         fill_table<1>(twl_table);
+        __syncthreads();
+        init_pass<0>(lg, roots);
+        if constexpr (P::tw_off(P::NP) > 0) __syncthreads();
     }
 
     // Workgroup-cooperative fill of the LDS twiddle table; the caller synchronises afterwards.
@@ -336,7 +348,7 @@ struct WaveFft {
     }
 
     template <int PI>
-    __device__ __forceinline__ void init_pass(int lg)
+    __device__ __forceinline__ void init_pass(int lg, const float2 *roots)
     {
         if constexpr (PI < P::NP) {
             constexpr int r = P::radix(PI), Ns = P::Ns(PI), NB = P::R / r;
@@ -352,14 +364,10 @@ struct WaveFft {
                 for (int u = 0; u < NSETS; ++u) {
                     const int k = (lg + P::G * u) % Ns;
 #pragma unroll
-                    for (int t = 1; t < r; ++t) {
-                        float s, c;
-                        sincospif(-2.0f * (float)(k * t) / (float)(Ns * r), &s, &c);
-                        tw[P::tw_off(PI) + u * (r - 1) + (t - 1)] = make_float2(c, s);
-                    }
+                    for (int t = 1; t < r; ++t) tw[P::tw_off(PI) + u * (r - 1) + (t - 1)] = roots[k * t * (P::D / (Ns * r))];
                 }
             }
-            init_pass<PI + 1>(lg);
+            init_pass<PI + 1>(lg, roots);
         }
     }
 
@@ -665,7 +673,7 @@ __global__ __launch_bounds__(64 * NTR)
     char *my_slot_bytes = reinterpret_cast<char *>(my_slot);
     // the workgroup's row of out, its sequence and its piece of that sequence (one piece: the whole sequence)
     const int64_t row_id = blockIdx.x;
-    const int64_t n = JOINT ? row_id / cut.pieces : row_id, piece = row_id - n * cut.pieces;
+    const int64_t n = JOINT ? blockIdx.x / (unsigned)cut.pieces : row_id, piece = row_id - n * cut.pieces;
     // this sequence's own number of points (variable-length batch: X is padded to L points, the steps beyond a
     // sequence's length do not exist); out-of-range entries are clamped, they are never used as addresses
     const int64_t Ln = lengths ? (lengths[n] < 1 ? 1 : (lengths[n] > L ? L : lengths[n])) : L;
@@ -676,7 +684,10 @@ __global__ __launch_bounds__(64 * NTR)
     const int64_t all_pairs = (T + 1) / 2;
     // pairs of a group (of the first ones; the last may have fewer or none): what the iterations run over
     const int64_t pairs = GR > 1 ? (all_pairs + GR - 1) / GR : all_pairs;
-    const int64_t last_grp = GR > 1 && pairs > 0 ? (all_pairs - 1) / pairs : 0, last_in_grp = all_pairs - 1 - last_grp * pairs;
+    int last_grp = 0;                                        // the group that holds the last pair
+#pragma unroll
+    for (int g = 1; g < GR; ++g) last_grp += all_pairs > g * pairs;
+    const int64_t last_in_grp = all_pairs - 1 - last_grp * pairs;
     // this thread's group in phase 3, its bin (f = tid + NT * b where there is one group) and its group's steps
     const int grp = GR > 1 ? tid / NB : 0, bin = GR > 1 ? tid - grp * NB : tid;
     const int64_t T_left = GR > 1 ? T - 2 * grp * pairs : T;
@@ -693,7 +704,7 @@ __global__ __launch_bounds__(64 * NTR)
     const int NG_fixed = kStream ? 0 : (int)tab_fixed[0];
 
     WaveFft<P> fft;
-    fft.init(lg, twl_table);
+    fft.init(lg, twl_table, lds);
     if (lg == 0) my_slot[ZS] = make_float2(0.f, 0.f);
     __syncthreads();
 
@@ -714,20 +725,25 @@ __global__ __launch_bounds__(64 * NTR)
                 const int f = tid + NT * b;
                 if (f >= NB) continue;
                 const bool pk = kPack && f == 0;
-                float2 J[M], B[kAcc];
+                float2 J[M], B[kAcc], next[kAcc];            // the next piece's numbers are in flight while one is folded in
 #pragma unroll
                 for (int l = 0; l < M; ++l) {
                     J[l] = spectra_row[l * (D / 2 + 1) + f];
                     if (pk) J[l].y = spectra_row[l * (D / 2 + 1) + D / 2].x;
                 }
-                for (int s = 1; s < cut.join; ++s) {
+                auto fetch = [&](int s) {
                     const float2 *sp = spectra_row + s * cut.piece_stride + f;
 #pragma unroll
-                    for (int q = 0; q < kAcc; ++q) B[q] = sp[q * (D / 2 + 1)];
-                    if (pk) {
-#pragma unroll
-                        for (int q = 0; q < kAcc; ++q) B[q].y = sp[q * (D / 2 + 1) + D / 2].x;
+                    for (int q = 0; q < kAcc; ++q) {
+                        next[q] = sp[q * (D / 2 + 1)];
+                        if (pk) next[q].y = sp[q * (D / 2 + 1) + D / 2].x;
                     }
+                };
+                if (cut.join > 1) fetch(1);
+                for (int s = 1; s < cut.join; ++s) {
+#pragma unroll
+                    for (int q = 0; q < kAcc; ++q) B[q] = next[q];
+                    if (s + 1 < cut.join) fetch(s + 1);
 #pragma unroll
                     for (int l = M - 1; l >= 0; --l) {       // descending: the lower levels are still the old ones
                         float2 acc = make_float2(J[l].x + B[acc_index(M, 0, l)].x, J[l].y + B[acc_index(M, 0, l)].y);
@@ -819,7 +835,7 @@ __global__ __launch_bounds__(64 * NTR)
             // its place (the increment across the sequence boundary) is cleared so that it cannot touch the result
             const int64_t last = last_in_grp - pair0;
             if ((T & 1) && last >= 0 && last < SPG) {
-                float2 *st = wave_lds + (int)(last_grp * SPG + last) * PS;
+                float2 *st = wave_lds + (last_grp * SPG + (int)last) * PS;
                 for (int a = lane; a < twoF; a += 64) st[a].y = 0.f;
             }
             transform_fence<P>();

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(64 * (1 << LOG2S) * NTR) __attribute__((amdgpu_wave
     const uint32_t *tab_fixed = table + (int64_t)wvl * tl.words;
 
     WaveFft<P> fft;
-    fft.init(lane, twl_table);
+    fft.init(lane, twl_table, lds);
     __syncthreads();
 
     float2 A[BPT][M];
