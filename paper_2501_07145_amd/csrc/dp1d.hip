@@ -18,22 +18,23 @@ constexpr int kRawBufferWord3 = 0x00020000;   // buffer descriptor, last word: u
 constexpr int kTileStride = 36;    // floats per component in the transposition tile: 16-byte accesses of 16
                                    // consecutive components then fall on 16 distinct groups of four banks
 
-// sqrt(2) cos(x) to 2.4e-7 absolute for |x| < 1e6: x = k pi + r with |r| <= pi/2 (k from adding 1.5 * 2^23,
-// whose lowest mantissa bit is then the parity of k; two-term Cody-Waite reduction), a degree-5 polynomial
-// in r^2 (Chebyshev interpolant of sqrt(2) cos(sqrt(u)) on [0, (pi/2)^2], 2e-10) and the sign (-1)^k.
-__device__ __forceinline__ float sqrt2_cos(float x)
+// sqrt(2) cos(pi x) to 1.2e-7 absolute (and what the rounding of x costs) for |x| < 2^22: x = k + r with |r| <= 1/2, k
+// from adding 1.5 * 2^23, whose lowest mantissa bit is then the parity of k, and r exact; a degree-5 polynomial in
+// r^2 (Chebyshev interpolant of sqrt(2) cos(pi sqrt(u)) on [0, 1/4]) and the sign (-1)^k, added to the sign bit.
+// Half-turns rather than radians: the reduction takes no multiplication and rounds nothing. `rest` is what rounding the
+// phase to half-turns has left of it. Eleven vector instructions against twelve, and vector instructions are what bounds
+// the kernel (three wavefronts per SIMD; running a wavefront's matrix instructions under its own cosines changed nothing).
+__device__ __forceinline__ float sqrt2_cospi(float x, float rest)
 {
-    const float t = fmaf(x, 0.318309886183790672f, 12582912.0f);
-    const float kf = t - 12582912.0f;
-    float r = fmaf(-kf, 3.14159274101257324f, x);
-    r = fmaf(-kf, -8.74227800037248566e-8f, r);
+    const float t = x + 12582912.0f;
+    const float r = (x - (t - 12582912.0f)) + rest;
     const float u = r * r;
-    float p = fmaf(u, -3.684157832e-07f, 3.501610627e-05f);
-    p = fmaf(u, p, -1.964110881e-03f);
-    p = fmaf(u, p, 5.892552063e-02f);
-    p = fmaf(u, p, -7.071067691e-01f);
-    p = fmaf(u, p, 1.414213538e+00f);
-    return __uint_as_float(__float_as_uint(p) ^ (__float_as_uint(t) << 31));
+    float p = fmaf(u, -0.0345010571f, 0.332251191f);
+    p = fmaf(u, p, -1.88827479f);
+    p = fmaf(u, p, 5.73988152f);
+    p = fmaf(u, p, -6.97886419f);
+    p = fmaf(u, p, 1.41421354f);
+    return __uint_as_float((__float_as_uint(t) << 31) + __float_as_uint(p));
 }
 
 // orders the LDS accesses of one wavefront (the hardware runs them in program order; this keeps the
@@ -147,6 +148,7 @@ void dp1d_features_kernel(
     put_tile(xs);
     __syncthreads();
     float *my_tile = tile[wave];
+    const float scale_turns = (float)((double)inv_lengthscale * 0.31830988618379067154);
     int cur = 0;
     for (int64_t t0 = 0; t0 < L; t0 += kRows, cur ^= 1) {
         const int nrow = (int)min((int64_t)kRows, L - t0);
@@ -170,13 +172,14 @@ void dp1d_features_kernel(
 #pragma unroll
                 for (int kk = 0; kk < KSTEPS; ++kk)
                     acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kKeepX ? xa[kk] : xt[2 * kk], w[cb][kk], acc, 0, 0, 0);
-                const float b = bm[cb];
+                const float b = bm[cb] * 0.318309886183790672f;          // phase in half-turns, and what its rounding left
+                const float rest = fmaf(bm[cb], 0.318309886183790672f, -b) + bm[cb] * 1.2841276486e-8f;
                 fetch_w(wn, mn, cb);
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
                     floatx4 v;
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) v[j] = sqrt2_cos(fmaf(acc[4 * g + j], inv_lengthscale, b));
+                    for (int j = 0; j < 4; ++j) v[j] = sqrt2_cospi(fmaf(acc[4 * g + j], scale_turns, b), rest);
                     *reinterpret_cast<floatx4 *>(my_tile + (32 * cb + col) * kTileStride + 8 * g + 4 * half) = v;
                     __builtin_amdgcn_sched_barrier(0);        // four cosines at a time: bounds their temporaries
                 }
