@@ -83,7 +83,7 @@ template <int KSTEPS>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(KSTEPS <= 4 ? 4 : KSTEPS <= 16 ? 3 : 2, 4)))
 void dp1d_features_kernel(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ bias,
-    float inv_lengthscale, int64_t L, int d, int M, int F, float *__restrict__ out, int64_t ld_out)
+    float scale_turns, int64_t L, int d, int M, int F, float *__restrict__ out, int64_t ld_out)
 {
     constexpr int KP = 2 * KSTEPS, XS = KP | 1;
     constexpr bool kKeepX = KSTEPS <= 16;              // the tile's A fragments stay in registers for all levels
@@ -148,7 +148,6 @@ void dp1d_features_kernel(
     put_tile(xs);
     __syncthreads();
     float *my_tile = tile[wave];
-    const float scale_turns = (float)((double)inv_lengthscale * 0.31830988618379067154);
     int cur = 0;
     for (int64_t t0 = 0; t0 < L; t0 += kRows, cur ^= 1) {
         const int nrow = (int)min((int64_t)kRows, L - t0);
@@ -210,12 +209,178 @@ void dp1d_features_kernel(
         for (int m = 0; m < M; ++m) row[1 + (int64_t)m * F + my_comp] = acc_state[m][tid] * scale;
 }
 
+// Few long sequences: workgroup = (sequence, 64 components), eight wavefronts that share out the time points, a stretch
+// of 31 or more steps each (whole tiles; a stretch starts with the last point of the one before). A wavefront runs the recurrence for
+// every first level at once, A^{(a..l)} for all a <= l (E[a][r]: the sum of the level below before row r), and the
+// first wavefront joins the eight stretches from left to right through LDS. Registers hold it all up to five levels
+// (four with more than 32 channels);
+// one workgroup per CU. Nothing but LDS is needed beyond what the whole-sequence kernel takes.
+constexpr int kStretches = 8;
+constexpr int kMaxSplitLevels = 5;
+constexpr int64_t kSplitPoints = 65, kSplitWorkgroups = 128;
+template <int KSTEPS, int M>
+__global__ __launch_bounds__(64 * kStretches) __attribute__((amdgpu_waves_per_eu(2, 2))) void dp1d_stretches_kernel(
+    const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ bias,
+    float scale_turns, int64_t L, int64_t steps, int d, int F, float *__restrict__ out, int64_t ld_out)
+{
+    constexpr int KP = 2 * KSTEPS, XS = KP | 1, NA = M * (M + 1) / 2;
+    static_assert(NA * 64 <= 64 * kTileStride, "the sums of a stretch fit its tile");
+    __shared__ __attribute__((aligned(16))) float tile[kStretches][64 * kTileStride];
+    __shared__ float xs[kStretches][kRows * XS];
+    constexpr auto at = [](int a, int l) { return a * M - a * (a - 1) / 2 + l - a; };
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int half = lane >> 5, col = lane & 31;
+    const int64_t n = blockIdx.x;
+    const int comp0 = blockIdx.y * 64;
+    const float *xseq = X + n * L * d;
+    float *my_tile = tile[wave], *my_x = xs[wave];
+    const int fcol[2] = {min(comp0 + col, F - 1), min(comp0 + 32 + col, F - 1)};
+    const int64_t begin = wave * steps, end = min(begin + steps, L - 1);       // first and last point of the stretch
+
+    float A[NA], pc[M], E[M][kRows];
+#pragma unroll
+    for (int i = 0; i < NA; ++i) A[i] = 0.f;
+#pragma unroll
+    for (int m = 0; m < M; ++m) pc[m] = 0.f;
+    float w[2][KSTEPS], bm[2];
+    const int w_lane_offset[2] = {4 * (half * F + fcol[0]), 4 * (half * F + fcol[1])};
+    auto fetch = [&](const float *Wp, const float *bp, int m, int cb) {        // as in the whole-sequence kernel
+        int pair_bytes = 2 * F * 4, left = d * F * 4;
+        const char *base = reinterpret_cast<const char *>(Wp + (int64_t)m * d * F);
+        asm volatile("" : "+s"(pair_bytes), "+s"(left));
+#pragma unroll
+        for (int kk = 0; kk < KSTEPS; ++kk) {
+            const __amdgpu_buffer_rsrc_t rows = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<char *>(base), (short)0, left, kRawBufferWord3);
+            w[cb][kk] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rows, w_lane_offset[cb], 0, 0));
+            const int adv = min(pair_bytes, left);
+            base += adv;
+            left -= adv;
+        }
+        bm[cb] = bp[(int64_t)m * F + fcol[cb]];
+    };
+    fetch(W, bias, 0, 0);
+    fetch(W, bias, 0, 1);
+    for (int64_t t0 = begin; begin < L - 1 && t0 <= end; t0 += kRows) {
+        const int nrow = (int)min((int64_t)kRows, end + 1 - t0);
+        for (int i = lane; i < kRows * KP; i += 64) {
+            const int r = i / KP, c = i - r * KP;
+            my_x[r * XS + c] = r < nrow && c < d ? xseq[(t0 + r) * d + c] : 0.f;
+        }
+        lds_order();
+        // (otherwise the compiler keeps the columns of all levels in registers, and spills them)
+        const float *wt = W, *bt = bias;
+        asm volatile("" : "+s"(wt), "+s"(bt));
+#pragma unroll
+        for (int m = 0; m < M; ++m) {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int kk = 0; kk < KSTEPS; ++kk)
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(my_x[col * XS + half + 2 * kk], w[cb][kk], acc, 0, 0, 0);
+                const float b = bm[cb] * 0.318309886183790672f;
+                const float rest = fmaf(bm[cb], 0.318309886183790672f, -b) + bm[cb] * 1.2841276486e-8f;
+                fetch(wt, bt, m + 1 < M ? m + 1 : 0, cb);              // the block's columns of the next level
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    floatx4 v;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) v[j] = sqrt2_cospi(fmaf(acc[4 * g + j], scale_turns, b), rest);
+                    *reinterpret_cast<floatx4 *>(my_tile + (32 * cb + col) * kTileStride + 8 * g + 4 * half) = v;
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            lds_order();
+#pragma unroll
+            for (int g = 0; g < kRows / 4; ++g) {
+                const floatx4 v = *reinterpret_cast<const floatx4 *>(my_tile + lane * kTileStride + 4 * g);
+                if (g == 0) pc[m] = t0 == begin ? v[0] : pc[m];       // first point of the stretch: no increment
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = 4 * g + j;
+                    const float u = r < nrow ? v[j] - pc[m] : 0.f;
+                    pc[m] = r < nrow ? v[j] : pc[m];
+#pragma unroll
+                    for (int a = 0; a <= m; ++a) {
+                        const float below = a < m ? E[a][r] : 1.0f, old = A[at(a, m)];
+                        E[a][r] = old;
+                        A[at(a, m)] = fmaf(below, u, old);
+                    }
+                }
+            }
+            lds_order();
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) my_tile[64 * i + lane] = A[i];
+    __syncthreads();
+    if (wave != 0) return;
+    for (int s = 1; s < kStretches; ++s) {                            // A^{(1..l)} of what is joined so far
+        float B[NA];
+#pragma unroll
+        for (int i = 0; i < NA; ++i) B[i] = tile[s][64 * i + lane];
+#pragma unroll
+        for (int l = M - 1; l >= 0; --l) {                            // descending: the lower levels are still the old ones
+            float acc = A[l] + B[l];
+#pragma unroll
+            for (int j = 1; j <= l; ++j) acc = fmaf(A[j - 1], B[at(j, l)], acc);
+            A[l] = acc;
+        }
+    }
+    float *row = out + n * ld_out;
+    if (blockIdx.y == 0 && lane == 0) row[0] = 1.0f;
+    const float scale = 1.0f / sqrtf((float)F);
+    if (comp0 + lane < F) {
+#pragma unroll
+        for (int m = 0; m < M; ++m) row[1 + (int64_t)m * F + comp0 + lane] = A[m] * scale;
+    }
+}
+
+template <int KSTEPS>
+hipError_t launch_stretches(const float *X, const float *W, const float *bias, float scale_turns, int64_t N,
+                            int64_t L, int d, int M, int F, float *out, int64_t ld_out, hipStream_t stream)
+{
+    // steps of a stretch: whole tiles with the point that it shares with the one before
+    const int64_t each = (L - 1 + kStretches - 1) / kStretches, steps = (each + 1 + kRows - 1) / kRows * kRows - 1;
+    const dim3 grid((unsigned)N, (unsigned)((F + 63) / 64));
+    switch (M) {
+#define RFSF_STRETCHES_CASE(LEVELS)                                                                           \
+    case LEVELS:                                                                                              \
+        hipLaunchKernelGGL((dp1d_stretches_kernel<KSTEPS, LEVELS>), grid, dim3(64 * kStretches), 0, stream, X, W, bias, \
+                           scale_turns, L, steps, d, F, out, ld_out);                                     \
+        break
+        RFSF_STRETCHES_CASE(1);
+        RFSF_STRETCHES_CASE(2);
+        RFSF_STRETCHES_CASE(3);
+        RFSF_STRETCHES_CASE(4);
+    case 5:
+        if constexpr (KSTEPS <= 16) {
+            hipLaunchKernelGGL((dp1d_stretches_kernel<KSTEPS, 5>), grid, dim3(64 * kStretches), 0, stream, X, W, bias,
+                               scale_turns, L, steps, d, F, out, ld_out);
+            break;
+        }
+        return hipErrorInvalidValue;
+#undef RFSF_STRETCHES_CASE
+    default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+}
+
 }  // namespace
 
-hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float inv_lengthscale, int64_t N,
+hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float scale_turns, int64_t N,
                        int64_t L, int d, int M, int F, float *out, int64_t ld_out, hipStream_t stream)
 {
     if (N == 0) return hipSuccess;
+    // Workgroups of the whole-sequence kernel, three of which a CU holds, against half the CUs
+    if (M <= (d <= 32 ? kMaxSplitLevels : kMaxSplitLevels - 1) && L >= kSplitPoints && N * ((F + 255) / 256) <= kSplitWorkgroups && (F + 63) / 64 <= 65535) {
+        if (d <= 4) return launch_stretches<2>(X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream);
+        if (d <= 8) return launch_stretches<4>(X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream);
+        if (d <= 18) return launch_stretches<9>(X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream);
+        if (d <= 32) return launch_stretches<16>(X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream);
+        return launch_stretches<32>(X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream);
+    }
     dim3 grid((unsigned)N, (unsigned)((F + 255) / 256));
     const size_t dyn = sizeof(float) * 2 * (size_t)M * 256;
     // static LDS of the kernel (X double buffer + transposition tiles) plus the per-level state can pass
@@ -231,7 +396,7 @@ hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float 
             raised = dyn;                                                                                     \
         }                                                                                                     \
         hipLaunchKernelGGL(dp1d_features_kernel<KS>, grid, dim3(256), dyn, stream, X, W, bias,                \
-                           inv_lengthscale, L, d, M, F, out, ld_out);                                         \
+                           scale_turns, L, d, M, F, out, ld_out);                                         \
     } while (0)
     if (d <= 4) RFSF_LAUNCH_DP1D(2);
     else if (d <= 8) RFSF_LAUNCH_DP1D(4);

@@ -91,8 +91,9 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
                        int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, int batch = 1,
                        int64_t step_x = 0, int64_t step_y = 0, int64_t step_k = 0);
 
-// RFSF-DP-1D features, one fused kernel; d <= 64 and M <= 16 (checked by the API layer).
-hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float inv_lengthscale, int64_t N,
+// RFSF-DP-1D features, one fused kernel; d <= 64 and M <= 16 (checked by the API layer). scale_turns: angles in
+// half-turns per unit of X . W, 1 / (pi lengthscale).
+hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float scale_turns, int64_t N,
                        int64_t L, int d, int M, int F, float *out, int64_t ld_out, hipStream_t stream);
 
 // RFSF-TRP second stage: recurrence over time on the projected increments P[n_seq*L][M][Q], which it may overwrite;

@@ -484,7 +484,8 @@ extern "C" int rfsf_dp1d_features(int64_t N, int64_t L, int32_t d, int32_t M, in
     if (!X || !W || !bias || !out) return RFSF_E_NULLPTR;
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     rfsf::ProfileScope scope(rfsf::kDp1d, stream);
-    return rfsf::launch_dp1d(X, W, bias, 1.0f / lengthscale, N, L, d, M, F, out, ld_out, stream) == hipSuccess
+    const float scale_turns = (float)(0.31830988618379067154 / (double)lengthscale);
+    return rfsf::launch_dp1d(X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream) == hipSuccess
                ? RFSF_OK : RFSF_E_HIP;
 }
 
