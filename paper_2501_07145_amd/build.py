@@ -8,8 +8,11 @@ import subprocess
 _HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(_HERE, "csrc")
 LIB = os.path.join(_HERE, "librfsf_ts.so")
-SOURCES = ["rfsf_ts_api.hip", "rff_increments.hip", "sketch_fft_scan.hip", "gram.hip", "normalize.hip", "dp1d.hip", "trp.hip", "join_pieces.hip", "probe.hip"] + \
-    [f"sketch_fft_scan_d{n}.hip" for n in [6, 7, 8, 9, 10, 12, 13, 100, 200, 500, 1000, 2048]]
+# the longest compilations first
+SOURCES = [f"sketch_fft_scan_d{n}.hip" for n in ["2048_order3", "2048_order2", "10_order3", "2048_order1", "10_order2",
+                                                 "1000", "500", "10_order1", "9", "12", "13", "8", "100", "200", "7", "6"]] + \
+    ["rff_increments.hip", "gram.hip", "dp1d.hip", "sketch_fft_scan.hip", "rfsf_ts_api.hip", "normalize.hip", "trp.hip",
+     "join_pieces.hip", "probe.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wextra",

@@ -270,7 +270,8 @@ bool sketch_table_job(const int32_t *hash, int M, int F, int D, int Dout, uint32
     // byte offsets within a slot: of position 0 and of the float2 that is always zero
     const uint32_t coord_base = wide_shape(D) ? 8u * tuned::kWideStageBase : 0u;
     const uint32_t zero_off = wide_shape(D) ? 0u : 8u * (uint32_t)tuned::zero_slot(g.PD, 2 * F);
-    *job = {hash, table, F, D, Dout, g.G, tl.words, tl.gather, tl.fold, coord_base, zero_off};
+    *job = {hash, table, F, D, Dout, g.G, tl.words, tl.gather, tl.fold, coord_base, zero_off,
+            wide_shape(D) ? 0 : D / g.G};
     return true;
 }
 

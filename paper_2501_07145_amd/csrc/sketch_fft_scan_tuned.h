@@ -143,11 +143,15 @@ __host__ __device__ constexpr int zero_slot(int PD, int twoF) { return PD > stag
 __host__ __device__ constexpr int slot_stride(int PD, int twoF) { return (zero_slot(PD, twoF) + 2) & ~1; }
 
 // Per-level table built once per call (uint32 words):
-//   [0]                 NG, number of fold rounds
+//   [0]                 NG, number of fold rounds (0 if the level has lists)
+//   [1]                 number of list rows (0 if the level has fold rounds)
+//   [2, 2 + R)          list rows of bucket group q (the buckets lg + G q)
 //   [64, 64 + D)        gather words: low 16 bits byte offset of the bucket's first coordinate in the
 //                       staging area, high 16 bits of its second one (zero float2 if there is none)
 //   [.., + 2F*G)        fold entries, G per round: low 16 bits byte offset of the coordinate to fold,
 //                       high 16 bits byte offset of the first coordinate of its bucket (0xffff: padding)
+//                       or list rows, G words each, group after group, a multiple of four per group: word lg holds
+//                       two more coordinates of bucket lg + G q, in the form of the gather words
 struct TableLayout {
     int gather, fold, words;
 };
@@ -702,6 +706,7 @@ __global__ __launch_bounds__(64 * NTR)
     const float *seq_fixed = seq + (int64_t)wv * 2 * twoF;
     const uint32_t *tab_fixed = table + (int64_t)wv * tl.words;
     const int NG_fixed = kStream ? 0 : (int)tab_fixed[0];
+    const int rows_fixed = kStream ? 0 : (int)tab_fixed[1];
 
     WaveFft<P> fft;
     fft.init(lg, twl_table, lds);
@@ -839,7 +844,7 @@ __global__ __launch_bounds__(64 * NTR)
                 for (int a = lane; a < twoF; a += 64) st[a].y = 0.f;
             }
             transform_fence<P>();
-            // 1b. fold the third and later coordinates of a bucket into its first one, one rank per round
+            // 1b. unless the level has lists: fold the third and later coordinates of a bucket into its first one, one rank per round
             auto fold = [&](uint32_t w) {
                 const uint32_t own = w & 0xffffu, tgt = w >> 16;
                 if (tgt != kFoldPad) {
@@ -862,6 +867,36 @@ __global__ __launch_bounds__(64 * NTR)
                 v[q] = make_float2(x0.x + x1.x, x0.y + x1.y);
                 // keep the scheduler from issuing all 2R reads at once (it would need 4R registers)
                 if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+            }
+            // 1d. lists: the third and later coordinates of a bucket straight from the staging area, two per row and
+            // bucket. Against folding, whose rounds each wait for an LDS round trip, they cost a table word per row:
+            // the table builder chooses (many coordinates per bucket: lists).
+            // Four rows at a time (each group has a multiple of four): eight reads in flight, the next four words under
+            // them; two beside the accumulators of JOINT, which four push into spills (D = 100, five levels: 15 -> 36).
+            if (const int rows = kStream ? (int)tabi[1] : rows_fixed) {
+                constexpr int kRows = JOINT ? 2 : 4;
+                const GlobalWords words = tabi + tl.fold + lg;
+                uint32_t w[kRows];
+#pragma unroll
+                for (int i = 0; i < kRows; ++i) w[i] = words[i * P::G];
+                int next = kRows;
+#pragma unroll
+                for (int q = 0; q < P::R; ++q) {
+                    for (int x = (int)tabi[2 + q]; x > 0; x -= kRows) {
+                        float2 c[2 * kRows];
+#pragma unroll
+                        for (int i = 0; i < kRows; ++i) {
+                            c[2 * i] = *reinterpret_cast<const float2 *>(my_slot_bytes + (w[i] & 0xffffu));
+                            c[2 * i + 1] = *reinterpret_cast<const float2 *>(my_slot_bytes + (w[i] >> 16));
+                        }
+                        const GlobalWords ahead = words + (next < rows ? next : 0) * P::G;
+#pragma unroll
+                        for (int i = 0; i < kRows; ++i) w[i] = ahead[i * P::G];
+                        next += kRows;
+#pragma unroll
+                        for (int i = 0; i < 2 * kRows; ++i) v[q] = make_float2(v[q].x + c[i].x, v[q].y + c[i].y);
+                    }
+                }
             }
             // 2. FPW transforms per wavefront, in place in the slots. The transform is the one long stretch of
             // arithmetic of an iteration; everything else is short pieces of work between waits (loads, LDS round
@@ -982,7 +1017,7 @@ __global__ __launch_bounds__(64 * NTR)
                 level_loop<M>([&](auto level_tag) {
                     constexpr int LL = decltype(level_tag)::value;
                     const float2 z = Z[(size_t)LL * P::FPW * PS + fi], zc = Z[(size_t)LL * P::FPW * PS + fc];
-                    level_loop<LL + 1>([&](auto start_tag) {
+                    level_loop<JOINT ? LL + 1 : 1>([&](auto start_tag) {
                         constexpr int a = decltype(start_tag)::value;
                         level_step<ORDER, LL - a, false>(z, zc, false, 2 * p + 1 < T_grp, A[0][acc_index(M, a, LL)], c[a]);
                     });

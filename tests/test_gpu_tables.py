@@ -20,6 +20,8 @@ pytestmark = pytest.mark.gpu
     (4, 1900, 1024, "random"),         # too much LDS for the projection launch
     (70, 40, 128, "random"),           # more channels than the matrix-core kernel takes
     (3, 60, 4096, "random"),
+    (3, 900, 256, "random"),           # lists instead of fold rounds: seven coordinates per bucket
+    (3, 260, 64, "random"), (3, 700, 100, "random"),
 ])
 def test_tables(oracle, d, F, D, kind):
     rng = np.random.default_rng(F + D)
