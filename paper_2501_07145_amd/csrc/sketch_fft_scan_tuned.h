@@ -683,8 +683,13 @@ __global__ __launch_bounds__(64 * NTR)
     const int64_t Ln = lengths ? (lengths[n] < 1 ? 1 : (lengths[n] > L ? L : lengths[n])) : L;
     // the piece's own steps: 2 * cut.pairs of them from its first one on, fewer (or none) at the sequence's end
     const int64_t steps_left = JOINT ? Ln - 1 - 2 * piece * cut.pairs : 0;
-    const int64_t T = !JOINT ? Ln - 1
-                      : cut.mode == 2 || steps_left < 0 ? 0 : (steps_left < 2 * cut.pairs ? steps_left : 2 * cut.pairs);
+    const int64_t T_all = !JOINT ? Ln - 1
+                          : cut.mode == 2 || steps_left < 0 ? 0 : (steps_left < 2 * cut.pairs ? steps_left : 2 * cut.pairs);
+    // One level: its block is the sum over time of the sketches, which is the sketch of the sum of the increments (the
+    // even and the odd steps' sums kept apart, as one pair). They are added up as they are read, and one iteration
+    // follows.
+    constexpr bool kSumFirst = M == 1;
+    const int64_t T = kSumFirst && T_all > 2 ? 2 : T_all;
     const int64_t all_pairs = (T + 1) / 2;
     // pairs of a group (of the first ones; the last may have fewer or none): what the iterations run over
     const int64_t pairs = GR > 1 ? (all_pairs + GR - 1) / GR : all_pairs;
@@ -815,8 +820,35 @@ __global__ __launch_bounds__(64 * NTR)
     int64_t pair0_first = 0;
     LevelCarry<ORDER> carry[kStream ? P::FPW : 1][kStream ? BPT : 1][kStarts];
 
+    if constexpr (kSumFirst) {
+        // a thread adds up two coordinates at a time over all pairs, eight pairs' loads in flight; the sums go where the
+        // first slot's pair would be staged
+        const int64_t pairs_all = (T_all + 1) / 2, whole = T_all / 2;
+        if (pairs_all > 0) {
+            float4 *sums = reinterpret_cast<float4 *>(lds);
+            for (int i = tid; i < F; i += NT) {
+                const float4 *src = reinterpret_cast<const float4 *>(seq) + i;
+                float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll 8
+                for (int64_t p = 0; p < whole; ++p) {
+                    const float4 x = src[p * F];
+                    sum.x += x.x;
+                    sum.y += x.y;
+                    sum.z += x.z;
+                    sum.w += x.w;
+                }
+                if (whole < pairs_all) {                     // the last pair has no second step
+                    const float4 x = src[whole * F];
+                    sum.x += x.x;
+                    sum.z += x.z;
+                }
+                sums[i] = sum;
+            }
+            __syncthreads();
+        }
+    }
     __builtin_amdgcn_s_setprio(1);
-    if (kEarly && pair0 < pairs) stage_direct(lvl, pair0);
+    if (kEarly && !kSumFirst && pair0 < pairs) stage_direct(lvl, pair0);
     // an iteration exists while its first item does
     while ((kStream ? pair0_first : pair0) < pairs) {
         if (!kStream || pair0 < pairs) {                      // streaming: the last iteration may have fewer items
@@ -834,7 +866,7 @@ __global__ __launch_bounds__(64 * NTR)
             for (int g = 0; g < kFoldInRegs; ++g) fw[g] = g < NG ? tabi[tl.fold + g * P::GF + (lg % P::GF)] : kFoldPad << 16;
 
             // 1a. staging
-            if (!kEarly) stage_direct(lvl, pair0);
+            if (!kEarly && !kSumFirst) stage_direct(lvl, pair0);
             __builtin_amdgcn_s_waitcnt(0x0f70);                 // vmcnt(0): the direct loads have landed
             // odd number of increments, last pair: its second step does not exist; what the producer left in
             // its place (the increment across the sequence boundary) is cleared so that it cannot touch the result
