@@ -129,7 +129,7 @@ def bench_dp1d(args, w, inp, dev, ls) -> int:
 
 def bench_trp(args, w, inp, dev, ls) -> int:
     """Sibling variant RFSF-TRP with Q = D projections per level: projection kernel (as in the main path),
-    one fp32 MFMA GEMM per level [N*L, 2F] x [2F, Q], a streaming scan over time, then the Gram."""
+    the levels' products [N*L, 2F] x [2F, Q] in one launch, a streaming scan over time, then the Gram."""
     import numpy as np
     import torch
 

@@ -217,6 +217,22 @@ __device__ __forceinline__ int64_t padded_row_to_x_row(int64_t G, const PaddedRo
     return n * L + (t < L ? t : L - 1);
 }
 
+// True if no increment of a tile exists, nor the one after it (whose lower row the tile hands on): a variable-length
+// batch, and the tile lies beyond the last point of its sequence. gt: row of the tile's first row.
+__device__ __forceinline__ bool tile_beyond_end(const int64_t *__restrict__ lengths, int64_t gt, const PaddedRowBase &b, int64_t Lp)
+{
+    const int64_t G = gt - 1 < b.G ? b.G : gt - 1;             // (increments before the range's first are not this workgroup's)
+    int64_t t = b.t + (G - b.G), n = b.n;
+    if (Lp >= 512) {
+        if (t >= Lp) { t -= Lp; ++n; }
+    } else {
+        const int q = (int)t / (int)Lp;
+        t -= (int64_t)q * Lp;
+        n += q;
+    }
+    return t + (gt + kRowsPerTile - 1 - G) < Lp && t >= lengths[n] - 1;
+}
+
 // The vector-ALU kernel in the pair layout (see sincos_difference_store_pairs), signs applied: a workgroup
 // owns increments k_lo .. k_lo + 253 of the padded row space.
 __global__ __launch_bounds__(256) void rff_increments_valu_pairs(
@@ -292,7 +308,7 @@ template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 2) padded: chann
 __global__ __launch_bounds__(256) void rff_increments_mfma(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
-    float *__restrict__ dphi, TableJob job)
+    float *__restrict__ dphi, const int64_t *__restrict__ lengths, TableJob job)
 {
     constexpr int KP = 2 * KSTEPS;              // padded channel count
     constexpr int XS = KP | 1;                  // odd LDS row stride: conflict-free A reads
@@ -369,6 +385,11 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
         const int nrow = (int)min((int64_t)kRowsPerTile, g1 - gt + 1);
         const bool more = gt + kRowsPerTile <= g1;
         if (more) fetch_tile(gt + kRowsPerTile);
+        if (PAIRED && lengths && tile_beyond_end(lengths, gt, row_base, Lp)) {
+            if (more) put_tile(xs + (cur ^ 1) * (kRowsPerTile * XS));
+            __syncthreads();
+            continue;
+        }
         const float *xt = xs + cur * (kRowsPerTile * XS);
         floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -404,7 +425,7 @@ template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 16): channels pa
 __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
-    float *__restrict__ dphi, TableJob job)
+    float *__restrict__ dphi, const int64_t *__restrict__ lengths, TableJob job)
 {
     constexpr int KP = 16 * KSTEPS;
     constexpr int XS = KP + 8;                  // bf16 elements per LDS row (16-byte padded)
@@ -489,6 +510,11 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
         const int nrow = (int)min((int64_t)kRowsPerTile, g1 - gt + 1);
         const bool more = gt + kRowsPerTile <= g1;
         if (more) fetch_tile(gt + kRowsPerTile);
+        if (PAIRED && lengths && tile_beyond_end(lengths, gt, row_base, Lp)) {
+            if (more) put_tile(cur ^ 1);
+            __syncthreads();
+            continue;
+        }
         floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < KSTEPS; ++kk) {
@@ -514,7 +540,7 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
 
 hipError_t launch_rff_increments(const float *X, const float *W, const float *sign, float inv_lengthscale,
                                  int64_t n_seq, int64_t L, int d, int M, int F, bool bf16,
-                                 float *dphi, hipStream_t stream, const TableJob *tables)
+                                 float *dphi, hipStream_t stream, const TableJob *tables, const int64_t *lengths)
 {
     const bool paired = sign != nullptr;
     const int64_t Lp = (L + 1) & ~(int64_t)1;
@@ -557,7 +583,7 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     const bool whole_lines = F % 8 == 0;           // 16 bytes per frequency and pair of steps
 #define RFSF_LAUNCH(KERNEL, KS, PAIRED, STREAM, TILE)                                                                \
     hipLaunchKernelGGL((KERNEL<KS, PAIRED, STREAM>), grid, dim3(256), job.table && table_lds > (TILE) ? table_lds : (TILE), \
-                       stream, X, W, sign, inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi, job)
+                       stream, X, W, sign, inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi, lengths, job)
 #define RFSF_LAUNCH_MFMA(KERNEL, KS, TILE)                                                                           \
     do {                                                                                                         \
         if (!paired) RFSF_LAUNCH(KERNEL, KS, false, false, TILE);                                                \

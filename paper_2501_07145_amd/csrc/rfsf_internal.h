@@ -39,11 +39,12 @@ struct PieceRows { const float2 *rows[kMaxCutLevels]; };
 // to even, increment k = n * Lp + t of coordinate a sits at ((((k / 2) * M + m) * 2F + p) * 2 + k % 2), p = 2a for a
 // cosine (a < F) and 2(a - F) + 1 for a sine: the two increments of a pair of consecutive time steps are one float2.
 // n_seq * Lp * M * 2F floats in all.
+// `lengths` (may be null, pair layout): each sequence's own number of points; increments beyond them may be left out.
 // `tables` (may be null): the sketch tables are built as well, by workgroups of the same launch where that pays.
 struct TableJob;
 hipError_t launch_rff_increments(const float *X, const float *W, const float *sign, float inv_lengthscale,
                                  int64_t n_seq, int64_t L, int d, int M, int F, bool bf16,
-                                 float *dphi, hipStream_t stream, const TableJob *tables);
+                                 float *dphi, hipStream_t stream, const TableJob *tables, const int64_t *lengths);
 
 // Steps 3-4: CountSketch, FFT-domain level recursion over time, inverse transform; writes
 // (D is the transform length, a power of two; Dout <= D the number of buckets per level: equal to D,

@@ -293,7 +293,8 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream, may_create);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, producer_sign, inv_ls, cnt, shape->L, shape->d,
                                             shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream,
-                                            n0 == 0 && has_tables ? &tables : nullptr) != hipSuccess)
+                                            n0 == 0 && has_tables ? &tables : nullptr,
+                                            producer_sign && lengths ? lengths + n0 : nullptr) != hipSuccess)
                 return RFSF_E_HIP;
         }
         const int64_t *chunk_lengths = lengths ? lengths + n0 : nullptr;
@@ -574,7 +575,7 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
         {
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, nullptr, inv_ls, cnt, shape->L, shape->d,
-                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr) != hipSuccess)
+                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr, nullptr) != hipSuccess)
                 return RFSF_E_HIP;
         }
         {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (rows whose increment does not
