@@ -501,7 +501,11 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
     }
     // 32 x 32 tiles while 64 x 64 ones would not give every CU one (700 rows with themselves, 121 tiles of 64 x 64:
     // 16 us against 22 with 1025 columns, 65 against 74 with 5121; 1500 rows, 300 tiles: 158 against 131 with 5121)
-    if (count(64) <= 256) return launch_small<1, 8>(g, sym, batch, stream);
+    // ... and between 150 and 256 of them 64 x 64 tiles with eight wavefronts, which leave the rows' panels to half as many
+    // readers (1000 x 1000, 501 columns 15.7 -> 12.6 us; 300 x 2000, 1501 columns, 160 tiles 36.3 -> 29.1; 1400 rows with
+    // themselves, 1025 columns, 253 tiles 29.8 -> 23.5; 1000 rows, 136 tiles 22.1 and 21.8; 700 rows, 66 tiles 10.8 and 20.1)
+    if (count(64) <= 150) return launch_small<1, 8>(g, sym, batch, stream);
+    if (count(64) <= 256) return launch_small<2, 8>(g, sym, batch, stream);
     return launch_small<2, 4>(g, sym, batch, stream);
 }
 
