@@ -37,7 +37,7 @@ constexpr size_t kAlign = 256;
 // small enough for the last-level cache (64 sequences) cannot fill the chip, since the consumer runs one
 // workgroup per sequence. Hence: as few launches as a 48 GiB scratch allows.
 constexpr size_t kChunkBytesTarget = (size_t)48 << 30;
-constexpr size_t kIncrementTail = 4096;   // the sketch kernel may read up to 1023 floats past the last row
+constexpr size_t kIncrementTail = 4096;   // the kernels for 4096 and 8192 points may read up to 1023 floats past the last row
 
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 

@@ -225,8 +225,8 @@ size_t sketch_fft_scan_lds_bytes(int M, int F, int D)
     while ((1 << log2d) < D) ++log2d;
     if ((1 << log2d) != D || D == 2048) log2d = D;       // (2048 has a plan of its own kind, too)
     // eight wavefronts taking the items in order where the plan prefers that and the slots fit, else one per level
-    const size_t preferred = tuned::tuned_lds_bytes(tuned::transforms_in_flight(M, log2d), g.FPW, g.PD, g.NTWL, F);
-    return preferred <= kLdsPerCu ? preferred : tuned::tuned_lds_bytes(M, g.FPW, g.PD, g.NTWL, F);
+    const size_t preferred = tuned::tuned_lds_bound(tuned::transforms_in_flight(M, log2d), g.FPW, g.PD, g.NTWL, F);
+    return preferred <= kLdsPerCu ? preferred : tuned::tuned_lds_bound(M, g.FPW, g.PD, g.NTWL, F);
 }
 
 bool sketch_fft_scan_is_tuned(int M, int F, int D)

@@ -108,7 +108,9 @@ struct MixedPlan {
     static constexpr int G = D / R;
     static constexpr int FPW = 64 / G;
     static constexpr int GF = G;
-    static constexpr int PD = D;
+    // D = 100: slots of 130 float2 although 102 would do. A third workgroup per CU gains nothing there (100 x 1000 points
+    // 101 -> 97 us, 1000 x 500 444 -> 460, 10 x 1e5 900 -> 943).
+    static constexpr int PD = D == 100 ? 128 : D;
     static constexpr int NP = D == 100 ? 2 : 3;
     static constexpr int radix(int p) { return p < 2 ? 10 : (D == 1000 ? 10 : (D == 500 ? 5 : 2)); }
     static constexpr int Ns(int p) { return p == 0 ? 1 : Ns(p - 1) * radix(p - 1); }
@@ -135,11 +137,13 @@ template <> struct Plan<1000> : MixedPlan<1000> {};
 // inside the transform). Selected as Plan<2048>.
 template <> struct Plan<2048> : Plan<11, 5> {};
 
-// Geometry of one LDS slot (float2 units): [0, ZS) data -- the staging area uses [0, 2F) and, because a
-// direct load always deposits 128 coordinates, junk up to the next multiple of 128; the transform uses
-// [0, PD) --, [ZS] a float2 that is always zero (source of buckets without a first or second coordinate).
-__host__ __device__ constexpr int staged(int twoF) { return (twoF + 127) & ~127; }
-__host__ __device__ constexpr int zero_slot(int PD, int twoF) { return PD > staged(twoF) ? PD : staged(twoF); }
+// Geometry of one LDS slot (float2 units): [0, ZS) data -- the staging area uses [0, 2F), the transform [0, PD) --,
+// [ZS] a float2 that is always zero (source of buckets without a first or second coordinate). A direct load deposits
+// 128 coordinates; of the last one of a pair the lanes beyond 2F stay out. (With all 64, F = 32 staged twice what it
+// has: 1000 x 100 points, four levels, D = 64 and F = 32 59 us against 43, D = 128 and F = 70 94 against 68, five
+// levels, D = 256 and F = 70 206 against 190.)
+__host__ __device__ constexpr int staged(int twoF) { return (twoF + 127) & ~127; }      // by whole direct loads
+__host__ __device__ constexpr int zero_slot(int PD, int twoF) { return PD > twoF ? PD : twoF; }
 __host__ __device__ constexpr int slot_stride(int PD, int twoF) { return (zero_slot(PD, twoF) + 2) & ~1; }
 
 // Per-level table built once per call (uint32 words):
@@ -455,6 +459,12 @@ __host__ __device__ constexpr size_t tuned_lds_bytes(int NTR, int FPW, int PD, i
 {
     return sizeof(float2) * ((size_t)NTR * FPW * slot_stride(PD, 2 * F) + NTWL);
 }
+// ... and with slots that hold whole direct loads: what decides at which transform length a shape runs (as it did when
+// slots were that large, so that routes and workspace sizes stay what they were).
+__host__ __device__ constexpr size_t tuned_lds_bound(int NTR, int FPW, int PD, int NTWL, int F)
+{
+    return tuned_lds_bytes(NTR, FPW, PD, NTWL, staged(2 * F) / 2);
+}
 
 template <int LL>
 struct LevelTag {
@@ -706,7 +716,7 @@ __global__ __launch_bounds__(64 * NTR)
     const int64_t pf = (int64_t)M * 2 * twoF;
     const float *seq = dphi + (n * ((L + 1) / 2) + (JOINT ? piece * cut.pairs : 0)) * pf;
     const TableLayout tl = table_layout(D, P::GF, twoF);
-    const int nload = staged(twoF) / 128;                    // direct loads per pair, 128 coordinates each
+    const int nload = twoF / 128, last_load = twoF % 128;    // direct loads per pair, 128 coordinates each, and the rest
     // one level per wavefront for good: its increments, table and number of fold rounds
     const float *seq_fixed = seq + (int64_t)wv * 2 * twoF;
     const uint32_t *tab_fixed = table + (int64_t)wv * tl.words;
@@ -773,9 +783,8 @@ __global__ __launch_bounds__(64 * NTR)
     }
 
     // Staging: pair pair0 + s of level lvl goes to slot s of the wavefront, 128 coordinates (1 KB) per
-    // instruction, lane i supplying coordinates 2i and 2i+1. Pairs beyond the last one (final group only) are redirected to the last pair and
-    // ignored later; coordinates beyond 2F read the following floats of the workspace (which is padded at its
-    // end for this) and land in the unused part of the staging area.
+    // instruction, lane i supplying coordinates 2i and 2i+1. Pairs beyond the last one (final group only) are redirected
+    // to the last pair and ignored later.
     auto stage_direct = [&](int lvl, int64_t pair0) {
 #pragma unroll
         for (int s = 0; s < P::FPW; ++s) {
@@ -786,6 +795,9 @@ __global__ __launch_bounds__(64 * NTR)
             for (int j = 0; j < nload; ++j)
                 __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + 256 * j),
                                                  (__attribute__((address_space(3))) void *)(dst + 128 * j), 16, 0, 0);
+            if (2 * lane < last_load)
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src + 256 * nload),
+                                                 (__attribute__((address_space(3))) void *)(dst + 128 * nload), 16, 0, 0);
         }
     };
 
