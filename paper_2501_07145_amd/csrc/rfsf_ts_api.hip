@@ -83,14 +83,13 @@ int check_shape(const rfsf_ts_shape *s)
 
 // Few long sequences (the shape of the paper's sequence-length runs, Sec. 4: N = 10, L up to 1e5) would keep one
 // workgroup per sequence busy and the rest of the chip idle. They are cut in time instead: `pieces` pieces of
-// `pairs` pairs of steps per sequence, the sketch kernel launched on every piece once per first tensor
-// position (M launches with M, M-1, .. 1 levels: (M+1)/2 times the work), the pieces joined by
-// csrc/join_pieces.hip and turned into features by one more launch. A function of the shape alone, so that
+// `pairs` pairs of steps per sequence, joined afterwards (csrc/join_pieces.hip). A function of the shape alone, so that
 // every entry point and every workspace size computes the same sums in the same order. The tuned kernels only
-// (any signature order they have: a step's truncated exponential is a factor of the product over steps either way). Measured (M = 5; D = 100, 256, 1024; L = 1e3, 1e4): up to 64 sequences every cut
-// into about 1024 / N pieces of at least 32 pairs wins (1.3x at N = 64 .. 30x at N = 1), around 100 sequences
-// it is a draw, from 128 on it loses; no cut unless it brings at least M + 1 pieces; at most 128 pieces (they
-// are joined one after the other).
+// (any signature order they have: a step's truncated exponential is a factor of the product over steps either way).
+// The rule comes from pieces that cost (M+1)/2 times the transforms (one launch per first tensor position, as transforms
+// of 4096 and 8192 points still take; M = 5; D = 100, 256, 1024; L = 1e3, 1e4): up to 64 sequences every cut
+// into about 1024 / N pieces of at least 32 pairs wins (1.3x at N = 64 .. 30x at N = 1); no cut unless it brings at
+// least M + 1 pieces; at most 128 pieces (they are joined one after the other). What it leaves whole, sketch_cut may split.
 struct TimeCutPlan { int pieces; int64_t pairs; };
 TimeCutPlan time_cut_plan(const rfsf_ts_shape *s)
 {
