@@ -695,11 +695,10 @@ __global__ __launch_bounds__(64 * NTR)
     const int64_t steps_left = JOINT ? Ln - 1 - 2 * piece * cut.pairs : 0;
     const int64_t T_all = !JOINT ? Ln - 1
                           : cut.mode == 2 || steps_left < 0 ? 0 : (steps_left < 2 * cut.pairs ? steps_left : 2 * cut.pairs);
-    // One level: its block is the sum over time of the sketches, which is the sketch of the sum of the increments (the
-    // even and the odd steps' sums kept apart, as one pair). They are added up as they are read, and one iteration
-    // follows.
+    // One level: its block is the sum over time of the sketches, which is the sketch of the sum of the increments. They
+    // are added up as they are read, and one iteration follows, on the sum as its only step.
     constexpr bool kSumFirst = M == 1;
-    const int64_t T = kSumFirst && T_all > 2 ? 2 : T_all;
+    const int64_t T = kSumFirst && T_all > 1 ? 1 : T_all;
     const int64_t all_pairs = (T + 1) / 2;
     // pairs of a group (of the first ones; the last may have fewer or none): what the iterations run over
     const int64_t pairs = GR > 1 ? (all_pairs + GR - 1) / GR : all_pairs;
@@ -834,27 +833,28 @@ __global__ __launch_bounds__(64 * NTR)
 
     if constexpr (kSumFirst) {
         // a thread adds up two coordinates at a time over all pairs, eight pairs' loads in flight; the sums go where the
-        // first slot's pair would be staged
+        // first slot's pair would be staged. The two steps of a pair are added to each other and then to one running
+        // sum: it telescopes, phi(x_k) - phi(x_0), and stays as small as the features are. (Sums of the even and the odd
+        // steps apart from each other grow without bound on rough paths, and their difference is what is left: 300
+        // sequences of 20001 points of white noise 2.4e-4, of 20001 alternating ones 1.8e-1.)
         const int64_t pairs_all = (T_all + 1) / 2, whole = T_all / 2;
         if (pairs_all > 0) {
             float4 *sums = reinterpret_cast<float4 *>(lds);
             for (int i = tid; i < F; i += NT) {
                 const float4 *src = reinterpret_cast<const float4 *>(seq) + i;
-                float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+                float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll 8
                 for (int64_t p = 0; p < whole; ++p) {
                     const float4 x = src[p * F];
-                    sum.x += x.x;
-                    sum.y += x.y;
-                    sum.z += x.z;
-                    sum.w += x.w;
+                    sum0 += x.x + x.y;
+                    sum1 += x.z + x.w;
                 }
                 if (whole < pairs_all) {                     // the last pair has no second step
                     const float4 x = src[whole * F];
-                    sum.x += x.x;
-                    sum.z += x.z;
+                    sum0 += x.x;
+                    sum1 += x.z;
                 }
-                sums[i] = sum;
+                sums[i] = make_float4(sum0, 0.f, sum1, 0.f);
             }
             __syncthreads();
         }

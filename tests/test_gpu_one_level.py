@@ -1,5 +1,5 @@
 """One level: the increments of a sequence are added up before the only transform. No, one, two and three steps, odd and
-even numbers of them, lengths of their own, split sequences and whole ones, every family of transforms."""
+even numbers of them, lengths of their own, split sequences and whole ones, every family of transforms; rough paths."""
 import numpy as np
 import pytest
 import torch
@@ -37,3 +37,44 @@ def test_one_level(oracle, N, L, F, D, order):
         err = block_errors(got, want, 1, D)
         print(f"N={N} L={L} F={F} D={D} order {order}: block errors {err}")
         assert np.all(err <= FP32_BLOCK_TOL)
+
+
+def _sketch64(phi, hash_, sign, D):
+    out = np.zeros(phi.shape[:-1] + (D,))
+    np.add.at(out.reshape(-1, D).T, hash_, (phi * sign).reshape(-1, phi.shape[-1]).T)
+    return out
+
+
+@pytest.mark.parametrize("kind", ["noise", "alternating"])
+@pytest.mark.parametrize("N,L,D", [(1, 20001, 256), (100, 2002, 100), (300, 201, 256), (300, 2001, 64), (300, 2002, 1024),
+                                   (260, 20001, 256)])
+def test_sums_of_rough_paths_telescope(kind, N, L, D):
+    """Increments as large as the features themselves: their sum over time stays phi(x_T) - phi(x_0). Against that
+    difference in 64 bits. Bound: the rounding of each of the T increments and of the T / 2 additions to a sum of their
+    size are independent, 2^-25 of an increment or of the sum (at most about twice an increment) each, a random
+    walk of below 2^-24 sqrt(T) increments; four times that."""
+    rng = np.random.default_rng(L + D)
+    F, d = 64, 1
+    X = rng.standard_normal((N, L, d)).astype(np.float32)
+    if kind == "alternating":
+        X = (X * np.float32(0.1) + (np.arange(L) % 2 * 2 - 1).astype(np.float32)[None, :, None]).astype(np.float32)
+    W = rng.standard_normal((1, d, F)).astype(np.float32)
+    hash_ = rng.integers(0, D, size=(1, 2 * F)).astype(np.int32)
+    sign = (2.0 * rng.integers(0, 2, size=(1, 2 * F)) - 1.0).astype(np.float32)
+    lengths = np.where(rng.random(N) < 0.5, L, rng.integers(L // 2, L + 1, size=N)).astype(np.int64)
+    for own in (None, lengths):
+        got = rfsf.rfsf_ts_features(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(hash_).cuda(),
+                                    torch.from_numpy(sign).cuda(), 1.0, D,
+                                    lengths=None if own is None else torch.from_numpy(own).cuda()).cpu().numpy()
+        ends = np.full(N, L) if own is None else own
+
+        def phi(points):
+            theta = points.astype(np.float64) @ W[0].astype(np.float64)
+            return np.concatenate([np.cos(theta), np.sin(theta)], axis=-1) / np.sqrt(F)
+
+        want = _sketch64(phi(X[np.arange(N), ends - 1]) - phi(X[:, 0]), hash_[0], sign[0], D)
+        steps = phi(X[:4, 1:200]) - phi(X[:4, :199])
+        step = np.sqrt((_sketch64(steps, hash_[0], sign[0], D) ** 2).sum(-1).mean())       # size of an increment's sketch
+        err = np.sqrt(((got[:, 1:] - want) ** 2).sum(axis=1).mean())
+        print(f"{kind} N={N} L={L} D={D}: error {err / step:.2e} increments, {err / step / np.sqrt(L - 1) * 2 ** 24:.2f} of the unit")
+        assert err <= 4 * np.sqrt(L - 1) * 2.0 ** -24 * step
