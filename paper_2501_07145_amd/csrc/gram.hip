@@ -9,7 +9,10 @@
 // left out (mid*lo, lo*mid, lo*lo) are together below 2^-25 of the product, half of what rounding it to 32 bits
 // may cost. Measured against 64 bits, the sums are a third closer than with v_mfma_f32_32x32x2f32, which rounds
 // after every product: relative error of K 1.2e-6 against 1.95e-6 on 10000 x 10000 x 5121, 1.8e-6 against 2.8e-6
-// on 50000 x 5000 x 10241.
+// on 50000 x 5000 x 10241. The instructions round downwards, though, whatever the sign of the sum: of products with 128
+// columns the error averages -1.1e-8 of their root mean square (its own 5.5e-8; v_mfma_f32_32x32x2f32: 1.8e-7, average zero).
+// RFSF-TRP adds products up over time, one row each, and there such a part grows with the number of rows
+// instead of its root: `FLIP`.
 // Infinite operands, and finite ones that round to an infinite bfloat16, would turn into NaN in the split
 // (inf - inf): an entry that comes out as NaN is computed again, one product after the other in 32 bits.
 #include "rfsf_internal.h"
@@ -23,6 +26,17 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+
+// FLIP: the rows of A for which this is the sign bit enter negated, and so do the results that they give, so that rounding
+// downwards comes out as rounding upwards for half of the rows. Rows are chosen by the top bit of their number times an
+// irrational fraction of 2^32 (the golden section), which takes half of the rows of every stretch and of every
+// arithmetic progression in it: rows that repeat with a short period, such as every second one zero, cancel as well.
+__device__ __forceinline__ uint32_t flip_of_row(int64_t row) { return ((uint32_t)row * 0x9e3779b1u) & 0x80000000u; }
+__device__ __forceinline__ void flip(float (&x)[8], uint32_t sign)
+{
+#pragma unroll
+    for (int e = 0; e < 8; ++e) x[e] = __uint_as_float(__float_as_uint(x[e]) ^ sign);
+}
 
 struct Split8 { bf16x8 hi, mid, lo; };
 __device__ __forceinline__ uint32_t round_pair(float a, float b)          // v_cvt_pk_bf16_f32
@@ -90,10 +104,15 @@ struct GramArgs {
 
 // Stores four consecutive rows i .. i+3 of column j; `mirror` also writes their mirror image, row j. `diagonal`: the
 // tile meets the diagonal, and only what lies on or above it counts.
+template <bool FLIP>
 __device__ __forceinline__ void store_quad(const GramArgs &g, const float *A, const float *B, float *C, int64_t i, int64_t j,
                                            float (&v)[4], bool mirror, bool diagonal, bool vec_mirror)
 {
     if (j >= g.Ny) return;
+    if constexpr (FLIP) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(__float_as_uint(v[e]) ^ flip_of_row(i + e));
+    }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
         if (i + e >= g.Nx) continue;
@@ -130,7 +149,7 @@ unsigned xcd_grid(int64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 // Any row stride and alignment (the loads need four bytes).
 struct __attribute__((packed, aligned(4))) Float4u { float x, y, z, w; };
 
-template <int T, int NW, bool SYM>
+template <int T, int NW, bool SYM, bool FLIP>
 __global__ __launch_bounds__(64 * NW) void gram_small(GramArgs g, int64_t tiles, int64_t tiles_j)
 {
     constexpr int NR = 2 * T, NH = NW / 2;      // 16-row blocks per side; wavefronts that keep a partial tile in LDS
@@ -154,8 +173,10 @@ __global__ __launch_bounds__(64 * NW) void gram_small(GramArgs g, int64_t tiles,
     const int64_t i0 = bi * (32 * T), j0 = bj * (32 * T);
     // rows beyond the matrix are redirected to its last one: what they contribute is never stored
     const float *p[2 * NR];
+    uint32_t sign[NR];
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
+        sign[t] = flip_of_row(i0 + 16 * t + col);
         p[t] = A + min(i0 + 16 * t + col, g.Nx - 1) * g.lda + 8 * quarter;
         p[NR + t] = B + min(j0 + 16 * t + col, g.Ny - 1) * g.ldb + 8 * quarter;
     }
@@ -180,6 +201,7 @@ __global__ __launch_bounds__(64 * NW) void gram_small(GramArgs g, int64_t tiles,
     auto split_all = [&](Split8 (&a)[NR], Split8 (&b)[NR]) {
 #pragma unroll
         for (int t = 0; t < NR; ++t) {
+            if (FLIP) flip(raw[t], sign[t]);
             a[t] = split8(raw[t]);
             b[t] = split8(raw[NR + t]);
         }
@@ -225,8 +247,8 @@ __global__ __launch_bounds__(64 * NW) void gram_small(GramArgs g, int64_t tiles,
 #pragma unroll
         for (int w = 1; w < NH; ++w) sum += red[slot(w, b)];
         float v[4] = {sum[0], sum[1], sum[2], sum[3]};
-        store_quad(g, A, B, C, i0 + (b / NR) * 16 + 4 * quarter, j0 + (b % NR) * 16 + col, v, SYM, SYM && bi == bj,
-                   vec_mirror);
+        store_quad<FLIP>(g, A, B, C, i0 + (b / NR) * 16 + 4 * quarter, j0 + (b % NR) * 16 + col, v, SYM, SYM && bi == bj,
+                         vec_mirror);
     }
 }
 
@@ -294,7 +316,7 @@ __device__ __forceinline__ void direct_load(const char *base, uint32_t off, floa
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory");
 }
 
-template <bool ALIGNED, bool SYM>
+template <bool ALIGNED, bool SYM, bool FLIP>
 __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, int64_t nti, int64_t ntj)
 {
     __shared__ __attribute__((aligned(16))) float buf[3][kBigBuffer];
@@ -381,6 +403,9 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
     // the loads of the step three ahead. The next step's first fragments are read and split under the last
     // block's matrix instructions.
     Split8 b[2], a;
+    uint32_t sign[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) sign[t] = flip_of_row(i0 + wi * 128 + 32 * t + col);
     auto first_fragments = [&](const float *rd, Split8 (&nb)[2], Split8 &na) {
         float x[3][8];
         read8(rd, frag_b, x[0]);
@@ -388,6 +413,7 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
         read8(rd, frag_a, x[2]);
         nb[0] = split8(x[0]);
         nb[1] = split8(x[1]);
+        if (FLIP) flip(x[2], sign[0]);
         na = split8(x[2]);
     };
     auto interleave = [&](auto vector_tag) {
@@ -404,6 +430,7 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             mfma_split<2>(a, b, acc[t]);
+            if (FLIP) flip(x[t], sign[t + 1]);
             a = split8(x[t]);
             interleave(std::integral_constant<int, 4>{});
             __builtin_amdgcn_sched_barrier(0);
@@ -446,33 +473,36 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float v[4] = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
-                store_quad(g, A, B, C, i0 + (wi * 4 + a) * 32 + 8 * q + 4 * half, j0 + (wj * 2 + b) * 32 + col, v, SYM,
-                           diagonal, vec_mirror);
+                store_quad<FLIP>(g, A, B, C, i0 + (wi * 4 + a) * 32 + 8 * q + 4 * half, j0 + (wj * 2 + b) * 32 + col, v, SYM,
+                                 diagonal, vec_mirror);
             }
 }
 
 template <int T, int NW>
-hipError_t launch_small(const GramArgs &g, bool sym, int batch, hipStream_t stream)
+hipError_t launch_small(const GramArgs &g, bool sym, bool flip, int batch, hipStream_t stream)
 {
     const int64_t ti = (g.Nx + 32 * T - 1) / (32 * T), tj = (g.Ny + 32 * T - 1) / (32 * T);
     const int64_t tiles = sym ? ti * (ti + 1) / 2 : ti * tj;
     if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
     const dim3 grid(xcd_grid(tiles), (unsigned)batch);
-    if (sym) hipLaunchKernelGGL((gram_small<T, NW, true>), grid, dim3(64 * NW), 0, stream, g, tiles, tj);
-    else hipLaunchKernelGGL((gram_small<T, NW, false>), grid, dim3(64 * NW), 0, stream, g, tiles, tj);
+#define RFSF_SMALL(SY, FL) hipLaunchKernelGGL((gram_small<T, NW, SY, FL>), grid, dim3(64 * NW), 0, stream, g, tiles, tj)
+    if (flip) RFSF_SMALL(false, true);
+    else if (sym) RFSF_SMALL(true, false);
+    else RFSF_SMALL(false, false);
+#undef RFSF_SMALL
     return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *PhiY, int64_t Ny,
-                       int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, int batch,
+                       int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, bool rows_add_up, int batch,
                        int64_t step_x, int64_t step_y, int64_t step_k)
 {
     if (Nx == 0 || Ny == 0) return hipSuccess;
     const GramArgs g = {PhiX, PhiY, K, Nx, Ny, ncols, ldx, ldy, ldk, step_x, step_y, step_k};
     // K = PhiX PhiX^T: only what lies on or above the diagonal is computed, and written twice
-    const bool sym = PhiX == PhiY && Nx == Ny && ldx == ldy;
+    const bool sym = PhiX == PhiY && Nx == Ny && ldx == ldy && !rows_add_up;
     const auto count = [&](int64_t edge) {
         const int64_t ti = (Nx + edge - 1) / edge, tj = (Ny + edge - 1) / edge;
         return (sym ? ti * (ti + 1) / 2 : ti * tj) * batch;
@@ -488,13 +518,15 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
                              reinterpret_cast<uintptr_t>(PhiX) % 16 == 0 && reinterpret_cast<uintptr_t>(PhiY) % 16 == 0;
         const int64_t nti = (Nx + kBigM - 1) / kBigM, ntj = (Ny + kBigN - 1) / kBigN;
         const dim3 grid(xcd_grid(tiles), (unsigned)batch);
-#define RFSF_BIG(AL, SY) hipLaunchKernelGGL((gram_big<AL, SY>), grid, dim3(256), 0, stream, g, tiles, nti, ntj)
+#define RFSF_BIG(AL, SY, FL) hipLaunchKernelGGL((gram_big<AL, SY, FL>), grid, dim3(256), 0, stream, g, tiles, nti, ntj)
         if (aligned) {
-            if (sym) RFSF_BIG(true, true);
-            else RFSF_BIG(true, false);
+            if (rows_add_up) RFSF_BIG(true, false, true);
+            else if (sym) RFSF_BIG(true, true, false);
+            else RFSF_BIG(true, false, false);
         } else {
-            if (sym) RFSF_BIG(false, true);
-            else RFSF_BIG(false, false);
+            if (rows_add_up) RFSF_BIG(false, false, true);
+            else if (sym) RFSF_BIG(false, true, false);
+            else RFSF_BIG(false, false, false);
         }
 #undef RFSF_BIG
         return hipGetLastError();
@@ -504,9 +536,9 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
     // ... and between 150 and 256 of them 64 x 64 tiles with eight wavefronts, which leave the rows' panels to half as many
     // readers (1000 x 1000, 501 columns 15.7 -> 12.6 us; 300 x 2000, 1501 columns, 160 tiles 36.3 -> 29.1; 1400 rows with
     // themselves, 1025 columns, 253 tiles 29.8 -> 23.5; 1000 rows, 136 tiles 22.1 and 21.8; 700 rows, 66 tiles 10.8 and 20.1)
-    if (count(64) <= 150) return launch_small<1, 8>(g, sym, batch, stream);
-    if (count(64) <= 256) return launch_small<2, 8>(g, sym, batch, stream);
-    return launch_small<2, 4>(g, sym, batch, stream);
+    if (count(64) <= 150) return launch_small<1, 8>(g, sym, rows_add_up, batch, stream);
+    if (count(64) <= 256) return launch_small<2, 8>(g, sym, rows_add_up, batch, stream);
+    return launch_small<2, 4>(g, sym, rows_add_up, batch, stream);
 }
 
 }  // namespace rfsf

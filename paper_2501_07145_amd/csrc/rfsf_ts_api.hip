@@ -580,8 +580,8 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
         {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (rows whose increment does not
             // exist are computed too and never read)
             rfsf::ProfileScope scope(rfsf::kTrpProject, stream);
-            if (rfsf::launch_gram(dphi, cnt * shape->L, rf, Z, Q, twoF, twoF, P, MQ, stream, shape->M, twoF,
-                                  (int64_t)Q * twoF, Q) != hipSuccess)
+            if (rfsf::launch_gram(dphi, cnt * shape->L, rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
+                                  twoF, (int64_t)Q * twoF, Q) != hipSuccess)
                 return RFSF_E_HIP;
         }
         {

@@ -75,3 +75,26 @@ def test_trp_more_sequences_than_one_launch_may_take(oracle):
     want = oracle.trp_features(X[sel], W, Z, ls)
     assert np.all(block_errors(got[sel], want, M, Q) <= FP32_BLOCK_TOL)
     assert np.all(got[:, 0] == 1.0) and np.all(np.isfinite(got))
+
+
+@pytest.mark.parametrize("L,M,F,Q", [
+    (4001, 1, 16, 33), (10001, 1, 32, 33), (20001, 1, 64, 40),       # the three small-tile product kernels
+    (20001, 5, 16, 200), (20001, 5, 7, 200),                         # large tiles, rows on 16 bytes and not
+])
+def test_errors_of_the_products_do_not_add_up_over_time(L, M, F, Q):
+    """Level 1 is the sum of all projected increments, Z (phi(x_T) - phi(x_0)): on noise no larger than one of its T
+    summands, so that a rounding error of the products with a sign of its own would grow past those that cancel. Bound:
+    T independent errors of a 32-bit sum of products, 2^-24 of its root mean square each, times four."""
+    rng = np.random.default_rng(L + F)
+    X = rng.standard_normal((1, L, 1)).astype(np.float32)
+    W = rng.standard_normal((M, 1, F)).astype(np.float32)
+    Z = rng.standard_normal((M, Q, 2 * F)).astype(np.float32)
+    got = _run(X, W, Z, 1.0).cpu().numpy()[0, 1:1 + Q].astype(np.float64) * math.sqrt(Q)
+
+    theta = X[0].astype(np.float64) @ W[0].astype(np.float64)
+    phi = np.concatenate([np.cos(theta), np.sin(theta)], axis=1) / math.sqrt(F)
+    z = Z[0].astype(np.float64).T
+    size = math.sqrt((((phi[1:2000] - phi[:1999]) @ z) ** 2).mean())
+    err = math.sqrt(((got - (phi[-1] - phi[0]) @ z) ** 2).mean()) / (math.sqrt(L - 1) * size)
+    print(f"L={L} M={M} F={F} Q={Q}: {err * 2 ** 24:.2f} units")
+    assert err <= 4 * 2.0 ** -24
