@@ -28,10 +28,10 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 // FLIP: the rows of A for which this is the sign bit enter negated, and so do the results that they give, so that rounding
-// downwards comes out as rounding upwards for half of the rows. Rows are chosen by the top bit of their number times an
-// irrational fraction of 2^32 (the golden section), which takes half of the rows of every stretch and of every
-// arithmetic progression in it: rows that repeat with a short period, such as every second one zero, cancel as well.
-__device__ __forceinline__ uint32_t flip_of_row(int64_t row) { return ((uint32_t)row * 0x9e3779b1u) & 0x80000000u; }
+// downwards comes out as rounding upwards for half of the rows: whole blocks of 32, the edge of the smallest tile, so that a
+// scalar register holds the sign. Blocks are chosen by the top bit of their number times an irrational fraction of 2^32
+// (the golden section), which takes half of the blocks of every stretch and of every arithmetic progression in it.
+__device__ __forceinline__ uint32_t flip_of_row(int64_t row) { return ((uint32_t)(row >> 5) * 0x9e3779b1u) & 0x80000000u; }
 __device__ __forceinline__ void flip(float (&x)[8], uint32_t sign)
 {
 #pragma unroll
@@ -147,10 +147,12 @@ unsigned xcd_grid(int64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 // 8 (l / 16) .. + 7 of row l mod 16) rather than 32 x 32: a 16-byte load then touches 16 rows instead of 32, and what
 // bounds the loop is one row (cache line) per cycle of the CU's address unit, 37 cycles a load with 32 rows.
 // Any row stride and alignment (the loads need four bytes).
+// Registers are bounded so that a CU holds two workgroups of four wavefronts or of 32 x 32 tiles (with one, 3000 rows with
+// themselves, 1025 columns, take 115 us instead of 90).
 struct __attribute__((packed, aligned(4))) Float4u { float x, y, z, w; };
 
 template <int T, int NW, bool SYM, bool FLIP>
-__global__ __launch_bounds__(64 * NW) void gram_small(GramArgs g, int64_t tiles, int64_t tiles_j)
+__global__ __launch_bounds__(64 * NW, T == 1 ? 4 : 2) void gram_small(GramArgs g, int64_t tiles, int64_t tiles_j)
 {
     constexpr int NR = 2 * T, NH = NW / 2;      // 16-row blocks per side; wavefronts that keep a partial tile in LDS
     __shared__ floatx4 red[NH * NR * NR * 64];
@@ -176,7 +178,7 @@ __global__ __launch_bounds__(64 * NW) void gram_small(GramArgs g, int64_t tiles,
     uint32_t sign[NR];
 #pragma unroll
     for (int t = 0; t < NR; ++t) {
-        sign[t] = flip_of_row(i0 + 16 * t + col);
+        sign[t] = __builtin_amdgcn_readfirstlane(flip_of_row(i0 + 16 * t));
         p[t] = A + min(i0 + 16 * t + col, g.Nx - 1) * g.lda + 8 * quarter;
         p[NR + t] = B + min(j0 + 16 * t + col, g.Ny - 1) * g.ldb + 8 * quarter;
     }
@@ -305,7 +307,10 @@ int64_t big_tiles(int64_t Nx, int64_t Ny, bool sym)
 }
 
 // Lane i's BYTES bytes at base + off to LDS at dst + BYTES * i. Written out so that the compiler, which cannot tell
-// the buffers apart, does not wait for the loads in flight before every read of LDS; the caller waits.
+// the buffers apart, does not wait for the loads in flight before every read of LDS; the caller waits. (m0 is a register
+// that the compiler manages by itself; that it is written here has to be said, and is warned about.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"
 template <int BYTES>
 __device__ __forceinline__ void direct_load(const char *base, uint32_t off, float *dst)
 {
@@ -315,6 +320,7 @@ __device__ __forceinline__ void direct_load(const char *base, uint32_t off, floa
     else
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dword %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory", "m0");
 }
+#pragma clang diagnostic pop
 
 template <bool ALIGNED, bool SYM, bool FLIP>
 __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, int64_t nti, int64_t ntj)
@@ -405,7 +411,7 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
     Split8 b[2], a;
     uint32_t sign[4];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) sign[t] = flip_of_row(i0 + wi * 128 + 32 * t + col);
+    for (int t = 0; t < 4; ++t) sign[t] = flip_of_row(i0 + wi * 128 + 32 * t);
     auto first_fragments = [&](const float *rd, Split8 (&nb)[2], Split8 &na) {
         float x[3][8];
         read8(rd, frag_b, x[0]);
