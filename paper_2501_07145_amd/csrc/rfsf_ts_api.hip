@@ -577,10 +577,10 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
                                             shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr, nullptr) != hipSuccess)
                 return RFSF_E_HIP;
         }
-        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (rows whose increment does not
-            // exist are computed too and never read)
+        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (the rows between two sequences are
+            // computed too and never read; the last row of the chunk has no increment at all)
             rfsf::ProfileScope scope(rfsf::kTrpProject, stream);
-            if (rfsf::launch_gram(dphi, cnt * shape->L, rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
+            if (rfsf::launch_gram(dphi, cnt * shape->L - 1, rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
                                   twoF, (int64_t)Q * twoF, Q) != hipSuccess)
                 return RFSF_E_HIP;
         }

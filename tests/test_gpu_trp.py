@@ -98,3 +98,17 @@ def test_errors_of_the_products_do_not_add_up_over_time(L, M, F, Q):
     err = math.sqrt(((got - (phi[-1] - phi[0]) @ z) ** 2).mean()) / (math.sqrt(L - 1) * size)
     print(f"L={L} M={M} F={F} Q={Q}: {err * 2 ** 24:.2f} units")
     assert err <= 4 * 2.0 ** -24
+
+
+@pytest.mark.parametrize("N,L,Q", [(6, 40, 33), (300, 2, 8), (1, 300, 20)])
+def test_nothing_is_computed_from_what_the_workspace_held(N, L, Q):
+    """A batch has one increment less than points. What the workspace held in the last row enters no product:
+    infinite, it would leave NaN behind in the workspace (with mixed signs in Z), and NaN takes time."""
+    M, F = 3, 12
+    X, W, Z, ls = _case(N + L, N, L, 3, M, F, Q, 1.0)
+    ws = torch.zeros(rfsf.rfsf_trp_workspace_bytes(N, L, 3, M, F, Q)[0] // 4 * 4, dtype=torch.uint8, device="cuda")
+    want = _run(X, W, Z, ls, workspace=ws).clone()
+    ws.view(torch.float32).fill_(float("inf"))
+    got = _run(X, W, Z, ls, workspace=ws)
+    assert torch.equal(got, want)
+    assert not bool(torch.isnan(ws.view(torch.float32)).any())
