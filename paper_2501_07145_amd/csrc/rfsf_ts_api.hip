@@ -586,7 +586,7 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
         }
         {
             rfsf::ProfileScope scope(rfsf::kTrpScan, stream);
-            if (rfsf::launch_trp_scan(P, cnt, shape->L, shape->M, Q, out + n0 * shape->ld_out, shape->ld_out,
+            if (rfsf::launch_trp_scan(P, shape->N, cnt, shape->L, shape->M, Q, out + n0 * shape->ld_out, shape->ld_out,
                                       stream) != hipSuccess)
                 return RFSF_E_HIP;
         }

@@ -157,12 +157,13 @@ __global__ __launch_bounds__(64) void trp_join_kernel(const float *__restrict__ 
 // Pieces per sequence (1: whole). A batch of four steps takes a thread about 1.5 us whatever the number of threads, a
 // piece of the join 0.25 us, so a sequence of T steps is best cut into about sqrt(1.5 T) pieces; no more than
 // fill the chip with four wavefronts per SIMD, at least 32 steps each, and no cut where the whole sequences have a thread
-// for every lane of one wavefront per SIMD.
+// for every lane of one wavefront per SIMD. A function of the batch, N sequences, however many of them a launch takes: the
+// workspace does not decide in which order a sequence is summed up.
+constexpr int64_t kLanes = 256 * 4 * 64;
 struct TrpCut { int pieces; int64_t steps; };
-TrpCut trp_cut(int64_t n_seq, int64_t L, int M, int Q)
+TrpCut trp_cut(int64_t N, int64_t L, int M, int Q)
 {
-    const int64_t T = L - 1, threads = n_seq * Q;
-    constexpr int64_t kLanes = 256 * 4 * 64;
+    const int64_t T = L - 1, threads = (N < kLanes ? N : kLanes) * Q;
     if (M > 8 || threads >= kLanes) return {1, T};
     int64_t want = (int64_t)sqrt(1.5 * (double)T);
     if (want > 4 * kLanes / threads) want = 4 * kLanes / threads;
@@ -177,12 +178,12 @@ TrpCut trp_cut(int64_t n_seq, int64_t L, int M, int Q)
 
 }  // namespace
 
-hipError_t launch_trp_scan(float *P, int64_t n_seq, int64_t L, int M, int Q, float *out, int64_t ld_out,
+hipError_t launch_trp_scan(float *P, int64_t N, int64_t n_seq, int64_t L, int M, int Q, float *out, int64_t ld_out,
                            hipStream_t stream)
 {
     if (n_seq == 0) return hipSuccess;
     const float scale = 1.0f / sqrtf((float)Q);
-    const TrpCut cut = trp_cut(n_seq, L, M, Q);
+    const TrpCut cut = trp_cut(N, L, M, Q);
     if (cut.pieces > 1) {
         const int64_t piece_blocks = (n_seq * cut.pieces * Q + 255) / 256, join_blocks = (n_seq * Q + 63) / 64;
         if (piece_blocks > 2147483647 || join_blocks > 2147483647) return hipErrorInvalidValue;

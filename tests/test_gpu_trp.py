@@ -112,3 +112,15 @@ def test_nothing_is_computed_from_what_the_workspace_held(N, L, Q):
     got = _run(X, W, Z, ls, workspace=ws)
     assert torch.equal(got, want)
     assert not bool(torch.isnan(ws.view(torch.float32)).any())
+
+
+def test_the_cut_in_time_does_not_depend_on_the_workspace():
+    """Sequences are cut by the shape of the batch, not by how many of them a launch takes: the same bits for a batch as a
+    whole and for one sequence at a time. (So many components that both run the same product kernel, and the first
+    sequence, whose rows are the first ones of their product either way.)"""
+    N, L, M, F, Q = 2, 129, 2, 16, 32768
+    X, W, Z, ls = _case(5, N, L, 3, M, F, Q, 1.0)
+    rec, mn = rfsf.rfsf_trp_workspace_bytes(N, L, 3, M, F, Q)
+    assert mn < rec
+    runs = [_run(X, W, Z, ls, workspace=torch.empty(n, dtype=torch.uint8, device="cuda")) for n in (rec, mn)]
+    assert torch.equal(runs[0][0], runs[1][0])
