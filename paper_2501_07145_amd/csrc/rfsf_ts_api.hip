@@ -135,7 +135,9 @@ SketchCut sketch_cut(const rfsf_ts_shape *s)
     const int64_t floats_per_pair = (int64_t)s->M * 4 * s->F;
     const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
     const int fpw = rfsf::sketch_fft_scan_pairs_per_iteration(P);
-    int64_t most = kCUs * rfsf::sketch_fft_scan_joint_per_cu(s->M, P) / s->N;           // pieces that fill the chip
+    const int64_t per_cu = rfsf::sketch_fft_scan_joint_per_cu(s->M, P), fit = rfsf::sketch_fft_scan_joint_fit(s->M, s->F, P, s->order < 2 ? 1 : s->order);
+    const int64_t at_once = kCUs * (fit < per_cu ? fit : per_cu);
+    int64_t most = kCUs * per_cu / s->N;           // pieces that fill the chip
     if (most > kSplitPieces) most = kSplitPieces;
     // iterations of the kernel per piece: the fewest that keep to `most`, and no fewer than balance the join
     int64_t its = (all_pairs + most * fpw - 1) / (most > 0 ? most * fpw : 1);
@@ -143,6 +145,13 @@ SketchCut sketch_cut(const rfsf_ts_shape *s)
     for (; most >= 2; ++its) {
         const int64_t pairs = its * fpw, pieces = (all_pairs + pairs - 1) / pairs;
         if (pieces < 2) break;
+        // Many frequencies leave a CU fewer workgroups than its registers do. Pieces then take several rounds, and gain only
+        // if there are more than twice as many of them: alone on its CU, the kernel that advances all ranges of positions
+        // takes 1.2 to 1.7 times as long per step. (500 points, four levels, 1000 frequencies, 512 buckets, sketch kernel: 200
+        // sequences in two pieces, two rounds, 1928 us, whole 1200; 150 in three, two rounds, 1369, whole 1058; 128 in four,
+        // two rounds, 1224, in two and one 1138. 300 points, 700 frequencies, 256 buckets: 100 in five pieces, two rounds, 393.)
+        const int64_t rounds = (s->N * pieces + at_once - 1) / at_once;
+        if (rounds > 1 && 2 * rounds >= pieces) continue;
         // every piece, the last one too, has to hold its accumulators
         if (pairs * floats_per_pair >= needed && (slots - (pieces - 1) * pairs) * floats_per_pair >= needed)
             return {(int)pieces, pairs, true, true};

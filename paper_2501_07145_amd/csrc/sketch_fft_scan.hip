@@ -214,6 +214,13 @@ bool tuned_geometry(int D, TunedGeometry *g)
         default: return false;
     }
 }
+// the key of the kernel's plan: log2 D, or D itself for the exact lengths (2048 has a plan of its own kind, too)
+int plan_key(int D)
+{
+    int log2d = 0;
+    while ((1 << log2d) < D) ++log2d;
+    return (1 << log2d) != D || D == 2048 ? D : log2d;
+}
 }  // namespace
 
 size_t sketch_fft_scan_lds_bytes(int M, int F, int D)
@@ -221,9 +228,7 @@ size_t sketch_fft_scan_lds_bytes(int M, int F, int D)
     TunedGeometry g;
     if (!tuned_geometry(D, &g)) return 0;
     if (wide_shape(D)) return tuned::wide_lds_bytes(D / 1024, M, F);
-    int log2d = 0;                        // the key of the kernel's plan: log2 D, or D itself for the exact lengths
-    while ((1 << log2d) < D) ++log2d;
-    if ((1 << log2d) != D || D == 2048) log2d = D;       // (2048 has a plan of its own kind, too)
+    const int log2d = plan_key(D);
     // eight wavefronts taking the items in order where the plan prefers that and the slots fit, else one per level
     const size_t preferred = tuned::tuned_lds_bound(tuned::transforms_in_flight(M, log2d), g.FPW, g.PD, g.NTWL, F);
     return preferred <= kLdsPerCu ? preferred : tuned::tuned_lds_bound(M, g.FPW, g.PD, g.NTWL, F);
@@ -243,6 +248,15 @@ bool sketch_fft_scan_is_tuned(int M, int F, int D)
 bool sketch_fft_scan_joint(int M, int F, int D) { return !wide_shape(D) && sketch_fft_scan_is_tuned(M, F, D); }
 
 int sketch_fft_scan_joint_per_cu(int M, int D) { return tuned::joint_workgroups_per_cu(M, D); }
+
+int sketch_fft_scan_joint_fit(int M, int F, int D, int order)
+{
+    TunedGeometry g;
+    if (!tuned_geometry(D, &g)) return 1;
+    size_t lds = tuned::tuned_lds_bytes(tuned::joint_transforms_in_flight(M, plan_key(D), order), g.FPW, g.PD, g.NTWL, F);
+    if (lds > kLdsPerCu) lds = tuned::tuned_lds_bytes(M, g.FPW, g.PD, g.NTWL, F);
+    return (int)(kLdsPerCu / lds);
+}
 
 int sketch_fft_scan_pairs_per_iteration(int D)
 {

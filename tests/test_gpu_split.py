@@ -55,3 +55,20 @@ def test_split_batches_match_the_oracle(oracle, N, L, d, M, F, D, order):
         err = block_errors(got, want, M, D)
         print(f"N={N} L={L} M={M} F={F} D={D} order {order}: block errors {err}")
         assert np.all(err <= FP32_BLOCK_TOL)
+
+
+@pytest.mark.parametrize("N,L,M,F,D,split", [
+    (200, 101, 4, 1000, 512, False),       # two pieces each, one workgroup per CU for the slots of 2000 coordinates: two rounds
+    (200, 101, 4, 700, 256, False),        # the same in a transform of 512 points
+    (200, 101, 4, 128, 512, True),         # two workgroups per CU
+    (150, 101, 4, 1000, 512, False),       # three pieces in two rounds
+    (128, 101, 4, 1000, 512, True),        # two pieces in one round
+    (100, 101, 4, 700, 256, True),         # five pieces in two rounds
+])
+def test_no_split_into_as_many_rounds_as_half_its_pieces(N, L, M, F, D, split):
+    """Sequences of a batch that is split are summed in another order than those of one that is too large to be."""
+    X, W, hash_, sign = _case(N + F, 300, L, 3, M, F, D)
+    x, w, h, s = (torch.from_numpy(a).cuda() for a in (X, W, hash_, sign))
+    whole = rfsf.rfsf_ts_features(x, w, h, s, 1.5, D)
+    got = rfsf.rfsf_ts_features(x[:N].contiguous(), w, h, s, 1.5, D)
+    assert torch.equal(got, whole[:N]) != split
