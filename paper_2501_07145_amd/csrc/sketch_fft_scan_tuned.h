@@ -108,9 +108,7 @@ struct MixedPlan {
     static constexpr int G = D / R;
     static constexpr int FPW = 64 / G;
     static constexpr int GF = G;
-    // D = 100: slots of 130 float2 although 102 would do. A third workgroup per CU gains nothing there (100 x 1000 points
-    // 101 -> 97 us, 1000 x 500 444 -> 460, 10 x 1e5 900 -> 943).
-    static constexpr int PD = D == 100 ? 128 : D;
+    static constexpr int PD = D;
     static constexpr int NP = D == 100 ? 2 : 3;
     static constexpr int radix(int p) { return p < 2 ? 10 : (D == 1000 ? 10 : (D == 500 ? 5 : 2)); }
     static constexpr int Ns(int p) { return p == 0 ? 1 : Ns(p - 1) * radix(p - 1); }
@@ -586,7 +584,9 @@ __device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool se
 
 // Wavefronts per SIMD the register budget of the kernel is set for: the plan's, except that workgroups of 5 or 6
 // wavefronts with 6 to 12 transforms per wavefront (D = 100, 128, 200) get 96 registers: their workgroups then
-// find room on a CU more often (see transforms_in_flight; measured +8-15 %).
+// find room on a CU more often (see transforms_in_flight; measured +8-15 %). Not the kernel for sequences cut in time,
+// where they cost it 13 to 78 spills (features of 100 x 1000 points, 50 frequencies, 96 against 128 registers: D = 100 138
+// and 128 us with five levels, 190 and 147 with six, D = 200 182 and 173, 241 and 200, D = 128 159 and 118, 231 and 152).
 //
 // The kernel for sequences cut in time (JOINT) holds M(M+1)/2 accumulators per bin instead of M. Four wavefronts per
 // SIMD (128 registers) cost it a few dozen spills of accumulators, which are touched once per iteration; from
@@ -599,9 +599,7 @@ constexpr int kernel_min_waves()
     using P = Plan<LOG2D>;
     constexpr int BPT = (P::D / 2 + 64 * NTR - 1) / (64 * NTR);
     if (JOINT && (P::kMinWaves <= 2 || NTR != M || 2 * BPT * accumulators(M, JOINT) > kJointRegs)) return 2;
-    // (JOINT: 96 registers cost spills; D = 100 with five levels 139 -> 117 us all the same, on 1000 sequences of 100
-    // points, but D = 128 192 -> 223, with six levels 228 -> 308)
-    return P::FPW > 4 && P::FPW < 16 && (M == 5 || M == 6) && (!JOINT || (LOG2D == 100 && M == 5)) ? 5 : P::kMinWaves;
+    return P::FPW > 4 && P::FPW < 16 && (M == 5 || M == 6) && !JOINT ? 5 : P::kMinWaves;
 }
 // Workgroups of the JOINT kernel that a CU holds: one where eight wavefronts, or five and more of the budget of two
 // wavefronts per SIMD, make up the workgroup; two otherwise (by LDS).
