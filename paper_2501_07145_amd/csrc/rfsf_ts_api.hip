@@ -460,7 +460,7 @@ extern "C" int rfsf_ts_gram(const float *PhiX, int64_t Nx, int64_t ldx, const fl
     if (ldx < ncols || ldy < ncols || ldk < Ny) return RFSF_E_BAD_STRIDE;
     if (Nx == 0 || Ny == 0) return RFSF_OK;
     if (!PhiX || !PhiY || !K) return RFSF_E_NULLPTR;
-    if ((Nx + 63) / 64 > 65535 || (Ny + 63) / 64 > 2147483647) return RFSF_E_UNSUPPORTED;
+    if ((Nx + 63) / 64 > 65535 || (Ny + 63) / 64 > 2147483647) return RFSF_E_UNSUPPORTED;     // (stated limits; tiles are counted in grid.x)
     hipStream_t stream = static_cast<hipStream_t>(hip_stream);
     rfsf::ProfileScope scope(rfsf::kGram, stream);
     return rfsf::launch_gram(PhiX, Nx, ldx, PhiY, Ny, ldy, ncols, K, ldk, stream) == hipSuccess
@@ -518,8 +518,8 @@ void trp_per_sequence_bytes(const rfsf_ts_shape *s, size_t *incr, size_t *proj)
     *proj = (size_t)s->L * (size_t)s->M * (size_t)s->D * sizeof(float);
 }
 constexpr size_t kTrpFixed = 3 * kAlign;
-// Sequences per launch of the TRP kernels: the scan puts the sequence and the per-level GEMMs put 64-row
-// tiles of the chunk's L*cnt rows on grid.y, which holds at most 65535.
+// Sequences per launch of the TRP kernels: at most 65535, and 65535 * 64 rows. The kernels count their tiles and threads
+// in grid.x and would take more; the recommended workspace, and what is refused, follow from these numbers.
 int64_t trp_chunk_cap(const rfsf_ts_shape *s)
 {
     const int64_t by_rows = (int64_t)65535 * 64 / s->L;
@@ -535,7 +535,7 @@ extern "C" int rfsf_trp_workspace_bytes(const rfsf_ts_shape *shape, size_t *reco
     size_t incr, proj;
     trp_per_sequence_bytes(shape, &incr, &proj);
     const size_t per = incr + proj;
-    if (trp_chunk_cap(shape) < 1) return RFSF_E_UNSUPPORTED;     // one sequence alone exceeds the grid
+    if (trp_chunk_cap(shape) < 1) return RFSF_E_UNSUPPORTED;     // one sequence alone is beyond the limit
     int64_t chunk = (int64_t)(kChunkBytesTarget / per);
     if (chunk > trp_chunk_cap(shape)) chunk = trp_chunk_cap(shape);
     if (chunk < 1) chunk = 1;

@@ -240,8 +240,6 @@ bool sketch_fft_scan_is_tuned(int M, int F, int D)
     // F <= 4032: the staging area (2F rounded up to 128 coordinates) and the zero float2 behind it are
     // addressed with 16-bit byte offsets
     if (M > 8 || F > 4032 || !tuned_geometry(D, &g)) return false;
-    // (the limit of an earlier table builder, kept so that the route of a shape stays what it was)
-    if (wide_shape(D) && sizeof(int) * (size_t)(3 * ((2 * F + 3) & ~3) + 4 + 2 * D) > kLdsPerCu) return false;
     return sketch_fft_scan_lds_bytes(M, F, D) <= kLdsPerCu;
 }
 

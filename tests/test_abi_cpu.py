@@ -109,7 +109,7 @@ def test_order_three_outside_the_tuned_shapes_is_refused_before_anything_is_enqu
     assert lib.rfsf_ts_features(ctypes.byref(shp), 256, 256, 256, 256, 1.0, 256, 256, 1 << 30, None) == -9
 
 
-def test_trp_chunks_respect_the_grid_limit():
+def test_trp_chunks_respect_the_launch_limit():
     # sequences per launch are capped at min(65535, 65535*64/L), whatever the workspace would hold
     lib = binding.load_library()
     rec, mn = ctypes.c_size_t(0), ctypes.c_size_t(0)
@@ -121,7 +121,7 @@ def test_trp_chunks_respect_the_grid_limit():
     assert lib.rfsf_trp_workspace_bytes(ctypes.byref(shp), ctypes.byref(rec), ctypes.byref(mn)) == 0
     per = (1 << 20) * 2 * 8 * 4 * 2
     assert (rec.value - 768) // per == 3                  # 65535*64 / 2^20 = 3 sequences per launch
-    shp = _shape(N=4, L=1 << 23, d=2, M=2, F=4, D=8, ld_out=17)    # one sequence alone exceeds the grid
+    shp = _shape(N=4, L=1 << 23, d=2, M=2, F=4, D=8, ld_out=17)    # one sequence alone is beyond the limit
     assert lib.rfsf_trp_workspace_bytes(ctypes.byref(shp), ctypes.byref(rec), ctypes.byref(mn)) == -9
 
 

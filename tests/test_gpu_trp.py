@@ -66,8 +66,8 @@ def test_trp_chunks_padding_and_errors(oracle):
 
 
 def test_trp_more_sequences_than_one_launch_may_take(oracle):
-    # 70000 sequences: the scan kernel puts sequences on grid.y (at most 65535), so the call must split
-    # the batch even though the workspace would hold it whole
+    # 70000 sequences: a launch takes at most 65535, so the call must split the batch even though the workspace
+    # would hold it whole
     N, L, d, M, F, Q = 70000, 3, 2, 2, 2, 4
     X, W, Z, ls = _case(11, N, L, d, M, F, Q, 1.0)
     got = _run(X, W, Z, ls).cpu().numpy()
