@@ -35,3 +35,15 @@ def test_stretches_match_the_oracle(oracle, N, L, d, M, F):
     err = block_errors(got.cpu().numpy(), oracle.dp1d_features(X, W, bias, ls), M, F)
     print(f"N={N} L={L} d={d} M={M} F={F}: block errors {err}")
     assert np.all(err <= FP32_BLOCK_TOL)
+
+
+@pytest.mark.parametrize("N,L,M,F", [(1, 2000, 5, 64), (3, 700, 4, 130)])
+def test_stretches_of_noise(oracle, N, L, M, F):
+    rng = np.random.default_rng(L + F)
+    X = rng.standard_normal((N, L, 1)).astype(np.float32)
+    W = rng.standard_normal((M, 1, F)).astype(np.float32)
+    bias = (rng.random((M, F)) * 2 * np.pi).astype(np.float32)
+    got = rfsf.rfsf_dp1d_features(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(bias).cuda(), 1.0)
+    err = block_errors(got.cpu().numpy(), oracle.dp1d_features(X, W, bias, 1.0), M, F)
+    print(f"noise N={N} L={L} M={M} F={F}: block errors {err}")
+    assert np.all(err <= FP32_BLOCK_TOL)

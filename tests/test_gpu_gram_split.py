@@ -1,7 +1,8 @@
 """The Gram's three-term bfloat16 products: every kernel and edge of its dispatch against 64-bit sums.
 
 Bound of an entry: 32-bit summation in any order is within (K + 1) 2^-24 sum_k |a_k b_k|, and the three products of
-terms that are left out are within 2^-25 of each |a_k b_k|: (K + 2) 2^-24 sum_k |a_k b_k|."""
+terms that are left out are together within 2^-24 of each |a_k b_k| (mid*lo and lo*mid 2^-25 each at most, lo*lo next to
+nothing): (K + 2) 2^-24 sum_k |a_k b_k|."""
 import numpy as np
 import pytest
 import torch

@@ -72,3 +72,25 @@ def test_no_split_into_as_many_rounds_as_half_its_pieces(N, L, M, F, D, split):
     whole = rfsf.rfsf_ts_features(x, w, h, s, 1.5, D)
     got = rfsf.rfsf_ts_features(x[:N].contiguous(), w, h, s, 1.5, D)
     assert torch.equal(got, whole[:N]) != split
+
+
+@pytest.mark.parametrize("N,L,d,M,F,D", [
+    (100, 700, 3, 5, 50, 200),         # split
+    (10, 3000, 3, 5, 50, 100),         # pieces
+    (2, 500, 3, 3, 64, 4096),          # pieces, a launch per first position
+    (300, 1398, 3, 8, 42, 64),         # whole sequences, the pairs of an iteration dealt to groups
+    (300, 700, 3, 4, 50, 100),
+    (300, 700, 3, 5, 64, 256),         # whole, no groups
+])
+def test_joined_sums_of_noise(oracle, N, L, d, M, F, D):
+    """Increments that do not get smaller with the number of points: what is joined cancels. A few sequences of the batch.
+    (Three channels: the first and last point of one are now and then so close to each other that the error of level 1,
+    which is their difference, is not small against it in any order of summation.)"""
+    X, W, hash_, sign = _case(N + L + D, 1, 2, d, M, F, D)
+    X = np.random.default_rng(L).standard_normal((N, L, d)).astype(np.float32)
+    got = rfsf.rfsf_ts_features(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(hash_).cuda(),
+                                torch.from_numpy(sign).cuda(), 1.0, D).cpu().numpy()
+    sel = np.r_[0, N // 2, N - 1]
+    err = block_errors(got[sel], oracle.features(X[sel], W, hash_, sign, 1.0, D), M, D)
+    print(f"noise N={N} L={L} M={M} F={F} D={D}: block errors {err}")
+    assert np.all(err <= FP32_BLOCK_TOL)

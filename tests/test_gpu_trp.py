@@ -51,6 +51,20 @@ def test_trp_matches_oracle(oracle, N, L, d, M, F, Q):
     assert np.all(err <= FP32_BLOCK_TOL)
 
 
+@pytest.mark.parametrize("F", [50, 7])
+def test_products_of_all_levels_in_large_tiles(oracle, F):
+    """So many rows that the levels' products take the 256 x 128 tiles, one level per grid row: rows on 16 bytes (2F = 100)
+    and not (2F = 14), neither whole steps of 16 columns nor whole tiles of rows or of projections."""
+    N, L, M, Q = 2500, 8, 5, 200
+    X, W, Z, ls = _case(F, N, L, 3, M, F, Q, math.sqrt(3))
+    got = _run(X, W, Z, ls).cpu().numpy()
+    sel = np.r_[0:40, 1020:1060, N - 40:N]
+    err = block_errors(got[sel], oracle.trp_features(X[sel], W, Z, ls), M, Q)
+    print(f"F={F}: block errors {err}")
+    assert np.all(err <= FP32_BLOCK_TOL)
+    assert np.all(got[:, 0] == 1.0) and np.all(np.isfinite(got))
+
+
 def test_trp_chunks_padding_and_errors(oracle):
     X, W, Z, ls = _case(3, 7, 12, 3, 2, 16, 20, 1.0)
     _, mn = rfsf.rfsf_trp_workspace_bytes(7, 12, 3, 2, 16, 20)

@@ -33,3 +33,17 @@ def test_pieces_match_the_oracle(oracle, N, L, M, Q):
     err = block_errors(got.cpu().numpy(), oracle.trp_features(X, W, Z, ls), M, Q)
     print(f"N={N} L={L} M={M} Q={Q}: block errors {err}")
     assert np.all(err <= FP32_BLOCK_TOL)
+
+
+@pytest.mark.parametrize("N,L,M,Q", [(1, 2000, 5, 33), (3, 700, 4, 50)])
+def test_pieces_of_noise(oracle, N, L, M, Q):
+    """Increments that do not get smaller with the number of points: what the pieces add up cancels."""
+    rng = np.random.default_rng(L + Q)
+    d, F = 1, 64
+    X = rng.standard_normal((N, L, d)).astype(np.float32)
+    W = rng.standard_normal((M, d, F)).astype(np.float32)
+    Z = rng.standard_normal((M, Q, 2 * F)).astype(np.float32)
+    got = rfsf.rfsf_trp_features(torch.from_numpy(X).cuda(), torch.from_numpy(W).cuda(), torch.from_numpy(Z).cuda(), 1.0)
+    err = block_errors(got.cpu().numpy(), oracle.trp_features(X, W, Z, 1.0), M, Q)
+    print(f"noise N={N} L={L} M={M} Q={Q}: block errors {err}")
+    assert np.all(err <= FP32_BLOCK_TOL)
