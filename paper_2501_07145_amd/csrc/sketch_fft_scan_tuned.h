@@ -314,14 +314,16 @@ struct WaveFft {
     int rbase;
     const float2 *twl;      // LDS twiddle table of the radix-16 passes, entry ((set*(r-1) + t-1)*G + lg)
 
-    // `roots`: D float2 of LDS that are free until the caller's next use of them. The register twiddles are picked out of
-    // a table of the D-th roots of unity: computed where they are needed, D = 64 and 128 have 12 and 14 inlined sine-cosine
-    // codes per lane, fetched and run once by every workgroup. Ends with a workgroup barrier.
+    // `roots`: D float2 of LDS that are free until the caller's next use of them. Short transforms pick their register
+    // twiddles out of a table of the D-th roots of unity: computed where they are needed, D = 64 and 128 have 12 and 14
+    // inlined sine-cosine codes per lane, fetched and run once by every workgroup. Long ones have few, and run long. Ends
+    // with a workgroup barrier.
+    static constexpr bool kRoots = P::tw_off(P::NP) > 0 && P::D <= 256;
     __device__ __forceinline__ void init(int lg, float2 *twl_table, float2 *roots)
     {
         rbase = P::pad(lg);
         twl = twl_table + lg;
-        if constexpr (P::tw_off(P::NP) > 0) {
+        if constexpr (kRoots) {
             for (int i = threadIdx.x; i < P::D; i += blockDim.x) {
                 float s, c;
                 sincospif(-2.0f * (float)i / (float)P::D, &s, &c);
@@ -331,7 +333,7 @@ struct WaveFft {
         fill_table<1>(twl_table);
         __syncthreads();
         init_pass<0>(lg, roots);
-        if constexpr (P::tw_off(P::NP) > 0) __syncthreads();
+        if constexpr (kRoots) __syncthreads();
     }
 
     // Workgroup-cooperative fill of the LDS twiddle table; the caller synchronises afterwards.
@@ -370,7 +372,16 @@ struct WaveFft {
                 for (int u = 0; u < NSETS; ++u) {
                     const int k = (lg + P::G * u) % Ns;
 #pragma unroll
-                    for (int t = 1; t < r; ++t) tw[P::tw_off(PI) + u * (r - 1) + (t - 1)] = roots[k * t * (P::D / (Ns * r))];
+                    for (int t = 1; t < r; ++t) {
+                        float2 &w = tw[P::tw_off(PI) + u * (r - 1) + (t - 1)];
+                        if constexpr (kRoots) {
+                            w = roots[k * t * (P::D / (Ns * r))];
+                        } else {
+                            float s, c;
+                            sincospif(-2.0f * (float)(k * t) / (float)(Ns * r), &s, &c);
+                            w = make_float2(c, s);
+                        }
+                    }
                 }
             }
             init_pass<PI + 1>(lg, roots);
