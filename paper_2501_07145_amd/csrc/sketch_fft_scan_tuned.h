@@ -603,12 +603,17 @@ __device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool se
 // SIMD (128 registers) cost it a few dozen spills of accumulators, which are touched once per iteration; from
 // kJointRegs registers of accumulators on, or with values carried from iteration to iteration, it gets the budget of two.
 constexpr int kJointRegs = 44;
+// Whether one thread carries both real bins (0 and D/2) where that saves a bin per thread. Not in the kernel for sequences
+// cut in time with transforms of a whole wavefront: the second copy of phase 3 that the packed thread needs pushes its
+// accumulators into spills (D = 1024, four levels, order 2: 101 spills packed, none unpacked and twice as fast; eight levels 1.4
+// times; D = 2048, four levels, order 2, 1.7 times; shorter transforms lose up to a tenth unpacked).
+constexpr bool packs(bool JOINT, bool stream, int FPW) { return !JOINT || stream || FPW > 1; }
 constexpr int accumulators(int M, bool JOINT) { return JOINT ? M * (M + 1) / 2 : M; }
 template <int LOG2D, int M, int NTR, bool JOINT>
 constexpr int kernel_min_waves()
 {
     using P = Plan<LOG2D>;
-    constexpr int BPT = (P::D / 2 + 64 * NTR - 1) / (64 * NTR);
+    constexpr int BPT = (P::D / 2 + !packs(JOINT, NTR != M, P::FPW) + 64 * NTR - 1) / (64 * NTR);
     if (JOINT && (P::kMinWaves <= 2 || NTR != M || 2 * BPT * accumulators(M, JOINT) > kJointRegs)) return 2;
     return P::FPW > 4 && P::FPW < 16 && (M == 5 || M == 6) && !JOINT ? 5 : P::kMinWaves;
 }
@@ -620,12 +625,11 @@ constexpr int joint_workgroups_per_cu(int M, int D)
     return D == 2048 || M >= 7 || (dealt && M >= 5) || ((D == 1000 || D == 1024) && M <= 3) ? 1 : 2;
 }
 // JOINT: transforms in flight as above where the values carried from one iteration to the next (one set per first
-// position) fit the registers.
+// position, larger for higher orders) fit the registers.
 constexpr int joint_transforms_in_flight(int M, int LOG2D, int order)
 {
-    return order == 1 && (LOG2D != 2048 || M <= 4) ? transforms_in_flight(M, LOG2D) : M;
+    return (order == 1 && (LOG2D != 2048 || M <= 4)) || M <= 2 ? transforms_in_flight(M, LOG2D) : M;
 }
-
 // Short transforms: a wavefront carries FPW = 4 .. 16 pairs of steps per iteration, while their D/2 + 1 bins occupy
 // a fraction of the workgroup's threads, which would take the pairs one after the other (D = 100, five levels: 51 of 320
 // threads, 12 pairs). The kernel for sequences cut in time therefore cuts its piece once more, into as many groups as
@@ -668,9 +672,9 @@ __global__ __launch_bounds__(64 * NTR)
     static_assert(!kStream || NTR > M, "streaming needs a slot per level");
     // Bins of phase 3: f = 0 .. D/2, thread t owning f = t, t + NT, ... The transforms of real sequences are real
     // at f = 0 and f = D/2. Where that saves a bin per thread (NT divides D/2), thread 0 carries both in one
-    // float2 (bin 0 in .x, bin D/2 in .y; kPack) and the bins are f = 0 .. D/2 - 1.
+    // float2 (bin 0 in .x, bin D/2 in .y; kPack, see packs) and the bins are f = 0 .. D/2 - 1.
     constexpr int D = P::D, NT = 64 * NTR;
-    constexpr bool kPack = (D / 2) % NT == 0;
+    constexpr bool kPack = (D / 2) % NT == 0 && packs(JOINT, NTR != M, P::FPW);
     constexpr int NB = kPack ? D / 2 : D / 2 + 1, BPT = (NB + NT - 1) / NT;
     constexpr int GR = JOINT && !kStream ? joint_groups(M, D, P::FPW, P::PD) : 1, SPG = P::FPW / GR;   // groups; transforms of each
     static_assert(GR == 1 || (BPT == 1 && !kPack), "a thread of a group owns one bin");
@@ -813,9 +817,11 @@ __global__ __launch_bounds__(64 * NTR)
     // copies them out of LDS, the slots are released by the second barrier at once, and the next iteration's
     // direct loads are issued before the recurrence arithmetic, which then runs under their latency.
     // (Measured: 3-4 % on D = 1024 and 2048 with five levels; with 32 float2 -- D = 512, four levels -- it no
-    // longer pays, and loading the next iteration's table words early as well costs more registers than it hides.)
+    // longer pays, and loading the next iteration's table words early as well costs more registers than it hides.) JOINT:
+    // where they fit beside its accumulators.
     constexpr int ZREGS = P::FPW * BPT * NTR * 2;
-    constexpr bool kEarly = GR == 1 && ZREGS <= (P::kMinWaves <= 2 ? 64 : 24);    // (a plan with twice the registers per wavefront affords more)
+    constexpr bool kEarly = GR == 1 && ZREGS <= (P::kMinWaves <= 2 ? 64 : 24)    // (a plan with twice the registers per wavefront affords more)
+                            && (!JOINT || 2 * (ZREGS + BPT * kAcc) <= 200);
     uint32_t gw[P::R], fw[kFoldInRegs];
 
     // The item of this wavefront: level and first pair of its transform in the current iteration (a transform

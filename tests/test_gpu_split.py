@@ -42,6 +42,15 @@ def _case(seed, N, L, d, M, F, D):
     (2, 50, 3, 5, 300, 1024, 2),
     (2, 131, 3, 3, 50, 200, 3),
     (1, 40, 3, 4, 200, 512, 3),
+    (2, 90, 3, 2, 200, 1024, 2),       # up to two levels: items dealt to eight wavefronts in every order
+    (1, 131, 3, 2, 250, 1000, 3),
+    (1, 90, 3, 2, 300, 2048, 2),
+    (2, 700, 3, 2, 64, 2048, 3),
+    (3, 800, 3, 1, 30, 1024, 3),
+    (1, 140, 3, 4, 200, 2048, 2),      # both real bins in threads of their own
+    (3, 100, 3, 8, 200, 1024, 2),
+    (3, 100, 3, 4, 200, 1024, 3),
+    (1, 1000, 2, 8, 200, 2048, 1),     # cut into pieces, accumulators beyond the registers
 ])
 def test_split_batches_match_the_oracle(oracle, N, L, d, M, F, D, order):
     X, W, hash_, sign = _case(N + L + D, N, L, d, M, F, D)
