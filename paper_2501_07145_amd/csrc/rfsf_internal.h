@@ -78,6 +78,8 @@ bool sketch_fft_scan_is_tuned(int M, int F, int D);
 bool sketch_fft_scan_joint(int M, int F, int D);
 int sketch_fft_scan_joint_per_cu(int M, int D);            // its workgroups that a CU holds, by registers
 int sketch_fft_scan_joint_fit(int M, int F, int D, int order);      // ... and by LDS
+bool sketch_fft_scan_joint_splits(int M, int D, int order);        // splitting whole sequences can gain
+int sketch_fft_scan_wavefronts(int M, int D);                      // of a workgroup for whole sequences
 int sketch_fft_scan_pairs_per_iteration(int D);            // pairs of steps a wavefront transforms at a time
 bool sketch_fft_scan_fits(int M, int F, int D, int order);  // false: neither kernel can run it (LDS need above a CU's)
 size_t sketch_fft_scan_table_bytes(int M, int F, int D);   // 0 when the generic kernel runs

@@ -122,6 +122,12 @@ constexpr int64_t kSplitSequences = 256, kCUs = 256;
 // i iterations, 3 i + 0.3 p / (i * pairs per iteration) is least at i^2 = p / (10 * pairs per iteration).
 constexpr int64_t kSplitPieces = 64, kJoinsPerIteration = 10;
 constexpr int kJoinInPlace = 16;    // more pieces are joined by a kernel of its own, which keeps several in flight
+// A single level only adds its increments up, a pair costs a thread a fortieth of that: whole sequences of fewer than this
+// many loads per thread are not split (60 points: 22 us whole, 25 split with 32 frequencies, 23 and 30 with 128; 150 points 33
+// and 32, 300 points 48 and 38, 512 frequencies, 60 points 64 and 52, all of 60 sequences in 256 buckets).
+constexpr int64_t kSumLoads = 128;
+// Order of the recurrence that a launch runs: a single level is the same in all of them.
+int kernel_order(const rfsf_ts_shape *s) { return s->order < 2 || s->M == 1 ? 1 : s->order; }
 struct SketchCut { int pieces; int64_t pairs; bool joint, in_place; };
 SketchCut sketch_cut(const rfsf_ts_shape *s)
 {
@@ -135,10 +141,13 @@ SketchCut sketch_cut(const rfsf_ts_shape *s)
     const int64_t floats_per_pair = (int64_t)s->M * 4 * s->F;
     const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
     const int fpw = rfsf::sketch_fft_scan_pairs_per_iteration(P);
-    const int64_t per_cu = rfsf::sketch_fft_scan_joint_per_cu(s->M, P), fit = rfsf::sketch_fft_scan_joint_fit(s->M, s->F, P, s->order < 2 ? 1 : s->order);
+    const int64_t per_cu = rfsf::sketch_fft_scan_joint_per_cu(s->M, P), fit = rfsf::sketch_fft_scan_joint_fit(s->M, s->F, P, kernel_order(s));
     const int64_t at_once = kCUs * (fit < per_cu ? fit : per_cu);
     int64_t most = kCUs * per_cu / s->N;           // pieces that fill the chip
     if (most > kSplitPieces) most = kSplitPieces;
+    if (!rfsf::sketch_fft_scan_joint_splits(s->M, P, kernel_order(s))) return whole;
+    const int threads = 64 * rfsf::sketch_fft_scan_wavefronts(s->M, P);
+    if (s->M == 1 && all_pairs * ((s->F + threads - 1) / threads) < kSumLoads) return whole;
     // iterations of the kernel per piece: the fewest that keep to `most`, and no fewer than balance the join
     int64_t its = (all_pairs + most * fpw - 1) / (most > 0 ? most * fpw : 1);
     while (its * its * kJoinsPerIteration * fpw < all_pairs) ++its;
@@ -309,7 +318,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
         if (plan.pieces == 1) {
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
             if (rfsf::launch_sketch_fft_scan(dphi, hash, sign, table, cnt, shape->L, chunk_lengths,
-                                             shape->M, shape->F, P, shape->D, shape->order < 2 ? 1 : shape->order,
+                                             shape->M, shape->F, P, shape->D, kernel_order(shape),
                                              out + n0 * shape->ld_out, shape->ld_out, state, stream,
                                              rfsf::TimeCut::whole(shape->L, shape->M)) != hipSuccess)
                 return RFSF_E_HIP;
@@ -317,7 +326,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
             // sequences cut in time: the accumulators of all ranges of tensor positions of every piece, the join (of many
             // pieces by a launch of its own) and the final transforms (timed as one launch of the sketch kernel class)
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
-            const int order = shape->order < 2 ? 1 : shape->order, bins = P / 2 + 1;
+            const int order = kernel_order(shape), bins = P / 2 + 1;
             rfsf::TimeCut cut = {plan.pieces, shape->M, plan.pairs, nullptr, 1, plan.pieces, 0, 0};
             if (plan.in_place) {
                 cut.piece_stride = plan.pairs * (int64_t)shape->M * 2 * shape->F;          // float2 per pair: M * 2F
@@ -348,7 +357,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
             // a = 0 .. M-1, the join, and the final transforms of the joined accumulators (timed as one launch of the sketch kernel class)
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
             rfsf::PieceRows rows = {};
-            const int order = shape->order < 2 ? 1 : shape->order;
+            const int order = kernel_order(shape);
             float2 *next = reinterpret_cast<float2 *>(state);
             const size_t bins = (size_t)P / 2 + 1;
             const size_t level_words = rfsf::sketch_fft_scan_table_bytes(shape->M, shape->F, P) / sizeof(uint32_t) / (size_t)shape->M;

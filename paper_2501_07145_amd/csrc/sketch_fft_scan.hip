@@ -256,6 +256,10 @@ int sketch_fft_scan_joint_fit(int M, int F, int D, int order)
     return (int)(kLdsPerCu / lds);
 }
 
+bool sketch_fft_scan_joint_splits(int M, int D, int order) { return tuned::joint_fits(M, D, plan_key(D), order); }
+
+int sketch_fft_scan_wavefronts(int M, int D) { return tuned::transforms_in_flight(M, plan_key(D)); }
+
 int sketch_fft_scan_pairs_per_iteration(int D)
 {
     TunedGeometry g;

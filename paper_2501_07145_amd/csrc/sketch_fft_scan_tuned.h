@@ -630,6 +630,16 @@ constexpr int joint_transforms_in_flight(int M, int LOG2D, int order)
 {
     return (order == 1 && (LOG2D != 2048 || M <= 4)) || M <= 2 ? transforms_in_flight(M, LOG2D) : M;
 }
+// Whether the accumulators of the JOINT kernel fit its registers. Where they do not (D = 2048 with seven and eight levels,
+// 200 to 400 spills) it takes 3 to 5 times as long per step as the kernel for whole sequences, and splitting those gains
+// nothing: 120 sequences of 100 points in two pieces were 0.6 and 0.5 times as fast as whole, 60 in four 0.95 and 0.8, nine of
+// 401 points in 25 (eight levels, order 2) 0.92.
+constexpr bool joint_fits(int M, int D, int LOG2D, int order)
+{
+    const int ntr = joint_transforms_in_flight(M, LOG2D, order), bpt = (D / 2 + 64 * ntr) / (64 * ntr);
+    return 2 * bpt * accumulators(M, true) < 160;
+}
+
 // Short transforms: a wavefront carries FPW = 4 .. 16 pairs of steps per iteration, while their D/2 + 1 bins occupy
 // a fraction of the workgroup's threads, which would take the pairs one after the other (D = 100, five levels: 51 of 320
 // threads, 12 pairs). The kernel for sequences cut in time therefore cuts its piece once more, into as many groups as

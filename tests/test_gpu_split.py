@@ -73,8 +73,12 @@ def test_split_batches_match_the_oracle(oracle, N, L, d, M, F, D, order):
     (150, 101, 4, 1000, 512, False),       # three pieces in two rounds
     (128, 101, 4, 1000, 512, True),        # two pieces in one round
     (100, 101, 4, 700, 256, True),         # five pieces in two rounds
+    (60, 61, 1, 128, 256, False),          # a single level: too few loads per thread
+    (60, 301, 1, 128, 256, True),
+    (60, 101, 8, 500, 2048, False),        # accumulators beyond the registers
+    (60, 101, 6, 500, 2048, True),
 ])
-def test_no_split_into_as_many_rounds_as_half_its_pieces(N, L, M, F, D, split):
+def test_no_split_that_gains_nothing(N, L, M, F, D, split):
     """Sequences of a batch that is split are summed in another order than those of one that is too large to be."""
     X, W, hash_, sign = _case(N + F, 300, L, 3, M, F, D)
     x, w, h, s = (torch.from_numpy(a).cuda() for a in (X, W, hash_, sign))
