@@ -653,10 +653,18 @@ constexpr int joint_groups(int M, int D, int FPW, int PD)
     return 1;
 }
 // ... and from three groups on that is also the faster way for a whole sequence, for all that it advances
-// M(M+1)/2 accumulators instead of M. (1000 sequences of 100 points: D = 64 82 -> 67 us with four levels, D = 100
-// 65 -> 56 with three, 248 -> 225 with eight, D = 128 218 -> 192 with five; D = 200, whose bins fill more of the threads,
-// 209 -> 257 with five and 389 -> 402 with eight.)
-constexpr bool grouped(int M, int D, int FPW, int PD) { return D <= 128 && joint_groups(M, D, FPW, PD) >= 3; }
+// M(M+1)/2 accumulators instead of M (sketch kernel, one wavefront after the other against grouped, 3000 sequences of 200
+// points: D = 64, 32 frequencies, 218 -> 149 us with three levels, 597 -> 388 with six; D = 100, 50 frequencies, 382 -> 352
+// with four, 768 -> 639 with six; D = 128, 64 frequencies, 731 -> 551 with five, 942 -> 677 with six). From seven levels on
+// these accumulators let a CU hold one workgroup where it would hold two of the others; where the slots let it hold only
+// one of those too, or with eight groups, it still gains (eight levels: D = 64, 32 frequencies, 609 -> 612; 64 buckets in
+// 128 points, 96 frequencies, 1557 -> 1358; but D = 100, 50 frequencies, 843 -> 1002, D = 128, 64, 751 -> 1048).
+enum class Grouped { kNever, kOneWorkgroup, kAlways };
+constexpr Grouped grouped(int M, int D, int FPW, int PD)
+{
+    if (D > 128 || joint_groups(M, D, FPW, PD) < 3) return Grouped::kNever;
+    return M <= 6 || joint_groups(M, D, FPW, PD) >= 8 ? Grouped::kAlways : Grouped::kOneWorkgroup;
+}
 
 // Index of the accumulator of tensor positions a+1 .. l+1 (0-based a <= l) among those of a bin; a = 0 first.
 __host__ __device__ constexpr int acc_index(int M, int a, int l) { return a * M - a * (a - 1) / 2 + l - a; }

@@ -107,3 +107,23 @@ def test_joined_sums_of_noise(oracle, N, L, d, M, F, D):
     err = block_errors(got[sel], oracle.features(X[sel], W, hash_, sign, 1.0, D), M, D)
     print(f"noise N={N} L={L} M={M} F={F} D={D}: block errors {err}")
     assert np.all(err <= FP32_BLOCK_TOL)
+
+
+@pytest.mark.parametrize("D", [100, 128])
+def test_eight_levels_cost_no_more_each_than_six(D):
+    """Whole sequences in short transforms: the kernel that keeps every range of levels is not taken where its registers
+    halve the wavefronts on a CU (sketch kernel, eight levels against six: 1.55 times with it at D = 128, 1.11 without;
+    1.57 and 1.32 at D = 100; the bound lies between)."""
+    def us(M):
+        x, w, h, s = (torch.from_numpy(a).cuda() for a in _case(M, 3000, 200, 3, M, D // 2, D))
+        times = []
+        for _ in range(7):
+            rfsf.rfsf_ts_profile_enable(True)
+            rfsf.rfsf_ts_profile_read(True)
+            rfsf.rfsf_ts_features(x, w, h, s, 1.5, D)
+            torch.cuda.synchronize()
+            times.append(rfsf.rfsf_ts_profile_read(True)["ms_sketch_fft_scan"] * 1e3)
+            rfsf.rfsf_ts_profile_enable(False)
+        return min(times)
+
+    assert us(8) < 1.45 * us(6)
