@@ -18,7 +18,7 @@ constexpr int kRawBufferWord3 = 0x00020000;   // buffer descriptor, last word: u
 constexpr int kTileStride = 36;    // floats per component in the transposition tile: 16-byte accesses of 16
                                    // consecutive components then fall on 16 distinct groups of four banks
 
-// sqrt(2) cos(pi x) to 1.2e-7 absolute (and what the rounding of x costs) for |x| < 2^22: x = k + r with |r| <= 1/2, k
+// sqrt(2) cos(pi x) to 1.5e-7 absolute (and what the rounding of x costs) for |x| < 2^22: x = k + r with |r| <= 1/2, k
 // from adding 1.5 * 2^23, whose lowest mantissa bit is then the parity of k, and r exact; a degree-5 polynomial in
 // r^2 (Chebyshev interpolant of sqrt(2) cos(pi sqrt(u)) on [0, 1/4]) and the sign (-1)^k, added to the sign bit.
 // Half-turns rather than radians: the reduction takes no multiplication and rounds nothing. `rest` is what rounding the

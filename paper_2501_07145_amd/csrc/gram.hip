@@ -6,8 +6,9 @@
 // numbers, x = hi + mid + lo (each the rounding of what the ones before it leave over, 8 significand bits each,
 // 24 in all: nothing is lost), a product of two bfloat16 numbers is exact in 32 bits, and of the nine products of
 // a pair of floats the six largest are added up in the 32-bit accumulators, smallest first. The three that are
-// left out (mid*lo, lo*mid, lo*lo) are together below 2^-25 of the product, half of what rounding it to 32 bits
-// may cost. Measured against 64 bits, the sums are a third closer than with v_mfma_f32_32x32x2f32, which rounds
+// left out (mid*lo, lo*mid, lo*lo) are together below 2^-24 of the product, as much as rounding it to 32 bits
+// may cost (numbers below about 2^-114 lose their last bits, whose bfloat16 would be too small: 1e-7 of a product with 2^-116,
+// 1.3e-5 with 2^-123). Measured against 64 bits, the sums are a third closer than with v_mfma_f32_32x32x2f32, which rounds
 // after every product: relative error of K 1.2e-6 against 1.95e-6 on 10000 x 10000 x 5121, 1.8e-6 against 2.8e-6
 // on 50000 x 5000 x 10241. The instructions round downwards, though, whatever the sign of the sum: of products with 128
 // columns the error averages -1.1e-8 of their root mean square (its own 5.5e-8; v_mfma_f32_32x32x2f32: 1.8e-7, average zero).
@@ -339,8 +340,8 @@ __global__ __launch_bounds__(64 * NW, T == 1 ? 4 : 2) void gram_small(GramArgs g
 // the other waits at its barrier.
 // Bound: power. On 50000 x 5000 x 10241 the matrix pipes are busy 66 % of the cycles and the clock falls from 2.4 to
 // 1.7 GHz: 26.0 ms, 1.18 PFLOP/s of bfloat16 products (the library's bfloat16 product of two 8192 x 8192 matrices
-// reaches 1.09 here), 197 TFLOP/s of the product asked for. v_mfma_f32_32x32x2f32 gave 38.8 ms, 132 TFLOP/s, 0.84 of
-// its peak. 10000 rows with themselves, 5121 columns: 2.88 ms against 3.90.
+// reaches 1.25 to 1.30 here), 197 TFLOP/s of the product asked for. v_mfma_f32_32x32x2f32 gave 38.8 ms, 132 TFLOP/s, 0.84 of
+// its peak. 10000 rows with themselves, 5121 columns: 2.97 ms against 3.90.
 // LDS layout of one buffer: 384 rows (256 of A, 128 of B) of 4 chunks of 16 bytes; slot p of row r holds chunk
 // p ^ ((r / 4) mod 4): the XOR makes the fragment reads (16 consecutive rows, same chunk) hit 16 distinct 16-byte
 // positions of the 256-byte bank row, and a direct load can produce it because each lane chooses what it fetches.

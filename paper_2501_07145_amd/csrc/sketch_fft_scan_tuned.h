@@ -138,7 +138,7 @@ template <> struct Plan<2048> : Plan<11, 5> {};
 // Geometry of one LDS slot (float2 units): [0, ZS) data -- the staging area uses [0, 2F), the transform [0, PD) --,
 // [ZS] a float2 that is always zero (source of buckets without a first or second coordinate). A direct load deposits
 // 128 coordinates; of the last one of a pair the lanes beyond 2F stay out. (With all 64, F = 32 staged twice what it
-// has: 1000 x 100 points, four levels, D = 64 and F = 32 59 us against 43, D = 128 and F = 70 94 against 68, five
+// has: 1000 x 100 points, four levels, D = 64 and F = 32 59 us against 45, D = 128 and F = 70 94 against 68, five
 // levels, D = 256 and F = 70 206 against 190.)
 __host__ __device__ constexpr int staged(int twoF) { return (twoF + 127) & ~127; }      // by whole direct loads
 __host__ __device__ constexpr int zero_slot(int PD, int twoF) { return PD > twoF ? PD : twoF; }
@@ -672,8 +672,8 @@ __host__ __device__ constexpr int acc_index(int M, int a, int l) { return a * M 
 // JOINT: the workgroup owns one piece of a sequence cut in time (TimeCut::mode 1) and runs the recurrence for
 // every first tensor position at once: per bin A^{(a..l)} += A^{(a..l-1)}(before the step) C_l for all a <= l. The
 // transforms, which are most of the work, are thus done once per step and level however many first positions
-// need them (one launch per first position did (M+1)/2 times as many: 10 x 1e5 steps, D = 100, five levels 2.68 ms, this
-// 1.52, with groups 0.87). In mode 2 the same kernel joins a sequence's pieces and runs the final
+// need them (one launch per first position did (M+1)/2 times as many: 10 x 1e5 steps, D = 100, five levels 2.68 ms, with
+// groups 1.00). In mode 2 the same kernel joins a sequence's pieces and runs the final
 // transforms.
 template <int LOG2D, int M, int ORDER, int NTR, bool JOINT>
 __global__ __launch_bounds__(64 * NTR)
