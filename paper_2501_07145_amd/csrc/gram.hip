@@ -16,6 +16,18 @@
 // instead of its root: `FLIP`.
 // Infinite operands, and finite ones that round to an infinite bfloat16, would turn into NaN in the split
 // (inf - inf): entries that come out as NaN without a NaN in their rows are computed again in 32 bits (settle_nan).
+//
+// Large tiles of 128 columns and more take two terms of 16-bit floating point instead, x s = hi + lo with a power of two s for
+// each row, and three products (lo*hi, hi*lo, hi*hi): half the matrix instructions. The two terms hold 11 significand
+// bits each and the sign of the second one more; what they leave over is one unit of the last place of a float for a
+// quarter of the numbers, nothing for the others, and lo*lo is left out (4e-8 of a product, root mean square). Both are less
+// than what adding up loses, where half as many additions round: relative error of K against 64 bits, three terms and two, 1.63e-7
+// and 1.43e-7 with 128 columns of normal numbers, 3.0e-7 and 2.3e-7 with 400, 5.3e-7 and 4.6e-7 with 1001 of features, 1.07e-6 and
+// 9.8e-7 with 5121, 1.5e-6 and 1.4e-6 with 10241 (mean error -2.37e-7 and -2.31e-7 of 5121 columns). The range of these
+// numbers is narrow. A row's scale brings the largest of 64 of its numbers to 2^9 (48 at its beginning, which are in LDS anyway,
+// and four at each of four places spread over it): numbers down to 2^-12 of that keep both terms in full, smaller ones an
+// error of 2^-34 of it; numbers more than 64 times as large overflow, which shows as NaN, and the tile is computed
+// again with three terms, as are tiles with rows beyond 2^-91 .. 2^109 from the outset.
 #include "rfsf_internal.h"
 #include <type_traits>
 
@@ -27,6 +39,8 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef _Float16 halfx8 __attribute__((ext_vector_type(8)));
+typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 
 // FLIP: the rows of A for which this is the sign bit enter negated, and so do the results that they give, so that rounding
 // downwards comes out as rounding upwards for half of the rows: whole blocks of 32, the edge of the smallest tile, so that a
@@ -84,6 +98,22 @@ __device__ __forceinline__ void mfma_split(const Split8 &a, const Split8 (&b)[NB
     RFSF_TERM(hi, mid);
     RFSF_TERM(hi, hi);
 #undef RFSF_TERM
+}
+
+// Two terms: eight consecutive numbers of a row times its scale, and the three products, smallest first.
+struct Half8 { uint32_t hi[4], lo[4]; };
+__device__ __forceinline__ void split_pair(Half8 &f, int i, float a, float b, float scale)
+{
+    const floatx2 v = {a * scale, b * scale};
+    const halfx2 hi = __builtin_convertvector(v, halfx2);                                                // v_cvt_pk_f16_f32
+    const floatx2 rest = {fmaf(a, scale, -(float)hi[0]), fmaf(b, scale, -(float)hi[1])};                 // v_fma_mix_f32
+    f.hi[i] = __builtin_bit_cast(uint32_t, hi);
+    f.lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, halfx2));
+}
+__device__ __forceinline__ floatx16 product(int k, const Half8 &a, const Half8 &b, const floatx16 &c)
+{
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(halfx8, k == 0 ? a.lo : a.hi),
+                                                  __builtin_bit_cast(halfx8, k == 1 ? b.lo : b.hi), c, 0, 0, 0);
 }
 
 // One operand pair of a launch: row-major, K-contiguous. Batched launches (one product per level of RFSF-TRP) add
@@ -333,15 +363,16 @@ __global__ __launch_bounds__(64 * NW, T == 1 ? 4 : 2) void gram_small(GramArgs g
 // Large problems: tile 256 x 128, four wavefronts 2 x 2 of 128 x 64, steps of 16 columns of K in three LDS buffers.
 // The floats go from global memory straight into LDS (global_load_lds: lane i of a wavefront deposits its bytes at
 // LDS base + i times their number, no register and no LDS-write instruction involved), two steps ahead, and are split
-// when they are read: a wavefront splits (128 + 64) x 16 numbers for 48 matrix instructions, 5.5 vector
-// instructions for each, which issue in the 32 cycles that it takes (measured: up to six are free, with
-// eight the rate falls by a fifth; 64 x 64 per wavefront would need 7.3). 128 x 64 also keeps the LDS reads at a
-// quarter of the matrix time. Two workgroups per CU (74 KB of LDS and 256 registers each), so that one computes while
-// the other waits at its barrier.
-// Bound: power. On 50000 x 5000 x 10241 the matrix pipes are busy 66 % of the cycles and the clock falls from 2.4 to
-// 1.7 GHz: 26.0 ms, 1.18 PFLOP/s of bfloat16 products (the library's bfloat16 product of two 8192 x 8192 matrices
-// reaches 1.25 to 1.30 here), 197 TFLOP/s of the product asked for. v_mfma_f32_32x32x2f32 gave 38.8 ms, 132 TFLOP/s, 0.84 of
-// its peak. 10000 rows with themselves, 5121 columns: 2.97 ms against 3.90.
+// when they are read: a wavefront splits (128 + 64) x 16 numbers for 48 matrix instructions of three terms, 5.5 vector
+// instructions for each, or 24 of two terms, 6 for each. 128 x 64 also keeps the LDS reads at a
+// quarter of the matrix time. Two workgroups per CU (75 KB of LDS and 256 registers each), so that one computes while
+// the other waits at its barrier, starts or stores.
+// Bound: power. With two terms the clock falls from 2.4 to 1.4 to 1.7 GHz on whole-chip products; a step of a CU takes 1650
+// cycles with one workgroup on it where its matrix instructions take 768, 2000 to 2200 with two. Three terms and two:
+// 50000 x 5000 x 10241 26.4 and 18.4 ms (58 % of the requests hit the L2), 10000 rows with themselves, 5121 columns 3.02 and 2.14,
+// 5000 rows 0.97 and 0.60, 7494 rows, 1001 columns 0.420 and 0.268, 59952 x 200 x 400 77 and 54 us. Tiles of 256 x 256 with
+// eight wavefronts, one workgroup per CU, take 16.6 ms for the largest but 320 us for 7494 rows and 66 for 59952 x 200 x 400: the
+// start and the stores of a tile, 35000 cycles, have nothing to hide behind. v_mfma_f32_32x32x2f32 gave 38.8 and 3.90 ms.
 // LDS layout of one buffer: 384 rows (256 of A, 128 of B) of 4 chunks of 16 bytes; slot p of row r holds chunk
 // p ^ ((r / 4) mod 4): the XOR makes the fragment reads (16 consecutive rows, same chunk) hit 16 distinct 16-byte
 // positions of the 256-byte bank row, and a direct load can produce it because each lane chooses what it fetches.
@@ -397,77 +428,101 @@ __device__ __forceinline__ void direct_load(const char *base, uint32_t off, floa
 }
 #pragma clang diagnostic pop
 
-template <bool ALIGNED, bool SYM, bool FLIP>
-__global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, int64_t nti, int64_t ntj)
+template <typename T>
+__device__ __forceinline__ T uniform(T x)
 {
-    __shared__ __attribute__((aligned(16))) float buf[3][kBigBuffer];
-    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int half = lane >> 5, col = lane & 31;
-    const int wi = wave >> 1, wj = wave & 1;
-    const int64_t rank = rank_of_block(tiles);
-    if (rank >= tiles) return;
-    const TileCoord tc = big_tile<SYM>(rank, nti, ntj);
-    const int64_t i0 = (int64_t)__builtin_amdgcn_readfirstlane((int)tc.bi) * kBigM;
-    const int64_t j0 = (int64_t)__builtin_amdgcn_readfirstlane((int)tc.bj) * kBigN;
-    const float *A = g.A + blockIdx.y * g.step_a, *B = g.B + blockIdx.y * g.step_b;
-    float *C = g.C + blockIdx.y * g.step_c;
-
-    floatx16 acc[4][2];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
-
+    const uint64_t bits = __builtin_bit_cast(uint64_t, x);
+    const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)bits), hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(bits >> 32));
+    return __builtin_bit_cast(T, hi << 32 | lo);
+}
+// A tile's place, the sources of its direct loads and the steps of its columns: what the kernels of large tiles share.
+typedef __attribute__((address_space(3))) float LdsFloat;
+template <bool ALIGNED, bool CALLED = false>
+struct BigTile {
     // Direct loads: instruction j of wavefront w fills rows RI (w NL + j) .. + RI - 1 of the buffer (RI rows per
     // instruction). Rows beyond the matrix are redirected to its last one.
-    constexpr int RI = ALIGNED ? 16 : 4, NL = kBigRows / RI / 4;
-    const int lrow = ALIGNED ? lane >> 2 : lane >> 4;
+    static constexpr int RI = ALIGNED ? 16 : 4, NL = kBigRows / RI / 4;
+    const GramArgs &g;
+    float *buf;                         // three buffers in LDS
+    const float *A, *B;
+    float *C;
+    int64_t i0, j0, nfull, nsteps;
+    int tid, lane, wave, half, col, wi, wj, rest, shift, fsw, frag_a, frag_b;
     uint32_t off[NL];                   // byte offset of this lane's source from the operand's tile
+
+    __device__ __forceinline__ BigTile(const GramArgs &args, float *buffers, int64_t i, int64_t j) : g(args), buf(buffers), i0(i), j0(j)
+    {
+        A = g.A + blockIdx.y * g.step_a;
+        B = g.B + blockIdx.y * g.step_b;
+        C = g.C + blockIdx.y * g.step_c;
+        tid = threadIdx.x;
+        lane = tid & 63;
+        wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        half = lane >> 5;
+        col = lane & 31;
+        wi = wave >> 1;
+        wj = wave & 1;
+        // the last, partial step comes first (buffer 0), number by number with zeros beyond K; full step s follows
+        // in buffer (s + shift) mod 3
+        nfull = g.K / kStep;
+        rest = (int)(g.K - kStep * nfull);
+        shift = rest != 0 ? 1 : 0;
+        nsteps = nfull + shift;
+        fsw = (col >> 2) & 3;
+        frag_a = (wi * 128 + col) * kStep;
+        frag_b = (kBigM + wj * 64 + col) * kStep;
+        const int lrow = ALIGNED ? lane >> 2 : lane >> 4;
 #pragma unroll
-    for (int j = 0; j < NL; ++j) {
-        const int row0 = RI * (wave * NL + j), row = row0 + lrow;
-        const int slot = ALIGNED ? lane & 3 : (lane >> 2) & 3;
-        const int column = 4 * (slot ^ ((row >> 2) & 3)) + (ALIGNED ? 0 : lane & 3);
-        const bool is_b = row0 >= kBigM;
+        for (int l = 0; l < NL; ++l) {
+            const int row0 = RI * (wave * NL + l), row = row0 + lrow;
+            const int slot = ALIGNED ? lane & 3 : (lane >> 2) & 3;
+            const int column = 4 * (slot ^ ((row >> 2) & 3)) + (ALIGNED ? 0 : lane & 3);
+            off[l] = (uint32_t)(row_of(row) * (row0 >= kBigM ? g.ldb : g.lda) + column) * 4u;
+        }
+    }
+    // row of the operand that row `row` of a buffer holds, counted from the tile's first one
+    __device__ __forceinline__ int64_t row_of(int row) const
+    {
+        const bool is_b = row >= kBigM;
         const int64_t left = is_b ? g.Ny - 1 - j0 : g.Nx - 1 - i0, r = is_b ? row - kBigM : row;
-        off[j] = (uint32_t)((r < left ? r : left) * (is_b ? g.ldb : g.lda) + column) * 4u;
+        return r < left ? r : left;
     }
-    const char *base_a = reinterpret_cast<const char *>(A + i0 * g.lda);
-    const char *base_b = reinterpret_cast<const char *>(B + j0 * g.ldb);
-    auto load = [&](float *dst, int64_t k0) {
+    __device__ __forceinline__ const float *source(int row) const
+    {
+        return row >= kBigM ? B + (j0 + row_of(row)) * g.ldb : A + (i0 + row_of(row)) * g.lda;
+    }
+    __device__ __forceinline__ void load(float *dst, int64_t k0) const
+    {
+        const char *base_a = reinterpret_cast<const char *>(A + i0 * g.lda), *base_b = reinterpret_cast<const char *>(B + j0 * g.ldb);
 #pragma unroll
-        for (int j = 0; j < NL; ++j) {
-            const int row0 = RI * (wave * NL + j);              // uniform
-            direct_load<ALIGNED ? 16 : 4>((row0 >= kBigM ? base_b : base_a) + 4 * k0, off[j], dst + row0 * kStep);
-        }
-    };
-    const int64_t nfull = g.K / kStep;
-    const int rest = (int)(g.K - kStep * nfull);
-    // the last, partial step comes first (buffer 0), number by number with zeros beyond K; full step s follows
-    // in buffer (s + shift) mod 3
-    const int shift = rest != 0 ? 1 : 0;
-    const int64_t nsteps = nfull + shift;
-    if (rest != 0) {
-        float v[kBigBuffer / 256];
-#pragma unroll
-        for (int u = 0; u < kBigBuffer / 256; ++u) {
-            const int e = tid + 256 * u, row = e / kStep, k = e % kStep;
-            const bool is_b = row >= kBigM;
-            const int64_t left = is_b ? g.Ny - 1 - j0 : g.Nx - 1 - i0, r = is_b ? row - kBigM : row;
-            const float *src = is_b ? B + j0 * g.ldb : A + i0 * g.lda;
-            v[u] = k < rest ? src[(r < left ? r : left) * (is_b ? g.ldb : g.lda) + kStep * nfull + k] : 0.f;
-        }
-#pragma unroll
-        for (int u = 0; u < kBigBuffer / 256; ++u) {
-            const int e = tid + 256 * u, row = e / kStep, k = e % kStep;
-            buf[0][row * kStep + 4 * ((k >> 2) ^ ((row >> 2) & 3)) + (k & 3)] = v[u];
+        for (int l = 0; l < NL; ++l) {
+            const int row0 = RI * (wave * NL + l);              // uniform
+            const char *base = (row0 >= kBigM ? base_b : base_a) + 4 * k0;
+            direct_load<ALIGNED ? 16 : 4>(CALLED ? uniform(base) : base, off[l], dst + row0 * kStep);
         }
     }
-    const int fsw = (col >> 2) & 3;
-    const int frag_a = (wi * 128 + col) * kStep, frag_b = (kBigM + wj * 64 + col) * kStep;
-    auto read8 = [&](const float *rd, int at, float (&x)[8]) {
+    __device__ __forceinline__ void first_steps() const
+    {
+        if (rest != 0) {
+            float v[kBigBuffer / 256];
+#pragma unroll
+            for (int u = 0; u < kBigBuffer / 256; ++u) {
+                const int e = tid + 256 * u, row = e / kStep, k = e % kStep;
+                v[u] = k < rest ? source(row)[kStep * nfull + k] : 0.f;
+            }
+#pragma unroll
+            for (int u = 0; u < kBigBuffer / 256; ++u) {
+                const int e = tid + 256 * u, row = e / kStep, k = e % kStep;
+                buf[row * kStep + 4 * ((k >> 2) ^ ((row >> 2) & 3)) + (k & 3)] = v[u];
+            }
+        } else if (nsteps > 0) {
+            load(buf, 0);
+        }
+        if (nsteps > 1) load(buf + kBigBuffer, kStep * (1 - shift));
+        if (nsteps > 2) load(buf + 2 * kBigBuffer, kStep * (2 - shift));
+    }
+    __device__ __forceinline__ void read8(const float *rd, int at, float (&x)[8]) const
+    {
 #pragma unroll
         for (int c = 0; c < 2; ++c) {
             const float4 v = *reinterpret_cast<const float4 *>(rd + at + 4 * ((2 * half + c) ^ fsw));
@@ -476,7 +531,56 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
             x[4 * c + 2] = v.z;
             x[4 * c + 3] = v.w;
         }
-    };
+    }
+    // waits for this wavefront's loads and LDS operations and then for everybody
+    __device__ __forceinline__ void everybody() const
+    {
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    }
+    // Called by step s when it has read all of its buffer: waits for this wavefront's loads of the next step (those of the
+    // step after it stay in flight) and then for everybody: the next step can be read, and this step's buffer takes the
+    // loads of the step three ahead.
+    __device__ __forceinline__ void next_step(int64_t s, float *rd) const
+    {
+        if (s + 2 < nsteps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NL) : "memory");
+        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (s + 3 < nsteps) load(rd, kStep * (s + 3 - shift));
+    }
+};
+__device__ __forceinline__ void clear(floatx16 (&acc)[4][2])
+{
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[a][b][v] = 0.f;
+}
+__device__ __forceinline__ bool any_nan(const floatx16 (&acc)[4][2])     // of the wavefront (or inf - inf)
+{
+    float sum = 0.f;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) sum += acc[a][b][e];
+    return __ballot(sum != sum) != 0;
+}
+
+// One tile with three terms, from the first load to the last entry.
+template <bool ALIGNED, bool SYM, bool FLIP, bool CALLED>
+__device__ __forceinline__ void three_term_tile(const GramArgs &g, float *buf, int64_t i0, int64_t j0)
+{
+    const BigTile<ALIGNED, CALLED> tile(g, buf, i0, j0);
+    const int wi = tile.wi, wj = tile.wj, half = tile.half, col = tile.col;
+    const int64_t nsteps = tile.nsteps;
+    floatx16 acc[4][2];
+    clear(acc);
     // Software pipeline. A step enters with the split fragments of its two blocks of B and of its first block of A; the
     // matrix instructions of one block of A run while the next one is split. Before the last block's, when
     // everything of this step has been read, the wavefront waits for its loads of the next step (those of the
@@ -489,9 +593,9 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
     for (int t = 0; t < 4; ++t) sign[t] = flip_of_row(i0 + wi * 128 + 32 * t);
     auto first_fragments = [&](const float *rd, Split8 (&nb)[2], Split8 &na) {
         float x[3][8];
-        read8(rd, frag_b, x[0]);
-        read8(rd, frag_b + 32 * kStep, x[1]);
-        read8(rd, frag_a, x[2]);
+        tile.read8(rd, tile.frag_b, x[0]);
+        tile.read8(rd, tile.frag_b + 32 * kStep, x[1]);
+        tile.read8(rd, tile.frag_a, x[2]);
         nb[0] = split8(x[0]);
         nb[1] = split8(x[1]);
         if (FLIP) flip(x[2], sign[0]);
@@ -507,7 +611,7 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
     auto step = [&](int64_t s, float *rd, const float *next) {
         float x[3][8];
 #pragma unroll
-        for (int t = 0; t < 3; ++t) read8(rd, frag_a + (t + 1) * 32 * kStep, x[t]);
+        for (int t = 0; t < 3; ++t) tile.read8(rd, tile.frag_a + (t + 1) * 32 * kStep, x[t]);
 #pragma unroll
         for (int t = 0; t < 3; ++t) {
             mfma_split<2>(a, b, acc[t]);
@@ -516,11 +620,7 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
             interleave(std::integral_constant<int, 4>{});
             __builtin_amdgcn_sched_barrier(0);
         }
-        if (s + 2 < nsteps) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(NL) : "memory");
-        else asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        if (s + 3 < nsteps) load(rd, kStep * (s + 3 - shift));
+        tile.next_step(s, rd);
         Split8 nb[2], na;
         first_fragments(next, nb, na);                          // (junk after the last step, not used)
         mfma_split<2>(a, b, acc[3]);
@@ -530,30 +630,19 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
         b[1] = nb[1];
         a = na;
     };
+    tile.first_steps();
     if (nsteps > 0) {
-        if (shift == 0) load(buf[0], 0);
-        if (nsteps > 1) load(buf[1], kStep * (1 - shift));
-        if (nsteps > 2) load(buf[2], kStep * (2 - shift));
-        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        first_fragments(buf[0], b, a);
+        tile.everybody();
+        first_fragments(buf, b, a);
         for (int64_t s = 0; s < nsteps; s += 3) {
-            step(s, buf[0], buf[1]);
-            if (s + 1 < nsteps) step(s + 1, buf[1], buf[2]);
-            if (s + 2 < nsteps) step(s + 2, buf[2], buf[0]);
+            step(s, buf, buf + kBigBuffer);
+            if (s + 1 < nsteps) step(s + 1, buf + kBigBuffer, buf + 2 * kBigBuffer);
+            if (s + 2 < nsteps) step(s + 2, buf + 2 * kBigBuffer, buf);
         }
     }
     // result layout of a 32x32 block: lane holds column lane % 32 and rows 8 q + 4 (lane / 32) + 0 .. 3
-    const bool vec_mirror = g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(C) % 16 == 0;
-    const bool diagonal = SYM && tc.bj < 2 * tc.bi + 2;
-    float any = 0.f;
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) any += acc[a][b][e];
+    const bool vec_mirror = g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(tile.C) % 16 == 0;
+    const bool diagonal = SYM && j0 < i0 + kBigM;
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -561,13 +650,242 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 float v[4] = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
-                store_quad<FLIP>(g, C, i0 + (wi * 4 + a) * 32 + 8 * q + 4 * half, j0 + (wj * 2 + b) * 32 + col, v, SYM,
+                store_quad<FLIP>(g, tile.C, i0 + (wi * 4 + a) * 32 + 8 * q + 4 * half, j0 + (wj * 2 + b) * 32 + col, v, SYM,
                                  diagonal, vec_mirror);
             }
-    if (__ballot(any != any)) {
+    if (any_nan(acc)) {
 #pragma unroll 1
-        for (int h = 0; h < 2; ++h) settle_nan<64, 64, SYM>(g, A, B, C, i0 + wi * 128 + 64 * h, j0 + wj * 64, diagonal);
+        for (int h = 0; h < 2; ++h) settle_nan<64, 64, SYM>(g, tile.A, tile.B, tile.C, i0 + wi * 128 + 64 * h, j0 + wj * 64, diagonal);
     }
+}
+
+// The same as a call: a kernel that ends with it keeps its registers to itself.
+// (A function's arguments come in vector registers; what is the same for all lanes goes back to scalar ones.)
+template <bool ALIGNED, bool SYM, bool FLIP>
+__device__ __attribute__((noinline)) void three_term_tile_call(GramArgs g, LdsFloat *buf, int64_t i0, int64_t j0)
+{
+    three_term_tile<ALIGNED, SYM, FLIP, true>(g, (float *)buf, uniform(i0), uniform(j0));
+}
+
+template <bool SYM>
+__device__ __forceinline__ bool place_of_tile(int64_t tiles, int64_t nti, int64_t ntj, int64_t &i0, int64_t &j0)
+{
+    const int64_t rank = rank_of_block(tiles);
+    if (rank >= tiles) return false;
+    const TileCoord tc = big_tile<SYM>(rank, nti, ntj);
+    i0 = (int64_t)__builtin_amdgcn_readfirstlane((int)tc.bi) * kBigM;
+    j0 = (int64_t)__builtin_amdgcn_readfirstlane((int)tc.bj) * kBigN;
+    return true;
+}
+
+template <bool ALIGNED, bool SYM, bool FLIP>
+__global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, int64_t nti, int64_t ntj)
+{
+    __shared__ __attribute__((aligned(16))) float buf[3 * kBigBuffer];
+    int64_t i0, j0;
+    if (!place_of_tile<SYM>(tiles, nti, ntj, i0, j0)) return;
+    three_term_tile<ALIGNED, SYM, FLIP, false>(g, buf, i0, j0);
+}
+
+template <bool SYM>
+__device__ __attribute__((noinline)) void settle_call(GramArgs g, int64_t i0, int64_t j0, bool diagonal)
+{
+#pragma unroll 1
+    for (int h = 0; h < 2; ++h)
+        settle_nan<64, 64, SYM>(g, g.A + blockIdx.y * g.step_a, g.B + blockIdx.y * g.step_b, g.C + blockIdx.y * g.step_c,
+                                i0 + 64 * h, j0, diagonal);
+}
+constexpr int kPartStride = 65;          // floats between the rows of a wavefront's 32 x 64 part of a result in LDS
+
+// Two terms (top of the file). Below 128 columns the three terms' error is the smaller one, and the scales take as long as
+// the products save. A tile that cannot do with two terms ends with a call of the three-term code: inlined, that code and
+// what it keeps alive pushes the registers of the loop below into scratch memory (2.1 -> 5.7 ms).
+constexpr int64_t kTwoTermColumns = 128;
+constexpr int kSamples = 4, kLargest = 9, kMostUp = 100;
+template <bool ALIGNED, bool SYM, bool FLIP>
+__global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t tiles, int64_t nti, int64_t ntj)
+{
+    __shared__ __attribute__((aligned(16))) float buf[3 * kBigBuffer];
+    __shared__ __attribute__((aligned(16))) float scales[kBigRows];
+    __shared__ int verdict;                     // 1: the tile takes three terms
+    int64_t i0, j0;
+    if (!place_of_tile<SYM>(tiles, nti, ntj, i0, j0)) return;
+    const BigTile<ALIGNED> tile(g, buf, i0, j0);
+    const int tid = tile.tid, lane = tile.lane, wi = tile.wi, wj = tile.wj, half = tile.half, col = tile.col;
+    floatx16 acc[4][2];
+    {
+        const int64_t nsteps = tile.nsteps;
+        tile.first_steps();
+        // Scales: from the largest of the first three steps' numbers of a row and of sixteen more spread over it.
+        constexpr int kOwn = (kBigRows + 255) / 256;             // rows of a thread
+        Float4u sample[kOwn][kSamples];
+#pragma unroll
+        for (int h = 0; h < kOwn; ++h) {
+            const float *src = tile.source(min(tid + 256 * h, kBigRows - 1));
+#pragma unroll
+            for (int k = 0; k < kSamples; ++k) sample[h][k] = *reinterpret_cast<const Float4u *>(src + (g.K - 4) * (k + 1) / kSamples);
+        }
+        if (tid == 0) verdict = 0;
+        tile.everybody();
+        bool outside = false;
+#pragma unroll
+        for (int h = 0; h < kOwn; ++h) {
+            const int row = min(tid + 256 * h, kBigRows - 1);
+            const float last = sample[h][kSamples - 1].w;
+            float most = 0.f;
+#pragma unroll
+            for (int k = 0; k < kSamples; ++k)
+                most = fmaxf(fmaxf(fmaxf(fabsf(sample[h][k].x), fabsf(sample[h][k].y)),
+                                   fmaxf(fabsf(sample[h][k].z), fabsf(sample[h][k].w))), most);
+#pragma unroll
+            for (int k = 0; k < 12; ++k) {
+                const float4 v = *reinterpret_cast<const float4 *>(&buf[k / 4 * kBigBuffer + row * kStep + 4 * ((k + (row >> 2)) & 3)]);
+                most = fmaxf(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))), most);
+            }
+            const int exponent = (int)(__float_as_uint(most) >> 23) - 127;      // of the largest; -127 for zero
+            const int up = most == 0.f ? kMostUp : kLargest - exponent;
+            outside |= up > kMostUp || up < -kMostUp;
+            scales[row] = last != last ? last : __uint_as_float((uint32_t)(127 + up) << 23);
+        }
+        if (__ballot(outside) && lane == 0) verdict = 1;
+        __syncthreads();
+        if (verdict != 0) {
+            three_term_tile_call<ALIGNED, SYM, FLIP>(g, (LdsFloat *)buf, i0, j0);
+            return;
+        }
+        float scale_a[4], scale_b[2];           // of this lane's rows in the blocks of A (flipped where those are) and B
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            scale_a[t] = scales[wi * 128 + 32 * t + col];
+            if (FLIP) scale_a[t] = __uint_as_float(__float_as_uint(scale_a[t]) ^ flip_of_row(i0 + wi * 128 + 32 * t));
+        }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) scale_b[t] = scales[kBigM + (wj * 2 + t) * 32 + col];
+        // Software pipeline. A step enters with the split fragments of its two blocks of B and of its first block of A, and
+        // with the numbers of the second. A pair of floats is split behind every matrix instruction (in this order: left to
+        // itself the scheduler makes lumps, and a matrix instruction hides about four others, not sixty): four instructions
+        // for each of blocks 1, 2, 3 of A and, of the next step, both of B and block 0 of A, read from LDS one fragment ahead.
+        Half8 b[2], nb[2], a[4];
+        float x[2][8];                                          // the fragment that is being split and the next one
+        auto step = [&](int64_t s, float *rd, const float *next) {
+#pragma unroll
+            for (int w = 0; w < 6; ++w) {
+                if (w == 2) tile.next_step(s, rd);
+                if (w < 2) tile.read8(rd, tile.frag_a + (w + 2) * 32 * kStep, x[(w + 1) % 2]);
+                else if (w < 4) tile.read8(next, tile.frag_b + (w - 2) * 32 * kStep, x[(w + 1) % 2]);
+                else tile.read8(next, tile.frag_a + (w - 4) * 32 * kStep, x[(w + 1) % 2]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int slot = 4 * w + i, t = slot / 6, u = slot % 2;
+                    acc[t][u] = product(slot % 6 / 2, a[t], b[u], acc[t][u]);
+                    Half8 &f = w < 3 ? a[w + 1] : w < 5 ? nb[w - 3] : a[0];
+                    split_pair(f, i, x[w % 2][2 * i], x[w % 2][2 * i + 1], w < 3 ? scale_a[w + 1] : w < 5 ? scale_b[w - 3] : scale_a[0]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            b[0] = nb[0];
+            b[1] = nb[1];
+        };
+        clear(acc);
+#pragma unroll
+        for (int w = 0; w < 3; ++w) {
+            tile.read8(buf, w < 2 ? tile.frag_b + w * 32 * kStep : tile.frag_a, x[0]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) split_pair(w < 2 ? b[w] : a[0], i, x[0][2 * i], x[0][2 * i + 1], w < 2 ? scale_b[w] : scale_a[0]);
+        }
+        tile.read8(buf, tile.frag_a + 32 * kStep, x[0]);
+        for (int64_t s = 0; s < nsteps; s += 3) {
+            step(s, buf, buf + kBigBuffer);
+            if (s + 1 < nsteps) step(s + 1, buf + kBigBuffer, buf + 2 * kBigBuffer);
+            if (s + 2 < nsteps) step(s + 2, buf + 2 * kBigBuffer, buf);
+        }
+    }
+    const bool nan_found = any_nan(acc);
+    bool open = false;          // entries that are NaN although neither of their rows ends in one: a row did not fit its scale
+    float down_b[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) down_b[u] = scales[kBigM + (wj * 2 + u) * 32 + col];
+    if (nan_found) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+            for (int e = 0; e < 16; ++e) {
+                const float of_row = scales[wi * 128 + 32 * t + 8 * (e / 4) + 4 * half + e % 4];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) open |= acc[t][u][e] != acc[t][u][e] && of_row == of_row && down_b[u] == down_b[u];
+            }
+    }
+    if (__ballot(open) && lane == 0) verdict = 1;
+    __syncthreads();
+    if (verdict != 0) {
+        three_term_tile_call<ALIGNED, SYM, FLIP>(g, (LdsFloat *)buf, i0, j0);
+        return;
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) down_b[u] = __uint_as_float(0x7f000000u - __float_as_uint(down_b[u]));
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            const float of_row = scales[wi * 128 + 32 * t + 8 * (e / 4) + 4 * half + e % 4];
+            float down_a = __uint_as_float(0x7f000000u - __float_as_uint(of_row));
+            if (FLIP) down_a = __uint_as_float(__float_as_uint(down_a) ^ flip_of_row(i0 + wi * 128 + 32 * t));
+#pragma unroll
+            for (int u = 0; u < 2; ++u) acc[t][u][e] *= down_a * down_b[u];
+        }
+    // result layout of a 32x32 block: lane holds column lane % 32 and rows 8 q + 4 (lane / 32) + 0 .. 3
+    const bool vec_mirror = g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(tile.C) % 16 == 0;
+    const bool diagonal = SYM && j0 < i0 + kBigM;
+    float *C = tile.C;
+    if (!diagonal && i0 + kBigM <= g.Nx && g.ldc <= kBigMaxStride && (!SYM || vec_mirror)) {
+        // all rows exist: scalar row addresses, one offset per lane
+        float *at_tile = C + (i0 + wi * 128) * g.ldc + j0 + wj * 64, *image = C + (j0 + wj * 64) * g.ldc + i0 + wi * 128;
+        const uint32_t at = (uint32_t)(4 * half * g.ldc + col) * 4u, image_at = (uint32_t)(col * g.ldc + 4 * half) * 4u;
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (j0 + (wj * 2 + u) * 32 + col >= g.Ny) continue;
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        float *row = at_tile + (32 * t + 8 * q + e) * g.ldc + 32 * u;
+                        *reinterpret_cast<float *>(reinterpret_cast<char *>(row) + at) = acc[t][u][4 * q + e];
+                    }
+                    if (SYM) {
+                        float *row = image + 32 * u * g.ldc + 32 * t + 8 * q;
+                        *reinterpret_cast<float4 *>(reinterpret_cast<char *>(row) + image_at) =
+                            make_float4(acc[t][u][4 * q], acc[t][u][4 * q + 1], acc[t][u][4 * q + 2], acc[t][u][4 * q + 3]);
+                    }
+                }
+        }
+    } else {
+        // through LDS, 32 rows at a time, a row or a column per instruction
+        float *part = buf + tile.wave * 32 * kPartStride;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) part[(8 * (e / 4) + 4 * half + e % 4) * kPartStride + 32 * u + col] = acc[t][u][e];
+            const int64_t ib = i0 + wi * 128 + 32 * t, jb = j0 + wj * 64;
+#pragma unroll 1
+            for (int r = 0; r < 32; ++r) {
+                const int64_t i = ib + r, j = jb + lane;
+                if (i < g.Nx && j < g.Ny && (!diagonal || i <= j)) C[i * g.ldc + j] = part[r * kPartStride + lane];
+            }
+            if (SYM) {
+#pragma unroll 1
+                for (int c = 0; c < 64; c += 2) {
+                    const int64_t i = ib + col, j = jb + c + half;
+                    if (i < g.Nx && j < g.Ny && (!diagonal || i < j)) C[j * g.ldc + i] = part[col * kPartStride + c + half];
+                }
+            }
+        }
+    }
+    if (nan_found) settle_call<SYM>(g, i0 + wi * 128, j0 + wj * 64, diagonal);
 }
 
 template <int T, int NW>
@@ -600,17 +918,21 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
         return (sym ? ti * (ti + 1) / 2 : ti * tj) * batch;
     };
     // Large tiles run one per CU at a time or, faster together, two; with `rounds` = their number over 256, rounded up,
-    // they take as long as about 1340 tiles of 64 x 64 per round do (measured for 201, 1025 and 5121 columns, both kinds,
-    // symmetric and not: 2500 x 2500, 200 large or 1600 small tiles, 32 / 98 / 411 us against 36 / 108 / 477;
-    // 4000 rows with themselves, 272 or 2016 tiles, 57 / 169 / 725 against 47 / 135 / 576).
+    // three terms take as long as about 1340 tiles of 64 x 64 per round do. Two terms: 64 x 64 tiles take about
+    // 0.57 (105 + columns) / 10000 us each and 12 more, large ones 20 us and 0.76 (200 + columns) / 17.5 us a round, fitted
+    // to both kinds at 201, 401, 1025 and 5121 columns (rows with themselves, 64 x 64 against large: 3500 rows 42, 56, 113,
+    // 496 us against 42, 52, 80, 269; 2500 rows 26, 35, 67, 279 against 41, 50, 75, 235; 4000 rows, two rounds, 48, 68, 137,
+    // 606 against 56, 70, 118, 464).
     const int64_t tiles = big_tiles(Nx, Ny, sym), rounds = (tiles * batch + 255) / 256;
-    if (count(64) > 1340 * rounds && ldx <= kBigMaxStride && ldy <= kBigMaxStride) {
+    const bool two = ncols >= kTwoTermColumns;
+    const bool large = two ? count(64) * (105 + ncols) > 140000 + rounds * (150000 + 760 * ncols) : count(64) > 1340 * rounds;
+    if (large && ldx <= kBigMaxStride && ldy <= kBigMaxStride) {
         if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
         const bool aligned = ldx % 4 == 0 && ldy % 4 == 0 && step_x % 4 == 0 && step_y % 4 == 0 &&
                              reinterpret_cast<uintptr_t>(PhiX) % 16 == 0 && reinterpret_cast<uintptr_t>(PhiY) % 16 == 0;
         const int64_t nti = (Nx + kBigM - 1) / kBigM, ntj = (Ny + kBigN - 1) / kBigN;
         const dim3 grid(xcd_grid(tiles), (unsigned)batch);
-#define RFSF_BIG(AL, SY, FL) hipLaunchKernelGGL((gram_big<AL, SY, FL>), grid, dim3(256), 0, stream, g, tiles, nti, ntj)
+#define RFSF_BIG(AL, SY, FL) hipLaunchKernelGGL((two ? gram_big_two_terms<AL, SY, FL> : gram_big<AL, SY, FL>), grid, dim3(256), 0, stream, g, tiles, nti, ntj)
         if (aligned) {
             if (rows_add_up) RFSF_BIG(true, false, true);
             else if (sym) RFSF_BIG(true, true, false);

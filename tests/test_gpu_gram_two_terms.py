@@ -1,0 +1,97 @@
+"""The Gram's two-term 16-bit products (large tiles, 128 columns and more): edges, scales and what does not fit them.
+
+Bound of an entry: 32-bit summation is within (K + 1) 2^-24 sum_k |a_k b_k|; a number's two terms are within 2^-22 of it or
+within 2^-33 of its row's largest number, for both operands, and the product that is left out is within 2^-22 of each
+|a_k b_k|: (K + 13) 2^-24 sum_k |a_k b_k| + 2^-33 (max|a| sum_k |b_k| + max|b| sum_k |a_k|)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_07145_amd as rfsf
+
+pytestmark = pytest.mark.gpu
+
+
+def _operand(rng, rows, cols, packed, kind):
+    ld = cols if packed else (cols + 3) // 4 * 4
+    a = rng.standard_normal((rows, ld)).astype(np.float32)
+    if kind == "wide":
+        a *= np.exp2(rng.integers(-12, 12, (rows, ld)))
+    elif kind == "rising":              # every column larger than the one before
+        a *= np.exp2(np.arange(ld) * (24.0 / ld))
+    elif kind == "hidden":              # numbers that no sample sees, far beyond the scale
+        a[:, 60::97] *= 2.0 ** 30
+    elif kind == "zeros":               # rows that are zero wherever they are sampled, rows that are zero
+        a[::3, :] = 0.0
+        a[::6, 52:60] = 1.5
+    elif kind == "small":
+        a *= 2.0 ** -60
+        a[1::2] *= 2.0 ** -50           # beyond the scales' range
+    elif kind == "large":
+        a[::2] *= 2.0 ** 50
+    return torch.from_numpy(a.astype(np.float32)).cuda()[:, :cols]
+
+
+def _check(K, A, B):
+    a, b = A.double(), B.double()
+    n = a.shape[1]
+    bound = (n + 13) * 2.0 ** -24 * (a.abs() @ b.abs().T.contiguous())
+    bound += 2.0 ** -33 * (a.abs().amax(1)[:, None] * b.abs().sum(1)[None] + a.abs().sum(1)[:, None] * b.abs().amax(1)[None])
+    bound += 2.0 ** -149
+    err = (K.double() - a @ b.T.contiguous()).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.parametrize("Nx,Ny,C,packed", [(2600, 2700, 128, False), (2561, 2689, 129, True), (2600, 2690, 143, False),
+                                            (2816, 2560, 144, True), (2600, 2561, 175, False), (2600, 2600, 1030, True)])
+@pytest.mark.parametrize("kind", ["normal", "wide", "rising", "hidden", "zeros", "small", "large"])
+def test_two_operands(Nx, Ny, C, packed, kind):
+    rng = np.random.default_rng(Nx + Ny + C)
+    A, B = _operand(rng, Nx, C, packed, kind), _operand(rng, Ny, C, packed, "normal" if kind == "small" else kind)
+    K = torch.full((Nx, Ny + 3), -3.0, device="cuda")
+    _check(rfsf.rfsf_ts_gram(A, B, K=K[:, :Ny]), A, B)
+    assert bool((K[:, Ny:] == -3.0).all())
+
+
+@pytest.mark.parametrize("N,C,packed", [(3585, 257, True), (3700, 400, False), (3841, 144, False)])
+@pytest.mark.parametrize("pad", [0, 3])
+@pytest.mark.parametrize("kind", ["wide", "hidden"])
+def test_one_operand_is_symmetric(N, C, packed, pad, kind):
+    A = _operand(np.random.default_rng(N), N, C, packed, kind)
+    K = torch.full((N, N + pad), -3.0, device="cuda")
+    rfsf.rfsf_ts_gram(A, K=K[:, :N])
+    _check(K[:, :N], A, A)
+    assert torch.equal(K[:, :N], K[:, :N].T)
+    assert bool((K[:, N:] == -3.0).all())
+
+
+def test_error_is_no_larger_than_three_terms():
+    """2-norm of the error over that of the result; three terms had 1.63e-7, 3.0e-7 and 5.3e-7 here (the rows of the first
+    two are normal numbers, the last has a column of ones), a margin of a tenth for other seeds."""
+    for n, C, limit in ((3000, 128, 1.8e-7), (3000, 400, 3.3e-7), (4000, 1001, 5.8e-7)):
+        A = _operand(np.random.default_rng(C), n, C, False, "normal")
+        if C == 1001:
+            A = A / C ** 0.5
+            A[:, 0] = 1.0
+        want = A.double() @ A.double().T.contiguous()
+        err = rfsf.rfsf_ts_gram(A, A.clone()).double() - want
+        assert float(err.norm() / want.norm()) <= limit, (C, float(err.norm() / want.norm()))
+
+
+def test_nan_and_infinite_rows():
+    rng = np.random.default_rng(5)
+    A, B = _operand(rng, 2600, 500, False, "normal"), _operand(rng, 2700, 500, False, "normal")
+    inf, nan = float("inf"), float("nan")
+    for r, c in ((1, 0), (300, 499), (700, 250), (2599, 3)):
+        A[r, c] = nan
+    A[900, 1], A[1300, 499], A[1301, 77], A[2000, 60] = inf, -inf, 3.4e38, inf
+    B[40, 200], B[2699, 499], B[1000, 9] = nan, nan, inf
+    B[12, 1] = 0.0                      # against A's infinite row: inf * 0
+    want = A.double() @ B.double().T.contiguous()
+    K = rfsf.rfsf_ts_gram(A, B)
+    assert torch.equal(torch.isnan(K), torch.isnan(want))
+    ok = torch.isfinite(want) & (want.abs() < 1e38)
+    assert torch.equal(torch.isposinf(K) & ~ok, torch.isposinf(want.float()) & ~ok)
+    assert torch.equal(torch.isneginf(K) & ~ok, torch.isneginf(want.float()) & ~ok)
+    bound = (500 + 13) * 2.0 ** -24 * (torch.nan_to_num(A, 0, 0, 0).double().abs() @ torch.nan_to_num(B, 0, 0, 0).double().abs().T.contiguous())
+    assert bool((((K.double() - want).abs() <= bound + 1e-6) | ~ok).all())
