@@ -17,12 +17,20 @@ namespace rfsf {
 // Transforms of 4096 and 8192 points: the sets are the levels of the launch, which may be the last ones of increment
 // rows that hold `row_levels` levels (the pointers to the increments and the tables are then advanced to the first
 // level to run); mode 2 reads joined accumulators.
+// `points`: see Points.
+struct Points {
+    const float *X = nullptr, *W = nullptr, *sign = nullptr;      // [n_seq, L, d], [M, d, F], [M, 2F]
+    int d = 0;
+    float quarters = 0.f;                                         // quarter-turns of angle per unit of X . W
+};
 struct TimeCut {
     int pieces, row_levels;
     int64_t pairs;
     float2 *spectra;
     int mode, join;
     int64_t seq_stride, piece_stride;
+    bool solo = false;           // mode 1: the kernel whose wavefronts work by themselves (sketch_fft_scan_solo.h)
+    Points points = {};          // ... and which, with X set, computes the increments itself: none are in memory
     static TimeCut whole(int64_t L, int M) { return {1, M, (L + 1) / 2, nullptr, 0, 1, 0, 0}; }
 };
 constexpr int kMaxCutLevels = 8;                       // the tuned kernels run at most eight levels
@@ -79,6 +87,12 @@ bool sketch_fft_scan_joint(int M, int F, int D);
 int sketch_fft_scan_joint_per_cu(int M, int D);            // its workgroups that a CU holds, by registers
 int sketch_fft_scan_joint_fit(int M, int F, int D, int order);      // ... and by LDS
 bool sketch_fft_scan_joint_splits(int M, int D, int order);        // splitting whole sequences can gain
+// Pieces of this shape run in the kernel whose wavefronts work by themselves; its tables hold no lists. The pairs of steps that
+// a workgroup of it transforms at a time, or 0; its workgroups that a CU holds.
+int sketch_fft_scan_solo_pairs(int M, int F, int D, int order, int d, bool bf16);
+int sketch_fft_scan_solo_per_cu(int M, int F, int D);
+bool sketch_fft_scan_solo_fused(int F, int d, int D);             // it can compute the increments itself
+uint32_t sketch_fft_scan_solo_zero(int F, int D);          // TableJob::zero_off of its tables
 int sketch_fft_scan_wavefronts(int M, int D);                      // of a workgroup for whole sequences
 int sketch_fft_scan_pairs_per_iteration(int D);            // pairs of steps a wavefront transforms at a time
 bool sketch_fft_scan_fits(int M, int F, int D, int order);  // false: neither kernel can run it (LDS need above a CU's)

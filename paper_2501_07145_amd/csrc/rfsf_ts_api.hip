@@ -128,18 +128,55 @@ constexpr int kJoinInPlace = 16;    // more pieces are joined by a kernel of its
 constexpr int64_t kSumLoads = 128;
 // Order of the recurrence that a launch runs: a single level is the same in all of them.
 int kernel_order(const rfsf_ts_shape *s) { return s->order < 2 || s->M == 1 ? 1 : s->order; }
-struct SketchCut { int pieces; int64_t pairs; bool joint, in_place; };
+struct SketchCut { int pieces; int64_t pairs; bool joint, in_place, solo; };
+// The cut for the kernel whose wavefronts work by themselves (csrc/sketch_fft_scan_solo.h), which takes whole sequences and
+// pieces alike and `step` pairs of steps per iteration of a workgroup. Time is counted in iterations: those of a round of
+// workgroups and one for its beginning and end, and for the join a tenth of one per piece and 18 MB of accumulators
+// (1000 x 100 points, 256 buckets, four levels: 768 workgroups at once; one, two, three pieces each 182, 149, 143 us).
+// Batches that leave CUs without a workgroup are left to the other kernels, whose wavefronts share out a piece's levels
+// (a single sequence of 100 points 27.8 us, 30.7 here; ten of 1000 49 and 56), and so are sequences that fill less than half
+// of an iteration (3000 x 14 points, 64 buckets, three levels 51 and 54) or, from 128 points per transform on, less than four
+// (1000 x 30 points, 256 buckets, four levels 64 and 70).
+SketchCut solo_cut(const rfsf_ts_shape *s, int P, int step)
+{
+    const SketchCut none = {0, 0, false, false, false};
+    const int64_t slots = (s->L + 1) / 2, all_pairs = s->L / 2, floats_per_pair = (int64_t)s->M * 4 * s->F;
+    const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
+    const int64_t at_once = kCUs * rfsf::sketch_fft_scan_solo_per_cu(s->M, s->F, P);
+    if (2 * all_pairs < step || (P >= 128 && all_pairs < 4 * step)) return none;
+    SketchCut best = none;
+    double least = 0.0;
+    for (int64_t want = 1; want <= kSplitPieces && want * step <= all_pairs + step; ++want) {
+        const int64_t pairs = ((all_pairs + want - 1) / want + step - 1) / step * step, pieces = (all_pairs + pairs - 1) / pairs;
+        // every piece, the last one too, has to hold its accumulators
+        if (pieces > kJoinInPlace || (pieces < 2 ? slots : pairs) * floats_per_pair < needed ||
+            (slots - (pieces - 1) * pairs) * floats_per_pair < needed)
+            continue;
+        const double cost = (double)((s->N * pieces + at_once - 1) / at_once) * (double)(pairs / step + 1) + 0.1 * (double)pieces +
+                            (double)(s->N * pieces) * (double)needed * 4.0 / 18e6;
+        if (best.pieces == 0 || cost < least) {
+            least = cost;
+            best = {(int)pieces, pieces < 2 ? slots : pairs, true, true, true};
+        }
+    }
+    return s->N * best.pieces > kCUs ? best : none;
+}
 SketchCut sketch_cut(const rfsf_ts_shape *s)
 {
     const TimeCutPlan plan = time_cut_plan(s);
     const int P = transform_length(s->M, s->F, s->D);
     const bool joint = rfsf::sketch_fft_scan_joint(s->M, s->F, P);
-    if (plan.pieces > 1) return {plan.pieces, plan.pairs, joint, false};
-    const SketchCut whole = {1, plan.pairs, false, false};
-    if (!joint || s->N < 1 || s->N > kSplitSequences || s->L < 3) return whole;
+    const int step = joint && s->L > 1 ? rfsf::sketch_fft_scan_solo_pairs(s->M, s->F, P, kernel_order(s), s->d, s->rff_bf16 != 0) : 0;
+    if (plan.pieces > 1) return {plan.pieces, plan.pairs, joint, false, step > 0 && s->N * plan.pieces > kCUs};
+    if (step > 0 && s->N > 0) {
+        const SketchCut cut = solo_cut(s, P, step);
+        if (cut.pieces > 0) return cut;
+    }
     const int64_t slots = (s->L + 1) / 2, all_pairs = s->L / 2;
     const int64_t floats_per_pair = (int64_t)s->M * 4 * s->F;
     const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
+    const SketchCut whole = {1, plan.pairs, false, false, false};
+    if (!joint || s->N < 1 || s->N > kSplitSequences || s->L < 3) return whole;
     const int fpw = rfsf::sketch_fft_scan_pairs_per_iteration(P);
     const int64_t per_cu = rfsf::sketch_fft_scan_joint_per_cu(s->M, P), fit = rfsf::sketch_fft_scan_joint_fit(s->M, s->F, P, kernel_order(s));
     const int64_t at_once = kCUs * (fit < per_cu ? fit : per_cu);
@@ -163,7 +200,7 @@ SketchCut sketch_cut(const rfsf_ts_shape *s)
         if (rounds > 1 && 2 * rounds >= pieces) continue;
         // every piece, the last one too, has to hold its accumulators
         if (pairs * floats_per_pair >= needed && (slots - (pieces - 1) * pairs) * floats_per_pair >= needed)
-            return {(int)pieces, pairs, true, true};
+            return {(int)pieces, pairs, true, true, false};
     }
     return whole;
 }
@@ -301,12 +338,21 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
     const bool has_tables = rfsf::sketch_table_job(hash, shape->M, shape->F, P, shape->D, table, &tables);
     const float inv_ls = 1.0f / lengthscale;
     const SketchCut plan = sketch_cut(shape);
+    if (plan.solo) {                                      // no lists, and slots of its own
+        tables.groups = 0;
+        tables.zero_off = rfsf::sketch_fft_scan_solo_zero(shape->F, P);
+    }
+    // ... whose increments it computes itself where it can
+    const bool fused = plan.solo && shape->rff_bf16 == 0 && rfsf::sketch_fft_scan_solo_fused(shape->F, shape->d, P);
     // the tuned consumer takes the increments in the pair layout with the signs applied, the generic one in
     // the row layout without
     const float *producer_sign = rfsf::sketch_fft_scan_is_tuned(shape->M, shape->F, P) ? sign : nullptr;
     for (int64_t n0 = 0; n0 < shape->N; n0 += chunk) {
         const int64_t cnt = shape->N - n0 < chunk ? shape->N - n0 : chunk;
-        {
+        if (fused) {
+            rfsf::ProfileScope scope(rfsf::kRffIncrements, stream, may_create);
+            if (n0 == 0 && rfsf::launch_build_tables(tables, shape->M, stream) != hipSuccess) return RFSF_E_HIP;
+        } else {
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream, may_create);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, producer_sign, inv_ls, cnt, shape->L, shape->d,
                                             shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream,
@@ -315,7 +361,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
                 return RFSF_E_HIP;
         }
         const int64_t *chunk_lengths = lengths ? lengths + n0 : nullptr;
-        if (plan.pieces == 1) {
+        if (plan.pieces == 1 && !plan.solo) {
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
             if (rfsf::launch_sketch_fft_scan(dphi, hash, sign, table, cnt, shape->L, chunk_lengths,
                                              shape->M, shape->F, P, shape->D, kernel_order(shape),
@@ -327,7 +373,8 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
             // pieces by a launch of its own) and the final transforms (timed as one launch of the sketch kernel class)
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
             const int order = kernel_order(shape), bins = P / 2 + 1;
-            rfsf::TimeCut cut = {plan.pieces, shape->M, plan.pairs, nullptr, 1, plan.pieces, 0, 0};
+            rfsf::TimeCut cut = {plan.pieces, shape->M, plan.pairs, nullptr, 1, plan.pieces, 0, 0, plan.solo};
+            if (fused) cut.points = {X + n0 * shape->L * shape->d, W, sign, shape->d, (float)(0.63661977236758134308 / (double)lengthscale)};
             if (plan.in_place) {
                 cut.piece_stride = plan.pairs * (int64_t)shape->M * 2 * shape->F;          // float2 per pair: M * 2F
                 cut.seq_stride = (shape->L + 1) / 2 * (int64_t)shape->M * 2 * shape->F;

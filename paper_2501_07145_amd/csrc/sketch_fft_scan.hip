@@ -8,6 +8,7 @@
 // level m, summed over time; Phi_m = IFFT(A_m). Two consecutive time steps share one complex
 // FFT (real parts = step k, imaginary parts = step k+1) and are separated again per bin.
 #include "rfsf_internal.h"
+#include "sketch_fft_scan_solo.h"
 #include "sketch_fft_scan_tuned.h"
 #include "sketch_fft_scan_wide.h"
 #include "sketch_fft_scan_dispatch.h"
@@ -257,6 +258,40 @@ int sketch_fft_scan_joint_fit(int M, int F, int D, int order)
 }
 
 bool sketch_fft_scan_joint_splits(int M, int D, int order) { return tuned::joint_fits(M, D, plan_key(D), order); }
+
+namespace {
+int solo_slot(int D, int PD) { return D == 100 ? tuned::SoloPlan<100>::PD : PD; }       // float2 of its slots
+}  // namespace
+
+uint32_t sketch_fft_scan_solo_zero(int F, int D)
+{
+    TunedGeometry g;
+    return tuned_geometry(D, &g) ? 8u * (uint32_t)tuned::zero_slot(solo_slot(D, g.PD), 2 * F) : 0u;
+}
+
+bool sketch_fft_scan_solo_fused(int F, int d, int D) { return F <= 64 * tuned::solo_columns(D) && d <= tuned::kSoloChannels; }
+
+int sketch_fft_scan_solo_per_cu(int M, int F, int D)
+{
+    TunedGeometry g;
+    if (!tuned_geometry(D, &g)) return 0;
+    const int by_lds = (int)(kLdsPerCu / tuned::solo_lds_bytes(M, g.FPW, solo_slot(D, g.PD), g.NTWL, F));
+    const int by_registers = tuned::solo_waves_per_simd(M, D);
+    return by_lds < by_registers ? by_lds : by_registers;
+}
+
+int sketch_fft_scan_solo_pairs(int M, int F, int D, int order, int d, bool bf16)
+{
+    TunedGeometry g;
+    if (!tuned::solo_fits(M, D, order) || F > D || !sketch_fft_scan_is_tuned(M, F, D) || !tuned_geometry(D, &g)) return 0;
+    // With increments from memory it is the faster kernel for the shortest transforms only (3000 x 200 points, 12 channels: D = 100,
+    // five levels 832 -> 695 us, D = 128, four levels 562 -> 581; 1000 x 100, D = 256, four levels 175 -> 209).
+    if (D > 100 && (bf16 || !sketch_fft_scan_solo_fused(F, d, D))) return 0;
+    // Few frequencies are computed soon, while the accumulators of all ranges cost the same (1000 x 100 points, D = 256: four
+    // levels, 128, 64, 32 frequencies 178, 130, 102 us and 169 to 182, 141, 136; three levels, 20 frequencies 85 and 89).
+    if (D == 256 && F < 32 * (M - 1)) return 0;
+    return sketch_fft_scan_solo_per_cu(M, F, D) < 2 ? 0 : tuned::kSoloWaves * tuned::solo_pairs(M, g.FPW);
+}
 
 int sketch_fft_scan_wavefronts(int M, int D) { return tuned::transforms_in_flight(M, plan_key(D)); }
 

@@ -98,9 +98,10 @@ struct Plan {
 // Transform lengths 2^a 5^b that the paper's own experiments use as bucket counts (100, 200, 500, 1000): exact
 // transforms of that length instead of a linear convolution in the next power of two above M (D - 1) + 1.
 // 20 points per lane, D / 20 lanes per transform (the remaining lanes of a wavefront repeat the work of the
-// first ones, see the kernel), passes of radix 10, 10 and 10 / 5 / 2 / none; slots are not padded; the
+// first ones, see the kernel), passes of radix 10, 10 and 10 / 5 / 2 / none; slots are padded where that keeps the positions of a
+// pass a base plus constants and pays (D = 1000: the writes of a transform take 140 bank rows instead of 180); the
 // twiddles of all passes after the first live in the LDS table. Selected as Plan<D>.
-template <int DD>
+template <int DD, int PAD>
 struct MixedPlan {
     static constexpr int LOG2D = DD;
     static constexpr int D = DD;
@@ -108,7 +109,8 @@ struct MixedPlan {
     static constexpr int G = D / R;
     static constexpr int FPW = 64 / G;
     static constexpr int GF = G;
-    static constexpr int PD = D;
+    static constexpr int kPad = PAD;            // one float2 of padding after every kPad of a slot
+    static constexpr int PD = D + (D - 1) / kPad;
     static constexpr int NP = D == 100 ? 2 : 3;
     static constexpr int radix(int p) { return p < 2 ? 10 : (D == 1000 ? 10 : (D == 500 ? 5 : 2)); }
     static constexpr int Ns(int p) { return p == 0 ? 1 : Ns(p - 1) * radix(p - 1); }
@@ -122,15 +124,15 @@ struct MixedPlan {
     static constexpr int wb_off(int p) { return p == 0 ? 0 : wb_off(p - 1) + R / radix(p - 1); }
     static constexpr int NTW = 1;
     static constexpr int NWB = wb_off(NP);
-    static constexpr int roff(int q) { return G * q; }
-    static constexpr int pad(int e) { return e; }
+    static constexpr int roff(int q) { return G * q + G * q / kPad; }
+    __host__ __device__ static constexpr int pad(int e) { return e + e / kPad; }
     static constexpr int kMinWaves = 4;
     static_assert(D % R == 0 && G * FPW <= 64, "");
 };
-template <> struct Plan<100> : MixedPlan<100> {};
-template <> struct Plan<200> : MixedPlan<200> {};
-template <> struct Plan<500> : MixedPlan<500> {};
-template <> struct Plan<1000> : MixedPlan<1000> {};
+template <> struct Plan<100> : MixedPlan<100, 100> {};
+template <> struct Plan<200> : MixedPlan<200, 200> {};
+template <> struct Plan<500> : MixedPlan<500, 500> {};
+template <> struct Plan<1000> : MixedPlan<1000, 50> {};
 // 2048 points in one wavefront: 32 points per lane (twice the registers, half the resident wavefronts, no barrier
 // inside the transform). Selected as Plan<2048>.
 template <> struct Plan<2048> : Plan<11, 5> {};

@@ -1,0 +1,78 @@
+"""Short transforms whose levels fit one wavefront: whole sequences and pieces, increments computed in the kernel or read from
+memory, at the edges of its rules (levels, channels, frequencies per lane, sequences of half an iteration and of one more
+pair than an iteration, the smallest batch that takes it, pieces, points beyond a sequence's end)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_07145_amd as rfsf
+from tests.parity import FP32_BLOCK_TOL, block_errors
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(seed, N, L, d, M, F, D):
+    rng = np.random.default_rng(seed)
+    X = np.cumsum(rng.standard_normal((N, L, d)) * 0.2, axis=1).astype(np.float32)
+    W = rng.standard_normal((M, d, F)).astype(np.float32)
+    hash_ = rng.integers(0, D, size=(M, 2 * F)).astype(np.int32)
+    sign = (2.0 * rng.integers(0, 2, size=(M, 2 * F)) - 1.0).astype(np.float32)
+    return X, W, hash_, sign
+
+
+@pytest.mark.parametrize("N,L,d,M,F,D", [
+    (257, 33, 1, 2, 64, 64), (300, 20, 2, 3, 33, 64), (300, 17, 3, 4, 64, 64), (300, 26, 4, 5, 17, 64),
+    (257, 49, 5, 2, 50, 100), (300, 50, 6, 3, 64, 100), (300, 25, 7, 4, 50, 100), (300, 18, 8, 5, 50, 100), (300, 19, 3, 6, 40, 100),
+    (300, 34, 9, 5, 50, 100), (300, 34, 3, 5, 65, 100), (300, 34, 3, 5, 100, 100),          # increments from memory
+    (300, 130, 3, 2, 64, 128), (300, 67, 1, 3, 30, 128), (300, 66, 8, 4, 64, 128),
+    (300, 100, 5, 2, 100, 200), (300, 67, 2, 3, 128, 200), (300, 35, 4, 5, 65, 200),
+    (300, 66, 8, 2, 32, 256), (300, 34, 3, 3, 64, 256), (300, 65, 8, 4, 128, 256), (300, 66, 3, 4, 97, 256),
+    (100, 300, 5, 5, 50, 100), (100, 301, 2, 3, 30, 64), (90, 200, 8, 4, 128, 256),          # split
+    (10, 2000, 5, 5, 50, 100), (60, 400, 3, 3, 64, 128),                                      # cut by the reported plan
+    (2000, 10, 2, 5, 50, 100), (1100, 40, 2, 4, 30, 64),
+])
+def test_rows_match_the_oracle(oracle, N, L, d, M, F, D):
+    X, W, hash_, sign = _case(N + L + D + d, N, L, d, M, F, D)
+    rng = np.random.default_rng(L)
+    rows = np.unique(rng.integers(0, N, size=8))
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)]
+    for lengths in (None, np.where(rng.random(N) < 0.3, L, rng.integers(1, L + 1, size=N)).astype(np.int64)):
+        kw = {}
+        if lengths is not None:
+            kw["lengths"] = torch.from_numpy(lengths).cuda()
+            dev[0] = dev[0].clone()
+            for n in rows:                 # what lies beyond a sequence's end is not read
+                dev[0][n, lengths[n]:] = float("nan")
+        got = rfsf.rfsf_ts_features(*dev, 1.5, D, **kw)
+        again = rfsf.rfsf_ts_features(*dev, 1.5, D, **kw)
+        assert torch.equal(got, again)
+        for n in rows:
+            x = X[n:n + 1] if lengths is None else X[n:n + 1, :lengths[n]]
+            want = oracle.features(x, W, hash_, sign, 1.5, D)
+            err = block_errors(got[int(n):int(n) + 1].cpu().numpy(), want, M, D)
+            assert np.all(err <= FP32_BLOCK_TOL), (n, err)
+
+
+def test_chunks_and_bf16_projection_take_the_same_sums(oracle):
+    """The cut is a function of the shape: a workspace for a part of the batch gives the same bits."""
+    X, W, hash_, sign = _case(1, 600, 60, 5, 5, 50, 100)
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)]
+    for bf16 in (False, True):
+        rec, least = rfsf.rfsf_ts_workspace_bytes(600, 60, 5, 5, 50, 100, bf16)
+        per = (rec - least) // 599
+        whole = rfsf.rfsf_ts_features(*dev, 1.5, 100, rff_bf16=bf16)
+        part = rfsf.rfsf_ts_features(*dev, 1.5, 100, rff_bf16=bf16,
+                                     workspace=torch.empty(least + 250 * per, dtype=torch.uint8, device="cuda"))
+        assert torch.equal(whole, part)
+
+
+def test_nan_stays_in_its_sequence():
+    X, W, hash_, sign = _case(2, 300, 40, 4, 4, 30, 64)
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)]
+    want = rfsf.rfsf_ts_features(*dev, 1.5, 64)
+    dev[0][7, 20, 1] = float("nan")
+    dev[0][9, 3, 0] = float("inf")
+    got = rfsf.rfsf_ts_features(*dev, 1.5, 64)
+    bad = torch.zeros(300, dtype=torch.bool, device="cuda")
+    bad[[7, 9]] = True
+    assert bool(torch.isnan(got[bad][:, 1:]).all()) and torch.equal(got[~bad], want[~bad])
