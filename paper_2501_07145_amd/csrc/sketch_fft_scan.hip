@@ -195,20 +195,20 @@ size_t sketch_fft_scan_state_bytes(int64_t n_seq, int M, int D, int order)
 }
 
 namespace {
-struct TunedGeometry { int G /* entries per fold round */, PD, FPW, NTWL; };
+struct TunedGeometry { int G /* entries per fold round */, PD, FPW, NTWL, bound_twiddles; };
 // transforms of 4096 and 8192: the kernel of sketch_fft_scan_wide.h
 bool wide_shape(int D) { return D == 4096 || D == 8192; }
 bool tuned_geometry(int D, TunedGeometry *g)
 {
     if (wide_shape(D)) {
-        *g = {64, 0, 1, tuned::Plan<10>::NTWL};
+        *g = {64, 0, 1, tuned::Plan<10>::NTWL, tuned::Plan<10>::kBoundTwiddles};
         return true;
     }
     switch (D) {
-#define RFSF_GEOM(L2) case 1 << L2: *g = {tuned::Plan<L2>::GF, tuned::Plan<L2>::PD, tuned::Plan<L2>::FPW, tuned::Plan<L2>::NTWL}; return true;
+#define RFSF_GEOM(L2) case 1 << L2: *g = {tuned::Plan<L2>::GF, tuned::Plan<L2>::PD, tuned::Plan<L2>::FPW, tuned::Plan<L2>::NTWL, tuned::Plan<L2>::kBoundTwiddles}; return true;
         RFSF_GEOM(6) RFSF_GEOM(7) RFSF_GEOM(8) RFSF_GEOM(9) RFSF_GEOM(10)
 #undef RFSF_GEOM
-#define RFSF_GEOM(DD) case DD: *g = {tuned::Plan<DD>::GF, tuned::Plan<DD>::PD, tuned::Plan<DD>::FPW, tuned::Plan<DD>::NTWL}; return true;
+#define RFSF_GEOM(DD) case DD: *g = {tuned::Plan<DD>::GF, tuned::Plan<DD>::PD, tuned::Plan<DD>::FPW, tuned::Plan<DD>::NTWL, tuned::Plan<DD>::kBoundTwiddles}; return true;
         RFSF_GEOM(100) RFSF_GEOM(200) RFSF_GEOM(500) RFSF_GEOM(1000)        // exact transforms, 2^a 5^b points
         RFSF_GEOM(2048)                                                     // 32 points per lane
 #undef RFSF_GEOM
@@ -231,8 +231,8 @@ size_t sketch_fft_scan_lds_bytes(int M, int F, int D)
     if (wide_shape(D)) return tuned::wide_lds_bytes(D / 1024, M, F);
     const int log2d = plan_key(D);
     // eight wavefronts taking the items in order where the plan prefers that and the slots fit, else one per level
-    const size_t preferred = tuned::tuned_lds_bound(tuned::transforms_in_flight(M, log2d), g.FPW, g.PD, g.NTWL, F);
-    return preferred <= kLdsPerCu ? preferred : tuned::tuned_lds_bound(M, g.FPW, g.PD, g.NTWL, F);
+    const size_t preferred = tuned::tuned_lds_bound(tuned::transforms_in_flight(M, log2d), g.FPW, g.PD, g.bound_twiddles, F);
+    return preferred <= kLdsPerCu ? preferred : tuned::tuned_lds_bound(M, g.FPW, g.PD, g.bound_twiddles, F);
 }
 
 bool sketch_fft_scan_is_tuned(int M, int F, int D)

@@ -44,6 +44,9 @@ namespace tuned {
 // Stockham passes and the contiguous accesses are both free of bank conflicts.
 __host__ __device__ constexpr int pad(int e) { return e + (e >> 4); }
 
+// Twiddles of a butterfly of r points behind the first pass (twiddle_entry).
+__host__ __device__ constexpr int twiddles(int r) { return (r & (r - 1)) == 0 ? r / 2 : r - 1; }
+
 template <int LOG2D_, int LOG2R_ = 4>
 struct Plan {
     static constexpr int LOG2D = LOG2D_;
@@ -79,11 +82,12 @@ struct Plan {
     // butterflies of pass p with distinct twiddles: butterfly u of a lane has k = (lg + G*u) mod Ns,
     // the same for every u when Ns divides G
     static constexpr int tw_sets(int p) { return G % Ns(p) == 0 ? 1 : R / radix(p); }
-    // The twiddles of a radix-16 pass (15 per set) would cost 30 registers per set; they live in an
+    // The twiddles of a radix-16 pass (8 per set) would cost 16 registers per set; they live in an
     // LDS table shared by the workgroup instead. Smaller passes keep theirs in registers.
     static constexpr bool tw_in_lds(int p) { return p > 0 && radix(p) >= 16; }
-    static constexpr int tw_regs(int p) { return (p == 0 || tw_in_lds(p)) ? 0 : tw_sets(p) * (radix(p) - 1); }
-    static constexpr int tw_lds(int p) { return tw_in_lds(p) ? tw_sets(p) * (radix(p) - 1) * G : 0; }   // float2 entries
+    static constexpr int tw_regs(int p) { return (p == 0 || tw_in_lds(p)) ? 0 : tw_sets(p) * twiddles(radix(p)); }
+    static constexpr int tw_lds(int p) { return tw_in_lds(p) ? tw_sets(p) * twiddles(radix(p)) * G : 0; }   // float2 entries
+    static constexpr int kBoundTwiddles = tw_in_lds(NP - 1) ? tw_sets(NP - 1) * (radix(NP - 1) - 1) * G : 0;   // see tuned_lds_bound
     // array offsets of pass p: register twiddles (complex), LDS twiddles (float2) and write bases
     static constexpr int tw_off(int p) { return p <= 1 ? 0 : tw_off(p - 1) + tw_regs(p - 1); }
     static constexpr int twl_off(int p) { return p <= 1 ? 0 : twl_off(p - 1) + tw_lds(p - 1); }
@@ -117,10 +121,11 @@ struct MixedPlan {
     static constexpr int tw_sets(int p) { return G % Ns(p) == 0 ? 1 : R / radix(p); }
     static constexpr bool tw_in_lds(int p) { return p > 0; }
     static constexpr int tw_regs(int) { return 0; }
-    static constexpr int tw_lds(int p) { return tw_in_lds(p) ? tw_sets(p) * (radix(p) - 1) * G : 0; }
+    static constexpr int tw_lds(int p) { return tw_in_lds(p) ? tw_sets(p) * twiddles(radix(p)) * G : 0; }
     static constexpr int tw_off(int) { return 0; }
     static constexpr int twl_off(int p) { return p <= 1 ? 0 : twl_off(p - 1) + tw_lds(p - 1); }
     static constexpr int NTWL = twl_off(NP);
+    static constexpr int kBoundTwiddles = NTWL;
     static constexpr int wb_off(int p) { return p == 0 ? 0 : wb_off(p - 1) + R / radix(p - 1); }
     static constexpr int NTW = 1;
     static constexpr int NWB = wb_off(NP);
@@ -171,13 +176,6 @@ constexpr uint32_t kFoldPad = 0xffffu;
 constexpr int kFoldInRegs = 4;      // fold rounds whose entries are fetched with the other tables; later rounds load
                                     // theirs on the spot (4 measured best of 2, 4, 6, 8)
 
-// cos(k pi / 16), k = 0..8
-__device__ constexpr float kCos16[9] = {1.0f, 0.98078528040323043f, 0.92387953251128674f, 0.83146961230254524f,
-                                        0.70710678118654752f, 0.55557023301960218f, 0.38268343236508977f,
-                                        0.19509032201612825f, 0.0f};
-constexpr float cos_pi16(int k) { return k <= 8 ? kCos16[k] : -kCos16[16 - k]; }   // k in [0, 16]
-constexpr float sin_pi16(int k) { return k <= 8 ? kCos16[8 - k] : kCos16[k - 8]; }
-
 constexpr int bitrev(int x, int bits)
 {
     int r = 0;
@@ -186,34 +184,102 @@ constexpr int bitrev(int x, int bits)
 }
 constexpr int ilog2(int n) { return n <= 1 ? 0 : 1 + ilog2(n / 2); }
 
-// In-register forward DFT of N = 2..32 points, decimation in frequency; result k is left at
-// position bitrev(k). Twiddles are compile-time constants; the trivial ones cost nothing.
-template <int N, int BASE, int TOTAL>
-__device__ __forceinline__ void dft_dif(float2 (&x)[TOTAL])
+// Butterflies with the twiddle inside: w = c (1 + i t) is kept as (c, t), w b = c (b.x - t b.y, b.y + t b.x) takes two
+// multiply-adds and a +- w b four more. Multiplying by w first and adding afterwards takes eight instructions and rounds
+// three times; this rounds twice. What bounds these transforms is the number of vector instructions and of LDS
+// accesses (1024 points: 436 instead of 508 vector instructions and 8 instead of 15 twiddles read per lane; the sketch kernel of
+// 2000 x 200 points, D = 512, four levels 817 -> 772 us, 3000 x 200, D = 256, six levels 1140 -> 1010, 1000 x 100, D = 2048 1323 ->
+// 1281, 500 x 100, D = 2000 in 8192 points 2748 -> 2501; D = 1024 is bound by its exchanges: 2097 and 2095). Errors of the features
+// against 64 bits over fifteen shapes of all lengths: 4.4e-7 -> 4.1e-7 (geometric mean), none larger by more than a hundredth.
+// Behind a first pass, input t of an r-point butterfly carries w^t: the butterfly is the polynomial of its inputs at the
+// points w exp(-2 pi i q / r), even and odd powers apart, which needs the powers w^(r/2), ..., w^2, w alone, times roots.
+// A right angle has c = 0: 2^-40 stands for it, whose square is lost beside 1.
+__device__ __forceinline__ float2 twiddle_form(float c, float s)
 {
-    if constexpr (N >= 2) {
+    return c == 0.f ? make_float2(0x1p-40f, s * 0x1p40f) : make_float2(c, s / c);
+}
+__device__ __forceinline__ void butterfly(float2 &a, float2 &b, float2 w)               // a + w b, a - w b
+{
+    const float u = fmaf(-w.y, b.y, b.x), v = fmaf(w.y, b.x, b.y), x = a.x, y = a.y;
+    a = make_float2(fmaf(w.x, u, x), fmaf(w.x, v, y));
+    b = make_float2(fmaf(-w.x, u, x), fmaf(-w.x, v, y));
+}
+__device__ __forceinline__ void butterfly_i(float2 &a, float2 &b, float2 w)             // a - i w b, a + i w b
+{
+    const float u = fmaf(-w.y, b.y, b.x), v = fmaf(w.y, b.x, b.y), x = a.x, y = a.y;
+    a = make_float2(fmaf(w.x, v, x), fmaf(-w.x, u, y));
+    b = make_float2(fmaf(-w.x, v, x), fmaf(w.x, u, y));
+}
+__device__ __forceinline__ void butterfly_one(float2 &a, float2 &b)                      // a + b, a - b
+{
+    const float2 x = a, y = b;
+    a = make_float2(x.x + y.x, x.y + y.y);
+    b = make_float2(x.x - y.x, x.y - y.y);
+}
+__device__ __forceinline__ void butterfly_one_i(float2 &a, float2 &b)                    // a - i b, a + i b
+{
+    const float2 x = a, y = b;
+    a = make_float2(x.x + y.y, x.y - y.x);
+    b = make_float2(x.x - y.y, x.y + y.x);
+}
+// Entry e of the twiddles of an r-point butterfly whose inputs carry powers of exp(-2 pi i k / (Ns r)). Powers of two: entry 0
+// belongs to the stage that combines single inputs, entries H/2 + j, j < H/2, to the one that combines H and H of
+// them, at its roots j (roots j + H/2 are -i times these). Ten points: entries 0 to 3 the even powers 2, 4, 6, 8, as real
+// and imaginary part, then those of the stage that combines five and five. Five points: the powers 1 to 4, likewise.
+template <int r>
+__device__ __forceinline__ float2 twiddle_entry(int e, int k, int Ns)
+{
+    float s, c;
+    if constexpr ((r & (r - 1)) == 0) {
+        const int H = e == 0 ? 1 : 2 << (31 - __clz(e)), j = e == 0 ? 0 : e - H / 2;
+        sincospif(-(float)(k + j * Ns) / (float)(H * Ns), &s, &c);
+        return twiddle_form(c, s);
+    } else if (r == 10 && e >= 4) {
+        sincospif(-2.0f * (float)(k + (e - 4) * Ns) / (float)(10 * Ns), &s, &c);
+        return twiddle_form(c, s);
+    } else {
+        sincospif(-2.0f * (float)(k * (e + 1) * (r == 10 ? 2 : 1)) / (float)(Ns * r), &s, &c);
+        return make_float2(c, s);
+    }
+}
+// Transform of the N inputs from B on (bit-reversed order in, natural order out), half after half, so that work can start with
+// the first inputs that arrive. tw[e]: twiddle_entry e.
+template <int B, int N, int r>
+__device__ __forceinline__ void dft_halves(float2 (&x)[r], const float2 (&tw)[twiddles(r)])
+{
+    if constexpr (N > 1) {
         constexpr int H = N / 2;
+        dft_halves<B, H>(x, tw);
+        dft_halves<B + H, H>(x, tw);
 #pragma unroll
-        for (int i = 0; i < H; ++i) {
-            const float2 a = x[BASE + i], b = x[BASE + i + H];
-            x[BASE + i] = make_float2(a.x + b.x, a.y + b.y);
-            const float dx = a.x - b.x, dy = a.y - b.y;
-            const int k = i * (32 / N);                     // angle = k * pi / 16, k in [0, 16)
-            if (k == 0) {
-                x[BASE + i + H] = make_float2(dx, dy);
-            } else if (k == 8) {                             // times -i
-                x[BASE + i + H] = make_float2(dy, -dx);
-            } else if (k == 4) {                             // times (1 - i) / sqrt 2
-                x[BASE + i + H] = make_float2((dx + dy) * kCos16[4], (dy - dx) * kCos16[4]);
-            } else if (k == 12) {                            // times (-1 - i) / sqrt 2
-                x[BASE + i + H] = make_float2((dy - dx) * kCos16[4], -(dx + dy) * kCos16[4]);
-            } else {                                         // times (c - i s)
-                const float c = cos_pi16(k), s = sin_pi16(k);
-                x[BASE + i + H] = make_float2(fmaf(dx, c, dy * s), fmaf(dy, c, -dx * s));
+        for (int j = 0; j < (H > 1 ? H / 2 : 1); ++j) {
+            const float2 w = tw[H > 1 ? H / 2 + j : 0];
+            butterfly(x[B + j], x[B + j + H], w);
+            if (H > 1) butterfly_i(x[B + j + H / 2], x[B + j + H / 2 + H], w);
+        }
+    }
+}
+// The same without twiddles (w = 1): their constants, and the trivial ones cost nothing.
+template <int B, int N, int r>
+__device__ __forceinline__ void dft_halves_plain(float2 (&x)[r])
+{
+    static_assert(r <= 16, "");
+    if constexpr (N > 1) {
+        constexpr float c[4] = {1.0f, 0.92387953251128674f, 0.70710678118654752f, 0.38268343236508977f};      // of j pi / 8
+        constexpr float t[4] = {0.0f, -0.41421356237309505f, -1.0f, -2.4142135623730950f};                    // minus tangent
+        constexpr int H = N / 2;
+        dft_halves_plain<B, H>(x);
+        dft_halves_plain<B + H, H>(x);
+#pragma unroll
+        for (int j = 0; j < (H > 1 ? H / 2 : 1); ++j) {
+            const int e = j * (8 / H);
+            if (j == 0) butterfly_one(x[B], x[B + H]);
+            else butterfly(x[B + j], x[B + j + H], make_float2(c[e], t[e]));
+            if (H > 1) {
+                if (j == 0) butterfly_one_i(x[B + H / 2], x[B + H / 2 + H]);
+                else butterfly_i(x[B + j + H / 2], x[B + j + H / 2 + H], make_float2(c[e], t[e]));
             }
         }
-        dft_dif<H, BASE, TOTAL>(x);
-        dft_dif<H, BASE + H, TOTAL>(x);
     }
 }
 
@@ -247,36 +313,91 @@ __device__ __forceinline__ void dft5(float2 (&x)[TOTAL])
     x[B + 3 * ST] = make_float2(a2.x - b2.y, a2.y + b2.x);
 }
 
-// In-register forward DFT of 10 points, natural order in and out: one radix-2 stage (decimation in frequency),
-// then the even outputs are the 5-point transform of the sums and the odd ones that of the twiddled differences.
-__device__ __forceinline__ void dft10(float2 (&x)[10])
+// In-register forward DFT of 10 points, natural order in and out: 5-point transforms of the even and the odd inputs, combined.
+__device__ __forceinline__ void dft10_plain(float2 (&x)[10])
 {
-    constexpr float wc[5] = {1.0f, 0.80901699437494742f, 0.30901699437494742f, -0.30901699437494742f, -0.80901699437494742f};
-    constexpr float ws[5] = {0.0f, 0.58778525229247313f, 0.95105651629515357f, 0.95105651629515357f, 0.58778525229247313f};
-    float2 y[10];                                            // y[2 t] sums, y[2 t + 1] differences times exp(-2 pi i t / 10)
+    constexpr float c[5] = {1.0f, 0.80901699437494742f, 0.30901699437494742f, -0.30901699437494742f, -0.80901699437494742f};
+    constexpr float t[5] = {0.0f, -0.72654252800536089f, -3.0776835371752534f, 3.0776835371752534f, 0.72654252800536089f};
+    dft5<0, 2, 10>(x);
+    dft5<1, 2, 10>(x);
+    float2 y[10];
 #pragma unroll
-    for (int t = 0; t < 5; ++t) {
-        const float2 a = x[t], b = x[t + 5];
-        y[2 * t] = make_float2(a.x + b.x, a.y + b.y);
-        const float dx = a.x - b.x, dy = a.y - b.y;
-        y[2 * t + 1] = t == 0 ? make_float2(dx, dy) : make_float2(fmaf(dx, wc[t], dy * ws[t]), fmaf(dy, wc[t], -dx * ws[t]));
+    for (int q = 0; q < 5; ++q) {
+        y[q] = x[2 * q];
+        y[q + 5] = x[2 * q + 1];
+        if (q == 0) butterfly_one(y[0], y[5]);
+        else butterfly(y[q], y[q + 5], make_float2(c[q], t[q]));
     }
-    dft5<0, 2, 10>(y);                                       // y[2 k]     = X[2 k]
-    dft5<1, 2, 10>(y);                                       // y[2 k + 1] = X[2 k + 1]
 #pragma unroll
-    for (int k = 0; k < 10; ++k) x[k] = y[k];
+    for (int q = 0; q < 10; ++q) x[q] = y[q];
+}
+// (Its nine twiddles are read as they are needed, tw(e): held in registers they cost 3000 x 200 points, D = 100, six levels 565 -> 600 us.)
+template <typename Twiddle>
+__device__ __forceinline__ void dft10(float2 (&x)[10], Twiddle tw)
+{
+#pragma unroll
+    for (int u = 1; u < 5; ++u) {
+        const float2 w = tw(u - 1);
+        x[2 * u] = cmulf(x[2 * u], w);
+        x[2 * u + 1] = cmulf(x[2 * u + 1], w);
+    }
+    dft5<0, 2, 10>(x);
+    dft5<1, 2, 10>(x);
+    float2 y[10];
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        y[q] = x[2 * q];
+        y[q + 5] = x[2 * q + 1];
+        butterfly(y[q], y[q + 5], tw(4 + q));
+    }
+#pragma unroll
+    for (int q = 0; q < 10; ++q) x[q] = y[q];
 }
 
-// Forward DFT of r points in registers; output k is left at position dft_out<r>(k).
-template <int r>
-__device__ __forceinline__ void dft_small(float2 (&x)[r])
+// Forward DFT of r points, natural order in and out; input t times the t-th power of the twiddle that tw stands for.
+template <int r, typename Twiddle>
+__device__ __forceinline__ void dft(float2 (&x)[r], Twiddle tw)
 {
-    if constexpr (r == 10) dft10(x);
-    else if constexpr (r == 5) dft5<0, 1, 5>(x);
-    else dft_dif<r, 0, r>(x);
+    if constexpr (r == 10) {
+        dft10(x, tw);
+    } else if constexpr (r == 5) {
+#pragma unroll
+        for (int t = 1; t < 5; ++t) x[t] = cmulf(x[t], tw(t - 1));
+        dft5<0, 1, 5>(x);
+    } else {
+        float2 w[twiddles(r)], y[r];
+#pragma unroll
+        for (int e = 0; e < twiddles(r); ++e) w[e] = tw(e);
+#pragma unroll
+        for (int t = 0; t < r; ++t) y[bitrev(t, ilog2(r))] = x[t];
+        dft_halves<0, r>(y, w);
+#pragma unroll
+        for (int t = 0; t < r; ++t) x[t] = y[t];
+    }
 }
 template <int r>
-constexpr int dft_out(int k) { return (r & (r - 1)) == 0 ? bitrev(k, ilog2(r)) : k; }
+__device__ __forceinline__ void dft_plain(float2 (&x)[r])
+{
+    if constexpr (r == 10) {
+        dft10_plain(x);
+    } else {
+        float2 y[r];
+#pragma unroll
+        for (int t = 0; t < r; ++t) y[bitrev(t, ilog2(r))] = x[t];
+        dft_halves_plain<0, r>(y);
+#pragma unroll
+        for (int t = 0; t < r; ++t) x[t] = y[t];
+    }
+}
+// Order in which a pass reads a lane's R points: butterfly after butterfly, each in the order in which it can start (that of memory
+// with ten and five points, where it made no difference).
+template <int R, int r>
+__device__ constexpr int read_order(int i)
+{
+    constexpr int NB = R / r;
+    const int u = i / r, t = i % r;
+    return (r & (r - 1)) == 0 ? u + NB * bitrev(t, ilog2(r)) : i;
+}
 
 // The same for a thread whose float2 are not complex numbers but two independent reals (pk; bins 0 and D/2
 // of a real sequence's transform, which one thread carries in the two halves of its values): the products
@@ -314,7 +435,7 @@ struct WaveFft {
     float2 tw[P::NTW];
     int wbase[P::NWB];
     int rbase;
-    const float2 *twl;      // LDS twiddle table of the radix-16 passes, entry ((set*(r-1) + t-1)*G + lg)
+    const float2 *twl;      // LDS twiddle table of the passes whose twiddles are there, entry ((set * twiddles(r) + e) * G + lg)
 
     // `roots`: D float2 of LDS that are free until the caller's next use of them. Short transforms pick their register
     // twiddles out of a table of the D-th roots of unity: computed where they are needed, D = 64 and 128 have 12 and 14
@@ -329,7 +450,7 @@ struct WaveFft {
             for (int i = threadIdx.x; i < P::D; i += blockDim.x) {
                 float s, c;
                 sincospif(-2.0f * (float)i / (float)P::D, &s, &c);
-                roots[i] = make_float2(c, s);
+                roots[i] = twiddle_form(c, s);
             }
         }
         fill_table<1>(twl_table);
@@ -344,13 +465,10 @@ struct WaveFft {
     {
         if constexpr (PI < P::NP) {
             if constexpr (P::tw_in_lds(PI)) {
-                constexpr int r = P::radix(PI), Ns = P::Ns(PI);
+                constexpr int r = P::radix(PI), Ns = P::Ns(PI), TW = twiddles(r);
                 for (int i = threadIdx.x; i < P::tw_lds(PI); i += blockDim.x) {
-                    const int l = i % P::G, ut = i / P::G, t = ut % (r - 1) + 1, u = ut / (r - 1);
-                    const int k = (l + P::G * u) % Ns;
-                    float s, c;
-                    sincospif(-2.0f * (float)(k * t) / (float)(Ns * r), &s, &c);
-                    twl_table[P::twl_off(PI) + i] = make_float2(c, s);
+                    const int l = i % P::G, ue = i / P::G, e = ue % TW, u = ue / TW;
+                    twl_table[P::twl_off(PI) + i] = twiddle_entry<r>(e, (l + P::G * u) % Ns, Ns);
                 }
             }
             fill_table<PI + 1>(twl_table);
@@ -374,14 +492,13 @@ struct WaveFft {
                 for (int u = 0; u < NSETS; ++u) {
                     const int k = (lg + P::G * u) % Ns;
 #pragma unroll
-                    for (int t = 1; t < r; ++t) {
-                        float2 &w = tw[P::tw_off(PI) + u * (r - 1) + (t - 1)];
+                    for (int e = 0; e < twiddles(r); ++e) {
+                        float2 &w = tw[P::tw_off(PI) + u * twiddles(r) + e];
                         if constexpr (kRoots) {
-                            w = roots[k * t * (P::D / (Ns * r))];
+                            const int H = e == 0 ? 1 : 2 << ilog2(e), j = e == 0 ? 0 : e - H / 2;
+                            w = roots[(k + j * Ns) * (P::D / (2 * H * Ns))];
                         } else {
-                            float s, c;
-                            sincospif(-2.0f * (float)(k * t) / (float)(Ns * r), &s, &c);
-                            w = make_float2(c, s);
+                            w = twiddle_entry<r>(e, k, Ns);
                         }
                     }
                 }
@@ -414,29 +531,27 @@ struct WaveFft {
             for (int u = 0; u < NB; ++u) {
                 float2 x[r];
 #pragma unroll
-                for (int t = 0; t < r; ++t) {
-                    x[t] = v[u + t * NB];
-                    if constexpr (PI > 0) {
-                        constexpr int set = P::tw_sets(PI) == 1 ? 0 : 1;    // multiplier of u below
-                        if (t > 0) {
-                            if constexpr (P::tw_in_lds(PI)) {
-                                x[t] = cmulf(x[t], twl[P::twl_off(PI) + ((set * u) * (r - 1) + (t - 1)) * P::G]);
-                                if (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);   // bound the twiddles in flight
-                            } else {
-                                x[t] = cmulf(x[t], tw[P::tw_off(PI) + (set * u) * (r - 1) + (t - 1)]);
-                            }
-                        }
-                    }
+                for (int t = 0; t < r; ++t) x[t] = v[u + t * NB];
+                if constexpr (PI == 0) {
+                    dft_plain(x);
+                } else {
+                    constexpr int TW = twiddles(r), set = P::tw_sets(PI) == 1 ? 0 : 1;    // multiplier of u below
+                    dft(x, [&](int e) {
+                        if constexpr (P::tw_in_lds(PI)) return twl[P::twl_off(PI) + (set * u * TW + e) * P::G];
+                        else return tw[P::tw_off(PI) + set * u * TW + e];
+                    });
                 }
-                dft_small<r>(x);
                 float2 *dst = slot + wbase[P::wb_off(PI) + u];
 #pragma unroll
-                for (int t = 0; t < r; ++t) dst[P::pad(t * Ns)] = x[dft_out<r>(t)];
+                for (int t = 0; t < r; ++t) dst[P::pad(t * Ns)] = x[t];
             }
             transform_fence<P>();
             if constexpr (PI + 1 < P::NP) {
 #pragma unroll
-                for (int q = 0; q < P::R; ++q) v[q] = slot[rbase + P::roff(q)];
+                for (int i = 0; i < P::R; ++i) {
+                    const int q = read_order<P::R, P::radix(PI + 1)>(i);
+                    v[q] = slot[rbase + P::roff(q)];
+                }
                 run_pass<PI + 1>(slot, v);
             }
         }
@@ -470,8 +585,9 @@ __host__ __device__ constexpr size_t tuned_lds_bytes(int NTR, int FPW, int PD, i
 {
     return sizeof(float2) * ((size_t)NTR * FPW * slot_stride(PD, 2 * F) + NTWL);
 }
-// ... and with slots that hold whole direct loads: what decides at which transform length a shape runs (as it did when
-// slots were that large, so that routes and workspace sizes stay what they were).
+// ... and with slots that hold whole direct loads, and a twiddle for every input but the first of a butterfly
+// (kBoundTwiddles): what decides at which transform length a shape runs (as it did when slots and tables were that large,
+// so that routes and workspace sizes stay what they were).
 __host__ __device__ constexpr size_t tuned_lds_bound(int NTR, int FPW, int PD, int NTWL, int F)
 {
     return tuned_lds_bytes(NTR, FPW, PD, NTWL, staged(2 * F) / 2);
@@ -1069,18 +1185,31 @@ __global__ __launch_bounds__(64 * NTR)
                 // with more than four transforms per wavefront and three or more levels the loop over the pairs
                 // stays a loop: unrolled it needs 50-150 spilled registers (measured rolled: D = 64 ... 200 with
                 // 4-8 levels 1.4-3 times faster; with one or two levels up to 45 % slower, hence the condition)
-#pragma unroll(P::FPW > 4 && M >= 3 ? 1 : P::FPW)
-                for (int s = 0; s < P::FPW; ++s) {
-                    if (!FULL && pair0_now + s >= pairs) continue;             // slot without a pair (last iteration only)
+                constexpr bool kRolled = P::FPW > 4 && M >= 3;
+                auto one_pair = [&](auto both_tag, int s) {
 #pragma unroll
                     for (int b = 0; b < BPT; ++b) {
                         if (NT * BPT == NB || tid_here + NT * b < NB) {
                             LevelCarry<ORDER> c[kStarts];
                             level_loop<M>([&](auto level_tag) {
-                                update_bin(level_tag, packed_tag, full_tag, s, b, decltype(level_tag)::value, pair0_now, c);
+                                update_bin(level_tag, packed_tag, both_tag, s, b, decltype(level_tag)::value, pair0_now, c);
                             });
                         }
                     }
+                };
+                if constexpr (kRolled) {
+                    // the pairs with both steps, then the one with the first step only, if this iteration has it: no selects
+                    // in the loop, whose chain of levels the other wavefronts wait for (3000 x 200 points, D = 100, 50
+                    // frequencies, eight levels 844 -> 825 us, D = 128 748 -> 710, D = 200, six levels 1168 -> 1133)
+                    const int64_t left = T / 2 - pair0_now;
+                    const int both = left < P::FPW ? (int)left : P::FPW;
+#pragma unroll 1
+                    for (int s = 0; s < both; ++s) one_pair(LevelTag<1>{}, s);
+                    if (both < P::FPW && pair0_now + both < pairs) one_pair(LevelTag<0>{}, both);
+                } else {
+#pragma unroll
+                    for (int s = 0; s < P::FPW; ++s)
+                        if (FULL || pair0_now + s < pairs) one_pair(full_tag, s);     // (slots without a pair: last iteration only)
                 }
             }
         };

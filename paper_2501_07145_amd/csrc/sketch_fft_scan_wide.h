@@ -35,7 +35,7 @@ __host__ __device__ constexpr int wide_slot_stride(int S, int twoF)
 }
 __host__ __device__ constexpr size_t wide_lds_bytes(int S, int M, int F)
 {
-    return sizeof(float2) * ((size_t)wide_levels_in_flight(M) * wide_slot_stride(S, 2 * F) + Plan<10>::NTWL);
+    return sizeof(float2) * ((size_t)wide_levels_in_flight(M) * wide_slot_stride(S, 2 * F) + Plan<10>::kBoundTwiddles);
 }
 
 template <int LOG2S, int M, int ORDER, int NTR>
@@ -124,9 +124,9 @@ __global__ __launch_bounds__(64 * (1 << LOG2S) * NTR) __attribute__((amdgpu_wave
             for (int r = 2; r < S; ++r) wp[r] = cmulf(wp[r / 2], wp[r - r / 2]);
 #pragma unroll
             for (int r = 1; r < S; ++r) x[r] = cmulf(x[r], wp[r]);
-            dft_dif<S, 0, S>(x);
+            dft_plain(x);
 #pragma unroll
-            for (int k = 0; k < S; ++k) base[k * P::PD] = x[bitrev(k, LOG2S)];
+            for (int k = 0; k < S; ++k) base[k * P::PD] = x[k];
         }
     };
 
