@@ -86,7 +86,6 @@ void dp1d_features_kernel(
     float scale_turns, int64_t L, int d, int M, int F, float *__restrict__ out, int64_t ld_out)
 {
     constexpr int KP = 2 * KSTEPS, XS = KP | 1;
-    constexpr bool kKeepX = KSTEPS <= 16;              // the tile's A fragments stay in registers for all levels
     __shared__ float xs[2 * kRows * XS];
     __shared__ __attribute__((aligned(16))) float tile[4][64 * kTileStride];
     extern __shared__ float level_state[];             // [2][M][256]: accumulators, then last cosines
@@ -154,11 +153,9 @@ void dp1d_features_kernel(
         const bool more = t0 + kRows < L;
         if (more) fetch_tile(t0 + kRows);
         const float *xt = xs + cur * (kRows * XS) + col * XS + half;
-        float xa[kKeepX ? KSTEPS : 1];
-        if (kKeepX) {
+        float xa[KSTEPS];                                  // the tile's A fragments, for all levels
 #pragma unroll
-            for (int kk = 0; kk < KSTEPS; ++kk) xa[kk] = xt[2 * kk];
-        }
+        for (int kk = 0; kk < KSTEPS; ++kk) xa[kk] = xt[2 * kk];
         float E[kRows];
         for (int m = 0; m < M; ++m) {
             const int mn = m + 1 == M ? 0 : m + 1;
@@ -170,7 +167,7 @@ void dp1d_features_kernel(
                 floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
                 for (int kk = 0; kk < KSTEPS; ++kk)
-                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(kKeepX ? xa[kk] : xt[2 * kk], w[cb][kk], acc, 0, 0, 0);
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[kk], w[cb][kk], acc, 0, 0, 0);
                 const float b = bm[cb] * 0.318309886183790672f;          // phase in half-turns, and what its rounding left
                 const float rest = fmaf(bm[cb], 0.318309886183790672f, -b) + bm[cb] * 1.2841276486e-8f;
                 fetch_w(wn, mn, cb);
@@ -398,10 +395,19 @@ hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float 
         hipLaunchKernelGGL(dp1d_features_kernel<KS>, grid, dim3(256), dyn, stream, X, W, bias,                \
                            scale_turns, L, d, M, F, out, ld_out);                                         \
     } while (0)
-    if (d <= 4) RFSF_LAUNCH_DP1D(2);
+    // Matrix instructions and loads of W for padding channels cost as much as for others, 0.26 ms per pair of them in 4999 x 257
+    // points, 1000 components, five levels: with pairs 2, 4, 9, 16 and 32 alone, d = 6 2.75 -> 2.52 ms, 12 3.79 -> 3.36, 24 5.71 ->
+    // 4.43, 40 9.73 -> 6.89, 48 9.74 -> 7.46, and 64 9.76 -> 8.90 with the points' fragments kept in registers.
+    if (d <= 2) RFSF_LAUNCH_DP1D(1);
+    else if (d <= 4) RFSF_LAUNCH_DP1D(2);
+    else if (d <= 6) RFSF_LAUNCH_DP1D(3);
     else if (d <= 8) RFSF_LAUNCH_DP1D(4);
+    else if (d <= 12) RFSF_LAUNCH_DP1D(6);
     else if (d <= 18) RFSF_LAUNCH_DP1D(9);
+    else if (d <= 24) RFSF_LAUNCH_DP1D(12);
     else if (d <= 32) RFSF_LAUNCH_DP1D(16);
+    else if (d <= 40) RFSF_LAUNCH_DP1D(20);
+    else if (d <= 48) RFSF_LAUNCH_DP1D(24);
     else RFSF_LAUNCH_DP1D(32);
 #undef RFSF_LAUNCH_DP1D
     return hipGetLastError();
