@@ -331,7 +331,6 @@ __device__ __forceinline__ void dft10_plain(float2 (&x)[10])
 #pragma unroll
     for (int q = 0; q < 10; ++q) x[q] = y[q];
 }
-// (Its nine twiddles are read as they are needed, tw(e): held in registers they cost 3000 x 200 points, D = 100, six levels 565 -> 600 us.)
 template <typename Twiddle>
 __device__ __forceinline__ void dft10(float2 (&x)[10], Twiddle tw)
 {
@@ -359,7 +358,10 @@ template <int r, typename Twiddle>
 __device__ __forceinline__ void dft(float2 (&x)[r], Twiddle tw)
 {
     if constexpr (r == 10) {
-        dft10(x, tw);
+        float2 w[9];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) w[e] = tw(e);
+        dft10(x, [&](int e) { return w[e]; });
     } else if constexpr (r == 5) {
 #pragma unroll
         for (int t = 1; t < 5; ++t) x[t] = cmulf(x[t], tw(t - 1));
