@@ -30,7 +30,8 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E, published
 MFMA_FP32_PEAK_TFLOPS = 157.3    # MI355X dense fp32 matrix, published
 
 MFMA_BF16_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix, published
-GRAM_TERMS = 6                   # bf16 products that the Gram kernels execute for one product of 32-bit numbers
+GRAM_TERMS = 3                   # 16-bit products that the large tiles of the Gram kernels execute for one product of 32-bit
+                                 # numbers (small tiles execute six and are counted too low)
 
 VALU_FP32_PEAK_TFLOPS = 157.3     # MI355X fp32 vector, published: 256 CUs x 128 fused multiply-adds per clock at 2.4 GHz. A loop of
                                   # plain (unpacked) v_fma_f32 chains measures 118 TFLOP/s here (rfsf_ts_probe_peaks), so the
@@ -337,13 +338,18 @@ def bench_ts(args, name: str, steps: int, warmup: int, cpu_baseline: bool) -> di
     entry("rff_increments", "hbm", n_seq * 4.0 * w.L * w.d + incr_units * incr_bytes, "GB/s", HBM_PEAK_GBS,
           mfma_tflops=units * proj_flops / 1e12, sincos_pairs_per_s=float(units * w.M * w.F),
           write_gbs=incr_units * incr_bytes / 1e9)
+    # faster than memory: the sketch kernel has computed the increments itself, and what was timed is the build of its tables
+    fused = kernels.get("rff_increments", {}).get("frac", 0.0) > 1.0
+    if fused:
+        del kernels["rff_increments"]
     if "rff_increments" in kernels:
         kernels["rff_increments"]["mfma_peak"] = mfma_peak
         kernels["rff_increments"]["mfma_frac"] = kernels["rff_increments"]["mfma_tflops"] / mfma_peak
-    entry("sketch_fft_scan", "hbm", incr_units * incr_bytes + 4.0 * n_seq * w.M * w.D, "GB/s", HBM_PEAK_GBS)
+    entry("sketch_fft_scan", "hbm", (4.0 * n_seq * w.L * w.d if fused else incr_units * incr_bytes) + 4.0 * n_seq * w.M * w.D,
+          "GB/s", HBM_PEAK_GBS)
     Ny = w.N2 if w.N2 else w.N
     # flops the kernel performs: the whole matrix for a cross Gram, for K = Phi Phi^T only the tiles on or above the
-    # diagonal (counted here as N(N+1)/2 inner products); six bf16 products each (csrc/gram.hip)
+    # diagonal (counted here as N(N+1)/2 inner products); GRAM_TERMS 16-bit products each (csrc/gram.hip)
     gram_pairs = w.N * Ny if w.N2 else w.N * (w.N + 1) / 2
     entry("gram", "mfma", 2.0 * GRAM_TERMS * gram_pairs * w.ncols, "TFLOP/s", MFMA_BF16_PEAK_TFLOPS)
     entry("normalize", "hbm", 2.0 * 4.0 * n_seq * w.ncols, "GB/s", HBM_PEAK_GBS)
