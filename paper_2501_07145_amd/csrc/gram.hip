@@ -803,9 +803,9 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
     }
     const bool nan_found = any_nan(acc);
     bool open = false;          // entries that are NaN although neither of their rows ends in one: a row did not fit its scale
-    float down_b[2];
+    float of_col[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) down_b[u] = scales[kBigM + (wj * 2 + u) * 32 + col];
+    for (int u = 0; u < 2; ++u) of_col[u] = scales[kBigM + (wj * 2 + u) * 32 + col];
     if (nan_found) {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
@@ -813,7 +813,7 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
             for (int e = 0; e < 16; ++e) {
                 const float of_row = scales[wi * 128 + 32 * t + 8 * (e / 4) + 4 * half + e % 4];
 #pragma unroll
-                for (int u = 0; u < 2; ++u) open |= acc[t][u][e] != acc[t][u][e] && of_row == of_row && down_b[u] == down_b[u];
+                for (int u = 0; u < 2; ++u) open |= acc[t][u][e] != acc[t][u][e] && of_row == of_row && of_col[u] == of_col[u];
             }
     }
     if (__ballot(open) && lane == 0) verdict = 1;
@@ -822,17 +822,22 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
         three_term_tile_call<ALIGNED, SYM, FLIP>(g, (LdsFloat *)buf, i0, j0);
         return;
     }
+    // Back from the scales 2^a and 2^b of its rows by one power of two, -(a + b): it rounds once and can be as large as 200, where
+    // the product of two powers would overflow (times a sum of zero: NaN) or vanish although the result is an ordinary number.
+    int down[2];
 #pragma unroll
-    for (int u = 0; u < 2; ++u) down_b[u] = __uint_as_float(0x7f000000u - __float_as_uint(down_b[u]));
+    for (int u = 0; u < 2; ++u) down[u] = 2 * 127 - (int)(__float_as_uint(of_col[u]) >> 23);
 #pragma unroll
     for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const float of_row = scales[wi * 128 + 32 * t + 8 * (e / 4) + 4 * half + e % 4];
-            float down_a = __uint_as_float(0x7f000000u - __float_as_uint(of_row));
-            if (FLIP) down_a = __uint_as_float(__float_as_uint(down_a) ^ flip_of_row(i0 + wi * 128 + 32 * t));
+            const int up = (int)(__float_as_uint(scales[wi * 128 + 32 * t + 8 * (e / 4) + 4 * half + e % 4]) >> 23);
 #pragma unroll
-            for (int u = 0; u < 2; ++u) acc[t][u][e] *= down_a * down_b[u];
+            for (int u = 0; u < 2; ++u) {
+                float v = acc[t][u][e];
+                if (FLIP) v = __uint_as_float(__float_as_uint(v) ^ flip_of_row(i0 + wi * 128 + 32 * t));
+                acc[t][u][e] = __builtin_amdgcn_ldexpf(v, down[u] - up);
+            }
         }
     // result layout of a 32x32 block: lane holds column lane % 32 and rows 8 q + 4 (lane / 32) + 0 .. 3
     const bool vec_mirror = g.ldc % 4 == 0 && reinterpret_cast<uintptr_t>(tile.C) % 16 == 0;

@@ -65,6 +65,37 @@ def test_one_operand_is_symmetric(N, C, packed, pad, kind):
     assert bool((K[:, N:] == -3.0).all())
 
 
+@pytest.mark.parametrize("packed", [True, False])
+@pytest.mark.parametrize("up_a,up_b", [(-62, -62), (-66, -66), (-80, -50), (-70, 70), (80, -75), (40, 60)])
+def test_scales_of_both_rows_together(up_a, up_b, packed):
+    """Rows whose scales multiply to more or less than a float holds, while the products of the rows do not."""
+    rng = np.random.default_rng(1000 + up_a)
+    A, B = _operand(rng, 2600, 1030, packed, "normal"), _operand(rng, 2700, 1030, packed, "normal")
+    A *= 2.0 ** up_a
+    B *= 2.0 ** up_b
+    _check(rfsf.rfsf_ts_gram(A, B), A, B)
+
+
+@pytest.mark.parametrize("both", [0.0, 2.0 ** -11])
+@pytest.mark.parametrize("up_a,up_b", [(73, 73), (80, 80), (95, 60)])
+def test_large_rows_that_hardly_meet(up_a, up_b, both):
+    """A has even columns and B odd ones, and both one that they share: sums of two or three ordinary numbers, or zero."""
+    rng = np.random.default_rng(up_a)
+    A, B = _operand(rng, 2600, 300, False, "normal"), _operand(rng, 2700, 300, False, "normal")
+    A[:, 1::2] = 0.0
+    B[:, ::2] = 0.0
+    if up_a + up_b < 150:
+        A[:, 101], B[:, 101] = both, -both
+    A *= 2.0 ** up_a
+    B *= 2.0 ** up_b
+    K = rfsf.rfsf_ts_gram(A, B)
+    want = (A.double() @ B.double().T.contiguous()).float()
+    if both == 0.0 or up_a + up_b >= 150:
+        assert bool((K == 0.0).all())
+    else:
+        assert torch.equal(K, want)                          # one product of powers of two per entry
+
+
 def test_error_is_no_larger_than_three_terms():
     """2-norm of the error over that of the result; three terms had 1.63e-7, 3.0e-7 and 5.3e-7 here (the rows of the first
     two are normal numbers, the last has a column of ones), a margin of a tenth for other seeds."""
