@@ -24,10 +24,15 @@
 // than what adding up loses, where half as many additions round: relative error of K against 64 bits, three terms and two, 1.63e-7
 // and 1.43e-7 with 128 columns of normal numbers, 3.0e-7 and 2.3e-7 with 400, 5.3e-7 and 4.6e-7 with 1001 of features, 1.07e-6 and
 // 9.8e-7 with 5121, 1.5e-6 and 1.4e-6 with 10241 (mean error -2.37e-7 and -2.31e-7 of 5121 columns). The range of these
-// numbers is narrow. A row's scale brings the largest of 64 of its numbers to 2^9 (48 at its beginning, which are in LDS anyway,
-// and four at each of four places spread over it): numbers down to 2^-12 of that keep both terms in full, smaller ones an
-// error of 2^-34 of it; numbers more than 64 times as large overflow, which shows as NaN, and the tile is computed
+// numbers is narrow. A row's scale brings the largest of about 48 of its numbers to 2^9 .. 2^10 (32 at its beginning, which are in LDS
+// anyway, and four at each of four places spread over it): numbers down to 2^-12 of that keep both terms in full, smaller ones an
+// error of 2^-25 (scaled); numbers more than 64 times as large overflow, which shows as NaN, and the tile is computed
 // again with three terms, as are tiles with rows beyond 2^-91 .. 2^109 from the outset.
+// The error of small numbers is no error of their products if those of the large ones are part of the same sum, and without limit if
+// the large ones meet zeros. So the sum of |a b| over the sampled columns is computed for every pair of rows, and a tile in which one
+// of them is below 2^15 takes three terms. What small numbers add to the error is K 2^-25 (2^10 + 2^10) at most, K / 32 units of
+// 2^-24 times that sum, and 2 K units if numbers that were not sampled are up to 2^16 and all meet small ones. (Features, raw
+// and normalised, of walks and of noise, and increments against normal numbers: 2^16.8 and more.)
 #include "rfsf_internal.h"
 #include <type_traits>
 
@@ -109,6 +114,17 @@ __device__ __forceinline__ void split_pair(Half8 &f, int i, float a, float b, fl
     const floatx2 rest = {fmaf(a, scale, -(float)hi[0]), fmaf(b, scale, -(float)hi[1])};                 // v_fma_mix_f32
     f.hi[i] = __builtin_bit_cast(uint32_t, hi);
     f.lo[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(rest, halfx2));
+}
+// Magnitudes of eight consecutive numbers of a row times its scale, or `zero` for those of a row without any.
+__device__ __forceinline__ halfx8 magnitudes(const float (&x)[8], float scale, float zero)
+{
+    uint32_t v[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const floatx2 pair = {fmaf(fabsf(x[2 * i]), fabsf(scale), zero), fmaf(fabsf(x[2 * i + 1]), fabsf(scale), zero)};
+        v[i] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pair, halfx2));
+    }
+    return __builtin_bit_cast(halfx8, make_uint4(v[0], v[1], v[2], v[3]));
 }
 __device__ __forceinline__ floatx16 product(int k, const Half8 &a, const Half8 &b, const floatx16 &c)
 {
@@ -412,15 +428,15 @@ int64_t big_tiles(int64_t Nx, int64_t Ny, bool sym)
     return sym ? nti * ntj - nti * (nti - 1) : nti * ntj;
 }
 
-// Lane i's BYTES bytes at base + off to LDS at dst + BYTES * i. Written out so that the compiler, which cannot tell
+// Lane i's BYTES bytes at base + off to LDS at address dst + BYTES * i. Written out so that the compiler, which cannot tell
 // the buffers apart, does not wait for the loads in flight before every read of LDS; the caller waits. (m0 is a register
 // that the compiler manages by itself; that it is written here has to be said, and is warned about.)
 #pragma clang diagnostic push
 #pragma clang diagnostic ignored "-Winline-asm"
 template <int BYTES>
-__device__ __forceinline__ void direct_load(const char *base, uint32_t off, float *dst)
+__device__ __forceinline__ void direct_load(const char *base, uint32_t off, uint32_t dst)
 {
-    const uint32_t to = __builtin_amdgcn_readfirstlane((uint32_t)(uintptr_t)(__attribute__((address_space(3))) float *)dst);
+    const uint32_t to = __builtin_amdgcn_readfirstlane(dst);
     if constexpr (BYTES == 16)
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(to), "v"(off), "s"(base) : "memory", "m0");
     else
@@ -444,13 +460,15 @@ struct BigTile {
     static constexpr int RI = ALIGNED ? 16 : 4, NL = kBigRows / RI / 4;
     const GramArgs &g;
     float *buf;                         // three buffers in LDS
+    uint32_t lds;                       // address of the first one there
     const float *A, *B;
     float *C;
     int64_t i0, j0, nfull, nsteps;
     int tid, lane, wave, half, col, wi, wj, rest, shift, fsw, frag_a, frag_b;
     uint32_t off[NL];                   // byte offset of this lane's source from the operand's tile
 
-    __device__ __forceinline__ BigTile(const GramArgs &args, float *buffers, int64_t i, int64_t j) : g(args), buf(buffers), i0(i), j0(j)
+    __device__ __forceinline__ BigTile(const GramArgs &args, LdsFloat *buffers, int64_t i, int64_t j)
+        : g(args), buf((float *)buffers), lds((uint32_t)(uintptr_t)buffers), i0(i), j0(j)
     {
         A = g.A + blockIdx.y * g.step_a;
         B = g.B + blockIdx.y * g.step_b;
@@ -498,9 +516,11 @@ struct BigTile {
         for (int l = 0; l < NL; ++l) {
             const int row0 = RI * (wave * NL + l);              // uniform
             const char *base = (row0 >= kBigM ? base_b : base_a) + 4 * k0;
-            direct_load<ALIGNED ? 16 : 4>(CALLED ? uniform(base) : base, off[l], dst + row0 * kStep);
+            direct_load<ALIGNED ? 16 : 4>(CALLED ? uniform(base) : base, off[l], lds + 4u * (uint32_t)(dst - buf + row0 * kStep));
         }
     }
+    // FEW: the first two steps only, their number being more than two; the third one is left to the caller.
+    template <bool FEW>
     __device__ __forceinline__ void first_steps() const
     {
         if (rest != 0) {
@@ -519,7 +539,7 @@ struct BigTile {
             load(buf, 0);
         }
         if (nsteps > 1) load(buf + kBigBuffer, kStep * (1 - shift));
-        if (nsteps > 2) load(buf + 2 * kBigBuffer, kStep * (2 - shift));
+        if (!FEW && nsteps > 2) load(buf + 2 * kBigBuffer, kStep * (2 - shift));
     }
     __device__ __forceinline__ void read8(const float *rd, int at, float (&x)[8]) const
     {
@@ -574,9 +594,10 @@ __device__ __forceinline__ bool any_nan(const floatx16 (&acc)[4][2])     // of t
 
 // One tile with three terms, from the first load to the last entry.
 template <bool ALIGNED, bool SYM, bool FLIP, bool CALLED>
-__device__ __forceinline__ void three_term_tile(const GramArgs &g, float *buf, int64_t i0, int64_t j0)
+__device__ __forceinline__ void three_term_tile(const GramArgs &g, LdsFloat *buffers, int64_t i0, int64_t j0)
 {
-    const BigTile<ALIGNED, CALLED> tile(g, buf, i0, j0);
+    const BigTile<ALIGNED, CALLED> tile(g, buffers, i0, j0);
+    float *buf = tile.buf;
     const int wi = tile.wi, wj = tile.wj, half = tile.half, col = tile.col;
     const int64_t nsteps = tile.nsteps;
     floatx16 acc[4][2];
@@ -630,7 +651,7 @@ __device__ __forceinline__ void three_term_tile(const GramArgs &g, float *buf, i
         b[1] = nb[1];
         a = na;
     };
-    tile.first_steps();
+    tile.template first_steps<false>();
     if (nsteps > 0) {
         tile.everybody();
         first_fragments(buf, b, a);
@@ -664,7 +685,7 @@ __device__ __forceinline__ void three_term_tile(const GramArgs &g, float *buf, i
 template <bool ALIGNED, bool SYM, bool FLIP>
 __device__ __attribute__((noinline)) void three_term_tile_call(GramArgs g, LdsFloat *buf, int64_t i0, int64_t j0)
 {
-    three_term_tile<ALIGNED, SYM, FLIP, true>(g, (float *)buf, uniform(i0), uniform(j0));
+    three_term_tile<ALIGNED, SYM, FLIP, true>(g, buf, uniform(i0), uniform(j0));
 }
 
 template <bool SYM>
@@ -684,7 +705,7 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
     __shared__ __attribute__((aligned(16))) float buf[3 * kBigBuffer];
     int64_t i0, j0;
     if (!place_of_tile<SYM>(tiles, nti, ntj, i0, j0)) return;
-    three_term_tile<ALIGNED, SYM, FLIP, false>(g, buf, i0, j0);
+    three_term_tile<ALIGNED, SYM, FLIP, false>(g, (LdsFloat *)buf, i0, j0);
 }
 
 template <bool SYM>
@@ -701,7 +722,8 @@ constexpr int kPartStride = 65;          // floats between the rows of a wavefro
 // the products save. A tile that cannot do with two terms ends with a call of the three-term code: inlined, that code and
 // what it keeps alive pushes the registers of the loop below into scratch memory (2.1 -> 5.7 ms).
 constexpr int64_t kTwoTermColumns = 128;
-constexpr int kSamples = 4, kLargest = 9, kMostUp = 100;
+constexpr int kSamples = 4, kLargest = 9, kMostUp = 100, kUpOfZeros = kMostUp + 1;
+constexpr float kLeastSum = 0x1p15f;
 template <bool ALIGNED, bool SYM, bool FLIP>
 __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t tiles, int64_t nti, int64_t ntj)
 {
@@ -710,20 +732,30 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
     __shared__ int verdict;                     // 1: the tile takes three terms
     int64_t i0, j0;
     if (!place_of_tile<SYM>(tiles, nti, ntj, i0, j0)) return;
-    const BigTile<ALIGNED> tile(g, buf, i0, j0);
+    const BigTile<ALIGNED> tile(g, (LdsFloat *)buf, i0, j0);
     const int tid = tile.tid, lane = tile.lane, wi = tile.wi, wj = tile.wj, half = tile.half, col = tile.col;
     floatx16 acc[4][2];
     {
         const int64_t nsteps = tile.nsteps;
-        tile.first_steps();
-        // Scales: from the largest of the first three steps' numbers of a row and of sixteen more spread over it.
+        tile.template first_steps<true>();
+        // Scales: from the largest of the first two steps' numbers of a row and of sixteen more spread over it, which lie where
+        // the third step's will.
         constexpr int kOwn = (kBigRows + 255) / 256;             // rows of a thread
+        float *samples = buf + 2 * kBigBuffer;
         Float4u sample[kOwn][kSamples];
 #pragma unroll
         for (int h = 0; h < kOwn; ++h) {
             const float *src = tile.source(min(tid + 256 * h, kBigRows - 1));
 #pragma unroll
             for (int k = 0; k < kSamples; ++k) sample[h][k] = *reinterpret_cast<const Float4u *>(src + (g.K - 4) * (k + 1) / kSamples);
+        }
+#pragma unroll
+        for (int h = 0; h < kOwn; ++h) {
+            const int row = min(tid + 256 * h, kBigRows - 1);
+#pragma unroll
+            for (int k = 0; k < kSamples; ++k)
+                *reinterpret_cast<float4 *>(&samples[row * kStep + 4 * (k ^ ((row >> 2) & 3))]) =
+                    make_float4(sample[h][k].x, sample[h][k].y, sample[h][k].z, sample[h][k].w);
         }
         if (tid == 0) verdict = 0;
         tile.everybody();
@@ -738,21 +770,17 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
                 most = fmaxf(fmaxf(fmaxf(fabsf(sample[h][k].x), fabsf(sample[h][k].y)),
                                    fmaxf(fabsf(sample[h][k].z), fabsf(sample[h][k].w))), most);
 #pragma unroll
-            for (int k = 0; k < 12; ++k) {
+            for (int k = 0; k < 8; ++k) {
                 const float4 v = *reinterpret_cast<const float4 *>(&buf[k / 4 * kBigBuffer + row * kStep + 4 * ((k + (row >> 2)) & 3)]);
                 most = fmaxf(fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))), most);
             }
             const int exponent = (int)(__float_as_uint(most) >> 23) - 127;      // of the largest; -127 for zero
-            const int up = most == 0.f ? kMostUp : kLargest - exponent;
-            outside |= up > kMostUp || up < -kMostUp;
+            const int up = most == 0.f ? kUpOfZeros : kLargest - exponent;
+            outside |= most != 0.f && (up > kMostUp || up < -kMostUp);
             scales[row] = last != last ? last : __uint_as_float((uint32_t)(127 + up) << 23);
         }
         if (__ballot(outside) && lane == 0) verdict = 1;
         __syncthreads();
-        if (verdict != 0) {
-            three_term_tile_call<ALIGNED, SYM, FLIP>(g, (LdsFloat *)buf, i0, j0);
-            return;
-        }
         float scale_a[4], scale_b[2];           // of this lane's rows in the blocks of A (flipped where those are) and B
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -761,6 +789,43 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
         }
 #pragma unroll
         for (int t = 0; t < 2; ++t) scale_b[t] = scales[kBigM + (wj * 2 + t) * 32 + col];
+        // The sums of |a b| over the sampled columns, by the matrix units (3000 rows with 3000, 400 columns 49.2 -> 50.9 us, 10000 with
+        // themselves, 5121 columns 2.03 ms with them and without).
+        {
+            const auto of_zeros = [](float scale) { return fabsf(scale) == __uint_as_float((uint32_t)(127 + kUpOfZeros) << 23) ? 0x1p9f : 0.f; };
+            clear(acc);
+#pragma unroll 1
+            for (int s = 0; s < 3; ++s) {
+                halfx8 of_b[2];
+                float x[8];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    tile.read8(buf + s * kBigBuffer, tile.frag_b + u * 32 * kStep, x);
+                    of_b[u] = magnitudes(x, scale_b[u], of_zeros(scale_b[u]));
+                }
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    tile.read8(buf + s * kBigBuffer, tile.frag_a + t * 32 * kStep, x);
+                    const halfx8 of_a = magnitudes(x, scale_a[t], of_zeros(scale_a[t]));
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) acc[t][u] = __builtin_amdgcn_mfma_f32_32x32x16_f16(of_a, of_b[u], acc[t][u], 0, 0, 0);
+                }
+            }
+            float least = acc[0][0][0];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int u = 0; u < 2; ++u)
+#pragma unroll
+                    for (int e = 0; e < 16; ++e) least = fminf(least, acc[t][u][e]);
+            if (__ballot(least < kLeastSum) && lane == 0) verdict = 1;
+        }
+        __syncthreads();
+        if (verdict != 0) {
+            three_term_tile_call<ALIGNED, SYM, FLIP>(g, (LdsFloat *)buf, i0, j0);
+            return;
+        }
+        tile.load(buf + 2 * kBigBuffer, kStep * (2 - tile.shift));            // nobody reads the samples any more
         // Software pipeline. A step enters with the split fragments of its two blocks of B and of its first block of A, and
         // with the numbers of the second. A pair of floats is split behind every matrix instruction (in this order: left to
         // itself the scheduler makes lumps, and a matrix instruction hides about four others, not sixty): four instructions

@@ -96,6 +96,40 @@ def test_large_rows_that_hardly_meet(up_a, up_b, both):
         assert torch.equal(K, want)                          # one product of powers of two per entry
 
 
+def _check_products(K, A, B):
+    """Against the products of the entry alone: (K + 13) 2^-24 of them as above, and K / 32 (the sampled products) more."""
+    a, b = A.double(), B.double()
+    bound = (1.04 * a.shape[1] + 13) * 2.0 ** -24 * (a.abs() @ b.abs().T.contiguous()) + 2.0 ** -149
+    err = (K.double() - a @ b.T.contiguous()).abs()
+    assert bool((err <= bound).all()), float((err / bound).max())
+
+
+@pytest.mark.parametrize("swap", [False, True])
+@pytest.mark.parametrize("kind", ["one", "one_hidden", "half", "one_row", "few_rows"])
+@pytest.mark.parametrize("C,packed", [(128, False), (300, True), (1030, False)])
+def test_large_numbers_against_zeros(C, packed, kind, swap):
+    """Rows with a range wider than two terms hold, whose large numbers meet zeros: what is left is made of their small ones."""
+    rng = np.random.default_rng(C)
+    A, B = _operand(rng, 2600, C, packed, "normal"), _operand(rng, 2700, C, packed, "normal")
+    where = {"one": 3, "one_hidden": 50}.get(kind, 20)
+    if kind == "half":
+        A[:, C // 2:] *= 2.0 ** -20
+        B[:, :C // 2] = 0.0
+    else:
+        small = {"one_row": slice(1500, 1501), "few_rows": slice(7, 2600, 301)}.get(kind, slice(None))
+        A[small] *= 2.0 ** -20
+        A[small, where] = 1.0
+        B[:, where] = 0.0
+    K = rfsf.rfsf_ts_gram(B, A).T if swap else rfsf.rfsf_ts_gram(A, B)
+    _check_products(K, A, B)
+
+
+def test_unit_vectors_give_the_numbers_themselves():
+    A = _operand(np.random.default_rng(3), 2600, 300, False, "wide")
+    K = rfsf.rfsf_ts_gram(A, torch.eye(300, device="cuda").repeat(9, 1))
+    assert torch.equal(K, A.repeat(1, 9))
+
+
 def test_error_is_no_larger_than_three_terms():
     """2-norm of the error over that of the result; three terms had 1.63e-7, 3.0e-7 and 5.3e-7 here (the rows of the first
     two are normal numbers, the last has a column of ones), a margin of a tenth for other seeds."""
