@@ -708,14 +708,6 @@ __global__ __launch_bounds__(256, 2) void gram_big(GramArgs g, int64_t tiles, in
     three_term_tile<ALIGNED, SYM, FLIP, false>(g, (LdsFloat *)buf, i0, j0);
 }
 
-template <bool SYM>
-__device__ __attribute__((noinline)) void settle_call(GramArgs g, int64_t i0, int64_t j0, bool diagonal)
-{
-#pragma unroll 1
-    for (int h = 0; h < 2; ++h)
-        settle_nan<64, 64, SYM>(g, g.A + blockIdx.y * g.step_a, g.B + blockIdx.y * g.step_b, g.C + blockIdx.y * g.step_c,
-                                i0 + 64 * h, j0, diagonal);
-}
 constexpr int kPartStride = 65;          // floats between the rows of a wavefront's 32 x 64 part of a result in LDS
 
 // Two terms (top of the file). Below 128 columns the three terms' error is the smaller one, and the scales take as long as
@@ -866,12 +858,13 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
             if (s + 2 < nsteps) step(s + 2, buf + 2 * kBigBuffer, buf);
         }
     }
-    const bool nan_found = any_nan(acc);
-    bool open = false;          // entries that are NaN although neither of their rows ends in one: a row did not fit its scale
+    // Entries that are NaN although neither of their rows ends in one: a row did not fit its scale, or a NaN or an infinity stands
+    // somewhere else in it. (NaN in a row that ends in one needs no second look: settle_nan would leave it alone, too.)
+    bool open = false;
     float of_col[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) of_col[u] = scales[kBigM + (wj * 2 + u) * 32 + col];
-    if (nan_found) {
+    if (any_nan(acc)) {
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
@@ -955,7 +948,6 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
             }
         }
     }
-    if (nan_found) settle_call<SYM>(g, i0 + wi * 128, j0 + wj * 64, diagonal);
 }
 
 template <int T, int NW>
