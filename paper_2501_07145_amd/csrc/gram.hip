@@ -141,16 +141,16 @@ struct GramArgs {
     int64_t step_a, step_b, step_c;
 };
 
-// Stores four consecutive rows i .. i+3 of column j; `mirror` also writes their mirror image, row j. `diagonal`: the
+// Stores four consecutive rows i .. i+3 of column j, of a block with this sign (FLIP); `mirror` also writes their mirror image, row j. `diagonal`: the
 // tile meets the diagonal, and only what lies on or above it counts.
 template <bool FLIP>
 __device__ __forceinline__ void store_quad(const GramArgs &g, float *C, int64_t i, int64_t j, float (&v)[4], bool mirror,
-                                           bool diagonal, bool vec_mirror)
+                                           bool diagonal, bool vec_mirror, uint32_t sign)
 {
     if (j >= g.Ny) return;
     if constexpr (FLIP) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(__float_as_uint(v[e]) ^ flip_of_row(i + e));
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(__float_as_uint(v[e]) ^ sign);
     }
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -370,7 +370,8 @@ __global__ __launch_bounds__(64 * NW, T == 1 ? 4 : 2) void gram_small(GramArgs g
         float v[4] = {sum[0], sum[1], sum[2], sum[3]};
         const int64_t ib = i0 + (b / NR) * 16, jb = j0 + (b % NR) * 16;
         const float any = v[0] + v[1] + v[2] + v[3];
-        store_quad<FLIP>(g, C, ib + 4 * quarter, jb + col, v, SYM, SYM && bi == bj, vec_mirror);
+        store_quad<FLIP>(g, C, ib + 4 * quarter, jb + col, v, SYM, SYM && bi == bj, vec_mirror,
+                         __builtin_amdgcn_readfirstlane(flip_of_row(ib)));
         if (__ballot(any != any)) settle_nan<16, 16, SYM>(g, A, B, C, ib, jb, SYM && bi == bj);
     }
 }
@@ -672,7 +673,7 @@ __device__ __forceinline__ void three_term_tile(const GramArgs &g, LdsFloat *buf
             for (int q = 0; q < 4; ++q) {
                 float v[4] = {acc[a][b][4 * q], acc[a][b][4 * q + 1], acc[a][b][4 * q + 2], acc[a][b][4 * q + 3]};
                 store_quad<FLIP>(g, tile.C, i0 + (wi * 4 + a) * 32 + 8 * q + 4 * half, j0 + (wj * 2 + b) * 32 + col, v, SYM,
-                                 diagonal, vec_mirror);
+                                 diagonal, vec_mirror, sign[a]);
             }
     if (any_nan(acc)) {
 #pragma unroll 1

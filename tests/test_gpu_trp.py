@@ -51,10 +51,11 @@ def test_trp_matches_oracle(oracle, N, L, d, M, F, Q):
     assert np.all(err <= FP32_BLOCK_TOL)
 
 
-@pytest.mark.parametrize("F", [50, 7])
+@pytest.mark.parametrize("F", [50, 7, 200, 65])
 def test_products_of_all_levels_in_large_tiles(oracle, F):
     """So many rows that the levels' products take the 256 x 128 tiles, one level per grid row: rows on 16 bytes (2F = 100)
-    and not (2F = 14), neither whole steps of 16 columns nor whole tiles of rows or of projections."""
+    and not (2F = 14), neither whole steps of 16 columns nor whole tiles of rows or of projections; from 128 columns on two
+    terms instead of three (2F = 400, 130)."""
     N, L, M, Q = 2500, 8, 5, 200
     X, W, Z, ls = _case(F, N, L, 3, M, F, Q, math.sqrt(3))
     got = _run(X, W, Z, ls).cpu().numpy()
@@ -63,6 +64,23 @@ def test_products_of_all_levels_in_large_tiles(oracle, F):
     print(f"F={F}: block errors {err}")
     assert np.all(err <= FP32_BLOCK_TOL)
     assert np.all(got[:, 0] == 1.0) and np.all(np.isfinite(got))
+
+
+@pytest.mark.parametrize("F", [200, 65])
+def test_products_that_fall_back_to_three_terms(oracle, F):
+    """Rows of Z that do not fit the scales of two terms, in some levels and tiles of the launch: from the outset (too small) and
+    when the products are known (numbers far larger than those that are looked at)."""
+    N, L, M, Q = 2500, 8, 5, 200
+    X, W, Z, ls = _case(F, N, L, 3, M, F, Q, math.sqrt(3))
+    Z[1, 150] *= np.float32(2.0 ** -95)
+    Z[3, 5, 60::97] *= np.float32(2.0 ** 30)
+    got = _run(X, W, Z, ls).cpu().numpy().astype(np.float64)
+    sel = np.r_[0:40, 1020:1060, N - 40:N]
+    got, want = got[sel], np.asarray(oracle.trp_features(X[sel], W, Z, ls), np.float64)
+    for m in range(M):
+        for part in ([150], [5], np.setdiff1d(np.arange(Q), [150, 5])):
+            a, b = got[:, 1 + m * Q + np.array(part)], want[:, 1 + m * Q + np.array(part)]
+            assert np.linalg.norm(a - b) <= FP32_BLOCK_TOL * np.linalg.norm(b), (m, part)
 
 
 def test_trp_chunks_padding_and_errors(oracle):
@@ -94,6 +112,7 @@ def test_trp_more_sequences_than_one_launch_may_take(oracle):
 @pytest.mark.parametrize("L,M,F,Q", [
     (4001, 1, 16, 33), (10001, 1, 32, 33), (20001, 1, 64, 40),       # the three small-tile product kernels
     (20001, 5, 16, 200), (20001, 5, 7, 200),                         # large tiles, rows on 16 bytes and not
+    (20001, 5, 64, 200), (20001, 5, 65, 200),                        # two terms
 ])
 def test_errors_of_the_products_do_not_add_up_over_time(L, M, F, Q):
     """Level 1 is the sum of all projected increments, Z (phi(x_T) - phi(x_0)): on noise no larger than one of its T
