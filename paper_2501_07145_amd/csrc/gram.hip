@@ -985,10 +985,12 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
     // 0.57 (105 + columns) / 10000 us each and 12 more, large ones 20 us and 0.76 (200 + columns) / 17.5 us a round, fitted
     // to both kinds at 201, 401, 1025 and 5121 columns (rows with themselves, 64 x 64 against large: 3500 rows 42, 56, 113,
     // 496 us against 42, 52, 80, 269; 2500 rows 26, 35, 67, 279 against 41, 50, 75, 235; 4000 rows, two rounds, 48, 68, 137,
-    // 606 against 56, 70, 118, 464).
+    // 606 against 56, 70, 118, 464). Two terms are for calls that three would run in large tiles as well: the small ones add up in four
+    // or eight sums, and their error is half that of a large tile's single one (5121 columns 5.0e-7 and 9.4e-7), which
+    // 2500, 3000 and 4000 rows, faster as they would be, are not to lose.
     const int64_t tiles = big_tiles(Nx, Ny, sym), rounds = (tiles * batch + 255) / 256;
     const bool two = ncols >= kTwoTermColumns;
-    const bool large = two ? count(64) * (105 + ncols) > 140000 + rounds * (150000 + 760 * ncols) : count(64) > 1340 * rounds;
+    const bool large = count(64) > 1340 * rounds && (!two || count(64) * (105 + ncols) > 140000 + rounds * (150000 + 760 * ncols));
     if (large && ldx <= kBigMaxStride && ldy <= kBigMaxStride) {
         if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
         const bool aligned = ldx % 4 == 0 && ldy % 4 == 0 && step_x % 4 == 0 && step_y % 4 == 0 &&

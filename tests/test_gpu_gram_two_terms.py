@@ -143,6 +143,17 @@ def test_error_is_no_larger_than_three_terms():
         assert float(err.norm() / want.norm()) <= limit, (C, float(err.norm() / want.norm()))
 
 
+@pytest.mark.parametrize("n", [2500, 3000, 4000])
+def test_sums_are_not_joined_for_speed(n):
+    """Sizes at which small tiles, which add up in several sums, and one sum of two terms take turns: the error of small tiles
+    (5.0e-7 here, measured, and 9.4e-7 in large ones; the limit lies between)."""
+    A = _operand(np.random.default_rng(n), n, 5121, False, "normal") / 5121 ** 0.5
+    A[:, 0] = 1.0
+    want = A.double() @ A.double().T.contiguous()
+    err = rfsf.rfsf_ts_gram(A).double() - want
+    assert float(err.norm() / want.norm()) <= 7e-7, float(err.norm() / want.norm())
+
+
 def test_nan_and_infinite_rows():
     rng = np.random.default_rng(5)
     A, B = _operand(rng, 2600, 500, False, "normal"), _operand(rng, 2700, 500, False, "normal")
