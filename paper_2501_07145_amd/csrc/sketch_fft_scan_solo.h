@@ -37,8 +37,8 @@ __host__ __device__ constexpr size_t solo_lds_bytes(int M, int FPW, int PD, int 
 }
 
 // Where the accumulators of a lane fit the registers (solo_waves_per_simd) and the levels fill the wavefront's
-// transforms: largest number of levels for which that holds, and for which four wavefronts per SIMD do without spills. What
-// is left out: four levels at D = 200 (four of six transforms used, 1000 x 100 points 185 -> 203 us), five at D = 128 (25
+// transforms: largest number of levels for which that holds. Six levels at D = 100 spill 4 to 6 registers, five at D = 200 3 or 4 (11 to
+// 14 and 10 with twiddles read ahead, see solo_reads_ahead), the others none. What is left out: four levels at D = 200 (four of six transforms used, 1000 x 100 points 185 -> 203 us), five at D = 128 (25
 // spills, split batches 142 -> 147), orders 2 and 3, whose carried values do not fit.
 __host__ __device__ constexpr bool solo_fits(int M, int D, int order)
 {
@@ -48,6 +48,10 @@ __host__ __device__ constexpr bool solo_fits(int M, int D, int order)
 // Wavefronts per SIMD that the registers are bounded for. (D = 256, four levels, 5000 x 100 points 639 us with three, 888 with
 // four and 48 spills; three levels, 1000 x 100, 149 and 123.)
 __host__ __device__ constexpr int solo_waves_per_simd(int M, int D) { return (D >= 128 && M >= 4) ? 3 : 4; }
+// Ten-point butterflies read their twiddles ahead where a lane's accumulators leave the registers for it (3000 x 200 points, 3 and 8
+// channels and 12 from memory, ahead and on the spot: D = 100, five levels, 30 registers of accumulators, 442, 444, 423 and 447, 446,
+// 430 us; six, 42 registers, 603, 611, 586 and 561, 579, 518; D = 200, five levels, 60 registers, 1002, 1174, 915 and 966, 1073, 923).
+__host__ __device__ constexpr bool solo_reads_ahead(int M, int D) { return (D / 2 + 64) / 64 * M * (M + 1) < 40; }
 constexpr int kSoloChannels = 8;
 __host__ __device__ constexpr int solo_columns(int D) { return D <= 128 ? 1 : 2; }     // frequencies of a lane
 typedef const __attribute__((address_space(1))) float *GlobalFloats;
@@ -226,7 +230,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
             if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
         }
         __builtin_amdgcn_s_setprio(0);
-        fft.run_from_registers(my_slot, v);
+        fft.template run_from_registers<solo_reads_ahead(M, D)>(my_slot, v);
         __builtin_amdgcn_s_setprio(1);
         wave_lds_fence();
         // separation and recurrence, a bin per lane, pair after pair

@@ -354,10 +354,14 @@ __device__ __forceinline__ void dft10(float2 (&x)[10], Twiddle tw)
 }
 
 // Forward DFT of r points, natural order in and out; input t times the t-th power of the twiddle that tw stands for.
-template <int r, typename Twiddle>
+// (AHEAD: the nine twiddles of a ten-point butterfly are read before it starts, which is faster by 1 to 2 per cent where the registers
+// hold them.)
+template <bool AHEAD, int r, typename Twiddle>
 __device__ __forceinline__ void dft(float2 (&x)[r], Twiddle tw)
 {
-    if constexpr (r == 10) {
+    if constexpr (r == 10 && !AHEAD) {
+        dft10(x, tw);
+    } else if constexpr (r == 10) {
         float2 w[9];
 #pragma unroll
         for (int e = 0; e < 9; ++e) w[e] = tw(e);
@@ -518,12 +522,13 @@ struct WaveFft {
         run_pass<0>(slot, v);
     }
     // The same with the input already in registers: v[q] is point lg + G*q of the lane's transform.
+    template <bool AHEAD = true>
     __device__ __forceinline__ void run_from_registers(float2 *slot, float2 (&v)[P::R]) const
     {
-        run_pass<0>(slot, v);
+        run_pass<0, AHEAD>(slot, v);
     }
 
-    template <int PI>
+    template <int PI, bool AHEAD = true>
     __device__ __forceinline__ void run_pass(float2 *slot, float2 (&v)[P::R]) const
     {
         if constexpr (PI < P::NP) {
@@ -538,7 +543,7 @@ struct WaveFft {
                     dft_plain(x);
                 } else {
                     constexpr int TW = twiddles(r), set = P::tw_sets(PI) == 1 ? 0 : 1;    // multiplier of u below
-                    dft(x, [&](int e) {
+                    dft<AHEAD>(x, [&](int e) {
                         if constexpr (P::tw_in_lds(PI)) return twl[P::twl_off(PI) + (set * u * TW + e) * P::G];
                         else return tw[P::tw_off(PI) + set * u * TW + e];
                     });
@@ -554,7 +559,7 @@ struct WaveFft {
                     const int q = read_order<P::R, P::radix(PI + 1)>(i);
                     v[q] = slot[rbase + P::roff(q)];
                 }
-                run_pass<PI + 1>(slot, v);
+                run_pass<PI + 1, AHEAD>(slot, v);
             }
         }
     }

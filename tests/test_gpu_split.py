@@ -112,9 +112,10 @@ def test_joined_sums_of_noise(oracle, N, L, d, M, F, D):
 @pytest.mark.parametrize("D", [100, 128])
 def test_eight_levels_cost_no_more_each_than_six(D):
     """Whole sequences in short transforms: the kernel that keeps every range of levels is not taken where its registers
-    halve the wavefronts on a CU (sketch kernel, eight levels against six: 1.55 times with it at D = 128, 1.11 without;
-    1.57 and 1.32 at D = 100; the bound lies between)."""
-    def us(M):
+    halve the wavefronts on a CU (sketch kernel, eight levels against six of D = 128: 1.70 times with it at D = 128, 1.16
+    without; 1.62 and 1.35 at D = 100; the bound lies between. Six levels of D = 100 are no measure for it: they run in a
+    kernel that computes their increments, too)."""
+    def us(M, D):
         x, w, h, s = (torch.from_numpy(a).cuda() for a in _case(M, 3000, 200, 3, M, D // 2, D))
         times = []
         for _ in range(7):
@@ -126,4 +127,4 @@ def test_eight_levels_cost_no_more_each_than_six(D):
             rfsf.rfsf_ts_profile_enable(False)
         return min(times)
 
-    assert us(8) < 1.45 * us(6)
+    assert us(8, D) < 1.45 * us(6, 128)
