@@ -137,6 +137,12 @@ struct SketchCut { int pieces; int64_t pairs; bool joint, in_place, solo; };
 // (a single sequence of 100 points 27.8 us, 30.7 here; ten of 1000 49 and 56), and so are sequences that fill less than half
 // of an iteration (3000 x 14 points, 64 buckets, three levels 51 and 54) or, from 128 points per transform on, less than four
 // (1000 x 30 points, 256 buckets, four levels 64 and 70).
+// With three and four levels the other kernels' workgroups fill a CU, and less is gained. Pieces of less than one and a
+// half iterations are left to them where there is nothing else to gain either: where the increments come from memory (whole
+// sequences; 1186 x 31 points, 20 channels, 56 frequencies, 64 buckets, three levels 54 and 66 us, 5816 x 66, 3, 73, 100 365 and 420;
+// of 38 such calls 29 were slower by more than 5 %, one faster), or where they are so few that projecting them costs less than
+// doing it on idle lanes, fewer than four frequencies per channel (774 x 43, 8, 13, 100, three levels 33 and 43; 23 and 5 of 37).
+bool solo_fused(const rfsf_ts_shape *s, int P) { return s->rff_bf16 == 0 && rfsf::sketch_fft_scan_solo_fused(s->F, s->d, P); }
 SketchCut solo_cut(const rfsf_ts_shape *s, int P, int step)
 {
     const SketchCut none = {0, 0, false, false, false};
@@ -159,7 +165,19 @@ SketchCut solo_cut(const rfsf_ts_shape *s, int P, int step)
             best = {(int)pieces, pieces < 2 ? slots : pairs, true, true, true};
         }
     }
+    if ((s->M == 3 || s->M == 4) && 2 * all_pairs < 3 * step * best.pieces &&
+        (solo_fused(s, P) ? s->F < 4 * s->d : best.pieces == 1))
+        return none;
     return s->N * best.pieces > kCUs ? best : none;
+}
+// The same for sequences that time_cut_plan cuts, hundreds of iterations each: the other kernels are the faster ones with 100 buckets
+// and increments from memory up to four levels (6 x 30072 points, 77 frequencies, three levels 280 and 341 us; of 48 such calls 17
+// slower by more than 5 %, 6 faster), and with 128, four levels and few frequencies per channel (22 x 12271 points, 8 channels, 22
+// frequencies 207 and 259; 6 of 8, none faster).
+bool solo_pieces(const rfsf_ts_shape *s, int P)
+{
+    if (!solo_fused(s, P)) return P != 100 || s->M > 4;
+    return P != 128 || s->M < 4 || s->F >= 6 * s->d;
 }
 SketchCut sketch_cut(const rfsf_ts_shape *s)
 {
@@ -167,7 +185,7 @@ SketchCut sketch_cut(const rfsf_ts_shape *s)
     const int P = transform_length(s->M, s->F, s->D);
     const bool joint = rfsf::sketch_fft_scan_joint(s->M, s->F, P);
     const int step = joint && s->L > 1 ? rfsf::sketch_fft_scan_solo_pairs(s->M, s->F, P, kernel_order(s), s->d, s->rff_bf16 != 0) : 0;
-    if (plan.pieces > 1) return {plan.pieces, plan.pairs, joint, false, step > 0 && s->N * plan.pieces > kCUs};
+    if (plan.pieces > 1) return {plan.pieces, plan.pairs, joint, false, step > 0 && s->N * plan.pieces > kCUs && solo_pieces(s, P)};
     if (step > 0 && s->N > 0) {
         const SketchCut cut = solo_cut(s, P, step);
         if (cut.pieces > 0) return cut;
@@ -343,7 +361,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
         tables.zero_off = rfsf::sketch_fft_scan_solo_zero(shape->F, P);
     }
     // ... whose increments it computes itself where it can
-    const bool fused = plan.solo && shape->rff_bf16 == 0 && rfsf::sketch_fft_scan_solo_fused(shape->F, shape->d, P);
+    const bool fused = plan.solo && solo_fused(shape, P);
     // the tuned consumer takes the increments in the pair layout with the signs applied, the generic one in
     // the row layout without
     const float *producer_sign = rfsf::sketch_fft_scan_is_tuned(shape->M, shape->F, P) ? sign : nullptr;

@@ -53,6 +53,19 @@ def test_rows_match_the_oracle(oracle, N, L, d, M, F, D):
             assert np.all(err <= FP32_BLOCK_TOL), (n, err)
 
 
+@pytest.mark.parametrize("N,L,d,M,F,D,solo", [
+    (600, 20, 8, 3, 20, 100, False), (600, 20, 4, 3, 20, 100, True),        # few frequencies per channel
+    (600, 20, 12, 3, 60, 100, False), (600, 20, 12, 5, 60, 100, True),      # increments from memory
+    (600, 18, 8, 4, 20, 64, False), (600, 18, 12, 4, 20, 64, False), (600, 18, 3, 4, 20, 64, True),
+])
+def test_short_sequences_that_gain_nothing(N, L, d, M, F, D, solo):
+    """The kernel with a wavefront per level runs a single sequence of so few points whole, and sums it in another order."""
+    X, W, hash_, sign = _case(N + F, N, L, d, M, F, D)
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)]
+    one = rfsf.rfsf_ts_features(dev[0][5:6].contiguous(), *dev[1:], 1.5, D)
+    assert torch.equal(rfsf.rfsf_ts_features(*dev, 1.5, D)[5:6], one) != solo
+
+
 def test_chunks_and_bf16_projection_take_the_same_sums(oracle):
     """The cut is a function of the shape: a workspace for a part of the batch gives the same bits."""
     X, W, hash_, sign = _case(1, 600, 60, 5, 5, 50, 100)
