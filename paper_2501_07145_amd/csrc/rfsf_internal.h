@@ -21,7 +21,7 @@ namespace rfsf {
 struct Points {
     const float *X = nullptr, *W = nullptr, *sign = nullptr;      // [n_seq, L, d], [M, d, F], [M, 2F]
     int d = 0;
-    float quarters = 0.f;                                         // quarter-turns of angle per unit of X . W
+    float quarters = 0.f, quarters_rest = 0.f;                    // quarter-turns of angle per unit of X . W, in two terms
 };
 struct TimeCut {
     int pieces, row_levels;

@@ -392,7 +392,10 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
             const int order = kernel_order(shape), bins = P / 2 + 1;
             rfsf::TimeCut cut = {plan.pieces, shape->M, plan.pairs, nullptr, 1, plan.pieces, 0, 0, plan.solo};
-            if (fused) cut.points = {X + n0 * shape->L * shape->d, W, sign, shape->d, (float)(0.63661977236758134308 / (double)lengthscale)};
+            if (fused) {
+                const double quarters = 0.63661977236758134308 / (double)lengthscale;
+                cut.points = {X + n0 * shape->L * shape->d, W, sign, shape->d, (float)quarters, (float)(quarters - (double)(float)quarters)};
+            }
             if (plan.in_place) {
                 cut.piece_stride = plan.pairs * (int64_t)shape->M * 2 * shape->F;          // float2 per pair: M * 2F
                 cut.seq_stride = (shape->L + 1) / 2 * (int64_t)shape->M * 2 * shape->F;

@@ -124,7 +124,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
         src += frequency;
         flips += frequency;
 #pragma unroll
-        for (int c = 0; c < d; ++c) w[c] = src[c * F] * cut.points.quarters;
+        for (int c = 0; c < d; ++c) w[c] = src[c * F];
         scale_c = flips[0] < 0.f ? -scale : scale;
         scale_s = flips[F] < 0.f ? -scale : scale;
     };
@@ -132,7 +132,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
         float t = x[0] * w[0];
 #pragma unroll
         for (int i = 1; i < d; ++i) t = fmaf(x[i], w[i], t);
-        sincos_quarters(t, s, c);
+        sincos_quarters(t, cut.points.quarters, cut.points.quarters_rest, s, c);
     };
     constexpr int COLS = solo_columns(D);
     [[maybe_unused]] float before_s[M * COLS], before_c[M * COLS];       // of the point before the pair, per level

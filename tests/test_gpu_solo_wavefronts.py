@@ -66,6 +66,23 @@ def test_short_sequences_that_gain_nothing(N, L, d, M, F, D, solo):
     assert torch.equal(rfsf.rfsf_ts_features(*dev, 1.5, D)[5:6], one) != solo
 
 
+@pytest.mark.parametrize("N,L,M,F,D", [(600, 40, 3, 32, 64), (600, 40, 5, 50, 100), (600, 66, 3, 64, 256)])
+def test_large_angles_are_as_accurate_as_the_products(oracle, N, L, M, F, D):
+    """Products of points and frequencies that are exact in 32 bits, angles of some hundred: what is left are the errors of sine and
+    cosine (6e-8) and of transforms and sums, 1e-7 to 3e-7 per level as for small angles. An angle rounded to 32 bits is off by
+    up to 2^-24 of itself, 1e-5 and more."""
+    rng = np.random.default_rng(D)
+    X = (rng.integers(-2000, 2000, size=(N, L, 1)) / 8.0).astype(np.float32)
+    W = (2.0 ** rng.integers(-2, 3, size=(M, 1, F)) * rng.choice((-1.0, 1.0), size=(M, 1, F))).astype(np.float32)
+    _, _, hash_, sign = _case(D, 1, 2, 1, M, F, D)
+    got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 1.5, D).cpu().numpy()
+    sel = [0, 5, N - 1]
+    want = np.asarray(oracle.features(X[sel], W, hash_, sign, 1.5, D), np.float64)
+    for m in range(1, M):                                    # (level 1 is a difference of two features, small against its sums)
+        a, b = got[sel, 1 + m * D:1 + (m + 1) * D], want[:, 1 + m * D:1 + (m + 1) * D]
+        assert np.linalg.norm(a - b) <= 3e-6 * np.linalg.norm(b), (m, np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
 def test_chunks_and_bf16_projection_take_the_same_sums(oracle):
     """The cut is a function of the shape: a workspace for a part of the batch gives the same bits."""
     X, W, hash_, sign = _case(1, 600, 60, 5, 5, 50, 100)
