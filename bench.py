@@ -18,6 +18,7 @@ from __future__ import annotations
 
 import argparse
 import json
+import math
 import os
 import sys
 import time
@@ -338,15 +339,16 @@ def bench_ts(args, name: str, steps: int, warmup: int, cpu_baseline: bool) -> di
     entry("rff_increments", "hbm", n_seq * 4.0 * w.L * w.d + incr_units * incr_bytes, "GB/s", HBM_PEAK_GBS,
           mfma_tflops=units * proj_flops / 1e12, sincos_pairs_per_s=float(units * w.M * w.F),
           write_gbs=incr_units * incr_bytes / 1e9)
-    # faster than memory: the sketch kernel has computed the increments itself, and what was timed is the build of its tables
-    fused = kernels.get("rff_increments", {}).get("frac", 0.0) > 1.0
-    if fused:
-        del kernels["rff_increments"]
+    fused = prof["launches_rff_increments"] == 0      # the sketch kernel has computed the increments itself
     if "rff_increments" in kernels:
         kernels["rff_increments"]["mfma_peak"] = mfma_peak
         kernels["rff_increments"]["mfma_frac"] = kernels["rff_increments"]["mfma_tflops"] / mfma_peak
-    entry("sketch_fft_scan", "hbm", (4.0 * n_seq * w.L * w.d if fused else incr_units * incr_bytes) + 4.0 * n_seq * w.M * w.D,
-          "GB/s", HBM_PEAK_GBS)
+    if fused:
+        # vector instructions: angles, sine and cosine (20 each pair), sketch, transforms of D real points, recurrence per bin
+        flops = 2.0 * w.d * w.F + 22.0 * w.F + 2.5 * w.D * math.log2(w.D) + 8.0 * (w.D // 2 + 1)
+        entry("sketch_fft_scan", "alu", units * w.M * flops, "TFLOP/s", VALU_FP32_PEAK_TFLOPS)
+    else:
+        entry("sketch_fft_scan", "hbm", incr_units * incr_bytes + 4.0 * n_seq * w.M * w.D, "GB/s", HBM_PEAK_GBS)
     Ny = w.N2 if w.N2 else w.N
     # flops the kernel performs: the whole matrix for a cross Gram, for K = Phi Phi^T only the tiles on or above the
     # diagonal (counted here as N(N+1)/2 inner products); GRAM_TERMS 16-bit products each (csrc/gram.hip)
@@ -357,7 +359,7 @@ def bench_ts(args, name: str, steps: int, warmup: int, cpu_baseline: bool) -> di
     # the kernel that reads the increments, non-temporal streaming writes for the one that writes them)
     peaks = getattr(args, "measured_peaks", None)
     if peaks:
-        for kname, key in (("rff_increments", "write_nt_gbs"), ("sketch_fft_scan", "read_gbs"),
+        for kname, key in (("rff_increments", "write_nt_gbs"), ("sketch_fft_scan", "valu_f32_tflops" if fused else "read_gbs"),
                            ("normalize", "copy_gbs")):
             if kname in kernels:
                 kernels[kname]["measured_peak"] = peaks[key]

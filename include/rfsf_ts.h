@@ -262,8 +262,8 @@ int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, const float *W
  * enabling costs a few microseconds per launch. Process-wide state, not thread-safe.
  */
 typedef struct {
-    double  ms_rff_increments;   int64_t launches_rff_increments;    /* steps 1-2 kernel */
-    double  ms_sketch_fft_scan;  int64_t launches_sketch_fft_scan;   /* steps 3-4 kernel */
+    double  ms_rff_increments;   int64_t launches_rff_increments;    /* steps 1-2 kernel: none where the next one does them */
+    double  ms_sketch_fft_scan;  int64_t launches_sketch_fft_scan;   /* steps 3-4 kernels, or steps 1-4 and their tables */
     double  ms_gram;             int64_t launches_gram;              /* Gram kernel(s)   */
     double  ms_normalize;        int64_t launches_normalize;         /* normalisation    */
     double  ms_dp1d;             int64_t launches_dp1d;              /* RFSF-DP-1D kernel */

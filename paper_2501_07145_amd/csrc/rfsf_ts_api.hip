@@ -368,8 +368,10 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
     for (int64_t n0 = 0; n0 < shape->N; n0 += chunk) {
         const int64_t cnt = shape->N - n0 < chunk ? shape->N - n0 : chunk;
         if (fused) {
-            rfsf::ProfileScope scope(rfsf::kRffIncrements, stream, may_create);
-            if (n0 == 0 && rfsf::launch_build_tables(tables, shape->M, stream) != hipSuccess) return RFSF_E_HIP;
+            if (n0 == 0) {                                // (no increments are launched: the tables belong to the sketch kernel)
+                rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
+                if (rfsf::launch_build_tables(tables, shape->M, stream) != hipSuccess) return RFSF_E_HIP;
+            }
         } else {
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream, may_create);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, producer_sign, inv_ls, cnt, shape->L, shape->d,

@@ -106,3 +106,19 @@ def test_nan_stays_in_its_sequence():
     bad = torch.zeros(300, dtype=torch.bool, device="cuda")
     bad[[7, 9]] = True
     assert bool(torch.isnan(got[bad][:, 1:]).all()) and torch.equal(got[~bad], want[~bad])
+
+
+@pytest.mark.parametrize("d,projections", [(5, 0), (12, 3)])
+def test_profile_counts_what_is_launched(d, projections):
+    """Three launches of a batch: no projection where the sketch kernel does it, and one launch more for its tables."""
+    X, W, hash_, sign = _case(3, 600, 60, d, 5, 50, 100)
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)]
+    rec, least = rfsf.rfsf_ts_workspace_bytes(600, 60, d, 5, 50, 100)
+    ws = torch.empty(least + 250 * ((rec - least) // 599), dtype=torch.uint8, device="cuda")
+    rfsf.rfsf_ts_profile_enable(True)
+    rfsf.rfsf_ts_profile_read(True)
+    rfsf.rfsf_ts_features(*dev, 1.5, 100, workspace=ws)
+    prof = rfsf.rfsf_ts_profile_read(True)
+    rfsf.rfsf_ts_profile_enable(False)
+    assert prof["launches_rff_increments"] == projections
+    assert prof["launches_sketch_fft_scan"] == (3 if projections else 4)
