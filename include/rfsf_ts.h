@@ -195,11 +195,12 @@ int rfsf_ts_validate_tables(const int32_t *hash, const float *sign,
  *   ncols = 1 + M*D for features made by rfsf_ts_features (the level-0 column is included)
  * Leading dimensions that are multiples of 4 floats with 16-byte aligned bases take the
  * vectorised path; anything else is still correct. Nx = 0 or Ny = 0 is a no-op.
- * Operands of any finite size enter with 23 significand bits or more; an entry is within
- * (3 ncols + 13) 2^-24 sum_c |PhiX[i, c] PhiY[j, c]| of the exact sum (and 2^-149), within
- * (1.04 ncols + 13) 2^-24 of it unless a row holds numbers more than twice as large as some 48 that are
- * looked at; errors of sums add up like independent ones, to far less. Which arithmetic an entry takes, and so its last
- * bits, depends on the size of the call and on the rows around it; equal calls give equal bits.
+ * An entry is within (3 ncols + 13) 2^-24 sum_c |PhiX[i, c] PhiY[j, c]| of the exact sum (and 2^-149; operands below 2^-110 may
+ * lose last bits), within (1.04 ncols + 13) 2^-24 of it unless a row holds numbers more than twice as large as some 48
+ * that are looked at; errors of sums add up like independent ones, to far less. Operands enter with 22 significand bits
+ * or more, or, where large products of the same entry keep it within these bounds, with an error of 2^-34 of their row's largest.
+ * Which arithmetic an entry takes, and so its last bits, depends on the size of the call and on the rows around it; equal calls
+ * give equal bits.
  */
 int rfsf_ts_gram(const float *PhiX, int64_t Nx, int64_t ldx,
                  const float *PhiY, int64_t Ny, int64_t ldy,

@@ -124,6 +124,19 @@ def test_large_numbers_against_zeros(C, packed, kind, swap):
     _check_products(K, A, B)
 
 
+@pytest.mark.parametrize("swap", [False, True])
+@pytest.mark.parametrize("up", [-112, -60])
+def test_rows_that_are_zero_where_they_are_sampled(up, swap):
+    """Small numbers in such rows enter with all their bits, as they do in others."""
+    rng = np.random.default_rng(-up)
+    A, B = _operand(rng, 2600, 300, True, "normal"), _operand(rng, 2700, 300, False, "normal")
+    A[5::7] = 0.0
+    A[5::35, 52:60] = torch.from_numpy(rng.uniform(1.0, 2.0, (75, 8)).astype(np.float32) * np.float32(2.0 ** up)).cuda()
+    K = rfsf.rfsf_ts_gram(B, A).T if swap else rfsf.rfsf_ts_gram(A, B)
+    _check_products(K, A, B)
+    assert bool((K[12::35] == 0.0).all())
+
+
 def test_unit_vectors_give_the_numbers_themselves():
     A = _operand(np.random.default_rng(3), 2600, 300, False, "wide")
     K = rfsf.rfsf_ts_gram(A, torch.eye(300, device="cuda").repeat(9, 1))
