@@ -23,14 +23,13 @@ __device__ __forceinline__ void store_increments(float *p, float c0, float c1, f
 namespace rfsf {
 namespace {
 
-// The same, times `scale`, with the scale folded into the polynomial coefficients (no extra
-// multiplies): sc = {scale, -scale/2, scale*c1, scale*c2, scale*c3} for the cosine, and the sine
+// sincos_reduced, times `scale`, with the scale folded into the polynomial coefficients (no extra
+// multiplies): sc = {scale, -scale/2, scale * kCosQ} for the cosine, and the sine
 // polynomial is evaluated on r*scale.
 struct ScaledCoeffs { float one, half, c1, c2, c3; };
 __device__ __forceinline__ ScaledCoeffs scaled_coeffs(float scale)
 {
-    return {scale, -0.5f * scale, 4.166664568298827e-2f * scale, -1.388731625493765e-3f * scale,
-            2.443315711809948e-5f * scale};
+    return {scale, -0.5f * scale, kCosQ[0] * scale, kCosQ[1] * scale, kCosQ[2] * scale};
 }
 __device__ __forceinline__ void sincos_scaled(float x, const ScaledCoeffs &k, float &s, float &c)
 {
@@ -39,7 +38,7 @@ __device__ __forceinline__ void sincos_scaled(float x, const ScaledCoeffs &k, fl
     r = fmaf(-kf, -4.37113900018624283e-8f, r);
     const float r2 = r * r;
     const float rs = r * k.one;
-    const float ps = fmaf(r2, fmaf(r2, -1.9515295891e-4f, 8.3321608736e-3f), -1.6666654611e-1f);
+    const float ps = fmaf(r2, fmaf(r2, kSinP[2], kSinP[1]), kSinP[0]);
     const float S = fmaf(rs * r2, ps, rs);
     const float pc = fmaf(r2, fmaf(r2, k.c3, k.c2), k.c1);
     const float C = fmaf(r2 * r2, pc, fmaf(k.half, r2, k.one));
