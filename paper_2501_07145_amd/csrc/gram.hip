@@ -29,6 +29,9 @@
 // error of 2^-25 (scaled); numbers more than 64 times as large overflow, which shows as NaN, and the tile is computed
 // again with three terms, as are, from the outset, tiles with rows beyond 2^-91 .. 2^109 or with rows that are zero wherever they are
 // sampled but not everywhere (a third of 7494 rows zero, 1001 columns: 267 -> 321 us for looking through them).
+// Such tiles cost what both ways cost: 10000 rows with themselves, 5121 columns 2.12 ms, with three terms from the outset in every
+// tile 3.63, with one number 2^20 times the others in one row 3.40, in a row of every tile 5.83 (a kernel of three terms alone 2.97;
+// 1025 columns 0.47, 0.86, 0.72 and 1.17).
 // The error of small numbers is no error of their products if those of the large ones are part of the same sum, and without limit if
 // the large ones meet zeros. So the sum of |a b| over the sampled columns is computed for every pair of rows, and a tile in which one
 // of them is below 2^15 takes three terms. What small numbers add to the error is K 2^-25 (2^10 + 2^10) at most, K / 32 units of
@@ -401,13 +404,16 @@ constexpr int64_t kBigMaxStride = (int64_t)1 << 21;           // offsets inside 
 
 struct TileCoord { int64_t bi, bj; };
 constexpr int kStrip = 4;        // tile rows per strip: 4 x 8 tiles, 1024 x 1024 entries, share their panels in an L2
+// A column of a strip begins one row further down than the one before it: the workgroups of an XCD go to its four shader
+// engines in turn, and one of these would get all tiles of a row, which one row of the matrix can make slow ones (10000 rows with
+// themselves, 5121 columns, one number that does not fit two terms 4.76 -> 3.40 ms, 1025 columns 1.00 -> 0.72; others unchanged).
 template <bool SYM>
 __device__ __forceinline__ TileCoord big_tile(int64_t rank, int64_t nti, int64_t ntj)
 {
     if (!SYM) {
         const int64_t full = kStrip * ntj, I = rank / full, r = rank - I * full;
         const int64_t h = min(nti - kStrip * I, (int64_t)kStrip);
-        return {kStrip * I + r % h, r / h};
+        return {kStrip * I + (r + r / h) % h, r / h};
     }
     // a strip starts at column tile 2 kStrip I; column c of its first 2 h ones holds rows 0 .. c / 2
     for (int64_t I = 0;; ++I) {
@@ -421,7 +427,7 @@ __device__ __forceinline__ TileCoord big_tile(int64_t rank, int64_t nti, int64_t
             if (rank <= c / 2) return {kStrip * I + rank, 2 * kStrip * I + c};
             rank -= c / 2 + 1;
         }
-        return {kStrip * I + rank % h, 2 * kStrip * I + 2 * h + rank / h};
+        return {kStrip * I + (rank + rank / h) % h, 2 * kStrip * I + 2 * h + rank / h};
     }
 }
 int64_t big_tiles(int64_t Nx, int64_t Ny, bool sym)
