@@ -95,9 +95,10 @@ int rfsf_ts_workspace_bytes(const rfsf_ts_shape *shape,
  * a product per bin in the transform domain, where the pieces' accumulators are kept) before the final
  * transforms. The result is the same feature map up to fp32 rounding. *pieces = 1 means that this rule makes no
  * cut: more than 64 sequences, sequences too short to give every piece 32 pairs and the batch at least M+1 pieces each,
- * M = 1 or M > 8, or a shape outside the tuned kernels. Such sequences may still be split, in the same way, among
- * the workgroups that a batch of up to 256 sequences would leave idle; that split is not reported, needs no
- * workspace of its own and is a function of the shape as well. A function of the shape alone (host code, no GPU
+ * M = 1 or M > 8, or a shape outside the tuned kernels. Such sequences may still be split, in the same way: among
+ * the workgroups that a batch of up to 256 sequences would leave idle, and in batches of any size with transforms of up to
+ * 256 points, whose workgroups cut their sequences in four as well. These splits are not reported, need no
+ * workspace of their own and are a function of the shape as well. A function of the shape alone (host code, no GPU
  * work); either output pointer may be NULL. Returns the shape check's code.
  */
 int rfsf_ts_time_cut(const rfsf_ts_shape *shape, int32_t *pieces, int64_t *pairs_per_piece);
