@@ -87,6 +87,7 @@ bool sketch_fft_scan_joint(int M, int F, int D);
 int sketch_fft_scan_joint_per_cu(int M, int D);            // its workgroups that a CU holds, by registers
 int sketch_fft_scan_joint_fit(int M, int F, int D, int order);      // ... and by LDS
 bool sketch_fft_scan_joint_splits(int M, int D, int order);        // splitting whole sequences can gain
+constexpr int kSoloWaves = 4;      // wavefronts of a workgroup of the kernel whose wavefronts work by themselves
 // Pieces of this shape run in the kernel whose wavefronts work by themselves; its tables hold no lists. The pairs of steps that
 // a workgroup of it transforms at a time, or 0; its workgroups that a CU holds.
 int sketch_fft_scan_solo_pairs(int M, int F, int D, int order, int d, bool bf16);

@@ -275,7 +275,7 @@ int sketch_fft_scan_solo_per_cu(int M, int F, int D)
 {
     TunedGeometry g;
     if (!tuned_geometry(D, &g)) return 0;
-    const int by_lds = (int)(kLdsPerCu / tuned::solo_lds_bytes(M, g.FPW, solo_slot(D, g.PD), g.NTWL, F));
+    const int by_lds = (int)(kLdsPerCu / tuned::solo_lds_bytes(D, M, g.FPW, solo_slot(D, g.PD), g.NTWL, F));
     const int by_registers = tuned::solo_waves_per_simd(M, D);
     return by_lds < by_registers ? by_lds : by_registers;
 }
@@ -290,7 +290,7 @@ int sketch_fft_scan_solo_pairs(int M, int F, int D, int order, int d, bool bf16)
     // Few frequencies are computed soon, while the accumulators of all ranges cost the same (1000 x 100 points, D = 256: four
     // levels, 128, 64, 32 frequencies 178, 130, 102 us and 169 to 182, 141, 136; three levels, 20 frequencies 85 and 89).
     if (D == 256 && F < 32 * (M - 1)) return 0;
-    return sketch_fft_scan_solo_per_cu(M, F, D) < 2 ? 0 : tuned::kSoloWaves * tuned::solo_pairs(M, g.FPW);
+    return sketch_fft_scan_solo_per_cu(M, F, D) < 2 ? 0 : kSoloWaves * tuned::solo_pairs(M, g.FPW);
 }
 
 int sketch_fft_scan_wavefronts(int M, int D) { return tuned::transforms_in_flight(M, plan_key(D)); }

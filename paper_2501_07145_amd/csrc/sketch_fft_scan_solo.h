@@ -21,19 +21,36 @@
 #include "sincos.h"
 #include "sketch_fft_scan_tuned.h"
 
+#include <type_traits>
+
 namespace rfsf {
 namespace tuned {
 
-constexpr int kSoloWaves = 4;
-// 100 points: the first pass writes with a stride of 10 float2, and one of padding after every 20 makes that 120 bank rows per
-// transform instead of 160 (not for whole sequences of eight levels, which the slots then leave one workgroup per CU).
+// Bank conflicts. 16 lanes at a time write float2, over 32 banks, at least 6.4 cycles for a wavefront, 32 lanes read, over 64 banks, at
+// least 3.5. The lanes of a transform that write next to each other are few here (4, 5 and 8 for 64, 100 and 128 points), so
+// that several transforms' meet in a bank unless the slots are the right distance apart: solo_stride; and with 100 points the first
+// pass turns its results (MixedPlan). Cycles of a transform's exchanges, gather and separation by that count, before and
+// after: 64 points 598 -> 526, 100 795 -> 695, 128 567 -> 499 (256: 517, at best 502; 200: 911, at best 843 with slots of 234).
 template <int LOG2D> struct SoloPlan : Plan<LOG2D> {};
-template <> struct SoloPlan<100> : MixedPlan<100, 20> {};
+template <> struct SoloPlan<100> : MixedPlan<100, 100, 11> {};
 // Pairs of steps of a wavefront's iteration; 0: the levels do not fit a wavefront.
 __host__ __device__ constexpr int solo_pairs(int M, int FPW) { return FPW / M; }
-__host__ __device__ constexpr size_t solo_lds_bytes(int M, int FPW, int PD, int NTWL, int F)
+__host__ __device__ constexpr size_t solo_lds_with(int M, int FPW, int stride, int NTWL)
 {
-    return sizeof(float2) * ((size_t)kSoloWaves * solo_pairs(M, FPW) * M * slot_stride(PD, 2 * F) + NTWL);
+    return sizeof(float2) * ((size_t)kSoloWaves * solo_pairs(M, FPW) * M * stride + NTWL);
+}
+// From slot to slot: 4 float2 beyond a multiple of 8 with 64 points, 8 beyond one of 16 with 100 and 128, unless a CU would hold
+// fewer workgroups for it.
+__host__ __device__ constexpr int solo_stride(int D, int M, int FPW, int PD, int NTWL, int F)
+{
+    const int least = slot_stride(PD, 2 * F), grain = D == 64 ? 8 : D <= 128 ? 16 : 1;
+    const int apart = (least + grain / 2 - 1) / grain * grain + grain / 2;
+    const size_t held = kLdsPerCu / solo_lds_with(M, FPW, least, NTWL);       // (no more than four by their registers)
+    return grain == 1 || kLdsPerCu / solo_lds_with(M, FPW, apart, NTWL) < (held < 4 ? held : 4) ? least : apart;
+}
+__host__ __device__ constexpr size_t solo_lds_bytes(int D, int M, int FPW, int PD, int NTWL, int F)
+{
+    return solo_lds_with(M, FPW, solo_stride(D, M, FPW, PD, NTWL, F), NTWL);
 }
 
 // Where the accumulators of a lane fit the registers (solo_waves_per_simd) and the levels fill the wavefront's
@@ -46,8 +63,8 @@ __host__ __device__ constexpr bool solo_fits(int M, int D, int order)
     return (D == 64 && M <= 5) || (D == 100 && M <= 6) || (D == 128 && M <= 4) || (D == 200 && (M <= 3 || M == 5)) || (D == 256 && M <= 4);
 }
 // Wavefronts per SIMD that the registers are bounded for. (D = 256, four levels, 5000 x 100 points 639 us with three, 888 with
-// four and 48 spills; three levels, 1000 x 100, 149 and 123.)
-__host__ __device__ constexpr int solo_waves_per_simd(int M, int D) { return (D >= 128 && M >= 4) ? 3 : 4; }
+// four and 48 spills; three levels, 1000 x 100, 149 and 123. D = 128, four levels, takes 123 registers.)
+__host__ __device__ constexpr int solo_waves_per_simd(int M, int D) { return (D >= 200 && M >= 4) ? 3 : 4; }
 // Ten-point butterflies read their twiddles ahead where a lane's accumulators leave the registers for it (3000 x 200 points, 3 and 8
 // channels and 12 from memory, ahead and on the spot: D = 100, five levels, 30 registers of accumulators, 442, 444, 423 and 447, 446,
 // 430 us; six, 42 registers, 603, 611, 586 and 561, 579, 518; D = 200, five levels, 60 registers, 1002, 1174, 915 and 966, 1073, 923).
@@ -58,7 +75,8 @@ typedef const __attribute__((address_space(1))) float *GlobalFloats;
 typedef const __attribute__((address_space(4))) float *ConstantFloats;      // scalar loads where the address is uniform
 
 // d > 0: the increments are not in memory, the wavefront computes them from points of d channels (Points), a frequency per
-// lane: angles by multiply-adds of the points' channels, in scalar registers, with the lane's column of W.
+// lane: angles by multiply-adds of the points' channels with the lane's column of W. The channels are the same for all lanes, but
+// a multiply-add with a scalar register takes 4.35 cycles of a SIMD instead of 2.6: they are in vector registers where there is room.
 template <int LOG2D, int M, int ORDER, int d>
 __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(solo_waves_per_simd(M, SoloPlan<LOG2D>::D), 4))) void sketch_fft_scan_solo_kernel(
     const float *__restrict__ dphi, const uint32_t *__restrict__ table, int64_t L, const int64_t *__restrict__ lengths, int F,
@@ -73,7 +91,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
     // lanes beyond those of the transforms repeat the work of the first ones: same addresses, same values
     constexpr int kLanesUsed = P::G * SLOTS;
     const int lane_t = lane % kLanesUsed, slot_id = lane_t / P::G, lg = lane_t % P::G;
-    const int twoF = 2 * F, ZS = zero_slot(P::PD, twoF), PS = slot_stride(P::PD, twoF);
+    const int twoF = 2 * F, ZS = zero_slot(P::PD, twoF), PS = solo_stride(D, M, P::FPW, P::PD, P::NTWL, F);
     float2 *wave_lds = lds + (size_t)wave * SLOTS * PS, *my_slot = wave_lds + slot_id * PS;
     char *my_slot_bytes = reinterpret_cast<char *>(my_slot);
     const int64_t n = blockIdx.x / (unsigned)cut.pieces, piece = blockIdx.x - n * cut.pieces;
@@ -110,12 +128,16 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
 
     // Features of the points, for d > 0. Points beyond the sequence's last one are that one: their increments are zero.
     constexpr int kChannels = d > 0 ? d : 1;
-    const ConstantFloats points = (ConstantFloats)(cut.points.X + n * L * d);
+    constexpr bool kVectorPoints = 2 * SP * d <= 24;         // registers for an iteration's points
+    typedef std::conditional_t<kVectorPoints, GlobalFloats, ConstantFloats> PointFloats;
+    const PointFloats points = (PointFloats)(cut.points.X + n * L * d);
     const float scale = 0.5f / sqrtf((float)F);
     auto point = [&](int64_t t, float (&x)[kChannels]) {
-        const ConstantFloats src = points + (t < Ln ? t : Ln - 1) * d;
+        const PointFloats src = points + (t < Ln ? t : Ln - 1) * d;
+        uint32_t here = 0;
+        if constexpr (kVectorPoints) asm volatile("" : "+v"(here));      // (vector loads of what is the same for all lanes)
 #pragma unroll
-        for (int c = 0; c < d; ++c) x[c] = src[c];
+        for (int c = 0; c < d; ++c) x[c] = src[here + c];
     };
     auto column = [&](int l, int col, float (&w)[kChannels], float &scale_c, float &scale_s) {
         const int frequency = lane + 64 * col < F ? lane + 64 * col : F - 1;
@@ -128,23 +150,24 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
         scale_c = flips[0] < 0.f ? -scale : scale;
         scale_s = flips[F] < 0.f ? -scale : scale;
     };
-    auto features = [&](const float (&x)[kChannels], const float (&w)[kChannels], float &s, float &c) {
+    auto features = [&](const float (&x)[kChannels], const float (&w)[kChannels], const Quarters &turn, float &s, float &c) {
         float t = x[0] * w[0];
 #pragma unroll
         for (int i = 1; i < d; ++i) t = fmaf(x[i], w[i], t);
-        sincos_quarters(t, cut.points.quarters, cut.points.quarters_rest, s, c);
+        sincos_quarters(t, turn, s, c);
     };
     constexpr int COLS = solo_columns(D);
     [[maybe_unused]] float before_s[M * COLS], before_c[M * COLS];       // of the point before the pair, per level
     if constexpr (d > 0) {
         float x[kChannels];
         point(t_first, x);
+        const Quarters turn(cut.points.quarters, cut.points.quarters_rest);
 #pragma unroll
         for (int j = 0; j < M * COLS; ++j) {
             if (64 * (j % COLS) >= F) continue;
             float w[kChannels], scale_c, scale_s;
             column(j / COLS, j % COLS, w, scale_c, scale_s);
-            features(x, w, before_s[j], before_c[j]);
+            features(x, w, turn, before_s[j], before_c[j]);
             __builtin_amdgcn_sched_barrier(0);
         }
     }
@@ -155,6 +178,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
             float x[2 * SP][kChannels];
 #pragma unroll
             for (int i = 0; i < 2 * SP; ++i) point(t0 + 1 + i, x[i]);
+            const Quarters turn(cut.points.quarters, cut.points.quarters_rest);
 #pragma unroll
             for (int j = 0; j < M * COLS; ++j) {
                 const int l = j / COLS, col = j % COLS;
@@ -164,8 +188,8 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
 #pragma unroll
                 for (int i = 0; i < SP; ++i) {
                     float s1, c1, s2, c2;
-                    features(x[2 * i], w, s1, c1);
-                    features(x[2 * i + 1], w, s2, c2);
+                    features(x[2 * i], w, turn, s1, c1);
+                    features(x[2 * i + 1], w, turn, s2, c2);
                     if (lane + 64 * col < F)
                         *reinterpret_cast<float4 *>(wave_lds + (l * SP + i) * PS + 2 * (lane + 64 * col)) =
                             make_float4((c1 - before_c[j]) * scale_c, (c2 - c1) * scale_c, (s1 - before_s[j]) * scale_s, (s2 - s1) * scale_s);
@@ -251,7 +275,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
                     const float2 z = Z[(size_t)LL * SP * PS + fi], zc = Z[(size_t)LL * SP * PS + fc];
                     level_loop<LL + 1>([&](auto start_tag) {
                         constexpr int a = decltype(start_tag)::value;
-                        level_step<ORDER, LL - a, kPack>(z, zc, pk, 2 * p + 1 < T, A[b][acc_index(M, a, LL)], c[a]);
+                        level_step<ORDER, LL - a, kPack, true>(z, zc, pk, 2 * p + 1 < T, A[b][acc_index(M, a, LL)], c[a]);
                     });
                 });
             }

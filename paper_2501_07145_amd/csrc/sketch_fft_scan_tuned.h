@@ -97,6 +97,7 @@ struct Plan {
     static constexpr int NWB = wb_off(NP);
     static constexpr int roff(int q) { return G >= 16 ? q * (G + G / 16) : tuned::pad(G * q); }
     static constexpr int pad(int e) { return tuned::pad(e); }     // position in a slot of element e
+    static constexpr int kTurned = 0;
 };
 
 // Transform lengths 2^a 5^b that the paper's own experiments use as bucket counts (100, 200, 500, 1000): exact
@@ -105,7 +106,9 @@ struct Plan {
 // first ones, see the kernel), passes of radix 10, 10 and 10 / 5 / 2 / none; slots are padded where that keeps the positions of a
 // pass a base plus constants and pays (D = 1000: the writes of a transform take 140 bank rows instead of 180); the
 // twiddles of all passes after the first live in the LDS table. Selected as Plan<D>.
-template <int DD, int PAD>
+// TURNED (100 points): behind the first pass result t of butterfly j is not at 10 j + t but at TURNED t + j, so that the lanes of a
+// transform write next to each other and read TURNED apart.
+template <int DD, int PAD, int TURNED = 0>
 struct MixedPlan {
     static constexpr int LOG2D = DD;
     static constexpr int D = DD;
@@ -114,7 +117,8 @@ struct MixedPlan {
     static constexpr int FPW = 64 / G;
     static constexpr int GF = G;
     static constexpr int kPad = PAD;            // one float2 of padding after every kPad of a slot
-    static constexpr int PD = D + (D - 1) / kPad;
+    static constexpr int kTurned = TURNED;
+    static constexpr int PD = TURNED ? 9 * TURNED + 10 : D + (D - 1) / kPad;
     static constexpr int NP = D == 100 ? 2 : 3;
     static constexpr int radix(int p) { return p < 2 ? 10 : (D == 1000 ? 10 : (D == 500 ? 5 : 2)); }
     static constexpr int Ns(int p) { return p == 0 ? 1 : Ns(p - 1) * radix(p - 1); }
@@ -133,6 +137,7 @@ struct MixedPlan {
     __host__ __device__ static constexpr int pad(int e) { return e + e / kPad; }
     static constexpr int kMinWaves = 4;
     static_assert(D % R == 0 && G * FPW <= 64, "");
+    static_assert(TURNED == 0 || (D == 100 && kPad >= D), "");
 };
 template <> struct Plan<100> : MixedPlan<100, 100> {};
 template <> struct Plan<200> : MixedPlan<200, 200> {};
@@ -440,7 +445,7 @@ template <typename P>
 struct WaveFft {
     float2 tw[P::NTW];
     int wbase[P::NWB];
-    int rbase;
+    int rbase, rturned;
     const float2 *twl;      // LDS twiddle table of the passes whose twiddles are there, entry ((set * twiddles(r) + e) * G + lg)
 
     // `roots`: D float2 of LDS that are free until the caller's next use of them. Short transforms pick their register
@@ -451,6 +456,7 @@ struct WaveFft {
     __device__ __forceinline__ void init(int lg, float2 *twl_table, float2 *roots)
     {
         rbase = P::pad(lg);
+        rturned = lg * P::kTurned;
         twl = twl_table + lg;
         if constexpr (kRoots) {
             for (int i = threadIdx.x; i < P::D; i += blockDim.x) {
@@ -490,7 +496,7 @@ struct WaveFft {
             for (int u = 0; u < NB; ++u) {
                 const int j = lg + P::G * u;
                 const int k = j % Ns;
-                wbase[P::wb_off(PI) + u] = P::pad((j - k) * r + k);
+                wbase[P::wb_off(PI) + u] = P::kTurned && PI == 0 ? j : P::pad((j - k) * r + k);
             }
             if constexpr (PI > 0 && !P::tw_in_lds(PI)) {
                 constexpr int NSETS = P::tw_sets(PI);
@@ -550,14 +556,15 @@ struct WaveFft {
                 }
                 float2 *dst = slot + wbase[P::wb_off(PI) + u];
 #pragma unroll
-                for (int t = 0; t < r; ++t) dst[P::pad(t * Ns)] = x[t];
+                for (int t = 0; t < r; ++t) dst[P::kTurned && PI == 0 ? t * P::kTurned : P::pad(t * Ns)] = x[t];
             }
             transform_fence<P>();
             if constexpr (PI + 1 < P::NP) {
 #pragma unroll
                 for (int i = 0; i < P::R; ++i) {
                     const int q = read_order<P::R, P::radix(PI + 1)>(i);
-                    v[q] = slot[rbase + P::roff(q)];
+                    if constexpr (P::kTurned && PI == 0) v[q] = slot[rturned + q / 2 + q % 2 * (5 * P::kTurned)];   // 5 q + lg
+                    else v[q] = slot[rbase + P::roff(q)];
                 }
                 run_pass<PI + 1, AHEAD>(slot, v);
             }
@@ -655,8 +662,10 @@ __device__ __forceinline__ void level_loop(Fn &&f)
 // One level of one pair of time steps at one bin (Sec. 3.5 eq. (ts_rec)): z and zc are the transform of the
 // level's slot at the bin and at its mirror image; separates the two real transforms and advances the bin's
 // accumulator a = A_LL by both steps, c carrying what level LL - 1 of the same pair left. PK: the thread may be
-// the packed one (pk), whose float2 hold bins 0 and D/2 and whose z, zc are Z[0], Z[D/2].
-template <int ORDER, int LL, bool PK>
+// the packed one (pk), whose float2 hold bins 0 and D/2 and whose z, zc are Z[0], Z[D/2]. ADDS: level 0, whose A_0 is 1, takes two
+// additions instead of four multiply-adds with one and zero (the kernel of whole sequences is no faster for it: 10000 x 200 points,
+// D = 1024, five levels 10.58 and 10.85 ms).
+template <int ORDER, int LL, bool PK, bool ADDS = false>
 __device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool second_step, float2 &a, LevelCarry<ORDER> &c)
 {
     auto mul = [&](float2 x, float2 y) { return PK ? cmulf_pk(x, y, pk) : cmulf(x, y); };
@@ -679,7 +688,7 @@ __device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool se
     }
     if (!second_step) C1 = make_float2(0.f, 0.f);
     const float2 a_old = a;
-    float2 a_mid = fma(c.p0, C0, a_old);
+    float2 a_mid = ADDS && LL == 0 ? make_float2(a_old.x + C0.x, a_old.y + C0.y) : fma(c.p0, C0, a_old);
     // order >= 2 (a time step may be used up to `order` times in a row, q equal indices weighted
     // 1/q!): also the values of levels l-2 (and l-3) before each step and the transforms of
     // levels l-1 (and l-2) at both steps
@@ -692,7 +701,7 @@ __device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool se
         const float2 g = mul(c.c0pp, h0);
         a_mid = fma(make_float2(c.r0.x * (1.0f / 6.0f), c.r0.y * (1.0f / 6.0f)), g, a_mid);
     }
-    float2 a_new = fma(c.p1, C1, a_mid);
+    float2 a_new = ADDS && LL == 0 ? make_float2(a_mid.x + C1.x, a_mid.y + C1.y) : fma(c.p1, C1, a_mid);
     if constexpr (ORDER >= 2 && LL > 0) {
         h1 = mul(c.c1p, C1);
         a_new = fma(make_float2(0.5f * c.q1.x, 0.5f * c.q1.y), h1, a_new);

@@ -83,6 +83,33 @@ def test_large_angles_are_as_accurate_as_the_products(oracle, N, L, M, F, D):
         assert np.linalg.norm(a - b) <= 3e-6 * np.linalg.norm(b), (m, np.linalg.norm(a - b) / np.linalg.norm(b))
 
 
+@pytest.mark.parametrize("N,L,d,M,F,D", [
+    (100, 1000, 5, 5, 50, 100), (300, 301, 2, 5, 50, 100), (420, 85, 3, 4, 60, 64), (350, 277, 2, 4, 64, 128), (500, 150, 7, 4, 41, 128),
+    (700, 131, 8, 4, 100, 256), (300, 120, 8, 2, 64, 64), (300, 120, 4, 2, 39, 100),
+])
+def test_pieces_that_end_at_any_pair(oracle, N, L, d, M, F, D):
+    """Pieces of no whole number of iterations; slots of all distances; points in vector and in scalar registers."""
+    X, W, hash_, sign = _case(N + L + D, N, L, d, M, F, D)
+    got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 1.5, D).cpu().numpy()
+    for n in (0, 7, N - 1):
+        err = block_errors(got[n:n + 1], oracle.features(X[n:n + 1], W, hash_, sign, 1.5, D), M, D)
+        assert np.all(err <= FP32_BLOCK_TOL), (n, err)
+
+
+def test_angles_of_millions(oracle):
+    """Quarter-turns are counted in the last bits of a 32-bit sum, up to 2^22 of them; products of these points and frequencies are
+    exact. (The number of quarter-turns in a unit is held to 2^-48 of itself, 1e-8 of a quarter-turn here.)"""
+    N, L, M, F, D = 600, 40, 3, 32, 64
+    rng = np.random.default_rng(4)
+    X = rng.integers(-2 ** 20, 2 ** 20, size=(N, L, 1)).astype(np.float32)
+    W = (2.0 ** rng.integers(-3, 3, size=(M, 1, F)) * rng.choice((-1.0, 1.0), size=(M, 1, F))).astype(np.float32)
+    _, _, hash_, sign = _case(D, 1, 2, 1, M, F, D)
+    got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 1.0, D).cpu().numpy()
+    for n in (0, 5, N - 1):
+        err = block_errors(got[n:n + 1], oracle.features(X[n:n + 1], W, hash_, sign, 1.0, D), M, D)
+        assert np.all(err <= FP32_BLOCK_TOL), (n, err)
+
+
 def test_chunks_and_bf16_projection_take_the_same_sums(oracle):
     """The cut is a function of the shape: a workspace for a part of the batch gives the same bits."""
     X, W, hash_, sign = _case(1, 600, 60, 5, 5, 50, 100)
