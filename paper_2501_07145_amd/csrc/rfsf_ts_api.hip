@@ -130,9 +130,14 @@ constexpr int64_t kSumLoads = 128;
 int kernel_order(const rfsf_ts_shape *s) { return s->order < 2 || s->M == 1 ? 1 : s->order; }
 struct SketchCut { int pieces; int64_t pairs; bool joint, in_place, solo; };
 // The cut for the kernel whose wavefronts work by themselves (csrc/sketch_fft_scan_solo.h), which takes whole sequences and
-// pieces alike and `step` pairs of steps per iteration of a workgroup. Time is counted in iterations: those of a round of
-// workgroups and one for its beginning and end, and for the join a tenth of one per piece and 18 MB of accumulators
-// (1000 x 100 points, 256 buckets, four levels: 768 workgroups at once; one, two, three pieces each 182, 149, 143 us).
+// pieces alike and `step` pairs of steps per iteration of a workgroup. Time is counted in iterations of a CU that holds as many
+// workgroups as it can: with n of them an iteration takes (1.5 + n) / (1.5 + that many) (D = 100, five levels, 2 to 4 on a CU 6.1,
+// 7.9 and 9.6 us); the beginning and the end of a workgroup take 0.6 of one, the join 0.1 per piece and 18 MB of accumulators. What is
+// left over when all CUs have been filled a whole number of times is spread over them, so that pieces are chosen to leave a little
+// over or nearly nothing; they end at any pair, wavefronts take two pairs more or less than each other.
+// (100 x 1000 points, D = 100, five levels: 8, 9, 10, 11 pieces, 800 to 1100 workgroups on 256 CUs that hold four, 106, 97, 93, 117 us;
+// 300 x 300 points 2, 3, 4: 102, 88, 95; 1280 x 257 1, 2, 3: 258, 236, 253; 1000 x 100, D = 256, four levels 1, 2, 3: 169, 160, 171. Pieces
+// of whole iterations, by their number in rounds of workgroups: 9, 3, 4 and 3 pieces, 107, 90, 249 and 165 us.)
 // Batches that leave CUs without a workgroup are left to the other kernels, whose wavefronts share out a piece's levels
 // (a single sequence of 100 points 27.8 us, 30.7 here; ten of 1000 49 and 56), and so are sequences that fill less than half
 // of an iteration (3000 x 14 points, 64 buckets, three levels 51 and 54) or, from 128 points per transform on, less than four
@@ -148,18 +153,22 @@ SketchCut solo_cut(const rfsf_ts_shape *s, int P, int step)
     const SketchCut none = {0, 0, false, false, false};
     const int64_t slots = (s->L + 1) / 2, all_pairs = s->L / 2, floats_per_pair = (int64_t)s->M * 4 * s->F;
     const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
-    const int64_t at_once = kCUs * rfsf::sketch_fft_scan_solo_per_cu(s->M, s->F, P);
+    const int64_t per_cu = rfsf::sketch_fft_scan_solo_per_cu(s->M, s->F, P), own = step / rfsf::kSoloWaves;    // pairs of a wavefront
     if (2 * all_pairs < step || (P >= 128 && all_pairs < 4 * step)) return none;
     SketchCut best = none;
     double least = 0.0;
     for (int64_t want = 1; want <= kSplitPieces && want * step <= all_pairs + step; ++want) {
-        const int64_t pairs = ((all_pairs + want - 1) / want + step - 1) / step * step, pieces = (all_pairs + pairs - 1) / pairs;
+        const int64_t pairs = ((all_pairs + want - 1) / want + own - 1) / own * own, pieces = (all_pairs + pairs - 1) / pairs;
         // every piece, the last one too, has to hold its accumulators
         if (pieces > kJoinInPlace || (pieces < 2 ? slots : pairs) * floats_per_pair < needed ||
             (slots - (pieces - 1) * pairs) * floats_per_pair < needed)
             continue;
-        const double cost = (double)((s->N * pieces + at_once - 1) / at_once) * (double)(pairs / step + 1) + 0.1 * (double)pieces +
-                            (double)(s->N * pieces) * (double)needed * 4.0 / 18e6;
+        const int64_t workgroups = s->N * pieces, full = workgroups / (kCUs * per_cu), rest = workgroups - full * kCUs * per_cu;
+        // iterations of a workgroup: between those of its longest wavefront and the mean
+        const double its = 0.5 * ((double)pairs / (double)step + (double)((pairs + step - 1) / step));
+        const double of_rest = (1.5 + (double)((rest + kCUs - 1) / kCUs)) / (1.5 + (double)per_cu);
+        const double cost = (double)full * (its + 0.6) + (rest > 0 ? its * of_rest + 0.6 : 0.0) + 0.1 * (double)pieces +
+                            (double)workgroups * (double)needed * 4.0 / 18e6;
         if (best.pieces == 0 || cost < least) {
             least = cost;
             best = {(int)pieces, pieces < 2 ? slots : pairs, true, true, true};
