@@ -8,6 +8,8 @@
 // no FFT are needed and the increments never leave the chip.
 #include "rfsf_internal.h"
 
+#include <type_traits>
+
 namespace rfsf {
 namespace {
 
@@ -206,6 +208,228 @@ void dp1d_features_kernel(
         for (int m = 0; m < M; ++m) row[1 + (int64_t)m * F + my_comp] = acc_state[m][tid] * scale;
 }
 
+// Many sequences: the frequencies of 64 S components, split for the 16-bit matrix instructions, stay in LDS while a workgroup's twelve
+// wavefronts go through sequences of their own, without meeting.
+// A float is the sum of three bfloat16 numbers and six of the nine products are added up, smallest first (as in gram.hip; the three
+// left out are below 2^-24 of the product): 8 instructions of 32 cycles for a tile of 32 points and 32 components of 17 channels
+// where v_mfma_f32_32x32x2f32 takes 9 of 64, with less error (angles of 10 radians, 17 channels: root mean square 7.7e-7 in 32 bits).
+// Two terms of half precision and three products would take 4, but err by 9.3e-7 there, 2.2e-7 instead of 1.0e-7 with 2 channels.
+// Splitting the frequencies again for every tile would cost what they spare.
+// Channels 2 k + half go to the lane's half of the products' columns, so that a lane splits the channels that it loads, in pairs p of
+// k = 2 p and 2 p + 1. What a pair multiplies with what is laid out in tuples of four registers (an operand): of four pairs
+// their hi, mid and lo; of a single one hi, mid, lo, hi; of two hi, hi, mid, mid and lo, lo, hi, hi.
+// The lane that holds rows 8 g + 4 half + (0 .. 3) of a component gets the other four from the other half of the wavefront (v_permlane32_swap
+// of the two blocks of 32 components): a transposition through LDS would take the room of the frequencies.
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float floatx2 __attribute__((ext_vector_type(2)));
+// Wavefronts of a workgroup, one per CU: as many as hold the points' operands in registers.
+__host__ __device__ constexpr int resident_waves(int KSTEPS) { return KSTEPS <= 9 ? 12 : 8; }
+constexpr size_t kResidentLds = 160 * 1024;
+struct Terms { uint32_t hi, mid, lo; };
+__device__ __forceinline__ uint32_t round_pair(float a, float b)
+{
+    const floatx2 v = {a, b};
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
+__device__ __forceinline__ Terms split_pair(float a, float b)
+{
+    Terms t;
+    t.hi = round_pair(a, b);
+    const float ra = a - __uint_as_float(t.hi << 16), rb = b - __uint_as_float(t.hi & 0xffff0000u);
+    t.mid = round_pair(ra, rb);
+    t.lo = round_pair(ra - __uint_as_float(t.mid << 16), rb - __uint_as_float(t.mid & 0xffff0000u));
+    return t;
+}
+__host__ __device__ constexpr int pairs_of(int KSTEPS) { return (KSTEPS + 1) / 2; }
+__host__ __device__ constexpr int right_tuples(int pairs) { return pairs / 4 * 3 + pairs % 4; }
+__host__ __device__ constexpr int left_tuples(int pairs) { return pairs / 4 * 3 + (pairs % 4 == 0 ? 0 : pairs % 4 == 1 ? 2 : pairs % 4 == 2 ? 3 : 5); }
+template <int PAIRS>
+__device__ __forceinline__ void tuples_of_frequencies(const Terms (&w)[PAIRS], uint4 (&t)[right_tuples(PAIRS)])
+{
+    constexpr int Q = PAIRS / 4;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const Terms &a = w[4 * q], &b = w[4 * q + 1], &c = w[4 * q + 2], &d = w[4 * q + 3];
+        t[3 * q] = make_uint4(a.hi, b.hi, c.hi, d.hi);
+        t[3 * q + 1] = make_uint4(a.mid, b.mid, c.mid, d.mid);
+        t[3 * q + 2] = make_uint4(a.lo, b.lo, c.lo, d.lo);
+    }
+    if constexpr (PAIRS % 4 >= 2) {
+        const Terms &a = w[4 * Q], &b = w[4 * Q + 1];
+        t[3 * Q] = make_uint4(a.hi, b.hi, a.mid, b.mid);
+        t[3 * Q + 1] = make_uint4(a.lo, b.lo, a.hi, b.hi);
+    }
+    if constexpr (PAIRS % 2 == 1) {
+        const Terms &a = w[PAIRS - 1];
+        t[right_tuples(PAIRS) - 1] = make_uint4(a.hi, a.mid, a.lo, a.hi);
+    }
+}
+template <int PAIRS>
+__device__ __forceinline__ void tuples_of_points(const Terms (&x)[PAIRS], uint4 (&t)[left_tuples(PAIRS)])
+{
+    constexpr int Q = PAIRS / 4;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const Terms &a = x[4 * q], &b = x[4 * q + 1], &c = x[4 * q + 2], &d = x[4 * q + 3];
+        t[3 * q] = make_uint4(a.hi, b.hi, c.hi, d.hi);
+        t[3 * q + 1] = make_uint4(a.mid, b.mid, c.mid, d.mid);
+        t[3 * q + 2] = make_uint4(a.lo, b.lo, c.lo, d.lo);
+    }
+    if constexpr (PAIRS % 4 >= 2) {
+        const Terms &a = x[4 * Q], &b = x[4 * Q + 1];
+        t[3 * Q] = make_uint4(a.lo, b.lo, a.mid, b.mid);
+        t[3 * Q + 1] = make_uint4(a.hi, b.hi, a.hi, b.hi);
+        t[3 * Q + 2] = make_uint4(a.hi, b.hi, a.mid, b.mid);
+    }
+    if constexpr (PAIRS % 2 == 1) {
+        const Terms &a = x[PAIRS - 1];
+        t[left_tuples(PAIRS) - 2] = make_uint4(a.lo, a.mid, 0u, 0u);
+        t[left_tuples(PAIRS) - 1] = make_uint4(a.hi, a.hi, a.hi, a.mid);
+    }
+}
+// Products of 32 points with 32 components; right: the lane's tuples of frequencies in LDS, 64 apart.
+template <int PAIRS>
+__device__ __forceinline__ floatx16 multiply(const uint4 (&x)[left_tuples(PAIRS)], const uint4 *right)
+{
+    constexpr int Q = PAIRS / 4;
+    floatx16 acc = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    auto product = [&](const uint4 &a, const uint4 &b) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), acc, 0, 0, 0);
+    };
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+        const uint4 hi = right[64 * (3 * q)], mid = right[64 * (3 * q + 1)], lo = right[64 * (3 * q + 2)];
+        product(x[3 * q + 2], hi);
+        product(x[3 * q], lo);
+        product(x[3 * q + 1], mid);
+        product(x[3 * q + 1], hi);
+        product(x[3 * q], mid);
+        product(x[3 * q], hi);
+    }
+    if constexpr (PAIRS % 4 >= 2) {
+        const uint4 a = right[64 * (3 * Q)], b = right[64 * (3 * Q + 1)];
+        product(x[3 * Q], a);
+        product(x[3 * Q + 2], b);
+        product(x[3 * Q + 1], a);
+    }
+    if constexpr (PAIRS % 2 == 1) {
+        const uint4 a = right[64 * (right_tuples(PAIRS) - 1)];
+        product(x[left_tuples(PAIRS) - 2], a);
+        product(x[left_tuples(PAIRS) - 1], a);
+    }
+    return acc;
+}
+// LDS of a resident workgroup: frequencies and phases of S blocks of 64 components, accumulators and last cosines of the wavefronts.
+__host__ __device__ constexpr size_t resident_lds(int KSTEPS, int M, int S)
+{
+    return (size_t)M * S * (2 * right_tuples(pairs_of(KSTEPS)) * 64 * sizeof(uint4) + 64 * sizeof(float)) +
+           (size_t)resident_waves(KSTEPS) * M * 2 * 64 * sizeof(float);
+}
+template <int KSTEPS>
+__global__ __launch_bounds__(64 * resident_waves(KSTEPS)) __attribute__((amdgpu_waves_per_eu(resident_waves(KSTEPS) / 4, resident_waves(KSTEPS) / 4))) void dp1d_resident_kernel(
+    const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ bias, float scale_turns, int64_t N,
+    int64_t L, int d, int M, int F, int S, float *__restrict__ out, int64_t ld_out)
+{
+    constexpr int PAIRS = pairs_of(KSTEPS), RT = right_tuples(PAIRS), WAVES = resident_waves(KSTEPS);
+    extern __shared__ __attribute__((aligned(16))) char resident[];
+    uint4 *freq = reinterpret_cast<uint4 *>(resident);                              // [M][S][2][RT][64]
+    float *phase = reinterpret_cast<float *>(freq + (size_t)M * S * 2 * RT * 64);   // [M][S][64]
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    float *state = phase + (size_t)M * S * 64 + (size_t)wave * M * 128;             // [M][2][64]
+    const int half = lane >> 5, col = lane & 31;
+    const int comp0 = blockIdx.y * (64 * S);
+    for (int i = tid; i < M * S * 128; i += 64 * WAVES) {
+        const int l = i & 63, cb = (i >> 6) & 1, ms = i >> 7, m = ms / S, s = ms - m * S;
+        const int comp = min(comp0 + 64 * s + 32 * cb + (l & 31), F - 1);
+        const float *src = W + (int64_t)m * d * F + comp;
+        Terms w[PAIRS];
+#pragma unroll
+        for (int p = 0; p < PAIRS; ++p) {
+            const int c0 = 4 * p + (l >> 5), c1 = c0 + 2;
+            w[p] = split_pair(c0 < d ? src[(int64_t)c0 * F] : 0.f, c1 < d ? src[(int64_t)c1 * F] : 0.f);
+        }
+        uint4 t[RT];
+        tuples_of_frequencies<PAIRS>(w, t);
+#pragma unroll
+        for (int r = 0; r < RT; ++r) freq[((size_t)(ms * 2 + cb) * RT + r) * 64 + l] = t[r];
+    }
+    for (int i = tid; i < M * S * 64; i += 64 * WAVES) {
+        const int m = i / (64 * S), comp = comp0 + i - m * (64 * S);
+        phase[i] = bias[(int64_t)m * F + min(comp, F - 1)];
+    }
+    __syncthreads();
+    const int sub = wave % S, my_comp = comp0 + 64 * sub + lane;
+    if (comp0 + 64 * sub >= F) return;                       // (no block of components for this wavefront)
+    const int64_t at_once = (int64_t)gridDim.x * (WAVES / S);
+    const float out_scale = 1.0f / sqrtf((float)F);
+    float raw[2 * PAIRS];
+    auto fetch = [&](int64_t n, int64_t t0) {                // rows beyond the sequence are its last one, channels beyond d meet zeros
+        const float *src = X + (n * L + min(t0 + col, L - 1)) * d;
+#pragma unroll
+        for (int k = 0; k < 2 * PAIRS; ++k) raw[k] = src[min(2 * k + half, d - 1)];
+    };
+    int64_t n = (int64_t)(wave / S) * gridDim.x + blockIdx.x;      // (what does not fill a round is spread over the CUs)
+    if (n < N) fetch(n, 0);
+    for (; n < N; n += at_once) {
+        for (int m = 0; m < M; ++m) state[m * 128 + lane] = 0.f;
+        for (int64_t t0 = 0; t0 < L; t0 += kRows) {
+            const int nrow = (int)min((int64_t)kRows, L - t0);
+            Terms xt[PAIRS];
+#pragma unroll
+            for (int p = 0; p < PAIRS; ++p) xt[p] = split_pair(raw[2 * p], raw[2 * p + 1]);
+            uint4 x[left_tuples(PAIRS)];
+            tuples_of_points<PAIRS>(xt, x);
+            const bool more = t0 + kRows < L;                // the next tile, or the first one of the next sequence
+            fetch(more ? n : min(n + at_once, N - 1), more ? t0 + kRows : 0);
+            float E[kRows];                                  // the level below before each row; level 0 is 1
+#pragma unroll
+            for (int r = 0; r < kRows; ++r) E[r] = 1.0f;
+            for (int m = 0; m < M; ++m) {
+                const uint4 *right = freq + (size_t)((m * S + sub) * 2) * RT * 64 + lane;
+                const floatx16 acc[2] = {multiply<PAIRS>(x, right), multiply<PAIRS>(x, right + RT * 64)};
+                const float bm = phase[(m * S + sub) * 64 + lane];
+                const float b = bm * 0.318309886183790672f;          // phase in half-turns, and what its rounding left
+                const float rest = fmaf(bm, 0.318309886183790672f, -b) + bm * 1.2841276486e-8f;
+                float a = state[m * 128 + lane], pc = state[m * 128 + 64 + lane];
+                auto rows = [&](auto full_tag) {
+                    constexpr bool FULL = decltype(full_tag)::value;
+#pragma unroll
+                    for (int g = 0; g < kRows / 8; ++g) {
+                        if (!FULL && 8 * g >= nrow) break;
+                        float c[8];
+#pragma unroll
+                        for (int j = 0; j < 4; ++j) {
+                            const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[0][4 * g + j]), __float_as_uint(acc[1][4 * g + j]), false, false);
+                            c[j] = sqrt2_cospi(fmaf(__uint_as_float(both[0]), scale_turns, b), rest);
+                            c[4 + j] = sqrt2_cospi(fmaf(__uint_as_float(both[1]), scale_turns, b), rest);
+                        }
+                        if (g == 0) pc = t0 == 0 ? c[0] : pc;        // first point of the sequence: no increment
+#pragma unroll
+                        for (int j = 0; j < 8; ++j) {
+                            const int r = 8 * g + j;
+                            const float u = FULL || r < nrow ? c[j] - pc : 0.f, below = E[r];
+                            pc = FULL || r < nrow ? c[j] : pc;
+                            E[r] = a;
+                            a = fmaf(below, u, a);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                };
+                if (nrow == kRows) rows(std::integral_constant<bool, true>{});
+                else rows(std::integral_constant<bool, false>{});
+                state[m * 128 + lane] = a;
+                state[m * 128 + 64 + lane] = pc;
+            }
+        }
+        if (my_comp < F) {
+            float *row = out + n * ld_out;
+            if (my_comp == 0) row[0] = 1.0f;
+            for (int m = 0; m < M; ++m) row[1 + (int64_t)m * F + my_comp] = state[m * 128 + lane] * out_scale;
+        }
+    }
+}
+
 // Few long sequences: workgroup = (sequence, 64 components), eight wavefronts that share out the time points, a stretch
 // of 31 or more steps each (whole tiles; a stretch starts with the last point of the one before). A wavefront runs the recurrence for
 // every first level at once, A^{(a..l)} for all a <= l (E[a][r]: the sum of the level below before row r), and the
@@ -364,6 +588,54 @@ hipError_t launch_stretches(const float *X, const float *W, const float *bias, f
     return hipGetLastError();
 }
 
+// Blocks of 64 components that a workgroup of the resident kernel holds: those of 1, 2, 3, 4 that keep most of the wavefronts of the chip
+// at work in every round of sequences; 0 where even one does not fit the LDS, or where the kernel above is the faster one: up to
+// six channels, whose 32-bit products cost little, unless it has more to do for its slabs of 256 components and whole last tiles.
+// Kernel above and this one, us: 4999 x 257 points, 1000 components, five levels, d = 4 2470 and 2535, 8 2840 and 2665, 12 3360 and 2880,
+// 17 3945 and 3170, 32 5700 and 3725, 64 8930 and 5830; 1500 x 256, 256 components, d = 2, 4, 6, 8 164, 174, 189, 204 and 191, 190, 195,
+// 195; 1500 x 100, 128 components, d = 2 73 and 42; 130 x 257, 256 components, d = 17 87 and 66; 20000 x 2, 64 components, d = 3 208 and 42.
+constexpr int64_t kCUs = 256;
+struct Resident { int blocks; int64_t per_slab; };
+template <int KSTEPS>
+Resident resident_plan(int64_t N, int64_t L, int M, int F)
+{
+    Resident best = {0, 0};
+    const int64_t blocks = (F + 63) / 64, rest = L % kRows;
+    // a tile of the other kernel's is 1, of this one's dearer by as much as was measured with whole tiles and slabs
+    const double dearer = KSTEPS == 1 ? 1.17 : KSTEPS == 2 ? 1.09 : KSTEPS == 3 ? 1.04 : 0.0;
+    const double tiles = (double)(L / kRows) + (rest == 0 ? 0.0 : 0.3 + 0.175 * (double)((rest + 7) / 8));
+    if (dearer * tiles * (double)blocks > (double)((L + kRows - 1) / kRows * ((F + 255) / 256 * 4))) return best;
+    double most = 0.0;
+    for (int S = 1; S <= 4; ++S) {
+        if (resident_lds(KSTEPS, M, S) > kResidentLds) break;
+        const int64_t slabs = (blocks + S - 1) / S;
+        if (resident_waves(KSTEPS) % S != 0 || slabs > 65535) continue;
+        const int64_t per_slab = slabs < kCUs ? kCUs / slabs : 1, at_once = per_slab * (resident_waves(KSTEPS) / S);
+        const int64_t rounds = (N + at_once - 1) / at_once;
+        // wavefronts with a sequence, of those of whole rounds of workgroups on all CUs
+        const double busy = (double)(blocks * N) / (double)(rounds * resident_waves(KSTEPS) * kCUs * ((slabs * per_slab + kCUs - 1) / kCUs));
+        if (busy > most) most = busy, best = {S, per_slab};
+    }
+    return best;
+}
+template <int KSTEPS>
+hipError_t launch_resident(const Resident &plan, const float *X, const float *W, const float *bias, float scale_turns, int64_t N,
+                           int64_t L, int d, int M, int F, float *out, int64_t ld_out, hipStream_t stream)
+{
+    const size_t lds = resident_lds(KSTEPS, M, plan.blocks);
+    static size_t raised = 0;
+    if (lds > 64 * 1024 && lds > raised) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(dp1d_resident_kernel<KSTEPS>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        raised = lds;
+    }
+    const dim3 grid((unsigned)plan.per_slab, (unsigned)((F + 64 * plan.blocks - 1) / (64 * plan.blocks)));
+    hipLaunchKernelGGL(dp1d_resident_kernel<KSTEPS>, grid, dim3(64 * resident_waves(KSTEPS)), lds, stream, X, W, bias, scale_turns, N, L, d, M, F,
+                       plan.blocks, out, ld_out);
+    return hipGetLastError();
+}
+
 }  // namespace
 
 hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float scale_turns, int64_t N,
@@ -384,6 +656,8 @@ hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float 
     // 64 KB for many levels on a wide state; the limit on the dynamic part is then raised once per kernel
 #define RFSF_LAUNCH_DP1D(KS)                                                                                  \
     do {                                                                                                      \
+        const Resident plan = resident_plan<KS>(N, L, M, F);                                                  \
+        if (plan.blocks > 0) return launch_resident<KS>(plan, X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream); \
         constexpr size_t kStatic = sizeof(float) * (2 * kRows * ((2 * KS) | 1) + 4 * 64 * kTileStride);             \
         static size_t raised = 0;                                                                             \
         if (kStatic + dyn > 64 * 1024 && dyn > raised) {                                                      \

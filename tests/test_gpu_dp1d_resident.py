@@ -1,0 +1,70 @@
+"""RFSF-DP-1D with frequencies resident in LDS: every number of channels that the kernel is compiled for, at both edges; last tiles of
+one row, of whole groups of eight and one more; blocks of components that are not full; more sequences than wavefronts, and fewer."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_07145_amd as rfsf
+from tests.parity import FP32_BLOCK_TOL, block_errors
+
+pytestmark = pytest.mark.gpu
+
+
+def _case(N, L, d, M, F):
+    rng = np.random.default_rng(N + L + d + F)
+    X = np.cumsum(rng.standard_normal((N, L, d)) / math.sqrt(L), axis=1).astype(np.float32)
+    W = rng.standard_normal((M, d, F)).astype(np.float32)
+    b = rng.uniform(0.0, 2.0 * math.pi, size=(M, F)).astype(np.float32)
+    return X, W, b, float(np.float32(math.sqrt(d)))
+
+
+@pytest.mark.parametrize("N,L,d,M,F", [
+    (200, 33, d, 3, 70) for d in (1, 2, 3, 4, 5, 6, 7, 8, 9, 12, 13, 18, 19, 24, 25, 32, 33, 40, 41, 48, 49, 64)
+] + [
+    (300, 1, 17, 2, 64), (300, 2, 17, 5, 65), (300, 8, 9, 4, 128), (300, 9, 9, 4, 129), (300, 31, 12, 3, 200), (300, 32, 12, 3, 200),
+    (300, 57, 17, 5, 1000), (300, 96, 20, 4, 63), (4000, 40, 17, 5, 64), (3100, 5, 30, 2, 300), (700, 70, 10, 16, 40), (150, 66, 64, 5, 130),
+    (150, 66, 64, 6, 130), (129, 70, 5, 2, 256),
+])
+def test_rows_match_the_oracle(oracle, N, L, d, M, F):
+    X, W, b, ls = _case(N, L, d, M, F)
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, b)]
+    got = rfsf.rfsf_dp1d_features(*dev, ls)
+    assert torch.equal(got, rfsf.rfsf_dp1d_features(*dev, ls))
+    rows = np.unique(np.array([0, 1, N // 2, N - 2, N - 1]))
+    err = block_errors(got.cpu().numpy()[rows], oracle.dp1d_features(X[rows], W, b, ls), M, F)
+    assert np.all(err <= FP32_BLOCK_TOL), err
+
+
+def test_nan_and_infinity_stay_where_they_are():
+    N, L, d, M, F = 300, 40, 17, 3, 130
+    X, W, b, ls = _case(N, L, d, M, F)
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, b)]
+    want = rfsf.rfsf_dp1d_features(*dev, ls)
+    dev[0][7, 20, 3] = float("nan")
+    dev[0][9, 39, 16] = float("inf")
+    dev[1][1, 4, 77] = float("nan")
+    dev[1][2, 0, 5] = float("-inf")
+    got = rfsf.rfsf_dp1d_features(*dev, ls)
+    bad = torch.zeros_like(want, dtype=torch.bool)
+    bad[[7, 9], 1:] = True
+    bad[:, 1 + F + 77] = bad[:, 1 + 2 * F + 77] = True       # a level and those above it
+    bad[:, 1 + 2 * F + 5] = True
+    assert bool(torch.isnan(got[bad]).all()) and torch.equal(got[~bad], want[~bad])
+
+
+def test_sums_of_products_are_as_good_as_in_32_bits():
+    """Phase 0 and one increment from the origin: level 1 is sqrt(2 / F) (cos(x . w) - 1). An angle is the sum of eight sums that
+    each round once, by 2^-23 of the largest one at most, and is rounded to half-turns, 2^-24 with the rounding of their number in
+    a radian; the cosine adds 2e-7. Root mean square 1.5e-6: a tenth of that bound for the mean angle; operands of 16 bits give 1e-2."""
+    rng = np.random.default_rng(5)
+    N, d, F = 400, 17, 256
+    X = np.zeros((N, 2, d), np.float32)
+    X[:, 1] = rng.standard_normal((N, d)) * 3.0
+    W = rng.standard_normal((1, d, F)).astype(np.float32)
+    got = rfsf.rfsf_dp1d_features(*(torch.from_numpy(a).cuda() for a in (X, W, np.zeros((1, F), np.float32))), 1.0).cpu().numpy()
+    angle = X[:, 1].astype(np.float64) @ W[0].astype(np.float64)
+    err = got[:, 1:].astype(np.float64) * math.sqrt(F) - math.sqrt(2.0) * (np.cos(angle) - 1.0)
+    bound = math.sqrt(2.0) * np.abs(angle).max() * (8 * 2.0 ** -23 + 2.0 ** -24) + 2e-7
+    assert np.abs(err).max() <= bound and np.sqrt(np.mean(err ** 2)) <= 1.5e-6, (np.abs(err).max(), np.sqrt(np.mean(err ** 2)))
