@@ -38,6 +38,7 @@
 // 2^-24 times that sum, and 2 K units if numbers that were not sampled are up to 2^16 and all meet small ones. (Features, raw
 // and normalised, of walks and of noise, and increments against normal numbers: 2^16.8 and more.)
 #include "rfsf_internal.h"
+#include <algorithm>
 #include <type_traits>
 
 namespace rfsf {
@@ -378,6 +379,104 @@ __global__ __launch_bounds__(64 * NW, T == 1 ? 4 : 2) void gram_small(GramArgs g
                          __builtin_amdgcn_readfirstlane(flip_of_row(ib)));
         if (__ballot(any != any)) settle_nan<16, 16, SYM>(g, A, B, C, ib, jb, SYM && bi == bj);
     }
+}
+
+// ---------------------------------------------------------------------------------------------------------------
+// Up to eight rows on one side (a request against stored features): a wavefront takes two rows of the other side (four of many, against more than four) and all of the few,
+// four columns of each per lane and step, adds up in plain 32-bit multiply-adds and then over its lanes; of few rows its
+// workgroup's wavefronts share out the columns (SPLIT). What bounds it is reading the long side once, and for hundreds of rows its
+// latency; tiles leave most of the chip without work and pad the short side to 32.
+// In tiles and here, us a call: 1 x 1000, 1025 columns 8.1 and 6.5, 1 x 30, 5121 columns 24 and 6.4, 3 x 40, 10241 columns 48 and 7.2, 1 x
+// 10000, 5121 columns 76 and 36 (5.7 TB/s), 8 x 10000 80 and 62. Errors against 64 bits 1.7e-7 and 1.0e-7 with 1025 columns, 3.9e-7 and
+// 1.7e-7 with 5121, 8.0e-8 both with 301, but 5.6e-8 and 8.1e-8 with 193, hence kThinColumns. Five to eight rows against thousands take
+// as long in tiles up to some 1000 columns (8 x 3000, 513 columns 6.5 and 6.9, 7 x 9000, 1025 15.4 and 15.8).
+constexpr int kFew = 8, kThinWaves = 4;
+constexpr int64_t kThinColumns = 320, kThinWide = 2048, kThinSplit = 2048, kThinMany = 8192;
+template <int FEW, int ROWS, bool SPLIT>
+__global__ __launch_bounds__(64 * kThinWaves) void gram_thin(const float *__restrict__ few, const float *__restrict__ many, float *__restrict__ C,
+                                                             int64_t n_few, int64_t n_many, int64_t K, int64_t ld_few, int64_t ld_many,
+                                                             int64_t step_few, int64_t step_many)
+{
+    __shared__ float part[SPLIT ? kThinWaves : 1][ROWS * FEW];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int64_t first = (SPLIT ? (int64_t)blockIdx.x : (int64_t)blockIdx.x * kThinWaves + wave) * ROWS;
+    if (first >= n_many) return;
+    const float *a[FEW], *b[ROWS];                           // rows that do not exist are the last one, and not stored
+#pragma unroll
+    for (int r = 0; r < FEW; ++r) a[r] = few + min((int64_t)r, n_few - 1) * ld_few;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) b[r] = many + min(first + r, n_many - 1) * ld_many;
+    float acc[ROWS][FEW];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+        for (int j = 0; j < FEW; ++j) acc[i][j] = 0.f;
+    const int64_t whole = K / 256 * 256;
+#pragma unroll 2
+    for (int64_t k = 4 * lane + (SPLIT ? 256 * wave : 0); k < whole; k += SPLIT ? 256 * kThinWaves : 256) {
+        Float4u x[ROWS], y[FEW];
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i) x[i] = *reinterpret_cast<const Float4u *>(b[i] + k);
+#pragma unroll
+        for (int j = 0; j < FEW; ++j) y[j] = *reinterpret_cast<const Float4u *>(a[j] + k);
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+            for (int j = 0; j < FEW; ++j)
+                acc[i][j] = fmaf(x[i].w, y[j].w, fmaf(x[i].z, y[j].z, fmaf(x[i].y, y[j].y, fmaf(x[i].x, y[j].x, acc[i][j]))));
+    }
+    // the columns left over, one per lane
+    for (int64_t k = whole + lane + (SPLIT ? 64 * wave : 0); k < K; k += SPLIT ? 64 * kThinWaves : 64) {
+#pragma unroll
+        for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+            for (int j = 0; j < FEW; ++j) acc[i][j] = fmaf(b[i][k], a[j][k], acc[i][j]);
+    }
+    auto store = [&](int i, int j, float v) {
+        if (j < n_few && first + i < n_many) C[j * step_few + (first + i) * step_many] = v;
+    };
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i)
+#pragma unroll
+        for (int j = 0; j < FEW; ++j) {
+#pragma unroll
+            for (int o = 32; o > 0; o /= 2) acc[i][j] += __shfl_xor(acc[i][j], o);
+            if (lane == 0) {
+                if constexpr (SPLIT) part[wave][i * FEW + j] = acc[i][j];
+                else store(i, j, acc[i][j]);
+            }
+        }
+    if constexpr (SPLIT) {
+        __syncthreads();
+        if (wave == 0 && lane < ROWS * FEW)
+            store(lane / FEW, lane % FEW, (part[0][lane] + part[1][lane]) + (part[2][lane] + part[3][lane]));
+    }
+}
+hipError_t launch_thin(const GramArgs &g, hipStream_t stream)
+{
+    const bool few_x = g.Nx <= g.Ny;
+    const float *few = few_x ? g.A : g.B, *many = few_x ? g.B : g.A;
+    const int64_t n_few = few_x ? g.Nx : g.Ny, n_many = few_x ? g.Ny : g.Nx, ld_few = few_x ? g.lda : g.ldb, ld_many = few_x ? g.ldb : g.lda;
+    const int64_t step_few = few_x ? g.ldc : 1, step_many = few_x ? 1 : g.ldc;
+    const bool split = n_many < kThinSplit;
+    const int64_t rows = n_few > 4 && n_many >= kThinMany ? 4 : 2, per_workgroup = split ? rows : rows * kThinWaves, workgroups = (n_many + per_workgroup - 1) / per_workgroup;
+    if (workgroups > 0x7fffffffLL) return hipErrorInvalidValue;
+#define RFSF_THIN(FEW, ROWS, SPLIT)                                                                                                              \
+    hipLaunchKernelGGL((gram_thin<FEW, ROWS, SPLIT>), dim3((unsigned)workgroups), dim3(64 * kThinWaves), 0, stream, few, many, g.C, n_few, \
+                       n_many, g.K, ld_few, ld_many, step_few, step_many)
+#define RFSF_THIN_ROWS(FEW, ROWS)            \
+    do {                                     \
+        if (split) RFSF_THIN(FEW, 2, true);  \
+        else RFSF_THIN(FEW, ROWS, false);    \
+    } while (0)
+    if (n_few <= 1) RFSF_THIN_ROWS(1, 2);
+    else if (n_few <= 2) RFSF_THIN_ROWS(2, 2);
+    else if (n_few <= 4) RFSF_THIN_ROWS(4, 2);
+    else if (rows == 2) RFSF_THIN_ROWS(kFew, 2);
+    else RFSF_THIN_ROWS(kFew, 4);
+#undef RFSF_THIN_ROWS
+#undef RFSF_THIN
+    return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------------------------------------------
@@ -1006,6 +1105,8 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
         const int64_t ti = (Nx + edge - 1) / edge, tj = (Ny + edge - 1) / edge;
         return (sym ? ti * (ti + 1) / 2 : ti * tj) * batch;
     };
+    const int64_t few = std::min(Nx, Ny), many = std::max(Nx, Ny);
+    if (!rows_add_up && batch == 1 && few <= kFew && ncols >= (few <= 4 || many < kThinSplit ? kThinColumns : kThinWide)) return launch_thin(g, stream);
     // Large tiles run one per CU at a time or, faster together, two; with `rounds` = their number over 256, rounded up,
     // three terms take as long as about 1340 tiles of 64 x 64 per round do. Two terms: 64 x 64 tiles take about
     // 0.57 (105 + columns) / 10000 us each and 12 more, large ones 20 us and 0.76 (200 + columns) / 17.5 us a round, fitted

@@ -1,0 +1,50 @@
+"""Gram of a few rows with others: both sides of every rule, columns around whole steps, packed rows, and what is not finite."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_07145_amd as rfsf
+
+pytestmark = pytest.mark.gpu
+
+
+def _gram(A, B):
+    K = torch.full((A.shape[0], B.shape[0] + 3), -7.0, device="cuda")
+    rfsf.rfsf_ts_gram(A, B, K=K[:, :B.shape[0]])
+    assert bool((K[:, B.shape[0]:] == -7.0).all())
+    return K[:, :B.shape[0]]
+
+
+@pytest.mark.parametrize("few,many,cols", [
+    (1, 1, 320), (1, 2, 319), (1, 1000, 1025), (2, 7, 511), (3, 100, 512), (4, 2047, 513), (4, 2048, 321), (5, 2047, 767), (8, 33, 1024),
+    (8, 2048, 2047), (8, 2048, 2048), (6, 8191, 2049), (5, 8192, 2050), (8, 8195, 2051), (9, 50, 1025), (1, 9000, 400), (8, 8, 5121),
+])
+def test_sums_match_64_bits(few, many, cols):
+    """A sum of products of `cols` numbers in 32 bits: a few times 2^-24 of the root sum of their squares, sqrt(cols) of them at random
+    signs; 2e-6 is the tolerance of the larger tiles' tests too."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(few * many + cols)
+    A = torch.randn((few, cols), generator=gen, device="cuda")
+    B = torch.randn((many, cols), generator=gen, device="cuda")
+    want = A.double() @ B.double().T
+    scale = (A.double() ** 2).sum(1).sqrt()[:, None] * (B.double() ** 2).sum(1).sqrt()[None, :]
+    wide = torch.zeros((many, cols + 5), device="cuda")[:, 1:cols + 1]           # a stride and an alignment of its own
+    wide.copy_(B)
+    for a, b, w, s in ((A, B, want, scale), (B, A, want.T, scale.T), (A, wide, want, scale)):
+        got = _gram(a, b)
+        assert float(((got.double() - w) / s).abs().max()) <= 2e-6
+        assert torch.equal(got, _gram(a, b))
+    own = _gram(A, A)
+    assert torch.equal(own, own.T)
+
+
+def test_what_is_not_finite_stays_in_its_entries():
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(1)
+    A, B = torch.rand((3, 700), generator=gen, device="cuda"), torch.rand((40, 700), generator=gen, device="cuda")
+    want = _gram(A, B)
+    B[5, 699], B[7, 3] = float("nan"), float("inf")
+    got = _gram(A, B)
+    assert bool(torch.isnan(got[:, 5]).all()) and bool(torch.isinf(got[:, 7]).all())
+    keep = [j for j in range(40) if j not in (5, 7)]
+    assert torch.equal(got[:, keep], want[:, keep])
