@@ -264,7 +264,7 @@ __device__ __forceinline__ int64_t rank_of_block(int64_t tiles)
 unsigned xcd_grid(int64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Small problems: too few tiles to fill the chip with large ones, time is latency. Tile (32 T) x (32 T), NW
+// Small problems: too few tiles to fill the chip with large ones, time is latency. Tile (16 NR) x (16 NR), NW
 // wavefronts that share out the columns of K in steps of 32, step s to wavefront s mod NW, and work without any
 // barrier: each loads its fragments from global memory straight into registers, one step ahead. The partial tiles are
 // added through LDS at the end in a fixed order. 16 x 16 blocks (v_mfma_f32_16x16x32_bf16: lane l holds columns
@@ -275,10 +275,10 @@ unsigned xcd_grid(int64_t tiles) { return (unsigned)((tiles + 7) / 8 * 8); }
 // themselves, 1025 columns, take 115 us instead of 90).
 struct __attribute__((packed, aligned(4))) Float4u { float x, y, z, w; };
 
-template <int T, int NW, bool SYM, bool FLIP>
-__global__ __launch_bounds__(64 * NW, T == 1 ? 4 : 2) void gram_small(GramArgs g, int64_t tiles, int64_t tiles_j)
+template <int NR, int NW, bool SYM, bool FLIP>
+__global__ __launch_bounds__(64 * NW, NR <= 2 ? 4 : 2) void gram_small(GramArgs g, int64_t tiles, int64_t tiles_j)
 {
-    constexpr int NR = 2 * T, NH = NW / 2;      // 16-row blocks per side; wavefronts that keep a partial tile in LDS
+    constexpr int NH = NW / 2;                  // wavefronts that keep a partial tile in LDS (NR: 16-row blocks per side)
     __shared__ floatx4 red[NH * NR * NR * 64];
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int quarter = lane >> 4, col = lane & 15;
@@ -296,7 +296,7 @@ __global__ __launch_bounds__(64 * NW, T == 1 ? 4 : 2) void gram_small(GramArgs g
     }
     const float *A = g.A + blockIdx.y * g.step_a, *B = g.B + blockIdx.y * g.step_b;
     float *C = g.C + blockIdx.y * g.step_c;
-    const int64_t i0 = bi * (32 * T), j0 = bj * (32 * T);
+    const int64_t i0 = bi * (16 * NR), j0 = bj * (16 * NR);
     // rows beyond the matrix are redirected to its last one: what they contribute is never stored
     const float *p[2 * NR];
     uint32_t sign[NR];
@@ -1076,14 +1076,14 @@ __global__ __launch_bounds__(256, 2) void gram_big_two_terms(GramArgs g, int64_t
     }
 }
 
-template <int T, int NW>
+template <int NR, int NW>
 hipError_t launch_small(const GramArgs &g, bool sym, bool flip, int batch, hipStream_t stream)
 {
-    const int64_t ti = (g.Nx + 32 * T - 1) / (32 * T), tj = (g.Ny + 32 * T - 1) / (32 * T);
+    const int64_t ti = (g.Nx + 16 * NR - 1) / (16 * NR), tj = (g.Ny + 16 * NR - 1) / (16 * NR);
     const int64_t tiles = sym ? ti * (ti + 1) / 2 : ti * tj;
     if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
     const dim3 grid(xcd_grid(tiles), (unsigned)batch);
-#define RFSF_SMALL(SY, FL) hipLaunchKernelGGL((gram_small<T, NW, SY, FL>), grid, dim3(64 * NW), 0, stream, g, tiles, tj)
+#define RFSF_SMALL(SY, FL) hipLaunchKernelGGL((gram_small<NR, NW, SY, FL>), grid, dim3(64 * NW), 0, stream, g, tiles, tj)
     if (flip) RFSF_SMALL(false, true);
     else if (sym) RFSF_SMALL(true, false);
     else RFSF_SMALL(false, false);
@@ -1142,9 +1142,14 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
     // ... and between 150 and 256 of them 64 x 64 tiles with eight wavefronts, which leave the rows' panels to half as many
     // readers (1000 x 1000, 501 columns 15.7 -> 12.6 us; 300 x 2000, 1501 columns, 160 tiles 36.3 -> 29.1; 1400 rows with
     // themselves, 1025 columns, 253 tiles 29.8 -> 23.5; 1000 rows, 136 tiles 22.1 and 21.8; 700 rows, 66 tiles 10.8 and 20.1)
-    if (count(64) <= 150) return launch_small<1, 8>(g, sym, rows_add_up, batch, stream);
-    if (count(64) <= 256) return launch_small<2, 8>(g, sym, rows_add_up, batch, stream);
-    return launch_small<2, 4>(g, sym, rows_add_up, batch, stream);
+    // ... and 16 x 16 while every CU gets at most one: what bounds a workgroup alone on its CU is how much it has to read (14 bytes a
+    // clock; sixteen wavefronts or two steps ahead change nothing), here half of what a tile of 32 x 32 does (100 x 100 rows, 5121 columns 41 ->
+    // 20 us, 200 x 200, 8191 60 -> 31, 16 x 1000, 5121 33 -> 20, 300 x 300, 361 tiles, 2049 columns and more about the same, 400 x 400, 625 tiles,
+    // 18 and 24 with 2049)
+    if (count(16) <= 256) return launch_small<1, 8>(g, sym, rows_add_up, batch, stream);
+    if (count(64) <= 150) return launch_small<2, 8>(g, sym, rows_add_up, batch, stream);
+    if (count(64) <= 256) return launch_small<4, 8>(g, sym, rows_add_up, batch, stream);
+    return launch_small<4, 4>(g, sym, rows_add_up, batch, stream);
 }
 
 }  // namespace rfsf

@@ -1,4 +1,5 @@
-"""Gram of a few rows with others: both sides of every rule, columns around whole steps, packed rows, and what is not finite."""
+"""Gram of a few rows with others, and of few tiles of 16 x 16: both sides of every rule, columns around whole steps, packed rows, and
+what is not finite."""
 import numpy as np
 import pytest
 import torch
@@ -47,4 +48,34 @@ def test_what_is_not_finite_stays_in_its_entries():
     got = _gram(A, B)
     assert bool(torch.isnan(got[:, 5]).all()) and bool(torch.isinf(got[:, 7]).all())
     keep = [j for j in range(40) if j not in (5, 7)]
+    assert torch.equal(got[:, keep], want[:, keep])
+
+
+@pytest.mark.parametrize("Nx,Ny,cols", [
+    (9, 9, 65), (16, 16, 193), (17, 15, 31), (31, 33, 1025), (100, 100, 257), (256, 256, 129), (256, 257, 129), (40, 1300, 511), (9, 4096, 300),
+    (352, 0, 97), (353, 0, 97), (20, 0, 2049),
+])
+def test_few_tiles(Nx, Ny, cols):
+    """The bound of the larger tiles' sums: a random walk of 1 + K / 32 roundings of 2^-24 of r = sqrt(sum a^2 b^2) + |sum a b|, eight times."""
+    rng = np.random.default_rng(Nx + cols)
+    A = rng.standard_normal((Nx, cols)).astype(np.float32)
+    B = A if Ny == 0 else rng.standard_normal((Ny, cols)).astype(np.float32)
+    a = torch.from_numpy(A).cuda()
+    got = (rfsf.rfsf_ts_gram(a) if Ny == 0 else rfsf.rfsf_ts_gram(a, torch.from_numpy(B).cuda())).cpu().numpy()
+    A, B = A.astype(np.float64), B.astype(np.float64)
+    r = np.sqrt((A ** 2) @ (B ** 2).T) + np.abs(A @ B.T)
+    assert (np.abs(got - A @ B.T) / (8 * np.sqrt(1 + cols / 32) * 2.0 ** -24 * r)).max() <= 1
+    if Ny == 0:
+        assert np.array_equal(got, got.T)
+
+
+def test_few_tiles_with_what_is_not_finite():
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(2)
+    A, B = torch.rand((20, 333), generator=gen, device="cuda"), torch.rand((50, 333), generator=gen, device="cuda")
+    want = rfsf.rfsf_ts_gram(A, B).clone()
+    B[5, 332], B[7, 3] = float("nan"), float("inf")
+    got = rfsf.rfsf_ts_gram(A, B)
+    assert bool(torch.isnan(got[:, 5]).all()) and bool(torch.isinf(got[:, 7]).all())
+    keep = [j for j in range(50) if j not in (5, 7)]
     assert torch.equal(got[:, keep], want[:, keep])
