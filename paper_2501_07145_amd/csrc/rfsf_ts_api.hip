@@ -139,7 +139,10 @@ struct SketchCut { int pieces; int64_t pairs; bool joint, in_place, solo; };
 // 300 x 300 points 2, 3, 4: 102, 88, 95; 1280 x 257 1, 2, 3: 258, 236, 253; 1000 x 100, D = 256, four levels 1, 2, 3: 169, 160, 171. Pieces
 // of whole iterations, by their number in rounds of workgroups: 9, 3, 4 and 3 pieces, 107, 90, 249 and 165 us.)
 // Batches that leave CUs without a workgroup are left to the other kernels, whose wavefronts share out a piece's levels
-// (a single sequence of 100 points 27.8 us, 30.7 here; ten of 1000 49 and 56), and so are sequences that fill less than half
+// (a single sequence of 100 points 27.8 us, 30.7 here; ten of 1000 49 and 56); from 10 pairs per CU on, 20 with five levels or more, the
+// number of pieces is one that leaves none (60 x 200 points, D = 100, four levels: elsewhere, for want of workgroups, 43 us, 35 here; 40 x
+// 200, D = 256 50.5 and 47.7; 50 x 120, D = 128, three levels 29.8 and 26.1; but 25 x 120, D = 256 34.7 and 39.6, 50 x 120, D = 100, five
+// levels 35.4 and 37.8). Left to them as well are sequences that fill less than half
 // of an iteration (3000 x 14 points, 64 buckets, three levels 51 and 54) or, from 128 points per transform on, less than four
 // (1000 x 30 points, 256 buckets, four levels 64 and 70).
 // With three and four levels the other kernels' workgroups fill a CU, and less is gained. Pieces of less than one and a
@@ -155,12 +158,13 @@ SketchCut solo_cut(const rfsf_ts_shape *s, int P, int step)
     const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
     const int64_t per_cu = rfsf::sketch_fft_scan_solo_per_cu(s->M, s->F, P), own = step / rfsf::kSoloWaves;    // pairs of a wavefront
     if (2 * all_pairs < step || (P >= 128 && all_pairs < 4 * step)) return none;
+    const int64_t fewest = s->N * all_pairs > kCUs * (s->M > 4 ? 20 : 10) ? kCUs : 0;
     SketchCut best = none;
     double least = 0.0;
     for (int64_t want = 1; want <= kSplitPieces && want * step <= all_pairs + step; ++want) {
         const int64_t pairs = ((all_pairs + want - 1) / want + own - 1) / own * own, pieces = (all_pairs + pairs - 1) / pairs;
         // every piece, the last one too, has to hold its accumulators
-        if (pieces > kJoinInPlace || (pieces < 2 ? slots : pairs) * floats_per_pair < needed ||
+        if (pieces > kJoinInPlace || s->N * pieces <= fewest || (pieces < 2 ? slots : pairs) * floats_per_pair < needed ||
             (slots - (pieces - 1) * pairs) * floats_per_pair < needed)
             continue;
         const int64_t workgroups = s->N * pieces, full = workgroups / (kCUs * per_cu), rest = workgroups - full * kCUs * per_cu;

@@ -86,6 +86,8 @@ def test_large_angles_are_as_accurate_as_the_products(oracle, N, L, M, F, D):
 @pytest.mark.parametrize("N,L,d,M,F,D", [
     (100, 1000, 5, 5, 50, 100), (300, 301, 2, 5, 50, 100), (420, 85, 3, 4, 60, 64), (350, 277, 2, 4, 64, 128), (500, 150, 7, 4, 41, 128),
     (700, 131, 8, 4, 100, 256), (300, 120, 8, 2, 64, 64), (300, 120, 4, 2, 39, 100),
+    (60, 200, 8, 4, 50, 100), (60, 200, 8, 3, 50, 100), (50, 120, 8, 3, 60, 128), (40, 129, 8, 4, 128, 256),      # one to a CU just so
+    (51, 200, 8, 5, 50, 100), (52, 200, 8, 5, 50, 100), (64, 81, 8, 3, 64, 256), (65, 81, 8, 3, 64, 256),         # both sides of the line
 ])
 def test_pieces_that_end_at_any_pair(oracle, N, L, d, M, F, D):
     """Pieces of no whole number of iterations; slots of all distances; points in vector and in scalar registers."""
