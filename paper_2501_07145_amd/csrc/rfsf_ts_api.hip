@@ -121,7 +121,18 @@ constexpr int64_t kSplitSequences = 256, kCUs = 256;
 // An iteration of a workgroup alone on its CU takes about 3 us, a piece in the join 0.3: with p pairs in all and pieces of
 // i iterations, 3 i + 0.3 p / (i * pairs per iteration) is least at i^2 = p / (10 * pairs per iteration).
 constexpr int64_t kSplitPieces = 64, kJoinsPerIteration = 10;
-constexpr int kJoinInPlace = 16;    // more pieces are joined by a kernel of its own, which keeps several in flight
+// More pieces than most_joined_in_place are joined by a kernel of its own, a wavefront per 64 bins that keeps several pieces in
+// flight, fewer by the kernel of the final transforms, where a thread takes its bins one after the other: one or two of them
+// up to 512 points, three to five from 1024 on. (A single sequence, joined there and by its own kernel: 1024 buckets, five levels,
+// 5 pieces 49 and 46 us, 10 pieces 63 and 49; three levels, 10 pieces 43 and 40; 2048 buckets, four levels, 5 pieces 63 and 58, 10 pieces 72
+// and 59. 40 sequences in 6 pieces: 83 and 79, 99 and 94, three levels 57 both; 1024 buckets, two levels, 8 pieces 31 and 33. 256 buckets,
+// four levels, 13 pieces: 30.4 and 31.4.)
+constexpr int kJoinInPlace = 16;
+int most_joined_in_place(int M, int P, bool solo)
+{
+    if (solo || P <= 512) return kJoinInPlace;
+    return M > 3 ? 4 : 9;
+}
 // A single level only adds its increments up, a pair costs a thread a fortieth of that: whole sequences of fewer than this
 // many loads per thread are not split (60 points: 22 us whole, 25 split with 32 frequencies, 23 and 30 with 128; 150 points 33
 // and 32, 300 points 48 and 38, 512 frequencies, 60 points 64 and 52, all of 60 sequences in 256 buckets).
@@ -423,7 +434,7 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
                                              shape->D, order, out + n0 * shape->ld_out, shape->ld_out, nullptr, stream,
                                              cut) != hipSuccess)
                 return RFSF_E_HIP;
-            if (plan.pieces > kJoinInPlace) {
+            if (plan.pieces > most_joined_in_place(shape->M, P, plan.solo)) {
                 if (rfsf::launch_join_chain(cut.spectra ? cut.spectra : reinterpret_cast<float2 *>(dphi), cnt, plan.pieces,
                                             shape->M, bins, cut.seq_stride, cut.piece_stride, stream) != hipSuccess)
                     return RFSF_E_HIP;

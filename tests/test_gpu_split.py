@@ -66,6 +66,21 @@ def test_split_batches_match_the_oracle(oracle, N, L, d, M, F, D, order):
         assert np.all(err <= FP32_BLOCK_TOL)
 
 
+@pytest.mark.parametrize("N,L,d,M,F,D,order", [
+    (1, 24, 3, 4, 300, 1024, 1), (1, 31, 3, 4, 300, 1024, 1), (40, 30, 3, 4, 300, 1024, 2),        # four pieces, five, five
+    (2, 37, 3, 3, 300, 1024, 1), (2, 40, 3, 3, 300, 1024, 3), (1, 61, 9, 5, 500, 2048, 1),         # nine, ten, ten
+    (64, 800, 2, 4, 40, 1000, 1),                                                                  # pieces of the reported plan
+])
+def test_pieces_joined_by_either_kernel(oracle, N, L, d, M, F, D, order):
+    """Numbers of pieces on both sides of those that the kernel of the final transforms joins; each sequence's rows are its own."""
+    X, W, hash_, sign = _case(N + L + D, N, L, d, M, F, D)
+    got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 1.5, D, order=order).cpu().numpy()
+    sel = sorted({0, N // 2, N - 1})
+    want = oracle.features_ragged(X[sel], np.full(len(sel), L, dtype=np.int64), W, hash_, sign, 1.5, D, order=order)
+    err = block_errors(got[sel], want, M, D)
+    assert np.all(err <= FP32_BLOCK_TOL), err
+
+
 @pytest.mark.parametrize("N,L,M,F,D,split", [
     (200, 101, 4, 1000, 512, False),       # two pieces each, one workgroup per CU for the slots of 2000 coordinates: two rounds
     (200, 101, 4, 700, 256, False),        # the same in a transform of 512 points
