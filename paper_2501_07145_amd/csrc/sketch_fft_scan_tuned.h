@@ -803,6 +803,72 @@ constexpr Grouped grouped(int M, int D, int FPW, int PD)
 // Index of the accumulator of tensor positions a+1 .. l+1 (0-based a <= l) among those of a bin; a = 0 first.
 __host__ __device__ constexpr int acc_index(int M, int a, int l) { return a * M - a * (a - 1) / 2 + l - a; }
 
+// Sequences of their own lengths: workgroups start in the order of their numbers, and a long sequence that starts late keeps
+// its CU busy while the others are done. So they take the sequences by length, the longest first, in 64 classes (in any order
+// within a class, the same for all workgroups). Every workgroup finds the sequence whose turn it is by itself, so that no
+// memory has to hold an order: the classes of all sequences are read into registers, the class whose turn it is is found by halving.
+// Lengths between half and whole, in order of numbers and of lengths, sketch kernel: 1501 x 333 points, 500 buckets, four levels, order 2
+// 1286 and 1018 us, 1000 x 200, 1024 buckets, five levels 934 and 789; lengths from 1 on 992 and 702, 806 and 544. More sequences than fit
+// the registers are left in their order: with many rounds of workgroups there is little to gain (10000 x 200, 500 buckets, sorted
+// before the call 4007 -> 3880).
+constexpr int kTurnRows = 32, kLengthClasses = 64;           // sequences of a lane; classes
+template <int WAVES>
+__device__ __forceinline__ int sequence_in_turn(const int64_t *__restrict__ lengths, int64_t L, int count, int turn, int *scratch /* [3 * WAVES + 1] */)
+{
+    if (count > 64 * kTurnRows * WAVES) return turn;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int *found = scratch + 3 * WAVES;
+    if (tid == 0) *found = turn;
+    const float classes_per_point = (float)kLengthClasses / (float)L;
+    int cls[kTurnRows];
+    // rows that there are, in groups of four
+    auto each_row = [&](auto body) {
+#pragma unroll
+        for (int g = 0; g < kTurnRows; g += 4) {
+            if (64 * WAVES * g >= count) break;
+#pragma unroll
+            for (int r = g; r < g + 4; ++r) body(r);
+        }
+    };
+    each_row([&](int r) {
+        const int i = 64 * (r * WAVES + wave) + lane;
+        const int64_t given = lengths[i < count ? i : 0], points = given < 1 ? 1 : (given > L ? L : given);
+        const int c = (int)((float)(int)(L - points) * classes_per_point);
+        cls[r] = i < count ? (c < kLengthClasses ? c : kLengthClasses - 1) : kLengthClasses;
+    });
+    int mine = 0, left = turn, buffer = 0;                   // class whose turn it is, sequences of it that come first
+#pragma unroll 1
+    for (int bit = kLengthClasses / 2; bit > 0; bit >>= 1) {
+        int here = 0, before = 0;
+        each_row([&](int r) { here += __popcll(__ballot(cls[r] < mine + bit)); });
+        if (lane == 0) scratch[buffer + wave] = here;
+        __syncthreads();
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) before += scratch[buffer + w];
+        buffer = WAVES - buffer;
+        if (before <= turn) {
+            mine += bit;
+            left = turn - before;
+        }
+    }
+    int here = 0;
+    each_row([&](int r) { here += __popcll(__ballot(cls[r] == mine)); });
+    if (lane == 0) scratch[2 * WAVES + wave] = here;
+    __syncthreads();
+    for (int w = 0; w < wave; ++w) left -= scratch[2 * WAVES + w];
+    if (left >= 0 && left < here)
+        each_row([&](int r) {
+            const uint64_t hits = __ballot(cls[r] == mine);
+            const int first = __builtin_amdgcn_mbcnt_hi((uint32_t)(hits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)hits, 0));
+            if (cls[r] == mine && first == left) *found = 64 * (r * WAVES + wave) + lane;
+            left -= __popcll(hits);
+        });
+    __syncthreads();
+    const int n = __builtin_amdgcn_readfirstlane(*found);
+    __syncthreads();
+    return n;
+}
+
 // JOINT: the workgroup owns one piece of a sequence cut in time (TimeCut::mode 1) and runs the recurrence for
 // every first tensor position at once: per bin A^{(a..l)} += A^{(a..l-1)}(before the step) C_l for all a <= l. The
 // transforms, which are most of the work, are thus done once per step and level however many first positions
@@ -851,8 +917,15 @@ __global__ __launch_bounds__(64 * NTR)
     float2 *my_slot = wave_lds + slot_id * PS;
     char *my_slot_bytes = reinterpret_cast<char *>(my_slot);
     // the workgroup's row of out, its sequence and its piece of that sequence (one piece: the whole sequence)
-    const int64_t row_id = blockIdx.x;
-    const int64_t n = JOINT ? blockIdx.x / (unsigned)cut.pieces : row_id, piece = row_id - n * cut.pieces;
+    unsigned row_id = blockIdx.x;
+    // (not from 2048 points on, where it costs the loops below registers: 600 x 300 points, four levels, no lengths given 1770 -> 1797 us)
+    if constexpr (D < 2048) {
+        if (cut.by_length) {
+            const unsigned pieces = (unsigned)cut.pieces, turn = row_id / pieces;
+            row_id = sequence_in_turn<NTR>(lengths, L, gridDim.x / pieces, turn, reinterpret_cast<int *>(lds)) * pieces + (row_id - turn * pieces);
+        }
+    }
+    const int64_t n = JOINT ? row_id / (unsigned)cut.pieces : row_id, piece = row_id - n * cut.pieces;
     // this sequence's own number of points (variable-length batch: X is padded to L points, the steps beyond a
     // sequence's length do not exist); out-of-range entries are clamped, they are never used as addresses
     const int64_t Ln = lengths ? (lengths[n] < 1 ? 1 : (lengths[n] > L ? L : lengths[n])) : L;
