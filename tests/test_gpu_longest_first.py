@@ -1,7 +1,7 @@
 """Batches of sequences with lengths of their own are taken by length, the longest first: each workgroup finds its sequence by counting.
 Every sequence is still computed exactly once, with the same sums; the sizes sit at the edges of the rule: the smallest batch it
-applies to and the one below, the largest that fits the registers of one to eight wavefronts and the next, pieces, equal
-lengths, lengths out of range, and a class with all sequences but one."""
+applies to and the one below, the most sequences per point and one more, the largest batch that fits the registers of three and four
+wavefronts and the next, pieces, equal lengths, lengths out of range, and a class with all sequences but one."""
 import numpy as np
 import pytest
 import torch
@@ -29,9 +29,10 @@ def _lengths(kind, N, L, rng):
 
 @pytest.mark.parametrize("kind", ["any", "half", "equal", "outside", "one short", "one long"])
 @pytest.mark.parametrize("N,L,d,M,F,D,order", [
-    (256, 40, 3, 5, 50, 100, 1), (257, 40, 3, 5, 50, 100, 1), (300, 333, 3, 4, 250, 500, 2), (90, 300, 5, 5, 50, 100, 1),
-    (2048, 9, 2, 1, 40, 512, 1), (2049, 9, 2, 1, 40, 512, 1), (8192, 7, 2, 4, 30, 500, 1), (8193, 7, 2, 4, 30, 500, 1),
-    (8192, 9, 12, 5, 33, 100, 1), (700, 33, 12, 3, 60, 64, 1), (300, 35, 9, 2, 100, 1024, 3), (270, 24, 3, 3, 40, 2048, 1),
+    (256, 40, 3, 5, 120, 512, 1), (257, 40, 3, 5, 120, 512, 1), (300, 333, 3, 4, 250, 500, 2), (90, 300, 5, 5, 50, 100, 1),
+    (320, 10, 3, 3, 60, 1024, 1), (321, 10, 3, 3, 60, 1024, 1), (300, 35, 9, 2, 100, 1024, 3), (270, 24, 3, 3, 40, 2048, 1),
+    (6144, 192, 2, 3, 8, 512, 1), (6145, 193, 2, 3, 8, 512, 1), (8192, 256, 2, 4, 8, 500, 1), (8193, 257, 2, 4, 8, 500, 1),
+    (700, 33, 12, 3, 60, 64, 2), (2048, 80, 2, 1, 40, 512, 1),
 ])
 def test_every_sequence_once(N, L, d, M, F, D, order, kind):
     """Rows do not depend on the place of their sequence in the batch, and are those of whole sequences whose last point stays."""
