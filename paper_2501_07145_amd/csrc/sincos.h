@@ -41,25 +41,28 @@ __device__ __forceinline__ void sincos_reduced(float x, float &s, float &c)
 //
 // Instructions are chosen by what they cost: with 16 wavefronts per CU, multiply-adds, additions and three-operand logic of vector
 // registers take 2.6 cycles of a SIMD, the same with a scalar register as an operand 4.35, and so do conversions, roundings, shifts,
-// comparisons and selects. So the number of quarter-turns comes from adding 1.5 * 2^23 (for |x a| < 2^22, angles of up to 6e6), which leaves
-// its last two bits where the sine and the cosine are chosen and signed by logic, and all that is constant is in vector
-// registers (Quarters, made where the registers are free). 59 cycles instead of 80.
+// comparisons and selects. So the sine and the cosine are chosen and signed by logic, and all that is constant is in vector registers
+// (Quarters, made where the registers are free): 65 cycles instead of 80. Counting quarter-turns by adding 1.5 * 2^23 would spare
+// another 6 (1500 x 200 points, 64 to 256 buckets, one to eight channels: none to 2.5 % of the kernel), but the sum's last bits count to 2^22
+// only, angles of 6.6e6. As it is, angles of exact products up to 2^23 radians give a level's block to 5e-7, and up to 2^24, where the
+// product's rounding takes r past 1/2, to 9e-6, as in the kernel that takes its increments from memory.
 struct Quarters {
-    float a, b, magic;
+    float a, b;
     uint32_t top;
-    __device__ __forceinline__ Quarters(float a_, float b_) : a(a_), b(b_), magic(12582912.0f), top(0x80000000u)
+    __device__ __forceinline__ Quarters(float a_, float b_) : a(a_), b(b_), top(0x80000000u)
     {
-        asm volatile("" : "+v"(a), "+v"(b), "+v"(magic), "+v"(top));
+        asm volatile("" : "+v"(a), "+v"(b), "+v"(top));
     }
 };
 __device__ __forceinline__ void sincos_quarters(float x, const Quarters &turn, float &s, float &c)
 {
-    const float t = fmaf(x, turn.a, turn.magic), k = t - turn.magic, r = fmaf(x, turn.b, fmaf(x, turn.a, -k)), r2 = r * r;
+    const float k = rintf(x * turn.a), r = fmaf(x, turn.b, fmaf(x, turn.a, -k)), r2 = r * r;
     const float rest = r * fmaf(r2, fmaf(r2, fmaf(r2, -4.592289216816425e-3f, 7.967590540647507e-2f), -6.459629535675049e-1f), -6.54208633932285e-8f);
     const uint32_t S = __float_as_uint(fmaf(r, 1.57079637050628662109375f, rest));
     const uint32_t C = __float_as_uint(fmaf(r2, fmaf(r2, fmaf(r2, fmaf(r2, 9.040216682478786e-4f, -2.086028829216957e-2f), 2.5366923213005066e-1f),
                                                      -1.2337005138397217f), 1.0f));
-    const uint32_t q = __float_as_uint(t), odd = (uint32_t)__builtin_amdgcn_sbfe((int)q, 0, 1), signs = q << 30;
+    const int q = (int)k;
+    const uint32_t odd = (uint32_t)__builtin_amdgcn_sbfe(q, 0, 1), signs = (uint32_t)q << 30;
     // odd ? one : the other, then the sign bit: sin flips in quadrants 2, 3; cos in quadrants 1, 2
     const uint32_t ss = __builtin_amdgcn_bitop3_b32(odd, C, S, 0xca), cc = __builtin_amdgcn_bitop3_b32(odd, S, C, 0xca);
     s = __uint_as_float(__builtin_amdgcn_bitop3_b32(ss, signs, turn.top, 0x78));

@@ -98,18 +98,24 @@ def test_pieces_that_end_at_any_pair(oracle, N, L, d, M, F, D):
         assert np.all(err <= FP32_BLOCK_TOL), (n, err)
 
 
-def test_angles_of_millions(oracle):
-    """Quarter-turns are counted in the last bits of a 32-bit sum, up to 2^22 of them; products of these points and frequencies are
-    exact. (The number of quarter-turns in a unit is held to 2^-48 of itself, 1e-8 of a quarter-turn here.)"""
+@pytest.mark.parametrize("bits", [22, 23, 24])
+def test_angles_of_millions(oracle, bits):
+    """Angles of up to 2^bits radians from exact products, that is, on both sides of 2^22 quarter-turns and up to 2^23.3 of them. The
+    number of quarter-turns in a unit is held to 2^-48 of itself: 2^-25 of a quarter-turn at 2^23 of them, which is what the
+    reduced argument is rounded to as well. A single sequence, whose increments another kernel computes, has the same features."""
     N, L, M, F, D = 600, 40, 3, 32, 64
     rng = np.random.default_rng(4)
     X = rng.integers(-2 ** 20, 2 ** 20, size=(N, L, 1)).astype(np.float32)
-    W = (2.0 ** rng.integers(-3, 3, size=(M, 1, F)) * rng.choice((-1.0, 1.0), size=(M, 1, F))).astype(np.float32)
+    W = (2.0 ** rng.integers(bits - 25, bits - 19, size=(M, 1, F)) * rng.choice((-1.0, 1.0), size=(M, 1, F))).astype(np.float32)
     _, _, hash_, sign = _case(D, 1, 2, 1, M, F, D)
-    got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 1.0, D).cpu().numpy()
+    dev = [torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)]
+    got = rfsf.rfsf_ts_features(*dev, 1.0, D).cpu().numpy()
     for n in (0, 5, N - 1):
-        err = block_errors(got[n:n + 1], oracle.features(X[n:n + 1], W, hash_, sign, 1.0, D), M, D)
-        assert np.all(err <= FP32_BLOCK_TOL), (n, err)
+        want = oracle.features(X[n:n + 1], W, hash_, sign, 1.0, D)
+        one = rfsf.rfsf_ts_features(dev[0][n:n + 1].contiguous(), *dev[1:], 1.0, D).cpu().numpy()
+        for row in (got[n:n + 1], one):
+            err = block_errors(row, want, M, D)
+            assert np.all(err <= FP32_BLOCK_TOL), (n, err)
 
 
 def test_chunks_and_bf16_projection_take_the_same_sums(oracle):
