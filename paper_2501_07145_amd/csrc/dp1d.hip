@@ -208,13 +208,17 @@ void dp1d_features_kernel(
         for (int m = 0; m < M; ++m) row[1 + (int64_t)m * F + my_comp] = acc_state[m][tid] * scale;
 }
 
-// Many sequences: the frequencies of 64 S components, split for the 16-bit matrix instructions, stay in LDS while a workgroup's twelve
-// wavefronts go through sequences of their own, without meeting.
+// Many sequences: the frequencies of 64 S components, split for the 16-bit matrix instructions, stay in LDS while a workgroup's
+// wavefronts (twelve, eight from 19 channels on) go through sequences of their own, without meeting.
 // A float is the sum of three bfloat16 numbers and six of the nine products are added up, smallest first (as in gram.hip; the three
 // left out are below 2^-24 of the product): 8 instructions of 32 cycles for a tile of 32 points and 32 components of 17 channels
 // where v_mfma_f32_32x32x2f32 takes 9 of 64, with less error (angles of 10 radians, 17 channels: root mean square 7.7e-7 in 32 bits).
 // Two terms of half precision and three products would take 4, but err by 9.3e-7 there, 2.2e-7 instead of 1.0e-7 with 2 channels.
 // Splitting the frequencies again for every tile would cost what they spare.
+// The last term is 2^-16 of a number, and bfloat16 loses bits below 2^-126 as 32-bit numbers do: points of a tile that are all below
+// 2^-63 are multiplied by kRaise before they are split, and the angle's factor is divided by it. (Points of 2^-120 with a lengthscale
+// of 2^-120: root mean square error 1.5e-4 without, 2.9e-7 with it; a raised number meets the largest of 32 bits without overflow. The
+// same for the frequencies of a workgroup would take 0.2 to 0.4 us of calls of 4 to 7 us.)
 // Channels 2 k + half go to the lane's half of the products' columns, so that a lane splits the channels that it loads, in pairs p of
 // k = 2 p and 2 p + 1. What a pair multiplies with what is laid out in tuples of four registers (an operand): of four pairs
 // their hi, mid and lo; of a single one hi, mid, lo, hi; of two hi, hi, mid, mid and lo, lo, hi, hi.
@@ -226,6 +230,8 @@ typedef float floatx2 __attribute__((ext_vector_type(2)));
 // Wavefronts of a workgroup, one per CU: as many as hold the points' operands in registers.
 __host__ __device__ constexpr int resident_waves(int KSTEPS) { return KSTEPS <= 9 ? 12 : 8; }
 constexpr size_t kResidentLds = 160 * 1024;
+constexpr uint32_t kNotSmall = 0x60000000u;                  // exponent bits of 2^-63 and more (and of what is not finite)
+constexpr float kRaise = 0x1p48f;
 struct Terms { uint32_t hi, mid, lo; };
 __device__ __forceinline__ uint32_t round_pair(float a, float b)
 {
@@ -375,6 +381,15 @@ __global__ __launch_bounds__(64 * resident_waves(KSTEPS)) __attribute__((amdgpu_
         for (int m = 0; m < M; ++m) state[m * 128 + lane] = 0.f;
         for (int64_t t0 = 0; t0 < L; t0 += kRows) {
             const int nrow = (int)min((int64_t)kRows, L - t0);
+            uint32_t bits = 0;
+#pragma unroll
+            for (int k = 0; k < 2 * PAIRS; ++k) bits |= __float_as_uint(raw[k]);
+            float turns = scale_turns;
+            if (__ballot(bits & kNotSmall) == 0) {
+                turns *= 1.0f / kRaise;
+#pragma unroll
+                for (int k = 0; k < 2 * PAIRS; ++k) raw[k] *= kRaise;
+            }
             Terms xt[PAIRS];
 #pragma unroll
             for (int p = 0; p < PAIRS; ++p) xt[p] = split_pair(raw[2 * p], raw[2 * p + 1]);
@@ -401,8 +416,8 @@ __global__ __launch_bounds__(64 * resident_waves(KSTEPS)) __attribute__((amdgpu_
 #pragma unroll
                         for (int j = 0; j < 4; ++j) {
                             const auto both = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[0][4 * g + j]), __float_as_uint(acc[1][4 * g + j]), false, false);
-                            c[j] = sqrt2_cospi(fmaf(__uint_as_float(both[0]), scale_turns, b), rest);
-                            c[4 + j] = sqrt2_cospi(fmaf(__uint_as_float(both[1]), scale_turns, b), rest);
+                            c[j] = sqrt2_cospi(fmaf(__uint_as_float(both[0]), turns, b), rest);
+                            c[4 + j] = sqrt2_cospi(fmaf(__uint_as_float(both[1]), turns, b), rest);
                         }
                         if (g == 0) pc = t0 == 0 ? c[0] : pc;        // first point of the sequence: no increment
 #pragma unroll

@@ -68,3 +68,20 @@ def test_sums_of_products_are_as_good_as_in_32_bits():
     err = got[:, 1:].astype(np.float64) * math.sqrt(F) - math.sqrt(2.0) * (np.cos(angle) - 1.0)
     bound = math.sqrt(2.0) * np.abs(angle).max() * (8 * 2.0 ** -23 + 2.0 ** -24) + 2e-7
     assert np.abs(err).max() <= bound and np.sqrt(np.mean(err ** 2)) <= 1.5e-6, (np.abs(err).max(), np.sqrt(np.mean(err ** 2)))
+
+
+@pytest.mark.parametrize("x,w,scale", [(-120, 0, -120), (-125, 125, 0), (-110, 70, -40), (100, -100, 0), (-20, -105, -126), (-62, 62, 0), (-66, 66, 0)])
+def test_small_numbers_keep_their_bits(x, w, scale):
+    """The same angles from points of 2^x and frequencies of 2^w over a lengthscale of 2^scale: powers of two change no bit of a
+    32-bit product, so the bound of the test above holds. Points whose last 16-bit
+    term would be lost (1e-4 and more) are raised before they are split."""
+    assert x + w in (scale, scale + 1)
+    rng = np.random.default_rng(6)
+    N, d, F = 400, 17, 256
+    X = np.zeros((N, 2, d), np.float32)
+    X[:, 1] = rng.standard_normal((N, d)) * 2.0 ** x
+    W = (rng.standard_normal((1, d, F)) * 2.0 ** w).astype(np.float32)
+    got = rfsf.rfsf_dp1d_features(*(torch.from_numpy(a).cuda() for a in (X, W, np.zeros((1, F), np.float32))), 2.0 ** scale).cpu().numpy()
+    angle = (X[:, 1].astype(np.float64) @ W[0].astype(np.float64)) / 2.0 ** scale
+    err = got[:, 1:].astype(np.float64) * math.sqrt(F) - math.sqrt(2.0) * (np.cos(angle) - 1.0)
+    assert np.sqrt(np.mean(err ** 2)) <= 1.5e-6, np.sqrt(np.mean(err ** 2))
