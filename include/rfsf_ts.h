@@ -26,7 +26,7 @@
  *     enqueued; the outputs and the workspace are then unspecified, but nothing of the
  *     library touches them any more once `hip_stream` has drained.
  *   - Threads: the library keeps process-wide state (the optional profiling record, the
- *     LDS limits already raised) without locks. Calls from several host threads must
+ *     addresses of the static scratch) without locks. Calls from several host threads must
  *     be serialised by the caller; calls from one thread on several streams are fine.
  */
 #ifndef RFSF_TS_H

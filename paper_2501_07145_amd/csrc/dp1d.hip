@@ -229,7 +229,6 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 // Wavefronts of a workgroup, one per CU: as many as hold the points' operands in registers.
 __host__ __device__ constexpr int resident_waves(int KSTEPS) { return KSTEPS <= 9 ? 12 : 8; }
-constexpr size_t kResidentLds = 160 * 1024;
 constexpr uint32_t kNotSmall = 0x60000000u;                  // exponent bits of 2^-63 and more (and of what is not finite)
 constexpr float kRaise = 0x1p48f;
 struct Terms { uint32_t hi, mid, lo; };
@@ -622,7 +621,7 @@ Resident resident_plan(int64_t N, int64_t L, int M, int F)
     if (dearer * tiles * (double)blocks > (double)((L + kRows - 1) / kRows * ((F + 255) / 256 * 4))) return best;
     double most = 0.0;
     for (int S = 1; S <= 4; ++S) {
-        if (resident_lds(KSTEPS, M, S) > kResidentLds) break;
+        if (resident_lds(KSTEPS, M, S) > kLdsPerCu) break;
         const int64_t slabs = (blocks + S - 1) / S;
         if (resident_waves(KSTEPS) % S != 0 || slabs > 65535) continue;
         const int64_t per_slab = slabs < kCUs ? kCUs / slabs : 1, at_once = per_slab * (resident_waves(KSTEPS) / S);
@@ -638,13 +637,9 @@ hipError_t launch_resident(const Resident &plan, const float *X, const float *W,
                            int64_t L, int d, int M, int F, float *out, int64_t ld_out, hipStream_t stream)
 {
     const size_t lds = resident_lds(KSTEPS, M, plan.blocks);
-    static size_t raised = 0;
-    if (lds > 64 * 1024 && lds > raised) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(dp1d_resident_kernel<KSTEPS>),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        raised = lds;
-    }
+    static LdsLimit limit;
+    const hipError_t e = allow_lds(limit, reinterpret_cast<const void *>(dp1d_resident_kernel<KSTEPS>), lds);
+    if (e != hipSuccess) return e;
     const dim3 grid((unsigned)plan.per_slab, (unsigned)((F + 64 * plan.blocks - 1) / (64 * plan.blocks)));
     hipLaunchKernelGGL(dp1d_resident_kernel<KSTEPS>, grid, dim3(64 * resident_waves(KSTEPS)), lds, stream, X, W, bias, scale_turns, N, L, d, M, F,
                        plan.blocks, out, ld_out);
@@ -668,19 +663,15 @@ hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float 
     dim3 grid((unsigned)N, (unsigned)((F + 255) / 256));
     const size_t dyn = sizeof(float) * 2 * (size_t)M * 256;
     // static LDS of the kernel (X double buffer + transposition tiles) plus the per-level state can pass
-    // 64 KB for many levels on a wide state; the limit on the dynamic part is then raised once per kernel
+    // 64 KB for many levels on a wide state
 #define RFSF_LAUNCH_DP1D(KS)                                                                                  \
     do {                                                                                                      \
         const Resident plan = resident_plan<KS>(N, L, M, F);                                                  \
         if (plan.blocks > 0) return launch_resident<KS>(plan, X, W, bias, scale_turns, N, L, d, M, F, out, ld_out, stream); \
         constexpr size_t kStatic = sizeof(float) * (2 * kRows * ((2 * KS) | 1) + 4 * 64 * kTileStride);             \
-        static size_t raised = 0;                                                                             \
-        if (kStatic + dyn > 64 * 1024 && dyn > raised) {                                                      \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(dp1d_features_kernel<KS>),      \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);         \
-            if (e != hipSuccess) return e;                                                                    \
-            raised = dyn;                                                                                     \
-        }                                                                                                     \
+        static LdsLimit limit;                                                                                \
+        const hipError_t e = allow_lds(limit, reinterpret_cast<const void *>(dp1d_features_kernel<KS>), dyn, kStatic); \
+        if (e != hipSuccess) return e;                                                                        \
         hipLaunchKernelGGL(dp1d_features_kernel<KS>, grid, dim3(256), dyn, stream, X, W, bias,                \
                            scale_turns, L, d, M, F, out, ld_out);                                         \
     } while (0)

@@ -5,7 +5,27 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <atomic>
+
 namespace rfsf {
+
+constexpr size_t kLdsPerCu = 160 * 1024;
+constexpr int kMaxDevices = 64;
+// More LDS than 64 KB has to be allowed for every kernel, on each device that runs it. It is allowed to all that a CU has, once, so
+// that neither calls of other sizes nor other threads take it back. One LdsLimit per kernel; `fixed`: its LDS that is not dynamic.
+struct LdsLimit { std::atomic<bool> raised[kMaxDevices]; };
+inline hipError_t allow_lds(LdsLimit &limit, const void *kernel, size_t dynamic, size_t fixed = 0)
+{
+    if (dynamic + fixed <= 64 * 1024) return hipSuccess;
+    int device = 0;
+    hipError_t e = hipGetDevice(&device);
+    if (e != hipSuccess) return e;
+    const bool known = device >= 0 && device < kMaxDevices;
+    if (known && limit.raised[device].load(std::memory_order_relaxed)) return hipSuccess;
+    e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)(kLdsPerCu - fixed));
+    if (e == hipSuccess && known) limit.raised[device].store(true, std::memory_order_relaxed);
+    return e;
+}
 
 // A launch of the tuned sketch kernels may cut every sequence into `pieces` pieces of `pairs` pairs of time
 // steps each (workgroup v then owns piece v % pieces of sequence v / pieces). `mode` 1: instead of the features, the

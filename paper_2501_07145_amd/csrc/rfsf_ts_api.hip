@@ -491,7 +491,6 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
 
 // Scratch of the entry point that allocates nothing: one array per GPU, part of the library's code object.
 constexpr size_t kStaticScratchBytes = (size_t)64 << 20;
-constexpr int kMaxDevices = 64;
 }  // namespace
 
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -501,9 +500,9 @@ namespace {
 // at its own address); nullptr if the lookup fails.
 void *static_scratch_address()
 {
-    static void *address[kMaxDevices] = {};
+    static void *address[rfsf::kMaxDevices] = {};
     int dev = -1;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return nullptr;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= rfsf::kMaxDevices) return nullptr;
     if (!address[dev]) {
         void *ptr = nullptr;
         if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess) return nullptr;

@@ -182,7 +182,6 @@ __global__ void validate_tables_kernel(const int32_t *hash, const float *sign, i
 }  // namespace
 
 namespace {
-using tuned::kLdsPerCu;
 size_t generic_lds_bytes(int D, int order) { return sizeof(float2) * (size_t)generic_buffer_elems(D, order); }
 bool generic_in_global(int D, int order) { return generic_lds_bytes(D, order) > kLdsPerCu; }
 }  // namespace
@@ -329,15 +328,9 @@ bool sketch_table_job(const int32_t *hash, int M, int F, int D, int Dout, uint32
 hipError_t launch_build_tables(const TableJob &job, int M, hipStream_t stream)
 {
     const size_t lds = table_lds_bytes(job.F, job.Dout);
-    if (lds > 64 * 1024) {
-        static size_t granted = 0;
-        if (lds > granted) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(build_tables_kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            granted = lds;
-        }
-    }
+    static LdsLimit limit;
+    const hipError_t e = allow_lds(limit, reinterpret_cast<const void *>(build_tables_kernel), lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(build_tables_kernel, dim3((unsigned)M), dim3(kTableThreads), lds, stream, job);
     return hipGetLastError();
 }
@@ -375,13 +368,9 @@ hipError_t launch_sketch_fft_scan(const float *dphi, const int32_t *hash, const 
     if (cut.pieces != 1 || cut.row_levels != M || cut.mode != 0) return hipErrorInvalidValue;      // and so do cuts in time
     const bool in_global = generic_in_global(D, order);
     const size_t lds = in_global ? 0 : generic_lds_bytes(D, order);
-    static size_t lds_granted = 0;        // per process; raising the limit is idempotent
-    if (lds > 64 * 1024 && lds > lds_granted) {
-        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(sketch_fft_scan_generic),
-                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-        if (e != hipSuccess) return e;
-        lds_granted = lds;
-    }
+    static LdsLimit limit;
+    const hipError_t e = allow_lds(limit, reinterpret_cast<const void *>(sketch_fft_scan_generic), lds);
+    if (e != hipSuccess) return e;
     float2 *acc = reinterpret_cast<float2 *>(state);
     float2 *scratch = in_global ? acc + n_seq * M * (D / 2 + 1) : nullptr;
     hipLaunchKernelGGL(sketch_fft_scan_generic, dim3((unsigned)n_seq), dim3(256), lds, stream,

@@ -331,15 +331,9 @@ hipError_t launch_wide(const float *dphi, const uint32_t *table, int64_t n_seq, 
     constexpr int S = 1 << LOG2S, NTR = wide_levels_in_flight(M);
     const size_t lds = wide_lds_bytes(S, M, F);
     auto kernel = sketch_fft_scan_wide_kernel<LOG2S, M, ORDER, NTR>;
-    if (lds > 64 * 1024) {
-        static size_t raised = 0;
-        if (lds > raised) {
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kernel),
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-            if (e != hipSuccess) return e;
-            raised = lds;
-        }
-    }
+    static LdsLimit limit;
+    const hipError_t e = allow_lds(limit, reinterpret_cast<const void *>(kernel), lds);
+    if (e != hipSuccess) return e;
     hipLaunchKernelGGL(kernel, dim3((unsigned)(n_seq * cut.pieces)), dim3(64 * S * NTR), lds, stream, dphi, table, L, lengths, F, Dout, out, ld_out, cut);
     return hipGetLastError();
 }
