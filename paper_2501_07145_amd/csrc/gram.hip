@@ -382,16 +382,31 @@ __global__ __launch_bounds__(64 * NW, NR <= 2 ? 4 : 2) void gram_small(GramArgs 
 }
 
 // ---------------------------------------------------------------------------------------------------------------
-// Up to eight rows on one side (a request against stored features): a wavefront takes two rows of the other side (four of many, against more than four) and all of the few,
-// four columns of each per lane and step, adds up in plain 32-bit multiply-adds and then over its lanes; of few rows its
-// workgroup's wavefronts share out the columns (SPLIT). What bounds it is reading the long side once, and for hundreds of rows its
-// latency; tiles leave most of the chip without work and pad the short side to 32.
-// In tiles and here, us a call: 1 x 1000, 1025 columns 8.1 and 6.5, 1 x 30, 5121 columns 24 and 6.4, 3 x 40, 10241 columns 48 and 7.2, 1 x
-// 10000, 5121 columns 76 and 36 (5.7 TB/s), 8 x 10000 80 and 62. Errors against 64 bits 1.7e-7 and 1.0e-7 with 1025 columns, 3.9e-7 and
-// 1.7e-7 with 5121, 8.0e-8 both with 301, but 5.6e-8 and 8.1e-8 with 193, hence kThinColumns. Five to eight rows against thousands take
-// as long in tiles up to some 1000 columns (8 x 3000, 513 columns 6.5 and 6.9, 7 x 9000, 1025 15.4 and 15.8).
+// Up to eight rows on one side (a request against stored features): a wavefront takes two rows of the other side (four of
+// kThinMany and more, against more than four) and all of the few, four columns of each per lane and step, adds up in plain 32-bit
+// multiply-adds and then over its lanes; of fewer than kThinSplit rows its workgroup's wavefronts share out the columns (SPLIT). What
+// bounds it is reading the long side once, and for hundreds of rows its latency; tiles leave most of the chip without work and pad the
+// short side to 16 or 32.
+// In tiles of 32 x 32 and more and here, us a call: 1 x 1000, 1025 columns 8.1 and 6.5, 1 x 30, 5121 columns 24 and 6.4, 3 x 40, 10241
+// columns 48 and 7.2, 1 x 10000, 5121 columns 76 and 36 (5.7 TB/s), 8 x 10000 80 and 62. Errors against 64 bits, of a row's length times
+// another's: 4.7e-9 and 4.5e-9 with 320 columns, 5.1e-9 and 2.7e-9 with 1025, 5.3e-9 and 2.7e-9 with 2049, but 4.5e-9 and 5.7e-9 with
+// 192, hence kThinColumns.
 constexpr int kFew = 8, kThinWaves = 4;
 constexpr int64_t kThinColumns = 320, kThinWide = 2048, kThinSplit = 2048, kThinMany = 8192;
+// Where it is the faster way: for one and two rows everywhere; for more it takes as many loads as there are rows, while a tile's cost
+// hardly grows. 768 workgroups run at once, the rows of 6144 (12288 of those of four per wavefront), and up to 8192 rows tiles are of 32 x 32,
+// one per CU, up to 16384 of 64 x 64. (Tiles and here, us in a graph: 8 x 2047, 513 columns 6.4 and 7.8, 901 8.4 and 8.1, 8 x 300, 513 6.3
+// and 6.0; 8 x 4097, 2049 14.6 and 11.9, 5 x 5500, 4097 23.3 and 21.9, 8 x 5500, 3001 18.3 and 19.6; 8 x 7000, 2049 14.8 and 18.3, 5121 30
+// and 39, 10241 69 and 103; 8 x 10000, 2049 29 and 23; 8 x 14000, 2049 30.3 and 31.2, 2561 36.3 and 35.0; 4 x 8192, 7169 38.7 and 38.4,
+// and past the last-level cache 8193 45 and 47, 10241 72 and 78; 4 x 6000, 10241 52 and 41.)
+bool thin_pays(int64_t few, int64_t many, int64_t ncols)
+{
+    if (few <= 2 || ncols < kThinColumns) return ncols >= kThinColumns;
+    if (few <= 4) return many <= 6144 || many > 8192 || 4 * many * ncols <= (int64_t)256 << 20;
+    if (many < kThinSplit) return ncols >= 576 + many / 7;
+    if (many <= 8192) return ncols >= kThinWide && many <= (few <= 6 ? 6144 : 4096);
+    return ncols >= (many > 12288 && many <= 16384 ? 2304 : kThinWide);
+}
 template <int FEW, int ROWS, bool SPLIT>
 __global__ __launch_bounds__(64 * kThinWaves) void gram_thin(const float *__restrict__ few, const float *__restrict__ many, float *__restrict__ C,
                                                              int64_t n_few, int64_t n_many, int64_t K, int64_t ld_few, int64_t ld_many,
@@ -1106,7 +1121,7 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
         return (sym ? ti * (ti + 1) / 2 : ti * tj) * batch;
     };
     const int64_t few = std::min(Nx, Ny), many = std::max(Nx, Ny);
-    if (!rows_add_up && batch == 1 && few <= kFew && ncols >= (few <= 4 || many < kThinSplit ? kThinColumns : kThinWide)) return launch_thin(g, stream);
+    if (!rows_add_up && batch == 1 && few <= kFew && thin_pays(few, many, ncols)) return launch_thin(g, stream);
     // Large tiles run one per CU at a time or, faster together, two; with `rounds` = their number over 256, rounded up,
     // three terms take as long as about 1340 tiles of 64 x 64 per round do. Two terms: 64 x 64 tiles take about
     // 0.57 (105 + columns) / 10000 us each and 12 more, large ones 20 us and 0.76 (200 + columns) / 17.5 us a round, fitted

@@ -39,6 +39,22 @@ def test_sums_match_64_bits(few, many, cols):
     assert torch.equal(own, own.T)
 
 
+@pytest.mark.parametrize("few,many,cols,thin", [
+    (8, 2047, 867, False), (8, 2047, 868, True), (5, 60, 583, False), (5, 60, 584, True), (8, 4096, 2048, True), (8, 4097, 2049, False),
+    (6, 6144, 2048, True), (6, 6145, 2049, False), (5, 8192, 5121, False), (8, 8193, 2048, True), (8, 12289, 2303, False), (5, 14000, 2304, True),
+    (4, 8192, 8192, True), (4, 8192, 8193, False), (3, 6144, 11000, True), (4, 8193, 8200, True), (2, 7000, 9700, True),
+])
+def test_tiles_are_taken_where_they_are_faster(few, many, cols, thin):
+    """A ninth row leaves the others in tiles, whose rows do not depend on each other: the same bits only where both are."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(many + cols)
+    A = torch.randn((9, cols), generator=gen, device="cuda")
+    B = torch.randn((many, cols), generator=gen, device="cuda")
+    for got, tiles in ((_gram(A[:few], B), _gram(A, B)[:few]), (_gram(B, A[:few]), _gram(B, A)[:, :few])):
+        assert torch.equal(got, tiles) != thin
+        assert float((got - tiles).abs().max()) <= 2e-6 * 2 * cols
+
+
 def test_what_is_not_finite_stays_in_its_entries():
     gen = torch.Generator(device="cuda")
     gen.manual_seed(1)
