@@ -50,7 +50,6 @@ struct TimeCut {
     int mode, join;
     int64_t seq_stride, piece_stride;
     bool solo = false;           // mode 1: the kernel whose wavefronts work by themselves (sketch_fft_scan_solo.h)
-    bool by_length = false;      // modes 0 and 1: the longest sequences first (sequence_in_turn)
     Points points = {};          // ... and which, with X set, computes the increments itself: none are in memory
     static TimeCut whole(int64_t L, int M) { return {1, M, (L + 1) / 2, nullptr, 0, 1, 0, 0}; }
 };

@@ -137,15 +137,6 @@ int most_joined_in_place(int M, int P, bool solo)
 // many loads per thread are not split (60 points: 22 us whole, 25 split with 32 frequencies, 23 and 30 with 128; 150 points 33
 // and 32, 300 points 48 and 38, 512 frequencies, 60 points 64 and 52, all of 60 sequences in 256 buckets).
 constexpr int64_t kSumLoads = 128;
-// Sequences of their own lengths, the longest first (sequence_in_turn): where there are more workgroups than CUs, and sequences long
-// enough for the few microseconds that a workgroup takes to find its own, which grow with their number. (Lengths from half to whole, in order
-// of their numbers and of length: 1000 x 40 points, 1024 buckets, five levels 213 and 191 us, 4000 x 40 726 both, and 885 and 920 with
-// equal lengths; 2000 x 100, 256 buckets in 512 points, two levels 167 and 155, one level 82 and 88. The kernel whose wavefronts work
-// by themselves is short: 1000 x 100, 256 buckets 168 and 180, 4000 x 40, 100 buckets 166 and 187, 300 x 500 128 and 122.)
-bool longest_first(const rfsf_ts_shape *s, int64_t sequences, int64_t pieces, bool solo)
-{
-    return !solo && s->M > 1 && sequences * pieces > kCUs && sequences <= 32 * s->L && s->L <= 0x7fffffffLL;
-}
 // Order of the recurrence that a launch runs: a single level is the same in all of them.
 int kernel_order(const rfsf_ts_shape *s) { return s->order < 2 || s->M == 1 ? 1 : s->order; }
 struct SketchCut { int pieces; int64_t pairs; bool joint, in_place, solo; };
@@ -416,11 +407,10 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
         const int64_t *chunk_lengths = lengths ? lengths + n0 : nullptr;
         if (plan.pieces == 1 && !plan.solo) {
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
-            rfsf::TimeCut cut = rfsf::TimeCut::whole(shape->L, shape->M);
-            cut.by_length = chunk_lengths && longest_first(shape, cnt, 1, false);
             if (rfsf::launch_sketch_fft_scan(dphi, hash, sign, table, cnt, shape->L, chunk_lengths,
                                              shape->M, shape->F, P, shape->D, kernel_order(shape),
-                                             out + n0 * shape->ld_out, shape->ld_out, state, stream, cut) != hipSuccess)
+                                             out + n0 * shape->ld_out, shape->ld_out, state, stream,
+                                             rfsf::TimeCut::whole(shape->L, shape->M)) != hipSuccess)
                 return RFSF_E_HIP;
         } else if (plan.joint) {
             // sequences cut in time: the accumulators of all ranges of tensor positions of every piece, the join (of many
@@ -428,7 +418,6 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
             rfsf::ProfileScope scope(rfsf::kSketchFftScan, stream, may_create);
             const int order = kernel_order(shape), bins = P / 2 + 1;
             rfsf::TimeCut cut = {plan.pieces, shape->M, plan.pairs, nullptr, 1, plan.pieces, 0, 0, plan.solo};
-            cut.by_length = chunk_lengths && longest_first(shape, cnt, plan.pieces, plan.solo);
             if (fused) {
                 const double quarters = 0.63661977236758134308 / (double)lengthscale;
                 cut.points = {X + n0 * shape->L * shape->d, W, sign, shape->d, (float)quarters, (float)(quarters - (double)(float)quarters)};
@@ -453,7 +442,6 @@ int features_impl(const rfsf_ts_shape *shape, const float *X, const int64_t *len
             }
             cut.pieces = 1;
             cut.mode = 2;
-            cut.by_length = false;
             if (rfsf::launch_sketch_fft_scan(dphi, hash, sign, table, cnt, shape->L, chunk_lengths, shape->M, shape->F, P,
                                              shape->D, order, out + n0 * shape->ld_out, shape->ld_out, nullptr, stream,
                                              cut) != hipSuccess)

@@ -809,12 +809,28 @@ __host__ __device__ constexpr int acc_index(int M, int a, int l) { return a * M 
 // Lengths between half and whole, in order of numbers and of lengths, sketch kernel: 1501 x 333 points, 500 buckets, four levels, order 2
 // 1286 and 1018 us, 1000 x 200, 1024 buckets, five levels 934 and 789; lengths from 1 on 992 and 702, 806 and 544. More sequences than fit
 // the registers are left in their order: with many rounds of workgroups there is little to gain (10000 x 200, 500 buckets, sorted
-// before the call 4007 -> 3880).
+// before the call 4007 -> 3880). The kernel whose wavefronts work by themselves is short and keeps its order (1000 x 100, 256 buckets 168
+// and 180, 4000 x 40, 100 buckets 166 and 187, 300 x 500 128 and 122).
 constexpr int kTurnRows = 32, kLengthClasses = 64;           // sequences of a lane; classes
+template <int M, int D> constexpr bool kTurns = M > 1 && D < 2048;
+constexpr int64_t kTurnWork = 65536;
+// Where that pays, in a kernel of its own (for batches whose sequences have one length the search would only cost registers: 600 x 200
+// points, 512 buckets, five levels 430 and 441 us): more workgroups than CUs, and enough work on each for the few microseconds of the
+// search, counted in points of its transforms times the workgroups on its CU, of which `held` fit. (Sketch kernels and projection, lengths
+// from half, from one and all the same, us in order of numbers and of length: 600 x 50 points, 512 buckets, five levels 105 and 96, 87 and 75,
+// 121 and 123; 1500 x 50, 1000, three 267 and 246, 219 and 186, 303 and 310; 600 x 300, 1024, five 824 and 760, 608 and 489, 950 and
+// 955; below the line 320 x 10, 1024, three 29.4 and 32.4 with lengths from half, 600 x 20, 1024, two 0.86 times as fast. Over 131 shapes
+// above it 1.07, 1.18 and 0.99 times as fast, over 72 below 0.97, 1.00 and 0.93.)
+inline bool turns_pay(int M, int D, int waves, int64_t held, int64_t sequences, int64_t pieces, int64_t pairs, int64_t L)
+{
+    constexpr int64_t kCUs = 256;
+    const int64_t workgroups = sequences * pieces, at_once = workgroups < held * kCUs ? workgroups : held * kCUs;
+    return workgroups > kCUs && (double)(M * pairs * D) * (double)at_once >= (double)(kTurnWork * kCUs) && sequences <= 64 * kTurnRows * waves &&
+           L <= 0x7fffffffLL;
+}
 template <int WAVES>
 __device__ __forceinline__ int sequence_in_turn(const int64_t *__restrict__ lengths, int64_t L, int count, int turn, int *scratch /* [3 * WAVES + 1] */)
 {
-    if (count > 64 * kTurnRows * WAVES) return turn;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int *found = scratch + 3 * WAVES;
     if (tid == 0) *found = turn;
@@ -835,6 +851,23 @@ __device__ __forceinline__ int sequence_in_turn(const int64_t *__restrict__ leng
         const int c = (int)((float)(int)(L - points) * classes_per_point);
         cls[r] = i < count ? (c < kLengthClasses ? c : kLengthClasses - 1) : kLengthClasses;
     });
+    // all in one class: in order of their numbers, which this finds at half the cost
+    {
+        const int64_t given = lengths[0], points = given < 1 ? 1 : (given > L ? L : given);
+        const int c = (int)((float)(int)(L - points) * classes_per_point), one = c < kLengthClasses ? c : kLengthClasses - 1;
+        int others = 0;
+        each_row([&](int r) { others |= cls[r] != one && cls[r] != kLengthClasses ? 1 : 0; });
+        const int any = __ballot(others) != 0 ? 1 : 0;
+        if (lane == 0) scratch[2 * WAVES + wave] = any;
+        __syncthreads();
+        int sum = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) sum += scratch[2 * WAVES + w];
+        if (sum == 0) {
+            __syncthreads();
+            return turn;
+        }
+    }
     int mine = 0, left = turn, buffer = 0;                   // class whose turn it is, sequences of it that come first
 #pragma unroll 1
     for (int bit = kLengthClasses / 2; bit > 0; bit >>= 1) {
@@ -874,7 +907,7 @@ __device__ __forceinline__ int sequence_in_turn(const int64_t *__restrict__ leng
 // need them (one launch per first position did (M+1)/2 times as many: 10 x 1e5 steps, D = 100, five levels 2.68 ms, with
 // groups 1.00). In mode 2 the same kernel joins a sequence's pieces and runs the final
 // transforms.
-template <int LOG2D, int M, int ORDER, int NTR, bool JOINT>
+template <int LOG2D, int M, int ORDER, int NTR, bool JOINT, bool BY_LENGTH>
 __global__ __launch_bounds__(64 * NTR)
     __attribute__((amdgpu_waves_per_eu(kernel_min_waves<LOG2D, M, NTR, JOINT>(),
                                        kernel_min_waves<LOG2D, M, NTR, JOINT>() > 4 ? 8 : 4))) void sketch_fft_scan_kernel(
@@ -916,15 +949,12 @@ __global__ __launch_bounds__(64 * NTR)
     float2 *my_slot = wave_lds + slot_id * PS;
     char *my_slot_bytes = reinterpret_cast<char *>(my_slot);
     // the workgroup's row of out, its sequence and its piece of that sequence (one piece: the whole sequence)
-    unsigned row_id = blockIdx.x;
-    // (not from 2048 points on, where it costs the loops below registers: 600 x 300 points, four levels, no lengths given 1770 -> 1797 us)
-    if constexpr (D < 2048) {
-        if (cut.by_length) {
-            const unsigned pieces = (unsigned)cut.pieces, turn = row_id / pieces;
-            row_id = sequence_in_turn<NTR>(lengths, L, gridDim.x / pieces, turn, reinterpret_cast<int *>(lds)) * pieces + (row_id - turn * pieces);
-        }
+    int64_t row_id = blockIdx.x;
+    if constexpr (BY_LENGTH) {
+        const unsigned pieces = (unsigned)cut.pieces, turn = blockIdx.x / pieces;
+        row_id = (unsigned)sequence_in_turn<NTR>(lengths, L, (int)(gridDim.x / pieces), (int)turn, reinterpret_cast<int *>(lds)) * pieces + (blockIdx.x - turn * pieces);
     }
-    const int64_t n = JOINT ? row_id / (unsigned)cut.pieces : row_id, piece = row_id - n * cut.pieces;
+    const int64_t n = JOINT ? (unsigned)row_id / (unsigned)cut.pieces : row_id, piece = row_id - n * cut.pieces;
     // this sequence's own number of points (variable-length batch: X is padded to L points, the steps beyond a
     // sequence's length do not exist); out-of-range entries are clamped, they are never used as addresses
     const int64_t Ln = lengths ? (lengths[n] < 1 ? 1 : (lengths[n] > L ? L : lengths[n])) : L;

@@ -1,7 +1,8 @@
 """Batches of sequences with lengths of their own are taken by length, the longest first: each workgroup finds its sequence by counting.
 Every sequence is still computed exactly once, with the same sums; the sizes sit at the edges of the rule: the smallest batch it
-applies to and the one below, the most sequences per point and one more, the largest batch that fits the registers of three and four
-wavefronts and the next, pieces, equal lengths, lengths out of range, and a class with all sequences but one."""
+applies to and the one below, the least work and a pair of steps less, the largest batch that fits the registers of three and four
+wavefronts and the next, pieces, equal lengths, lengths out of range, and a class with all sequences but one. Small sequences are taken in
+order of their numbers, which gives the same rows."""
 import numpy as np
 import pytest
 import torch
@@ -27,13 +28,17 @@ def _lengths(kind, N, L, rng):
     return lengths
 
 
-@pytest.mark.parametrize("kind", ["any", "half", "equal", "outside", "one short", "one long"])
-@pytest.mark.parametrize("N,L,d,M,F,D,order", [
+@pytest.mark.parametrize("N,L,d,M,F,D,order,kind", [
+    shape + (kind,) for kind in ("any", "equal") for shape in [
+        (256, 300, 3, 5, 60, 512, 1), (257, 300, 3, 5, 60, 512, 1), (1100, 60, 3, 3, 60, 1024, 1), (520, 66, 3, 4, 100, 500, 2),
+        (64, 2100, 3, 3, 60, 512, 1), (200, 900, 3, 4, 40, 500, 1), (1200, 250, 3, 5, 60, 64, 2),          # pieces; grouped transforms
+        (300, 108, 3, 2, 20, 512, 1), (300, 110, 3, 2, 20, 512, 1), (260, 62, 3, 2, 30, 1000, 3)]
+] + [shape + (kind,) for kind in ("any", "half", "equal", "outside", "one short", "one long") for shape in [
     (256, 40, 3, 5, 120, 512, 1), (257, 40, 3, 5, 120, 512, 1), (300, 333, 3, 4, 250, 500, 2), (90, 300, 5, 5, 50, 100, 1),
     (320, 10, 3, 3, 60, 1024, 1), (321, 10, 3, 3, 60, 1024, 1), (300, 35, 9, 2, 100, 1024, 3), (270, 24, 3, 3, 40, 2048, 1),
     (6144, 192, 2, 3, 8, 512, 1), (6145, 193, 2, 3, 8, 512, 1), (8192, 256, 2, 4, 8, 500, 1), (8193, 257, 2, 4, 8, 500, 1),
     (700, 33, 12, 3, 60, 64, 2), (2048, 80, 2, 1, 40, 512, 1),
-])
+]])
 def test_every_sequence_once(N, L, d, M, F, D, order, kind):
     """Rows do not depend on the place of their sequence in the batch, and are those of whole sequences whose last point stays."""
     rng = np.random.default_rng(N + L + D)
