@@ -142,16 +142,20 @@ int kernel_order(const rfsf_ts_shape *s) { return s->order < 2 || s->M == 1 ? 1 
 struct SketchCut { int pieces; int64_t pairs; bool joint, in_place, solo; };
 // The cut for the kernel whose wavefronts work by themselves (csrc/sketch_fft_scan_solo.h), which takes whole sequences and
 // pieces alike and `step` pairs of steps per iteration of a workgroup. Time is counted in iterations of a CU that holds as many
-// workgroups as it can: with n of them an iteration takes (1.5 + n) / (1.5 + that many) (D = 100, five levels, 2 to 4 on a CU 6.1,
-// 7.9 and 9.6 us); the beginning and the end of a workgroup take 0.6 of one, the join 0.1 per piece and 18 MB of accumulators. What is
+// workgroups as it can: with n of them an iteration takes (2 + n) / (2 + that many) (D = 100, five levels, 2 to 4 on a CU 6.1,
+// 7.9 and 9.6 us); the beginning and the end of a workgroup take 0.4 of one, the join 0.05 per piece and 18 MB of accumulators. What is
 // left over when all CUs have been filled a whole number of times is spread over them, so that pieces are chosen to leave a little
-// over or nearly nothing; they end at any pair, wavefronts take two pairs more or less than each other.
+// over or nearly nothing. Pieces end at a multiple of the pairs that a wavefront takes per iteration (step / 4); each of its wavefronts takes a
+// quarter, rounded up to such a multiple, and the last ones up to three times that less, or nothing: where one of them has an iteration more
+// than others, that counts 0.6.
 // (100 x 1000 points, D = 100, five levels: 8, 9, 10, 11 pieces, 800 to 1100 workgroups on 256 CUs that hold four, 106, 97, 93, 117 us;
-// 300 x 300 points 2, 3, 4: 102, 88, 95; 1280 x 257 1, 2, 3: 258, 236, 253; 1000 x 100, D = 256, four levels 1, 2, 3: 169, 160, 171. Pieces
-// of whole iterations, by their number in rounds of workgroups: 9, 3, 4 and 3 pieces, 107, 90, 249 and 165 us.)
+// 300 x 300 points 2, 3, 4: 102, 88, 95; 1280 x 257 1, 2, 3: 258, 236, 253; 59 x 172, D = 64, five levels 4, 6, 8: 31, 32, 28. Over 726 shapes
+// of 12 to 3000 sequences whose numbers of pieces were all timed, the one chosen is 1.8 % slower than the best on average, by 7 % or more for
+// one in ten.)
 // Batches that leave CUs without a workgroup are left to the other kernels, whose wavefronts share out a piece's levels
-// (a single sequence of 100 points 27.8 us, 30.7 here; ten of 1000 49 and 56); from 10 pairs per CU on, 20 with five levels or more, the
-// number of pieces is one that leaves none (60 x 200 points, D = 100, four levels: elsewhere, for want of workgroups, 43 us, 35 here; 40 x
+// (a single sequence of 100 points 27.8 us, 30.7 here; ten of 1000 49 and 56); from 7 pairs per CU on, 15 with five levels or
+// more and few frequencies, the number of pieces is one that leaves none (59 x 172, D = 64, five levels, in the other kernels 39 us, 28 here; 39 x 179,
+// D = 100, six, 59 frequencies 42 and 36; 60 x 200 points, D = 100, four levels: elsewhere, for want of workgroups, 43 us, 35 here; 40 x
 // 200, D = 256 50.5 and 47.7; 50 x 120, D = 128, three levels 29.8 and 26.1; but 25 x 120, D = 256 34.7 and 39.6, 50 x 120, D = 100, five
 // levels 35.4 and 37.8). Left to them as well are sequences that fill less than half
 // of an iteration (3000 x 14 points, 64 buckets, three levels 51 and 54) or, from 128 points per transform on, less than four
@@ -160,7 +164,8 @@ struct SketchCut { int pieces; int64_t pairs; bool joint, in_place, solo; };
 // half iterations are left to them where there is nothing else to gain either: where the increments come from memory (whole
 // sequences; 1186 x 31 points, 20 channels, 56 frequencies, 64 buckets, three levels 54 and 66 us, 5816 x 66, 3, 73, 100 365 and 420;
 // of 38 such calls 29 were slower by more than 5 %, one faster), or where they are so few that projecting them costs less than
-// doing it on idle lanes, fewer than four frequencies per channel (774 x 43, 8, 13, 100, three levels 33 and 43; 23 and 5 of 37).
+// doing it on idle lanes, fewer than four frequencies per channel (774 x 43, 8, 13, 100, three levels 33 and 43; 23 and 5 of 37); longer
+// sequences are then cut in fewer pieces (90 x 165, 6 channels, 18 frequencies, 128 buckets, four levels 30, elsewhere 36; 318 x 56, 8, 24, 100 41 and 36).
 bool solo_fused(const rfsf_ts_shape *s, int P) { return s->rff_bf16 == 0 && rfsf::sketch_fft_scan_solo_fused(s->F, s->d, P); }
 SketchCut solo_cut(const rfsf_ts_shape *s, int P, int step)
 {
@@ -169,29 +174,29 @@ SketchCut solo_cut(const rfsf_ts_shape *s, int P, int step)
     const int64_t needed = (int64_t)s->M * (s->M + 1) * (P / 2 + 1);                   // floats of a piece's accumulators
     const int64_t per_cu = rfsf::sketch_fft_scan_solo_per_cu(s->M, s->F, P), own = step / rfsf::kSoloWaves;    // pairs of a wavefront
     if (2 * all_pairs < step || (P >= 128 && all_pairs < 4 * step)) return none;
-    const int64_t fewest = s->N * all_pairs > kCUs * (s->M > 4 ? 20 : 10) ? kCUs : 0;
+    const bool fused = solo_fused(s, P), little = (s->M == 3 || s->M == 4) && (!fused || s->F < 4 * s->d);
+    const int64_t fewest = s->N * all_pairs > kCUs * (s->M > 4 && s->F < 48 ? 15 : 7) ? kCUs : 0;
     SketchCut best = none;
     double least = 0.0;
     for (int64_t want = 1; want <= kSplitPieces && want * step <= all_pairs + step; ++want) {
         const int64_t pairs = ((all_pairs + want - 1) / want + own - 1) / own * own, pieces = (all_pairs + pairs - 1) / pairs;
         // every piece, the last one too, has to hold its accumulators
+        if (little && fused && all_pairs >= 3 * step && 2 * all_pairs < 3 * step * pieces) continue;
         if (pieces > kJoinInPlace || s->N * pieces <= fewest || (pieces < 2 ? slots : pairs) * floats_per_pair < needed ||
             (slots - (pieces - 1) * pairs) * floats_per_pair < needed)
             continue;
         const int64_t workgroups = s->N * pieces, full = workgroups / (kCUs * per_cu), rest = workgroups - full * kCUs * per_cu;
         // iterations of a workgroup: between those of its longest wavefront and the mean
-        const double its = 0.5 * ((double)pairs / (double)step + (double)((pairs + step - 1) / step));
-        const double of_rest = (1.5 + (double)((rest + kCUs - 1) / kCUs)) / (1.5 + (double)per_cu);
-        const double cost = (double)full * (its + 0.6) + (rest > 0 ? its * of_rest + 0.6 : 0.0) + 0.1 * (double)pieces +
+        const double its = 0.4 * (double)pairs / (double)step + 0.6 * (double)((pairs + step - 1) / step);
+        const double of_rest = (2.0 + (double)((rest + kCUs - 1) / kCUs)) / (2.0 + (double)per_cu);
+        const double cost = (double)full * (its + 0.4) + (rest > 0 ? its * of_rest + 0.4 : 0.0) + 0.05 * (double)pieces +
                             (double)workgroups * (double)needed * 4.0 / 18e6;
         if (best.pieces == 0 || cost < least) {
             least = cost;
             best = {(int)pieces, pieces < 2 ? slots : pairs, true, true, true};
         }
     }
-    if ((s->M == 3 || s->M == 4) && 2 * all_pairs < 3 * step * best.pieces &&
-        (solo_fused(s, P) ? s->F < 4 * s->d : best.pieces == 1))
-        return none;
+    if (little && 2 * all_pairs < 3 * step * best.pieces && (fused || best.pieces == 1)) return none;
     return s->N * best.pieces > kCUs ? best : none;
 }
 // The same for sequences that time_cut_plan cuts, hundreds of iterations each: the other kernels are the faster ones with 100 buckets

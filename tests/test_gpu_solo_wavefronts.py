@@ -87,10 +87,13 @@ def test_large_angles_are_as_accurate_as_the_products(oracle, N, L, M, F, D):
     (100, 1000, 5, 5, 50, 100), (300, 301, 2, 5, 50, 100), (420, 85, 3, 4, 60, 64), (350, 277, 2, 4, 64, 128), (500, 150, 7, 4, 41, 128),
     (700, 131, 8, 4, 100, 256), (300, 120, 8, 2, 64, 64), (300, 120, 4, 2, 39, 100),
     (60, 200, 8, 4, 50, 100), (60, 200, 8, 3, 50, 100), (50, 120, 8, 3, 60, 128), (40, 129, 8, 4, 128, 256),      # one to a CU just so
-    (51, 200, 8, 5, 50, 100), (52, 200, 8, 5, 50, 100), (64, 81, 8, 3, 64, 256), (65, 81, 8, 3, 64, 256),         # both sides of the line
+    (51, 200, 8, 5, 50, 100), (52, 200, 8, 5, 50, 100), (64, 81, 8, 3, 64, 256), (65, 81, 8, 3, 64, 256),
+    (38, 200, 8, 5, 50, 100), (39, 200, 8, 5, 50, 100), (51, 81, 8, 3, 64, 256), (52, 81, 8, 3, 64, 256),         # both sides of the line
+    (59, 172, 3, 5, 47, 64), (47, 184, 3, 5, 20, 64), (43, 118, 7, 4, 58, 128),                                    # one iteration each
 ])
-def test_pieces_that_end_at_any_pair(oracle, N, L, d, M, F, D):
-    """Pieces of no whole number of iterations; slots of all distances; points in vector and in scalar registers."""
+def test_pieces_of_a_wavefronts_pairs(oracle, N, L, d, M, F, D):
+    """Pieces of whole numbers of a wavefront's pairs and no whole number of iterations, so that the last wavefronts have less to do
+    or nothing; slots of all distances; points in vector and in scalar registers."""
     X, W, hash_, sign = _case(N + L + D, N, L, d, M, F, D)
     got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 1.5, D).cpu().numpy()
     for n in (0, 7, N - 1):
