@@ -219,6 +219,8 @@ void dp1d_features_kernel(
 // 2^-63 are multiplied by kRaise before they are split, and the angle's factor is divided by it. (Points of 2^-120 with a lengthscale
 // of 2^-120: root mean square error 1.5e-4 without, 2.9e-7 with it; a raised number meets the largest of 32 bits without overflow. The
 // same for the frequencies of a workgroup would take 0.2 to 0.4 us of calls of 4 to 7 us.)
+// Finite numbers from 0x1.ffp127 on are rounded to an infinite first term, whose rest is NaN: a tile with points of 2^127 and more is
+// halved, and the first terms of frequencies end at the largest bfloat16 number (an infinity still leaves NaN: its last term is).
 // Channels 2 k + half go to the lane's half of the products' columns, so that a lane splits the channels that it loads, in pairs p of
 // k = 2 p and 2 p + 1. What a pair multiplies with what is laid out in tuples of four registers (an operand): of four pairs
 // their hi, mid and lo; of a single one hi, mid, lo, hi; of two hi, hi, mid, mid and lo, lo, hi, hi.
@@ -229,18 +231,21 @@ typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float floatx2 __attribute__((ext_vector_type(2)));
 // Wavefronts of a workgroup, one per CU: as many as hold the points' operands in registers.
 __host__ __device__ constexpr int resident_waves(int KSTEPS) { return KSTEPS <= 9 ? 12 : 8; }
-constexpr uint32_t kNotSmall = 0x60000000u;                  // exponent bits of 2^-63 and more (and of what is not finite)
-constexpr float kRaise = 0x1p48f;
+constexpr float kSmall = 0x1p-63f, kHuge = 0x1p127f, kRaise = 0x1p48f, kLargestTerm = 0x1.fep127f;
 struct Terms { uint32_t hi, mid, lo; };
 __device__ __forceinline__ uint32_t round_pair(float a, float b)
 {
     const floatx2 v = {a, b};
     return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
 }
+template <bool ANY_SIZE = false>
 __device__ __forceinline__ Terms split_pair(float a, float b)
 {
     Terms t;
-    t.hi = round_pair(a, b);
+    if constexpr (ANY_SIZE)
+        t.hi = round_pair(__builtin_amdgcn_fmed3f(a, -kLargestTerm, kLargestTerm), __builtin_amdgcn_fmed3f(b, -kLargestTerm, kLargestTerm));
+    else
+        t.hi = round_pair(a, b);
     const float ra = a - __uint_as_float(t.hi << 16), rb = b - __uint_as_float(t.hi & 0xffff0000u);
     t.mid = round_pair(ra, rb);
     t.lo = round_pair(ra - __uint_as_float(t.mid << 16), rb - __uint_as_float(t.mid & 0xffff0000u));
@@ -352,7 +357,7 @@ __global__ __launch_bounds__(64 * resident_waves(KSTEPS)) __attribute__((amdgpu_
 #pragma unroll
         for (int p = 0; p < PAIRS; ++p) {
             const int c0 = 4 * p + (l >> 5), c1 = c0 + 2;
-            w[p] = split_pair(c0 < d ? src[(int64_t)c0 * F] : 0.f, c1 < d ? src[(int64_t)c1 * F] : 0.f);
+            w[p] = split_pair<true>(c0 < d ? src[(int64_t)c0 * F] : 0.f, c1 < d ? src[(int64_t)c1 * F] : 0.f);
         }
         uint4 t[RT];
         tuples_of_frequencies<PAIRS>(w, t);
@@ -380,14 +385,16 @@ __global__ __launch_bounds__(64 * resident_waves(KSTEPS)) __attribute__((amdgpu_
         for (int m = 0; m < M; ++m) state[m * 128 + lane] = 0.f;
         for (int64_t t0 = 0; t0 < L; t0 += kRows) {
             const int nrow = (int)min((int64_t)kRows, L - t0);
-            uint32_t bits = 0;
+            float most = 0.f;                                // the largest point, a NaN aside
 #pragma unroll
-            for (int k = 0; k < 2 * PAIRS; ++k) bits |= __float_as_uint(raw[k]);
+            for (int k = 0; k < 2 * PAIRS; k += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(raw[k]), "v"(raw[k + 1]));
             float turns = scale_turns;
-            if (__ballot(bits & kNotSmall) == 0) {
-                turns *= 1.0f / kRaise;
+            const bool small = __ballot(!(most < kSmall)) == 0;
+            if (small || __ballot(most >= kHuge) != 0) {
+                const float factor = small ? kRaise : 0.5f;
+                turns *= small ? 1.0f / kRaise : 2.0f;
 #pragma unroll
-                for (int k = 0; k < 2 * PAIRS; ++k) raw[k] *= kRaise;
+                for (int k = 0; k < 2 * PAIRS; ++k) raw[k] *= factor;
             }
             Terms xt[PAIRS];
 #pragma unroll

@@ -57,7 +57,8 @@ def test_nan_and_infinity_stay_where_they_are():
 def test_sums_of_products_are_as_good_as_in_32_bits():
     """Phase 0 and one increment from the origin: level 1 is sqrt(2 / F) (cos(x . w) - 1). An angle is the sum of eight sums that
     each round once, by 2^-23 of the largest one at most, and is rounded to half-turns, 2^-24 with the rounding of their number in
-    a radian; the cosine adds 2e-7. Root mean square 1.5e-6: a tenth of that bound for the mean angle; operands of 16 bits give 1e-2."""
+    a radian; the cosine adds 2e-7. Root mean square 1.5e-6: a tenth of that bound for the mean angle; operands of 16 bits give 1e-2. Nor is it
+    larger than what products added one after another in 32 bits give, rounded once each, with an exact cosine of half-turns in 32 bits (1.1e-6)."""
     rng = np.random.default_rng(5)
     N, d, F = 400, 17, 256
     X = np.zeros((N, 2, d), np.float32)
@@ -68,6 +69,11 @@ def test_sums_of_products_are_as_good_as_in_32_bits():
     err = got[:, 1:].astype(np.float64) * math.sqrt(F) - math.sqrt(2.0) * (np.cos(angle) - 1.0)
     bound = math.sqrt(2.0) * np.abs(angle).max() * (8 * 2.0 ** -23 + 2.0 ** -24) + 2e-7
     assert np.abs(err).max() <= bound and np.sqrt(np.mean(err ** 2)) <= 1.5e-6, (np.abs(err).max(), np.sqrt(np.mean(err ** 2)))
+    sums = np.zeros((N, F), np.float32)
+    for c in range(d):
+        sums = (sums + np.outer(X[:, 1, c].astype(np.float64), W[0, c])).astype(np.float32)
+    err_32 = math.sqrt(2.0) * (np.cos((sums * np.float32(1.0 / math.pi)).astype(np.float64) * math.pi) - np.cos(angle))
+    assert np.sqrt(np.mean(err ** 2)) <= np.sqrt(np.mean(err_32 ** 2)), (np.sqrt(np.mean(err ** 2)), np.sqrt(np.mean(err_32 ** 2)))
 
 
 @pytest.mark.parametrize("x,w,scale", [(-120, 0, -120), (-125, 125, 0), (-110, 70, -40), (100, -100, 0), (-20, -105, -126), (-62, 62, 0), (-66, 66, 0)])
@@ -83,5 +89,24 @@ def test_small_numbers_keep_their_bits(x, w, scale):
     W = (rng.standard_normal((1, d, F)) * 2.0 ** w).astype(np.float32)
     got = rfsf.rfsf_dp1d_features(*(torch.from_numpy(a).cuda() for a in (X, W, np.zeros((1, F), np.float32))), 2.0 ** scale).cpu().numpy()
     angle = (X[:, 1].astype(np.float64) @ W[0].astype(np.float64)) / 2.0 ** scale
+    err = got[:, 1:].astype(np.float64) * math.sqrt(F) - math.sqrt(2.0) * (np.cos(angle) - 1.0)
+    assert np.sqrt(np.mean(err ** 2)) <= 1.5e-6, np.sqrt(np.mean(err ** 2))
+
+
+@pytest.mark.parametrize("large", ["points", "frequencies"])
+def test_largest_numbers_stay_finite(large):
+    """Numbers within 2^-8 of the largest 32-bit one, beyond the largest of 16 bits, which a first term must not round up to; the others
+    are small, so that the angles are of a few radians as above, with the bound of the test of sums."""
+    rng = np.random.default_rng(7)
+    N, d, F = 400, 17, 256
+    X = np.zeros((N, 2, d), np.float32)
+    X[:, 1] = rng.standard_normal((N, d))
+    W = rng.standard_normal((1, d, F)).astype(np.float32)
+    a, b = (X[:, 1], W) if large == "points" else (W, X[:, 1])
+    a[...] = np.float32(np.finfo(np.float32).max) * rng.uniform(1.0 - 2.0 ** -9, 1.0, a.shape).astype(np.float32) * rng.choice((-1.0, 1.0), a.shape).astype(np.float32)
+    b[...] *= 2.0 ** -60
+    scale = 2.0 ** 67
+    got = rfsf.rfsf_dp1d_features(*(torch.from_numpy(a).cuda() for a in (X, W, np.zeros((1, F), np.float32))), scale).cpu().numpy()
+    angle = (X[:, 1].astype(np.float64) @ W[0].astype(np.float64)) / scale
     err = got[:, 1:].astype(np.float64) * math.sqrt(F) - math.sqrt(2.0) * (np.cos(angle) - 1.0)
     assert np.sqrt(np.mean(err ** 2)) <= 1.5e-6, np.sqrt(np.mean(err ** 2))
