@@ -389,12 +389,14 @@ __global__ __launch_bounds__(64 * resident_waves(KSTEPS)) __attribute__((amdgpu_
 #pragma unroll
             for (int k = 0; k < 2 * PAIRS; k += 2) asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(most) : "v"(raw[k]), "v"(raw[k + 1]));
             float turns = scale_turns;
-            const bool small = __ballot(!(most < kSmall)) == 0;
-            if (small || __ballot(most >= kHuge) != 0) {
-                const float factor = small ? kRaise : 0.5f;
-                turns *= small ? 1.0f / kRaise : 2.0f;
+            if (__ballot(!(most < kSmall)) == 0) {
+                turns *= 1.0f / kRaise;
 #pragma unroll
-                for (int k = 0; k < 2 * PAIRS; ++k) raw[k] *= factor;
+                for (int k = 0; k < 2 * PAIRS; ++k) raw[k] *= kRaise;
+            } else if (__ballot(most >= kHuge) != 0) {
+                turns *= 2.0f;
+#pragma unroll
+                for (int k = 0; k < 2 * PAIRS; ++k) raw[k] *= 0.5f;
             }
             Terms xt[PAIRS];
 #pragma unroll
