@@ -614,20 +614,37 @@ hipError_t launch_stretches(const float *X, const float *W, const float *bias, f
 // Blocks of 64 components that a workgroup of the resident kernel holds: those of 1, 2, 3, 4 that keep most of the wavefronts of the chip
 // at work in every round of sequences; 0 where even one does not fit the LDS, or where the kernel above is the faster one: up to
 // six channels, whose 32-bit products cost little, unless it has more to do for its slabs of 256 components and whole last tiles.
-// Kernel above and this one, us: 4999 x 257 points, 1000 components, five levels, d = 4 2470 and 2535, 8 2840 and 2665, 12 3360 and 2880,
-// 17 3945 and 3170, 32 5700 and 3725, 64 8930 and 5830; 1500 x 256, 256 components, d = 2, 4, 6, 8 164, 174, 189, 204 and 191, 190, 195,
-// 195; 1500 x 100, 128 components, d = 2 73 and 42; 130 x 257, 256 components, d = 17 87 and 66; 20000 x 2, 64 components, d = 3 208 and 42.
+// Kernel above and this one, us: 4999 x 257 points, 1000 components, five levels, d = 4 2470 and 2535, 8 2805 and 2690, 12 3375 and 2900,
+// 17 3840 and 3235 (3250 to 3530 from box to box), 32 5735 and 3775, 64 9010 and 5805; 1500 x 256, 256 components, d = 2, 4, 6, 8 164, 174,
+// 189, 203 and 191, 190, 195, 195; 1500 x 100, 128 components, d = 2 84 and 44; 130 x 257, 256 components, d = 17 81 and 61; 20000 x 2,
+// 64 components, d = 3 310 and 45.
+// Of few levels the loads and the split of a tile's points are more of its cost, and batches that leave each workgroup of the kernel
+// above a CU or half of one have less to gain: with one level 7 x 22 points, six channels, 97 components 4.1 and 4.6 us, 36 x 53, 50,
+// 1461 10.9 and 14.6, 30 x 23, 5, 419 4.2 and 4.7, 864 x 151, 5, 1719 105 and 121, 364 x 55, 56, 507 24 and 34, but 407 x 55, 34, 354 26
+// and 17; two levels 4916 x 262, 6, 2047 2100 and 2285, 97 x 18, 60, 492 10.1 and 11.8; small batches of more levels
+// gain as large ones do (24 x 3, 39, 1010, three levels 11.3 and 8.2, 80 x 237, 49, 935, five 204 and 116). Of 4300 drawn shapes, 2000 of one
+// level, 1500 of two and three with F just below multiples of 256, 24 are slower by these lines by more than 4 % and 0.3 us, one by 21 %; on
+// average they take 0.74 of the time of the kernel above.
 constexpr int64_t kCUs = 256;
+// What a whole tile of 64 components costs, where one of the kernel above costs 1 (0: less, whatever that has to do for its slabs).
+template <int KSTEPS>
+double dearer_tile(int M, bool few)
+{
+    if (KSTEPS <= 3) return (KSTEPS == 1 ? 1.08 : KSTEPS == 2 ? 1.0 : 0.95) + 0.43 / (double)(M < 5 ? M : 5);
+    if (M == 1 && (few || KSTEPS > 24)) return 1.4;
+    if (M <= 2 && KSTEPS == 4) return 1.1;
+    return M <= 3 && few && KSTEPS > 24 ? 1.25 : 0.0;
+}
 struct Resident { int blocks; int64_t per_slab; };
 template <int KSTEPS>
 Resident resident_plan(int64_t N, int64_t L, int M, int F)
 {
     Resident best = {0, 0};
     const int64_t blocks = (F + 63) / 64, rest = L % kRows;
-    // a tile of the other kernel's is 1, of this one's dearer by as much as was measured with whole tiles and slabs
-    const double dearer = KSTEPS == 1 ? 1.17 : KSTEPS == 2 ? 1.09 : KSTEPS == 3 ? 1.04 : 0.0;
+    const int64_t others = N * ((F + 255) / 256);            // workgroups of the kernel above
     const double tiles = (double)(L / kRows) + (rest == 0 ? 0.0 : 0.3 + 0.175 * (double)((rest + 7) / 8));
-    if (dearer * tiles * (double)blocks > (double)((L + kRows - 1) / kRows * ((F + 255) / 256 * 4))) return best;
+    if (dearer_tile<KSTEPS>(M, others <= 2 * kCUs) * tiles * (double)blocks > (double)((L + kRows - 1) / kRows * ((F + 255) / 256 * 4))) return best;
+    if (M == 1 && others <= (KSTEPS <= 3 && L <= kRows ? 2 : 1) * kCUs && (L > 8 || KSTEPS > 16) && L <= (KSTEPS <= 3 ? 2 : 1) * kRows) return best;
     double most = 0.0;
     for (int S = 1; S <= 4; ++S) {
         if (resident_lds(KSTEPS, M, S) > kLdsPerCu) break;
@@ -649,7 +666,7 @@ hipError_t launch_resident(const Resident &plan, const float *X, const float *W,
     static LdsLimit limit;
     const hipError_t e = allow_lds(limit, reinterpret_cast<const void *>(dp1d_resident_kernel<KSTEPS>), lds);
     if (e != hipSuccess) return e;
-    const dim3 grid((unsigned)plan.per_slab, (unsigned)((F + 64 * plan.blocks - 1) / (64 * plan.blocks)));
+    const dim3 grid((unsigned)(N < plan.per_slab ? N : plan.per_slab), (unsigned)((F + 64 * plan.blocks - 1) / (64 * plan.blocks)));
     hipLaunchKernelGGL(dp1d_resident_kernel<KSTEPS>, grid, dim3(64 * resident_waves(KSTEPS)), lds, stream, X, W, bias, scale_turns, N, L, d, M, F,
                        plan.blocks, out, ld_out);
     return hipGetLastError();

@@ -110,3 +110,20 @@ def test_largest_numbers_stay_finite(large):
     angle = (X[:, 1].astype(np.float64) @ W[0].astype(np.float64)) / scale
     err = got[:, 1:].astype(np.float64) * math.sqrt(F) - math.sqrt(2.0) * (np.cos(angle) - 1.0)
     assert np.sqrt(np.mean(err ** 2)) <= 1.5e-6, np.sqrt(np.mean(err ** 2))
+
+
+@pytest.mark.parametrize("N,L,d,M,F", [
+    (N, L, d, M, 130) for N in (1, 2, 13) for L, d, M in ((2, 17, 3), (33, 7, 2), (64, 40, 5), (100, 12, 6))         # mostly idle workgroups
+] + [
+    (1, 8, 9, 1, 60), (1, 9, 9, 1, 60), (256, 20, 9, 1, 60), (257, 20, 9, 1, 60), (512, 20, 5, 1, 60), (513, 20, 5, 1, 60),         # one level
+    (256, 5, 33, 1, 60), (257, 5, 33, 1, 60), (300, 33, 18, 1, 400), (300, 33, 18, 1, 500), (700, 64, 50, 1, 180), (700, 64, 50, 1, 250),
+    (60, 18, 60, 2, 1010), (500, 32, 6, 2, 190), (500, 32, 6, 2, 250),
+])
+def test_small_batches_and_few_levels(oracle, N, L, d, M, F):
+    """Sizes on both sides of the lines between this kernel and the one for one workgroup per sequence, which small batches of one level and
+    a few points take."""
+    X, W, b, ls = _case(N, L, d, M, F)
+    got = rfsf.rfsf_dp1d_features(*(torch.from_numpy(a).cuda() for a in (X, W, b)), ls).cpu().numpy()
+    rows = np.unique(np.array([0, N // 2, N - 1]))
+    err = block_errors(got[rows], oracle.dp1d_features(X[rows], W, b, ls), M, F)
+    assert np.all(err <= FP32_BLOCK_TOL), err
