@@ -31,6 +31,8 @@ namespace tuned {
 // that several transforms' meet in a bank unless the slots are the right distance apart: solo_stride; and with 100 points the first
 // pass turns its results (MixedPlan). Cycles of a transform's exchanges, gather and separation by that count, before and
 // after: 64 points 598 -> 526, 100 795 -> 695, 128 567 -> 499 (256: 517, at best 502; 200: 911, at best 843 with slots of 234).
+// SQ_LDS_BANK_CONFLICT of a launch: 1500 x 200 points, five levels, 32 frequencies, 64 points 1.71e7 -> 1.03e7; 3000 x 200, five, 50,
+// 100 7.96e7 -> 6.65e7; 1500 x 200, four, 64, 128 2.54e7 -> 1.04e7: some are left.
 template <int LOG2D> struct SoloPlan : Plan<LOG2D> {};
 template <> struct SoloPlan<100> : MixedPlan<100, 100, 11> {};
 // Pairs of steps of a wavefront's iteration; 0: the levels do not fit a wavefront.

@@ -812,6 +812,8 @@ __host__ __device__ constexpr int acc_index(int M, int a, int l) { return a * M 
 // before the call 4007 -> 3880). The kernel whose wavefronts work by themselves is short and keeps its order (1000 x 100, 256 buckets 168
 // and 180, 4000 x 40, 100 buckets 166 and 187, 300 x 500 128 and 122).
 constexpr int kTurnRows = 32, kLengthClasses = 64;           // sequences of a lane; classes
+// (From 2048 points on it is not compiled, though it would pay there, 600 x 300 points, four levels, lengths from half 1467 -> 1300 us: these
+// kernels take the longest to compile.)
 template <int M, int D> constexpr bool kTurns = M > 1 && D < 2048;
 constexpr int64_t kTurnWork = 65536;
 // Where that pays, in a kernel of its own (for batches whose sequences have one length the search would only cost registers: 600 x 200
