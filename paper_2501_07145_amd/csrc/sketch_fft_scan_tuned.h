@@ -817,18 +817,22 @@ constexpr int kTurnRows = 32, kLengthClasses = 64;           // sequences of a l
 template <int M, int D> constexpr bool kTurns = M > 1 && D < 2048;
 constexpr int64_t kTurnWork = 65536;
 // Where that pays, in a kernel of its own (for batches whose sequences have one length the search would only cost registers: 600 x 200
-// points, 512 buckets, five levels 430 and 441 us): more workgroups than CUs, and enough work on each for the few microseconds of the
-// search, counted in points of its transforms times the workgroups on its CU, of which `held` fit. (Sketch kernels and projection, lengths
+// points, 512 buckets, five levels 430 and 441 us): more whole sequences than CUs, and enough work on each for the few microseconds of the
+// search, counted in points of its transforms times the workgroups on its CU, of which `held` fit, and against the number of
+// sequences that it goes through. (Sketch kernels and projection, lengths
 // from half, from one and all the same, us in order of numbers and of length: 600 x 50 points, 512 buckets, five levels 105 and 96, 87 and 75,
 // 121 and 123; 1500 x 50, 1000, three 267 and 246, 219 and 186, 303 and 310; 600 x 300, 1024, five 824 and 760, 608 and 489, 950 and
-// 955; below the line 320 x 10, 1024, three 29.4 and 32.4 with lengths from half, 600 x 20, 1024, two 0.86 times as fast. Over 131 shapes
-// above it 1.07, 1.18 and 0.99 times as fast, over 72 below 0.97, 1.00 and 0.93.)
+// 955; below the lines 320 x 10, 1024, three 29.4 and 32.4 with lengths from half, 2707 x 11, 1024, six 168 and 191, 2663 x 34, 1024, two, order
+// 2 169 and 187; sequences in pieces 61 x 1134, 512, four, order 2 189 and 221, 45 x 572, 512, five 170 and 180. Of 681 drawn shapes of more
+// sequences than CUs, lengths from half, 485 lie above: 0.946 of the time on average, 8 slower by more than 3 %; the others took
+// 1.003. Sequences in pieces: 563 shapes, 26 slower by more than 3 %, 6 faster.)
 inline bool turns_pay(int M, int D, int waves, int64_t held, int64_t sequences, int64_t pieces, int64_t pairs, int64_t L)
 {
-    constexpr int64_t kCUs = 256;
-    const int64_t workgroups = sequences * pieces, at_once = workgroups < held * kCUs ? workgroups : held * kCUs;
-    return workgroups > kCUs && (double)(M * pairs * D) * (double)at_once >= (double)(kTurnWork * kCUs) && sequences <= 64 * kTurnRows * waves &&
-           L <= 0x7fffffffLL;
+    constexpr int64_t kCUs = 256, kWorkPerSequence = 24;
+    const int64_t at_once = sequences < held * kCUs ? sequences : held * kCUs;
+    const double work = (double)(M * pairs * D);
+    return pieces == 1 && sequences > kCUs && work * (double)at_once >= (double)(kTurnWork * kCUs) && work >= (double)(kWorkPerSequence * sequences) &&
+           sequences <= 64 * kTurnRows * waves && L <= 0x7fffffffLL;
 }
 template <int WAVES>
 __device__ __forceinline__ int sequence_in_turn(const int64_t *__restrict__ lengths, int64_t L, int count, int turn, int *scratch /* [3 * WAVES + 1] */)

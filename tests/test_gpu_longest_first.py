@@ -1,7 +1,7 @@
 """Batches of sequences with lengths of their own are taken by length, the longest first: each workgroup finds its sequence by counting.
 Every sequence is still computed exactly once, with the same sums; the sizes sit at the edges of the rule: the smallest batch it
 applies to and the one below, the least work and a pair of steps less, the largest batch that fits the registers of three and four
-wavefronts and the next, pieces, equal lengths, lengths out of range, and a class with all sequences but one. Small sequences are taken in
+wavefronts and the next, equal lengths, lengths out of range, and a class with all sequences but one. Small sequences and pieces are taken in
 order of their numbers, which gives the same rows."""
 import numpy as np
 import pytest
@@ -32,7 +32,8 @@ def _lengths(kind, N, L, rng):
     shape + (kind,) for kind in ("any", "equal") for shape in [
         (256, 300, 3, 5, 60, 512, 1), (257, 300, 3, 5, 60, 512, 1), (1100, 60, 3, 3, 60, 1024, 1), (520, 66, 3, 4, 100, 500, 2),
         (64, 2100, 3, 3, 60, 512, 1), (200, 900, 3, 4, 40, 500, 1), (1200, 250, 3, 5, 60, 64, 2),          # pieces; grouped transforms
-        (300, 108, 3, 2, 20, 512, 1), (300, 110, 3, 2, 20, 512, 1), (260, 62, 3, 2, 30, 1000, 3)]
+        (300, 108, 3, 2, 20, 512, 1), (300, 110, 3, 2, 20, 512, 1), (260, 62, 3, 2, 30, 1000, 3),
+        (1536, 48, 3, 3, 20, 512, 1), (1537, 48, 3, 3, 20, 512, 1)]          # the most sequences for their work, and one more
 ] + [shape + (kind,) for kind in ("any", "half", "equal", "outside", "one short", "one long") for shape in [
     (256, 40, 3, 5, 120, 512, 1), (257, 40, 3, 5, 120, 512, 1), (300, 333, 3, 4, 250, 500, 2), (90, 300, 5, 5, 50, 100, 1),
     (320, 10, 3, 3, 60, 1024, 1), (321, 10, 3, 3, 60, 1024, 1), (300, 35, 9, 2, 100, 1024, 3), (270, 24, 3, 3, 40, 2048, 1),
