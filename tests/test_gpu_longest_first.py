@@ -33,7 +33,8 @@ def _lengths(kind, N, L, rng):
         (256, 300, 3, 5, 60, 512, 1), (257, 300, 3, 5, 60, 512, 1), (1100, 60, 3, 3, 60, 1024, 1), (520, 66, 3, 4, 100, 500, 2),
         (64, 2100, 3, 3, 60, 512, 1), (200, 900, 3, 4, 40, 500, 1), (1200, 250, 3, 5, 60, 64, 2),          # pieces; grouped transforms
         (300, 108, 3, 2, 20, 512, 1), (300, 110, 3, 2, 20, 512, 1), (260, 62, 3, 2, 30, 1000, 3),
-        (1536, 48, 3, 3, 20, 512, 1), (1537, 48, 3, 3, 20, 512, 1)]          # the most sequences for their work, and one more
+        (1536, 48, 3, 3, 20, 512, 1), (1537, 48, 3, 3, 20, 512, 1),          # the most sequences for their work, and one more
+        (400, 120, 2, 5, 18, 64, 1), (300, 301, 2, 5, 50, 100, 1)]           # single wavefronts, two and three pieces that start with any of them
 ] + [shape + (kind,) for kind in ("any", "half", "equal", "outside", "one short", "one long") for shape in [
     (256, 40, 3, 5, 120, 512, 1), (257, 40, 3, 5, 120, 512, 1), (300, 333, 3, 4, 250, 500, 2), (90, 300, 5, 5, 50, 100, 1),
     (320, 10, 3, 3, 60, 1024, 1), (321, 10, 3, 3, 60, 1024, 1), (300, 35, 9, 2, 100, 1024, 3), (270, 24, 3, 3, 40, 2048, 1),
