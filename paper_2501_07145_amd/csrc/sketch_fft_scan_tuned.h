@@ -58,6 +58,10 @@ struct Plan {
     static_assert(G <= 64, "a transform lives in one wavefront");
     static constexpr int FPW = 64 / G;          // transforms per wavefront
     static constexpr int GF = G;                // entries per fold round
+    // Lanes of a transform in rows of 16 (ROWS of them): the middle pass meets in registers (WaveFft::run_rows)
+    static constexpr bool kRowed = LOG2D >= 9 && LOG2D <= 11;
+    static constexpr int ROWS = G / 16, MID = kRowed ? ROWS * (R / 16) : 1;
+    static constexpr int kMidTwiddles = kRowed ? 16 * (MID / 2) : 0;     // float2: 16 / ROWS butterflies of a lane, ROWS rows
     static constexpr int PD = D + D / 16;       // padded transform length in float2
     static constexpr int NP = LOG2D <= 4 ? 1 : (LOG2D <= 8 ? 2 : 3);
     static constexpr int radix(int p)
@@ -85,13 +89,13 @@ struct Plan {
     // The twiddles of a radix-16 pass (8 per set) would cost 16 registers per set; they live in an
     // LDS table shared by the workgroup instead. Smaller passes keep theirs in registers.
     static constexpr bool tw_in_lds(int p) { return p > 0 && radix(p) >= 16; }
-    static constexpr int tw_regs(int p) { return (p == 0 || tw_in_lds(p)) ? 0 : tw_sets(p) * twiddles(radix(p)); }
+    static constexpr int tw_regs(int p) { return (p == 0 || tw_in_lds(p) || kRowed) ? 0 : tw_sets(p) * twiddles(radix(p)); }
     static constexpr int tw_lds(int p) { return tw_in_lds(p) ? tw_sets(p) * twiddles(radix(p)) * G : 0; }   // float2 entries
     static constexpr int kBoundTwiddles = tw_in_lds(NP - 1) ? tw_sets(NP - 1) * (radix(NP - 1) - 1) * G : 0;   // see tuned_lds_bound
     // array offsets of pass p: register twiddles (complex), LDS twiddles (float2) and write bases
     static constexpr int tw_off(int p) { return p <= 1 ? 0 : tw_off(p - 1) + tw_regs(p - 1); }
     static constexpr int twl_off(int p) { return p <= 1 ? 0 : twl_off(p - 1) + tw_lds(p - 1); }
-    static constexpr int NTWL = twl_off(NP);
+    static constexpr int NTWL = twl_off(NP) + kMidTwiddles;
     static constexpr int wb_off(int p) { return p == 0 ? 0 : wb_off(p - 1) + R / radix(p - 1); }
     static constexpr int NTW = tw_off(NP) == 0 ? 1 : tw_off(NP);
     static constexpr int NWB = wb_off(NP);
@@ -116,6 +120,7 @@ struct MixedPlan {
     static constexpr int G = D / R;
     static constexpr int FPW = 64 / G;
     static constexpr int GF = G;
+    static constexpr bool kRowed = false;
     static constexpr int kPad = PAD;            // one float2 of padding after every kPad of a slot
     static constexpr int kTurned = TURNED;
     static constexpr int PD = TURNED ? 9 * TURNED + 10 : D + (D - 1) / kPad;
@@ -424,6 +429,28 @@ __device__ __forceinline__ float2 cfmaf_pk(float2 a, float2 b, float2 c, bool pk
     return make_float2(fmaf(a.x, b.x, fmaf(-a.y, s, c.x)), fmaf(a.x, s, fmaf(a.y, r, c.y)));
 }
 
+// Exchanges the odd halves (BY = 32) or rows of 16 lanes (BY = 16) of a with the even ones of b.
+template <int BY>
+__device__ __forceinline__ void swap_rows(float &a, float &b)
+{
+    const unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    if constexpr (BY == 32) {
+        const auto s = __builtin_amdgcn_permlane32_swap(x, y, false, false);
+        a = __uint_as_float(s[0]);
+        b = __uint_as_float(s[1]);
+    } else {
+        const auto s = __builtin_amdgcn_permlane16_swap(x, y, false, false);
+        a = __uint_as_float(s[0]);
+        b = __uint_as_float(s[1]);
+    }
+}
+template <int BY>
+__device__ __forceinline__ void swap_rows(float2 &a, float2 &b)
+{
+    swap_rows<BY>(a.x, b.x);
+    swap_rows<BY>(a.y, b.y);
+}
+
 // Orders the LDS traffic of one wavefront: its LDS instructions execute in order, so only the
 // compiler has to be kept from moving accesses across this point.
 __device__ __forceinline__ void wave_lds_fence()
@@ -445,7 +472,8 @@ template <typename P>
 struct WaveFft {
     float2 tw[P::NTW];
     int wbase[P::NWB];
-    int rbase, rturned;
+    int rbase, rturned, rows_in, rows_out;
+    const float2 *mid;      // rows: this lane's twiddles of the middle pass
     const float2 *twl;      // LDS twiddle table of the passes whose twiddles are there, entry ((set * twiddles(r) + e) * G + lg)
 
     // `roots`: D float2 of LDS that are free until the caller's next use of them. Short transforms pick their register
@@ -465,7 +493,22 @@ struct WaveFft {
                 roots[i] = twiddle_form(c, s);
             }
         }
-        fill_table<1>(twl_table);
+        if constexpr (P::kRowed) {
+            // the last pass's, then the middle one's: [row][butterfly g][entry], k1 = ROWS g + row (one loop for both: a second
+            // inlined sine-cosine is a function call)
+            constexpr int LAST = P::tw_lds(P::NP - 1), TW = P::MID / 2, BF = 16 / P::ROWS;
+            for (int i = threadIdx.x; i < P::NTWL; i += blockDim.x) {
+                const int m = i - LAST, l = i % P::G, ue = i / P::G;
+                const bool last = m < 0;
+                const int e = last ? ue % 8 : m % TW, k = last ? l + P::G * (ue / 8) : P::ROWS * (m / TW % BF) + m / (TW * BF);
+                twl_table[i] = twiddle_entry<16>(e, k, last ? P::D / 16 : 16);
+            }
+            mid = twl_table + LAST + (lg >> 4) * (TW * BF);
+            rows_in = lg * 17;
+            rows_out = (lg >> 4) * 17 + (lg & 15);
+        } else {
+            fill_table<1>(twl_table);
+        }
         __syncthreads();
         init_pass<0>(lg, roots);
         if constexpr (kRoots) __syncthreads();
@@ -498,7 +541,7 @@ struct WaveFft {
                 const int k = j % Ns;
                 wbase[P::wb_off(PI) + u] = P::kTurned && PI == 0 ? j : P::pad((j - k) * r + k);
             }
-            if constexpr (PI > 0 && !P::tw_in_lds(PI)) {
+            if constexpr (PI > 0 && !P::tw_in_lds(PI) && !P::kRowed) {
                 constexpr int NSETS = P::tw_sets(PI);
 #pragma unroll
                 for (int u = 0; u < NSETS; ++u) {
@@ -525,13 +568,85 @@ struct WaveFft {
         float2 v[P::R];
 #pragma unroll
         for (int q = 0; q < P::R; ++q) v[q] = slot[rbase + P::roff(q)];
-        run_pass<0>(slot, v);
+        run_from_registers(slot, v);
     }
     // The same with the input already in registers: v[q] is point lg + G*q of the lane's transform.
     template <bool AHEAD = true>
     __device__ __forceinline__ void run_from_registers(float2 *slot, float2 (&v)[P::R]) const
     {
-        run_pass<0, AHEAD>(slot, v);
+        if constexpr (P::kRowed) run_rows(slot, v);
+        else run_pass<0, AHEAD>(slot, v);
+    }
+
+    // 512, 1024 and 2048 points as 16 x MID x 16. Point l + G q, l = l0 + 16 l1, is in lane l. The first pass, over q, leaves k1 = 0 .. 15 in
+    // a lane's registers; the middle one runs over l1, which is the row of 16 lanes (and, with 2048 points, one of the lane's two
+    // halves). Rows meet by v_permlane32_swap and v_permlane16_swap, which exchange halves of two registers: afterwards row r holds, of
+    // every row, the k1 that are r modulo ROWS, and the butterflies are a lane's own. That spares one of two exchanges through LDS,
+    // whose 16 writes hold a SIMD for 18 cycles each and take 7 of the CU's LDS, for 32 swaps of 8 cycles of a SIMD. (Meeting by
+    // swaps of copies, which leave both partners' values in both lanes, took 64 and 100 other instructions and was slower than the
+    // exchange.) Sketch kernel, 10000 x 200 points, 1024 buckets, five levels 10.6 -> 10.0 ms, 2000 x 2000, 512, four 7.6 -> 7.2,
+    // 50000 x 64, 2048, five 46 -> 45.4: most of what it spares is hidden behind the wait for the increments.
+    __device__ __forceinline__ static void meet_rows(float2 (&y)[16])
+    {
+        if constexpr (P::ROWS == 4) {
+#pragma unroll
+            for (int a = 0; a < 16; ++a)
+                if (!(a & 2)) swap_rows<32>(y[a], y[a | 2]);
+        }
+#pragma unroll
+        for (int a = 0; a < 16; a += 2) swap_rows<16>(y[a], y[a | 1]);
+    }
+    __device__ __forceinline__ void run_rows(float2 *slot, float2 (&v)[P::R]) const
+    {
+        constexpr int NB = P::R / 16, ROWS = P::ROWS, MID = P::MID;
+        float2 y[NB][16];
+        int in = rows_in, out = rows_out;
+        if constexpr (NB > 1) asm volatile("" : "+v"(in), "+v"(out));
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+#pragma unroll
+            for (int t = 0; t < 16; ++t) y[u][t] = v[u + t * NB];
+            dft_plain(y[u]);
+            meet_rows(y[u]);
+            if constexpr (NB > 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        transform_fence<P>();                                // every lane has its inputs in registers
+#pragma unroll
+        for (int g = 0; g < 16 / ROWS; ++g) {
+            float2 x[MID];
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+#pragma unroll
+                for (int i = 0; i < ROWS; ++i) x[i + ROWS * u] = y[u][ROWS * g + i];
+            dft<true>(x, [&](int e) { return mid[g * (MID / 2) + e]; });
+            float2 *dst = slot + out + 17 * ROWS * g;
+#pragma unroll
+            for (int k2 = 0; k2 < MID; ++k2) dst[17 * 16 * k2] = x[k2];
+            if constexpr (NB > 1) __builtin_amdgcn_sched_barrier(0);     // (no twiddles of butterflies to come: registers)
+        }
+        transform_fence<P>();
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int t = bitrev(i, 4);                  // (in the order in which the butterfly can start)
+                v[16 * u + t] = slot[in + 17 * P::G * u + t];
+            }
+        }
+        transform_fence<P>();
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            float2 x[16];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) x[t] = v[16 * u + t];
+            constexpr int set = P::tw_sets(P::NP - 1) == 1 ? 0 : 1;
+            dft<true>(x, [&](int e) { return twl[P::twl_off(P::NP - 1) + (set * u * 8 + e) * P::G]; });
+            float2 *dst = slot + wbase[P::wb_off(P::NP - 1) + u];
+#pragma unroll
+            for (int t = 0; t < 16; ++t) dst[P::pad(t * (P::D / 16))] = x[t];
+            if constexpr (NB > 1) __builtin_amdgcn_sched_barrier(0);
+        }
+        transform_fence<P>();
     }
 
     template <int PI, bool AHEAD = true>
