@@ -258,14 +258,10 @@ int sketch_fft_scan_joint_fit(int M, int F, int D, int order)
 
 bool sketch_fft_scan_joint_splits(int M, int D, int order) { return tuned::joint_fits(M, D, plan_key(D), order); }
 
-namespace {
-int solo_slot(int D, int PD) { return D == 100 ? tuned::SoloPlan<100>::PD : PD; }       // float2 of its slots
-}  // namespace
-
 uint32_t sketch_fft_scan_solo_zero(int F, int D)
 {
     TunedGeometry g;
-    return tuned_geometry(D, &g) ? 8u * (uint32_t)tuned::zero_slot(solo_slot(D, g.PD), 2 * F) : 0u;
+    return tuned_geometry(D, &g) ? 8u * (uint32_t)tuned::zero_slot(g.PD, 2 * F) : 0u;
 }
 
 bool sketch_fft_scan_solo_fused(int F, int d, int D) { return F <= 64 * tuned::solo_columns(D) && d <= tuned::kSoloChannels; }
@@ -274,7 +270,7 @@ int sketch_fft_scan_solo_per_cu(int M, int F, int D)
 {
     TunedGeometry g;
     if (!tuned_geometry(D, &g)) return 0;
-    const int by_lds = (int)(kLdsPerCu / tuned::solo_lds_bytes(D, M, g.FPW, solo_slot(D, g.PD), g.NTWL, F));
+    const int by_lds = (int)(kLdsPerCu / tuned::solo_lds_bytes(D, M, g.FPW, g.PD, g.NTWL, F));
     const int by_registers = tuned::solo_waves_per_simd(M, D);
     return by_lds < by_registers ? by_lds : by_registers;
 }

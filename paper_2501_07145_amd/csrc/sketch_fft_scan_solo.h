@@ -30,11 +30,8 @@ namespace tuned {
 // least 3.5. The lanes of a transform that write next to each other are few here (4, 5 and 8 for 64, 100 and 128 points), so
 // that several transforms' meet in a bank unless the slots are the right distance apart: solo_stride; and with 100 points the first
 // pass turns its results (MixedPlan). Cycles of a transform's exchanges, gather and separation by that count, before and
-// after: 64 points 598 -> 526, 100 795 -> 695, 128 567 -> 499 (256: 517, at best 502; 200: 911, at best 843 with slots of 234).
-// SQ_LDS_BANK_CONFLICT of a launch: 1500 x 200 points, five levels, 32 frequencies, 64 points 1.71e7 -> 1.03e7; 3000 x 200, five, 50,
-// 100 7.96e7 -> 6.65e7; 1500 x 200, four, 64, 128 2.54e7 -> 1.04e7: some are left.
-template <int LOG2D> struct SoloPlan : Plan<LOG2D> {};
-template <> struct SoloPlan<100> : MixedPlan<100, 100, 11> {};
+// after: 64 points 598 -> 526, 128 567 -> 499 (256: 517, at best 502). SQ_LDS_BANK_CONFLICT of a launch: 1500 x 200 points, five levels, 32
+// frequencies, 64 points 1.71e7 -> 1.03e7; 1500 x 200, four, 64, 128 2.54e7 -> 1.04e7: some are left.
 // Pairs of steps of a wavefront's iteration; 0: the levels do not fit a wavefront.
 __host__ __device__ constexpr int solo_pairs(int M, int FPW) { return FPW / M; }
 __host__ __device__ constexpr size_t solo_lds_with(int M, int FPW, int stride, int NTWL)
@@ -80,11 +77,11 @@ typedef const __attribute__((address_space(4))) float *ConstantFloats;      // s
 // lane: angles by multiply-adds of the points' channels with the lane's column of W. The channels are the same for all lanes, but
 // a multiply-add with a scalar register takes 4.35 cycles of a SIMD instead of 2.6: they are in vector registers where there is room.
 template <int LOG2D, int M, int ORDER, int d>
-__global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(solo_waves_per_simd(M, SoloPlan<LOG2D>::D), 4))) void sketch_fft_scan_solo_kernel(
+__global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu(solo_waves_per_simd(M, Plan<LOG2D>::D), 4))) void sketch_fft_scan_solo_kernel(
     const float *__restrict__ dphi, const uint32_t *__restrict__ table, int64_t L, const int64_t *__restrict__ lengths, int F,
     TimeCut cut)
 {
-    using P = SoloPlan<LOG2D>;
+    using P = Plan<LOG2D>;
     constexpr int D = P::D, SP = solo_pairs(M, P::FPW), SLOTS = SP * M, Q = M * (M + 1) / 2;
     constexpr bool kPack = (D / 2) % 64 == 0;                // lane 0 carries the two real bins, 0 and D/2
     constexpr int NB = kPack ? D / 2 : D / 2 + 1, BPT = (NB + 63) / 64;

@@ -59,7 +59,7 @@ struct Plan {
     static constexpr int FPW = 64 / G;          // transforms per wavefront
     static constexpr int GF = G;                // entries per fold round
     // Lanes of a transform in rows of 16 (ROWS of them): the middle pass meets in registers (WaveFft::run_rows)
-    static constexpr bool kRowed = LOG2D >= 9 && LOG2D <= 11;
+    static constexpr bool kRowed = LOG2D >= 9 && LOG2D <= 11, kTwoPass = false;
     static constexpr int ROWS = G / 16, MID = kRowed ? ROWS * (R / 16) : 1;
     static constexpr int kMidTwiddles = kRowed ? 16 * (MID / 2) : 0;     // float2: 16 / ROWS butterflies of a lane, ROWS rows
     static constexpr int PD = D + D / 16;       // padded transform length in float2
@@ -101,31 +101,57 @@ struct Plan {
     static constexpr int NWB = wb_off(NP);
     static constexpr int roff(int q) { return G >= 16 ? q * (G + G / 16) : tuned::pad(G * q); }
     static constexpr int pad(int e) { return tuned::pad(e); }     // position in a slot of element e
-    static constexpr int kTurned = 0;
 };
 
 // Transform lengths 2^a 5^b that the paper's own experiments use as bucket counts (100, 200, 500, 1000): exact
 // transforms of that length instead of a linear convolution in the next power of two above M (D - 1) + 1.
 // 20 points per lane, D / 20 lanes per transform (the remaining lanes of a wavefront repeat the work of the
-// first ones, see the kernel), passes of radix 10, 10 and 10 / 5 / 2 / none; slots are padded where that keeps the positions of a
-// pass a base plus constants and pays (D = 1000: the writes of a transform take 140 bank rows instead of 180); the
-// twiddles of all passes after the first live in the LDS table. Selected as Plan<D>.
-// TURNED (100 points): behind the first pass result t of butterfly j is not at 10 j + t but at TURNED t + j, so that the lanes of a
-// transform write next to each other and read TURNED apart.
-template <int DD, int PAD, int TURNED = 0>
-struct MixedPlan {
+// first ones, see the kernel). Selected as Plan<D>.
+//
+// 100, 200 and 500 points as 20 x G, G lanes: a lane transforms the 20 points it holds, which needs no twiddles, then the 20 butterflies of
+// G points are dealt to the lanes: four, two or one each (with 500 points the last five lanes repeat others). One exchange; passes of radix 10, 10 and
+// 5, 2 or none took one more from 200 points on, and twiddles behind each. Features (with the
+// projection kernel where they have one), three passes and two, us: 2000 x 200 points, two levels, 100 buckets 132 -> 112, 200 200 -> 180, 500
+// 986 -> 793, five levels 287 -> 286, 665 -> 609, 2569 -> 2327; 1500 x 333, 500 buckets, order 2, four levels 1632 -> 1543, five 2999 -> 3020. (With 100
+// points most of it is LDS that slots without padding leave to a fourth workgroup of single wavefronts.)
+template <int DD>
+struct TwoPassPlan {
     static constexpr int LOG2D = DD;
     static constexpr int D = DD;
     static constexpr int R = 20;
     static constexpr int G = D / R;
     static constexpr int FPW = 64 / G;
     static constexpr int GF = G;
-    static constexpr bool kRowed = false;
-    static constexpr int kPad = PAD;            // one float2 of padding after every kPad of a slot
-    static constexpr int kTurned = TURNED;
-    static constexpr int PD = TURNED ? 9 * TURNED + 10 : D + (D - 1) / kPad;
-    static constexpr int NP = D == 100 ? 2 : 3;
-    static constexpr int radix(int p) { return p < 2 ? 10 : (D == 1000 ? 10 : (D == 500 ? 5 : 2)); }
+    static constexpr bool kRowed = false, kTwoPass = true;
+    static constexpr int PD = D;
+    static constexpr int NB = G > R ? 1 : R / G;        // butterflies of a lane in the second pass
+    static constexpr int kButterflyLanes = R / NB;      // lanes with butterflies of their own
+    static constexpr int NTWL = NB * twiddles(G) * kButterflyLanes;
+    static constexpr int kBoundTwiddles = D == 100 ? 90 : D == 200 ? 190 : 850;      // of three passes, see tuned_lds_bound
+    static constexpr int NTW = 1, NWB = 1;
+    static constexpr int roff(int q) { return G * q; }
+    __host__ __device__ static constexpr int pad(int e) { return e; }
+    static constexpr int kMinWaves = 4;
+    static_assert(D == R * G && G * FPW <= 64 && R == NB * kButterflyLanes, "");
+};
+template <> struct Plan<100> : TwoPassPlan<100> {};
+template <> struct Plan<200> : TwoPassPlan<200> {};
+template <> struct Plan<500> : TwoPassPlan<500> {};
+// 1000 points: three passes of radix 10; slots are padded so that the positions of a pass are a base plus constants and the writes of a
+// transform take 140 bank rows instead of 180; the twiddles of all passes after the first live in the LDS table.
+template <int DD>
+struct ThreePassPlan {
+    static constexpr int LOG2D = DD;
+    static constexpr int D = DD;
+    static constexpr int R = 20;
+    static constexpr int G = D / R;
+    static constexpr int FPW = 64 / G;
+    static constexpr int GF = G;
+    static constexpr bool kRowed = false, kTwoPass = false;
+    static constexpr int kPad = 50;             // one float2 of padding after every kPad of a slot
+    static constexpr int PD = D + (D - 1) / kPad;
+    static constexpr int NP = 3;
+    static constexpr int radix(int) { return 10; }
     static constexpr int Ns(int p) { return p == 0 ? 1 : Ns(p - 1) * radix(p - 1); }
     static constexpr int tw_sets(int p) { return G % Ns(p) == 0 ? 1 : R / radix(p); }
     static constexpr bool tw_in_lds(int p) { return p > 0; }
@@ -141,13 +167,8 @@ struct MixedPlan {
     static constexpr int roff(int q) { return G * q + G * q / kPad; }
     __host__ __device__ static constexpr int pad(int e) { return e + e / kPad; }
     static constexpr int kMinWaves = 4;
-    static_assert(D % R == 0 && G * FPW <= 64, "");
-    static_assert(TURNED == 0 || (D == 100 && kPad >= D), "");
 };
-template <> struct Plan<100> : MixedPlan<100, 100> {};
-template <> struct Plan<200> : MixedPlan<200, 200> {};
-template <> struct Plan<500> : MixedPlan<500, 500> {};
-template <> struct Plan<1000> : MixedPlan<1000, 50> {};
+template <> struct Plan<1000> : ThreePassPlan<1000> {};
 // 2048 points in one wavefront: 32 points per lane (twice the registers, half the resident wavefronts, no barrier
 // inside the transform). Selected as Plan<2048>.
 template <> struct Plan<2048> : Plan<11, 5> {};
@@ -235,7 +256,8 @@ __device__ __forceinline__ void butterfly_one_i(float2 &a, float2 &b)           
 // Entry e of the twiddles of an r-point butterfly whose inputs carry powers of exp(-2 pi i k / (Ns r)). Powers of two: entry 0
 // belongs to the stage that combines single inputs, entries H/2 + j, j < H/2, to the one that combines H and H of
 // them, at its roots j (roots j + H/2 are -i times these). Ten points: entries 0 to 3 the even powers 2, 4, 6, 8, as real
-// and imaginary part, then those of the stage that combines five and five. Five points: the powers 1 to 4, likewise.
+// and imaginary part, then those of the stage that combines five and five. Five points: the powers 1 to 4, likewise. 25 points: the powers
+// 5, 10, 15, 20, then, for inputs b = 1 .. 4 modulo 5 and q = 0 .. 4, power b times the 25th root of unity to the b q.
 template <int r>
 __device__ __forceinline__ float2 twiddle_entry(int e, int k, int Ns)
 {
@@ -248,7 +270,8 @@ __device__ __forceinline__ float2 twiddle_entry(int e, int k, int Ns)
         sincospif(-2.0f * (float)(k + (e - 4) * Ns) / (float)(10 * Ns), &s, &c);
         return twiddle_form(c, s);
     } else {
-        sincospif(-2.0f * (float)(k * (e + 1) * (r == 10 ? 2 : 1)) / (float)(Ns * r), &s, &c);
+        const int power = r == 25 && e >= 4 ? ((e - 4) / 5 + 1) * (k + (e - 4) % 5 * Ns) : k * (e + 1) * (r == 10 ? 2 : r == 25 ? 5 : 1);
+        sincospif(-2.0f * (float)power / (float)(Ns * r), &s, &c);
         return make_float2(c, s);
     }
 }
@@ -323,23 +346,42 @@ __device__ __forceinline__ void dft5(float2 (&x)[TOTAL])
     x[B + 3 * ST] = make_float2(a2.x - b2.y, a2.y + b2.x);
 }
 
-// In-register forward DFT of 10 points, natural order in and out: 5-point transforms of the even and the odd inputs, combined.
+// In-register forward DFTs of 10 and 20 points, natural order in and out. 5 has no factor in common with 2 and 4, so that points numbered
+// by both remainders fall into transforms of five and of two or four points with no twiddles between them.
 __device__ __forceinline__ void dft10_plain(float2 (&x)[10])
 {
-    constexpr float c[5] = {1.0f, 0.80901699437494742f, 0.30901699437494742f, -0.30901699437494742f, -0.80901699437494742f};
-    constexpr float t[5] = {0.0f, -0.72654252800536089f, -3.0776835371752534f, 3.0776835371752534f, 0.72654252800536089f};
-    dft5<0, 2, 10>(x);
-    dft5<1, 2, 10>(x);
     float2 y[10];
 #pragma unroll
-    for (int q = 0; q < 5; ++q) {
-        y[q] = x[2 * q];
-        y[q + 5] = x[2 * q + 1];
-        if (q == 0) butterfly_one(y[0], y[5]);
-        else butterfly(y[q], y[q + 5], make_float2(c[q], t[q]));
-    }
+    for (int n = 0; n < 10; ++n) y[n] = x[(n / 5 * 5 + n % 5 * 2) % 10];
+    dft5<0, 1, 10>(y);
+    dft5<5, 1, 10>(y);
 #pragma unroll
-    for (int q = 0; q < 10; ++q) x[q] = y[q];
+    for (int q = 0; q < 5; ++q) {
+        butterfly_one(y[q], y[5 + q]);
+        x[6 * q % 10] = y[q];
+        x[(5 + 6 * q) % 10] = y[5 + q];
+    }
+}
+__device__ __forceinline__ void dft20_plain(float2 (&x)[20])
+{
+    float2 y[20];
+#pragma unroll
+    for (int n = 0; n < 20; ++n) y[n] = x[(n / 5 * 5 + n % 5 * 4) % 20];
+    dft5<0, 1, 20>(y);
+    dft5<5, 1, 20>(y);
+    dft5<10, 1, 20>(y);
+    dft5<15, 1, 20>(y);
+#pragma unroll
+    for (int q = 0; q < 5; ++q) {
+        butterfly_one(y[q], y[10 + q]);
+        butterfly_one(y[5 + q], y[15 + q]);
+        butterfly_one(y[q], y[5 + q]);
+        butterfly_one_i(y[10 + q], y[15 + q]);
+        x[16 * q % 20] = y[q];
+        x[(5 + 16 * q) % 20] = y[10 + q];
+        x[(10 + 16 * q) % 20] = y[5 + q];
+        x[(15 + 16 * q) % 20] = y[15 + q];
+    }
 }
 template <typename Twiddle>
 __device__ __forceinline__ void dft10(float2 (&x)[10], Twiddle tw)
@@ -362,6 +404,41 @@ __device__ __forceinline__ void dft10(float2 (&x)[10], Twiddle tw)
 #pragma unroll
     for (int q = 0; q < 10; ++q) x[q] = y[q];
 }
+template <int Q, typename Twiddle>
+__device__ __forceinline__ void dft25_row(float2 (&x)[25], Twiddle tw)
+{
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int b = 1; b < 5; ++b) x[5 * Q + b] = cmulf(x[5 * Q + b], tw(4 + 5 * (b - 1) + Q));
+    dft5<5 * Q, 1, 25>(x);
+}
+// 25 points as 5 x 5; the twiddles of the inputs b modulo 5 wait until the transforms over those inputs are done (twiddle_entry).
+template <typename Twiddle>
+__device__ __forceinline__ void dft25(float2 (&x)[25], Twiddle tw)
+{
+#pragma unroll
+    for (int a = 1; a < 5; ++a) {
+        const float2 w = tw(a - 1);
+#pragma unroll
+        for (int b = 0; b < 5; ++b) x[5 * a + b] = cmulf(x[5 * a + b], w);
+    }
+    dft5<0, 5, 25>(x);
+    dft5<1, 5, 25>(x);
+    dft5<2, 5, 25>(x);
+    dft5<3, 5, 25>(x);
+    dft5<4, 5, 25>(x);
+    // (no twiddles of transforms to come: registers)
+    dft25_row<0>(x, tw);
+    dft25_row<1>(x, tw);
+    dft25_row<2>(x, tw);
+    dft25_row<3>(x, tw);
+    dft25_row<4>(x, tw);
+    float2 y[25];
+#pragma unroll
+    for (int n = 0; n < 25; ++n) y[n / 5 + 5 * (n % 5)] = x[n];
+#pragma unroll
+    for (int n = 0; n < 25; ++n) x[n] = y[n];
+}
 
 // Forward DFT of r points, natural order in and out; input t times the t-th power of the twiddle that tw stands for.
 // (AHEAD: the nine twiddles of a ten-point butterfly are read before it starts, which is faster by 1 to 2 per cent where the registers
@@ -376,6 +453,8 @@ __device__ __forceinline__ void dft(float2 (&x)[r], Twiddle tw)
 #pragma unroll
         for (int e = 0; e < 9; ++e) w[e] = tw(e);
         dft10(x, [&](int e) { return w[e]; });
+    } else if constexpr (r == 25) {
+        dft25(x, tw);
     } else if constexpr (r == 5) {
 #pragma unroll
         for (int t = 1; t < 5; ++t) x[t] = cmulf(x[t], tw(t - 1));
@@ -396,6 +475,8 @@ __device__ __forceinline__ void dft_plain(float2 (&x)[r])
 {
     if constexpr (r == 10) {
         dft10_plain(x);
+    } else if constexpr (r == 20) {
+        dft20_plain(x);
     } else {
         float2 y[r];
 #pragma unroll
@@ -472,7 +553,7 @@ template <typename P>
 struct WaveFft {
     float2 tw[P::NTW];
     int wbase[P::NWB];
-    int rbase, rturned, rows_in, rows_out;
+    int rbase, second, rows_in, rows_out;      // second: this lane's first butterfly of the second of two passes
     const float2 *mid;      // rows: this lane's twiddles of the middle pass
     const float2 *twl;      // LDS twiddle table of the passes whose twiddles are there, entry ((set * twiddles(r) + e) * G + lg)
 
@@ -480,11 +561,15 @@ struct WaveFft {
     // twiddles out of a table of the D-th roots of unity: computed where they are needed, D = 64 and 128 have 12 and 14
     // inlined sine-cosine codes per lane, fetched and run once by every workgroup. Long ones have few, and run long. Ends
     // with a workgroup barrier.
-    static constexpr bool kRoots = P::tw_off(P::NP) > 0 && P::D <= 256;
+    static constexpr bool has_roots()
+    {
+        if constexpr (P::kTwoPass) return false;
+        else return P::tw_off(P::NP) > 0 && P::D <= 256;
+    }
+    static constexpr bool kRoots = has_roots();
     __device__ __forceinline__ void init(int lg, float2 *twl_table, float2 *roots)
     {
         rbase = P::pad(lg);
-        rturned = lg * P::kTurned;
         twl = twl_table + lg;
         if constexpr (kRoots) {
             for (int i = threadIdx.x; i < P::D; i += blockDim.x) {
@@ -506,11 +591,18 @@ struct WaveFft {
             mid = twl_table + LAST + (lg >> 4) * (TW * BF);
             rows_in = lg * 17;
             rows_out = (lg >> 4) * 17 + (lg & 15);
+        } else if constexpr (P::kTwoPass) {
+            // [butterfly of a lane][entry][lane]
+            constexpr int TW = twiddles(P::G), LANES = P::kButterflyLanes;
+            for (int i = threadIdx.x; i < P::NTWL; i += blockDim.x)
+                twl_table[i] = twiddle_entry<P::G>(i / LANES % TW, i % LANES + P::G * (i / (LANES * TW)), P::R);
+            second = lg % LANES;
+            twl = twl_table + second;
         } else {
             fill_table<1>(twl_table);
         }
         __syncthreads();
-        init_pass<0>(lg, roots);
+        if constexpr (!P::kTwoPass) init_pass<0>(lg, roots);
         if constexpr (kRoots) __syncthreads();
     }
 
@@ -539,7 +631,7 @@ struct WaveFft {
             for (int u = 0; u < NB; ++u) {
                 const int j = lg + P::G * u;
                 const int k = j % Ns;
-                wbase[P::wb_off(PI) + u] = P::kTurned && PI == 0 ? j : P::pad((j - k) * r + k);
+                wbase[P::wb_off(PI) + u] = P::pad((j - k) * r + k);
             }
             if constexpr (PI > 0 && !P::tw_in_lds(PI) && !P::kRowed) {
                 constexpr int NSETS = P::tw_sets(PI);
@@ -575,7 +667,33 @@ struct WaveFft {
     __device__ __forceinline__ void run_from_registers(float2 *slot, float2 (&v)[P::R]) const
     {
         if constexpr (P::kRowed) run_rows(slot, v);
+        else if constexpr (P::kTwoPass) run_two<AHEAD>(slot, v);
         else run_pass<0, AHEAD>(slot, v);
+    }
+    // 100, 200 and 500 points. Result t of lane l lies at G t + l in between, which the lanes write next to each other and read G apart: 25 and
+    // 5 share no factor with the number of banks.
+    template <bool AHEAD>
+    __device__ __forceinline__ void run_two(float2 *slot, float2 (&v)[P::R]) const
+    {
+        constexpr int G = P::G, NB = P::NB, TW = twiddles(G);
+        dft_plain(v);
+        transform_fence<P>();                                // every lane has its inputs in registers
+#pragma unroll
+        for (int t = 0; t < P::R; ++t) slot[rbase + G * t] = v[t];
+        transform_fence<P>();
+        float2 x[NB][G];
+#pragma unroll
+        for (int u = 0; u < NB; ++u)
+#pragma unroll
+            for (int t = 0; t < G; ++t) x[u][t] = slot[G * second + G * G * u + t];
+        transform_fence<P>();
+#pragma unroll
+        for (int u = 0; u < NB; ++u) {
+            dft<AHEAD>(x[u], [&](int e) { return twl[(u * TW + e) * P::kButterflyLanes]; });
+#pragma unroll
+            for (int t = 0; t < G; ++t) slot[second + G * u + P::R * t] = x[u][t];
+        }
+        transform_fence<P>();
     }
 
     // 512, 1024 and 2048 points as 16 x MID x 16. Point l + G q, l = l0 + 16 l1, is in lane l. The first pass, over q, leaves k1 = 0 .. 15 in
@@ -671,15 +789,14 @@ struct WaveFft {
                 }
                 float2 *dst = slot + wbase[P::wb_off(PI) + u];
 #pragma unroll
-                for (int t = 0; t < r; ++t) dst[P::kTurned && PI == 0 ? t * P::kTurned : P::pad(t * Ns)] = x[t];
+                for (int t = 0; t < r; ++t) dst[P::pad(t * Ns)] = x[t];
             }
             transform_fence<P>();
             if constexpr (PI + 1 < P::NP) {
 #pragma unroll
                 for (int i = 0; i < P::R; ++i) {
                     const int q = read_order<P::R, P::radix(PI + 1)>(i);
-                    if constexpr (P::kTurned && PI == 0) v[q] = slot[rturned + q / 2 + q % 2 * (5 * P::kTurned)];   // 5 q + lg
-                    else v[q] = slot[rbase + P::roff(q)];
+                    v[q] = slot[rbase + P::roff(q)];
                 }
                 run_pass<PI + 1, AHEAD>(slot, v);
             }
