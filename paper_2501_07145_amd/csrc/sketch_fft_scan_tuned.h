@@ -292,17 +292,21 @@ __device__ __forceinline__ void dft_halves(float2 (&x)[r], const float2 (&tw)[tw
         }
     }
 }
-// The same without twiddles (w = 1): their constants, and the trivial ones cost nothing.
-template <int B, int N, int r>
+// The same without twiddles (w = 1): their constants, and the trivial ones cost nothing. Z > 1: only the first r / Z inputs (of natural
+// order) are not zero, so that stages of up to Z points copy them.
+template <int B, int N, int Z, int r>
 __device__ __forceinline__ void dft_halves_plain(float2 (&x)[r])
 {
     static_assert(r <= 16, "");
-    if constexpr (N > 1) {
+    if constexpr (N == Z) {
+#pragma unroll
+        for (int j = 1; j < N; ++j) x[B + j] = x[B];
+    } else if constexpr (N > 1) {
         constexpr float c[4] = {1.0f, 0.92387953251128674f, 0.70710678118654752f, 0.38268343236508977f};      // of j pi / 8
         constexpr float t[4] = {0.0f, -0.41421356237309505f, -1.0f, -2.4142135623730950f};                    // minus tangent
         constexpr int H = N / 2;
-        dft_halves_plain<B, H>(x);
-        dft_halves_plain<B + H, H>(x);
+        dft_halves_plain<B, H, Z>(x);
+        dft_halves_plain<B + H, H, Z>(x);
 #pragma unroll
         for (int j = 0; j < (H > 1 ? H / 2 : 1); ++j) {
             const int e = j * (8 / H);
@@ -470,9 +474,10 @@ __device__ __forceinline__ void dft(float2 (&x)[r], Twiddle tw)
         for (int t = 0; t < r; ++t) x[t] = y[t];
     }
 }
-template <int r>
+template <int Z = 1, int r>
 __device__ __forceinline__ void dft_plain(float2 (&x)[r])
 {
+    static_assert(Z == 1 || r == 16, "");
     if constexpr (r == 10) {
         dft10_plain(x);
     } else if constexpr (r == 20) {
@@ -481,7 +486,7 @@ __device__ __forceinline__ void dft_plain(float2 (&x)[r])
         float2 y[r];
 #pragma unroll
         for (int t = 0; t < r; ++t) y[bitrev(t, ilog2(r))] = x[t];
-        dft_halves_plain<0, r>(y);
+        dft_halves_plain<0, r, Z>(y);
 #pragma unroll
         for (int t = 0; t < r; ++t) x[t] = y[t];
     }
@@ -663,10 +668,11 @@ struct WaveFft {
         run_from_registers(slot, v);
     }
     // The same with the input already in registers: v[q] is point lg + G*q of the lane's transform.
-    template <bool AHEAD = true>
-    __device__ __forceinline__ void run_from_registers(float2 *slot, float2 (&v)[P::R]) const
+    // FEW (where few is set): only the first R / FEW of them are not zero.
+    template <bool AHEAD = true, int FEW = 1>
+    __device__ __forceinline__ void run_from_registers(float2 *slot, float2 (&v)[P::R], [[maybe_unused]] bool few = false) const
     {
-        if constexpr (P::kRowed) run_rows(slot, v);
+        if constexpr (P::kRowed) run_rows<FEW>(slot, v, few);
         else if constexpr (P::kTwoPass) run_two<AHEAD>(slot, v);
         else run_pass<0, AHEAD>(slot, v);
     }
@@ -714,7 +720,8 @@ struct WaveFft {
 #pragma unroll
         for (int a = 0; a < 16; a += 2) swap_rows<16>(y[a], y[a | 1]);
     }
-    __device__ __forceinline__ void run_rows(float2 *slot, float2 (&v)[P::R]) const
+    template <int FEW>
+    __device__ __forceinline__ void run_rows(float2 *slot, float2 (&v)[P::R], [[maybe_unused]] bool few) const
     {
         constexpr int NB = P::R / 16, ROWS = P::ROWS, MID = P::MID;
         float2 y[NB][16];
@@ -724,7 +731,8 @@ struct WaveFft {
         for (int u = 0; u < NB; ++u) {
 #pragma unroll
             for (int t = 0; t < 16; ++t) y[u][t] = v[u + t * NB];
-            dft_plain(y[u]);
+            if (FEW > 1 && few) dft_plain<FEW>(y[u]);
+            else dft_plain(y[u]);
             meet_rows(y[u]);
             if constexpr (NB > 1) __builtin_amdgcn_sched_barrier(0);
         }
@@ -1315,6 +1323,14 @@ __global__ __launch_bounds__(64 * NTR)
     constexpr bool kEarly = GR == 1 && ZREGS <= (P::kMinWaves <= 2 ? 64 : 24)    // (a plan with twice the registers per wavefront affords more)
                             && (!JOINT || 2 * (ZREGS + BPT * kAcc) <= 200);
     uint32_t gw[P::R], fw[kFoldInRegs];
+    // Fewer buckets than points (the linear route takes M D - M + 1 points at least): groups of G buckets, R of D points, that are not
+    // all empty. Where they are half or a quarter of all at most (as many as the linear route's with M levels can be), the reads of the others
+    // and the stages of the first pass that would only copy are left out. Features of 1000 x 151 points, projection included, us: 300 buckets in
+    // 1024 points, three levels, 190 frequencies 503 -> 490, 150 in 512, four 538 -> 499, 150 in 1024, five 667 -> 632; as many buckets as
+    // points 829 and 829, 1366 and 1363.
+    constexpr int kFew = !P::kRowed || M < 2 ? 1 : M < 4 ? 2 : 4;
+    const int groups = (Dout + P::G - 1) / P::G;
+    const bool few = kFew > 1 && groups <= P::R / kFew;
 
     // The item of this wavefront: level and first pair of its transform in the current iteration (a transform
     // carries FPW consecutive pairs of one level, a pair group). Streaming: the items of the sequence are counted
@@ -1418,6 +1434,11 @@ __global__ __launch_bounds__(64 * NTR)
                 v[q] = make_float2(x0.x + x1.x, x0.y + x1.y);
                 // keep the scheduler from issuing all 2R reads at once (it would need 4R registers)
                 if (q % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+                if (kFew > 1 && q + 1 == P::R / kFew && few) {
+#pragma unroll
+                    for (int z = P::R / kFew; z < P::R; ++z) v[z] = make_float2(0.f, 0.f);
+                    break;
+                }
             }
             // 1d. lists: the third and later coordinates of a bucket straight from the staging area, two per row and
             // bucket. Against folding, whose rounds each wait for an LDS round trip, they cost a table word per row:
@@ -1455,7 +1476,7 @@ __global__ __launch_bounds__(64 * NTR)
             // instructions issued at once and goes back to waiting instead of queueing behind other wavefronts'
             // transforms (measured: 3-7 % on every workload; the other way round, 2-3 % slower).
             __builtin_amdgcn_s_setprio(0);
-            fft.run_from_registers(my_slot, v);
+            fft.template run_from_registers<true, kFew>(my_slot, v, few);
             __builtin_amdgcn_s_setprio(1);
         }
         __syncthreads();

@@ -1,0 +1,33 @@
+"""Transforms with more points than buckets: the linear route at the largest bucket counts that a length holds and just below, whose
+empty groups of buckets are neither read nor transformed, and bucket counts that many features move to a longer transform, some of
+which have too many groups for that. Tolerance: that of the butterflies' test (three times the error of 32-bit angles, sums and roots)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_07145_amd as rfsf
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("M,F,D,order", [
+    (2, 40, 256 - 1, 1), (2, 40, 511, 1), (2, 40, 1023, 1),          # 512, 1024 and 2048 points, half of the groups
+    (3, 40, 171, 1), (3, 40, 342, 1), (3, 40, 683, 1), (3, 40, 342, 3),
+    (4, 40, 127, 1), (4, 40, 255, 2), (4, 40, 511, 1),               # a quarter
+    (5, 40, 103, 1), (5, 40, 205, 1), (5, 40, 410, 2),
+    (8, 40, 64 + 1, 1), (8, 200, 128 - 1, 1),
+    (4, 1000, 64, 1), (4, 2000, 256, 1), (5, 2000, 512, 1),          # powers of two in longer transforms
+])
+@pytest.mark.parametrize("L", [4, 23])
+def test_empty_groups_of_buckets_are_left_out(oracle, M, F, D, order, L):
+    rng = np.random.default_rng(D + L)
+    X = np.cumsum(rng.standard_normal((3, L, 9)) * 0.2, axis=1).astype(np.float32)
+    W = rng.standard_normal((M, 9, F)).astype(np.float32)
+    hash_ = rng.integers(0, D, size=(M, 2 * F)).astype(np.int32)
+    hash_[:, 0] = D - 1                                              # the last bucket is used
+    sign = (2.0 * rng.integers(0, 2, size=(M, 2 * F)) - 1.0).astype(np.float32)
+    got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 3.0, D, order=order).cpu().numpy()
+    want = oracle.features(X, W, hash_, sign, 3.0, D, order=order)
+    for m in range(min(M, L - 1) if order == 1 else M):              # (no more steps than levels: blocks of zeros)
+        g, w = (a[:, 1 + m * D:1 + (m + 1) * D].astype(np.float64) for a in (got, want))
+        assert np.linalg.norm(g - w) <= 1.5e-6 * np.linalg.norm(w), m
