@@ -1110,14 +1110,15 @@ hipError_t launch_small(const GramArgs &g, bool sym, bool flip, int batch, hipSt
 
 hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *PhiY, int64_t Ny,
                        int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, bool rows_add_up, int batch,
-                       int64_t step_x, int64_t step_y, int64_t step_k)
+                       int64_t step_x, int64_t step_y, int64_t step_k, int64_t route_rows)
 {
     if (Nx == 0 || Ny == 0) return hipSuccess;
     const GramArgs g = {PhiX, PhiY, K, Nx, Ny, ncols, ldx, ldy, ldk, step_x, step_y, step_k};
     // K = PhiX PhiX^T: only what lies on or above the diagonal is computed, and written twice
     const bool sym = PhiX == PhiY && Nx == Ny && ldx == ldy && !rows_add_up;
+    const int64_t rows = route_rows ? route_rows : Nx;        // rows by which the kind of tile is chosen
     const auto count = [&](int64_t edge) {
-        const int64_t ti = (Nx + edge - 1) / edge, tj = (Ny + edge - 1) / edge;
+        const int64_t ti = (rows + edge - 1) / edge, tj = (Ny + edge - 1) / edge;
         return (sym ? ti * (ti + 1) / 2 : ti * tj) * batch;
     };
     const int64_t few = std::min(Nx, Ny), many = std::max(Nx, Ny);
@@ -1130,7 +1131,7 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
     // 606 against 56, 70, 118, 464). Two terms are for calls that three would run in large tiles as well: the small ones add up in four
     // or eight sums, and their error is half that of a large tile's single one (5121 columns 5.0e-7 and 9.4e-7), which
     // 2500, 3000 and 4000 rows, faster as they would be, are not to lose.
-    const int64_t tiles = big_tiles(Nx, Ny, sym), rounds = (tiles * batch + 255) / 256;
+    const int64_t tiles = big_tiles(Nx, Ny, sym), rounds = (big_tiles(rows, Ny, sym) * batch + 255) / 256;
     const bool two = ncols >= kTwoTermColumns;
     const bool large = count(64) > 1340 * rounds && (!two || count(64) * (105 + ncols) > 140000 + rounds * (150000 + 760 * ncols));
     if (large && ldx <= kBigMaxStride && ldy <= kBigMaxStride) {

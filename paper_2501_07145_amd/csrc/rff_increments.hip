@@ -57,18 +57,18 @@ constexpr int kRowsPerTile = 32;
 // from the partner half-wavefront (its block q for the upper half, q-1 for the lower half) or, for
 // the first block of the lower half, from the previous tile (carry).
 // Row layout (PAIRED = false): increment k = phi(row k+1) - phi(row k) is stored at row k, scalar base +
-// 32-bit lane offset, one predicate per row.
+// 32-bit lane offset, one predicate per row. `last`: bit r is set if row k of tile row r is a sequence's last point, whose increment
+// into the next sequence is left out; the rows behind it then move up.
 template <typename AngleOf>
 __device__ __forceinline__ void sincos_difference_store(
     AngleOf angle, const ScaledCoeffs &coeffs, float &carry_c, float &carry_s, int half, bool f_ok, int nrow,
-    int64_t gt, int64_t g0, int64_t rf, int F, float *__restrict__ dphi, int cos_at)
+    int64_t gt, int64_t g0, int64_t rf, int F, float *__restrict__ dphi, int cos_at, int64_t row0, uint32_t last)
 {
     // One store path for every tile: scalar base + 32-bit lane offset. The first row of a range has no
     // increment to store (it belongs to the previous range) and rows past the end of the range do not
     // exist; both cases are lane-uniform per row and folded into one predicate per store.
-    float *cos_base = dphi + (gt - 1) * rf;               // uniform (gt = g0: row -1 is never stored)
+    float *cos_base = dphi + row0 * rf;                   // uniform (gt = 0: row -1 is never stored)
     float *sin_base = cos_base + F;
-    const uint32_t lane_off = (uint32_t)cos_at + (uint32_t)(4 * half) * (uint32_t)rf;
     const int first = gt > g0 ? 0 : 1;                          // first tile row whose increment is ours
     float below_c = carry_c, below_s = carry_s;                 // lower half: partner's previous block
 #pragma unroll
@@ -85,8 +85,12 @@ __device__ __forceinline__ void sincos_difference_store(
             const float dc = cs[i] - (i ? cs[i - 1] : up_c);
             const float ds = sn[i] - (i ? sn[i - 1] : up_s);
             const int r = 8 * q + 4 * half + i;
-            if (f_ok && r >= first && r < nrow) {
-                const uint32_t off = lane_off + (uint32_t)(8 * q + i) * (uint32_t)rf;
+            // (both halves' places in scalar registers: one select)
+            const int lower = 8 * q + i, upper = lower + 4;
+            const uint32_t at_lower = (uint32_t)(lower - __popc(last & ((1u << lower) - 1u))) * (uint32_t)rf;
+            const uint32_t at_upper = (uint32_t)(upper - __popc(last & ((1u << upper) - 1u))) * (uint32_t)rf;
+            if (f_ok && r >= first && r < nrow && !(last >> r & 1u)) {
+                const uint32_t off = (uint32_t)cos_at + (half ? at_upper : at_lower);
                 cos_base[off] = dc;
                 sin_base[off] = ds;
             }
@@ -94,6 +98,21 @@ __device__ __forceinline__ void sincos_difference_store(
     }
     carry_c = below_c;      // row 31 of this tile as seen by the lower half (unused by the upper half)
     carry_s = below_s;
+}
+
+// Where the increment of the first row of the tile at row gt goes in the row layout, and the tile's rows without one (`last` above).
+// last_rows: 0 (rows are kept), or a bit at every multiple of L below 32.
+__device__ __forceinline__ int64_t tile_place(int64_t gt, int64_t L, uint32_t last_rows, uint32_t &last)
+{
+    last = 0;
+    const int64_t k = gt - 1;
+    if (!last_rows || k < 0) {
+        if (last_rows && L < 32) last = last_rows << L;               // row -1, then the L rows of the first sequence
+        return k;
+    }
+    const uint32_t n = (uint32_t)k / (uint32_t)L, to_last = (uint32_t)L - 1u - ((uint32_t)k - n * (uint32_t)L);    // (the host has checked the rows)
+    if (to_last < 32) last = last_rows << to_last;
+    return k - n;
 }
 
 // Pair layout: increments 2P and 2P+1 of a coordinate are stored next to each other as a float2, the form in which
@@ -144,7 +163,7 @@ __device__ __forceinline__ void sincos_difference_store_pairs(
 // flattened rows (n * L + t) and carries the previous row's features in registers.
 __global__ __launch_bounds__(256) void rff_increments_valu(
     const float *__restrict__ X, const float *__restrict__ W, float inv_lengthscale, float scale,
-    int64_t rows, int d, int M, int F, int64_t rows_per_block, float *__restrict__ dphi)
+    int64_t rows, int64_t L, int d, int M, int F, int64_t rows_per_block, float *__restrict__ dphi, bool compact)
 {
     extern __shared__ float xs[];                     // kRowsPerTile * d
     const int fblocks = (F + 255) / 256;
@@ -169,9 +188,9 @@ __global__ __launch_bounds__(256) void rff_increments_valu(
             sincos_reduced(acc * inv_lengthscale, s, co);
             s *= scale;
             co *= scale;
-            const int64_t g = gt + r;
-            if (g > g0) {
-                float *dst = dphi + (g - 1) * rf + (int64_t)m * 2 * F;
+            const int64_t g = gt + r, n = compact ? g / L : 0;        // (compact: a sequence's first row ends no increment)
+            if (g > g0 && !(compact && g == n * L)) {
+                float *dst = dphi + (g - 1 - n) * rf + (int64_t)m * 2 * F;
                 dst[a] = co - pc;
                 dst[F + a] = s - ps;
             }
@@ -307,7 +326,7 @@ template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 2) padded: chann
 __global__ __launch_bounds__(256) void rff_increments_mfma(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
-    float *__restrict__ dphi, const int64_t *__restrict__ lengths, TableJob job)
+    float *__restrict__ dphi, const int64_t *__restrict__ lengths, uint32_t last_rows, TableJob job)
 {
     constexpr int KP = 2 * KSTEPS;              // padded channel count
     constexpr int XS = KP | 1;                  // odd LDS row stride: conflict-free A reads
@@ -398,9 +417,12 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
         if (PAIRED)
             sincos_difference_store_pairs<STREAM>([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, gt, g0,
                                           min(g0 + rows_per_block - 2, rows - 2), 2 * rf, dphi, column);
-        else
+        else {
+            uint32_t last;
+            const int64_t row0 = tile_place(gt, L, last_rows, last);
             sincos_difference_store([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, nrow, gt, g0,
-                                    rf, F, dphi, m * 2 * F + f);
+                                    rf, F, dphi, m * 2 * F + f, row0, last);
+        }
         if (more) put_tile(xs + (cur ^ 1) * (kRowsPerTile * XS));
         __syncthreads();
     }
@@ -424,7 +446,7 @@ template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 16): channels pa
 __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
-    float *__restrict__ dphi, const int64_t *__restrict__ lengths, TableJob job)
+    float *__restrict__ dphi, const int64_t *__restrict__ lengths, uint32_t last_rows, TableJob job)
 {
     constexpr int KP = 16 * KSTEPS;
     constexpr int XS = KP + 8;                  // bf16 elements per LDS row (16-byte padded)
@@ -527,9 +549,12 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
             sincos_difference_store_pairs<STREAM>([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s,
                                           half, f_ok, gt, g0, min(g0 + rows_per_block - 2, rows - 2), 2 * rf,
                                           dphi, column);
-        else
+        else {
+            uint32_t last;
+            const int64_t row0 = tile_place(gt, L, last_rows, last);
             sincos_difference_store([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s, half,
-                                    f_ok, nrow, gt, g0, rf, F, dphi, m * 2 * F + f);
+                                    f_ok, nrow, gt, g0, rf, F, dphi, m * 2 * F + f, row0, last);
+        }
         if (more) put_tile(cur ^ 1);
         __syncthreads();
     }
@@ -539,9 +564,13 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
 
 hipError_t launch_rff_increments(const float *X, const float *W, const float *sign, float inv_lengthscale,
                                  int64_t n_seq, int64_t L, int d, int M, int F, bool bf16,
-                                 float *dphi, hipStream_t stream, const TableJob *tables, const int64_t *lengths)
+                                 float *dphi, hipStream_t stream, const TableJob *tables, const int64_t *lengths, bool compact)
 {
     const bool paired = sign != nullptr;
+    uint32_t last_rows = 0;
+    if (compact && (paired || n_seq * L > 0xffffffffLL)) return hipErrorInvalidValue;
+    if (compact)
+        for (int64_t r = 0; r < 32; r += L) last_rows |= 1u << r;
     const int64_t Lp = (L + 1) & ~(int64_t)1;
     const int64_t rows = paired ? n_seq * Lp : n_seq * L;
     const bool matrix_cores = bf16 || d <= 64;        // bf16: the caller (API layer) has checked d <= 128
@@ -582,7 +611,7 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     const bool whole_lines = F % 8 == 0;           // 16 bytes per frequency and pair of steps
 #define RFSF_LAUNCH(KERNEL, KS, PAIRED, STREAM, TILE)                                                                \
     hipLaunchKernelGGL((KERNEL<KS, PAIRED, STREAM>), grid, dim3(256), job.table && table_lds > (TILE) ? table_lds : (TILE), \
-                       stream, X, W, sign, inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi, lengths, job)
+                       stream, X, W, sign, inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi, lengths, last_rows, job)
 #define RFSF_LAUNCH_MFMA(KERNEL, KS, TILE)                                                                           \
     do {                                                                                                         \
         if (!paired) RFSF_LAUNCH(KERNEL, KS, false, false, TILE);                                                \
@@ -622,7 +651,7 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     }
     const dim3 rows_grid((unsigned)nblk, (unsigned)(M * fblocks));
     hipLaunchKernelGGL(rff_increments_valu, rows_grid, dim3(256), sizeof(float) * kRowsPerTile * d, stream,
-                       X, W, inv_lengthscale, scale, rows, d, M, F, rows_per_block, dphi);
+                       X, W, inv_lengthscale, scale, rows, L, d, M, F, rows_per_block, dphi, compact);
     return hipGetLastError();
 }
 

@@ -69,10 +69,11 @@ struct PieceRows { const float2 *rows[kMaxCutLevels]; };
 // n_seq * Lp * M * 2F floats in all.
 // `lengths` (may be null, pair layout): each sequence's own number of points; increments beyond them may be left out.
 // `tables` (may be null): the sketch tables are built as well, by workgroups of the same launch where that pays.
+// `compact` (row layout): the rows with t = L-1 do not exist and row n * (L - 1) + t follows row n * (L - 1) + t - 1.
 struct TableJob;
 hipError_t launch_rff_increments(const float *X, const float *W, const float *sign, float inv_lengthscale,
                                  int64_t n_seq, int64_t L, int d, int M, int F, bool bf16,
-                                 float *dphi, hipStream_t stream, const TableJob *tables, const int64_t *lengths);
+                                 float *dphi, hipStream_t stream, const TableJob *tables, const int64_t *lengths, bool compact = false);
 
 // Steps 3-4: CountSketch, FFT-domain level recursion over time, inverse transform; writes
 // (D is the transform length, a power of two; Dout <= D the number of buckets per level: equal to D,
@@ -126,10 +127,10 @@ hipError_t launch_fill_trivial(float *out, int64_t n_seq, int64_t ld_out, int64_
 
 // K[Nx, Ny] = PhiX PhiY^T. `rows_add_up`: the caller sums over rows of K, so that their rounding errors must not
 // share a sign. `batch` > 1: that many products in one launch, the pointers advanced by the steps (floats) from one to
-// the next.
+// the next. `route_rows` > 0: the kind of tile is chosen as for that many rows of PhiX.
 hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *PhiY, int64_t Ny,
                        int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, bool rows_add_up = false,
-                       int batch = 1, int64_t step_x = 0, int64_t step_y = 0, int64_t step_k = 0);
+                       int batch = 1, int64_t step_x = 0, int64_t step_y = 0, int64_t step_k = 0, int64_t route_rows = 0);
 
 // RFSF-DP-1D features, one fused kernel; d <= 64 and M <= 16 (checked by the API layer). scale_turns: angles in
 // half-turns per unit of X . W, 1 / (pi lengthscale).

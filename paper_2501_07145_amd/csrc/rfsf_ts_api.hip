@@ -690,14 +690,14 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
         {
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, nullptr, inv_ls, cnt, shape->L, shape->d,
-                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr, nullptr) != hipSuccess)
+                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr, nullptr, true) != hipSuccess)
                 return RFSF_E_HIP;
         }
-        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (the rows between two sequences are
-            // computed too and never read; the last row of the chunk has no increment at all)
+        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (in the kind of tile, which decides the order of the
+            // sums, that rows for all points but the chunk's last one take)
             rfsf::ProfileScope scope(rfsf::kTrpProject, stream);
-            if (rfsf::launch_gram(dphi, cnt * shape->L - 1, rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
-                                  twoF, (int64_t)Q * twoF, Q) != hipSuccess)
+            if (rfsf::launch_gram(dphi, cnt * (shape->L - 1), rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
+                                  twoF, (int64_t)Q * twoF, Q, cnt * shape->L - 1) != hipSuccess)
                 return RFSF_E_HIP;
         }
         {

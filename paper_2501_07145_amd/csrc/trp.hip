@@ -21,7 +21,7 @@ template <> struct Vec<4> { typedef floatv4 type; };
 __device__ __forceinline__ float lane_of(float v, int) { return v; }
 __device__ __forceinline__ float lane_of(floatv4 v, int i) { return v[i]; }
 
-// P[(n*L + k)*M*Q + m*Q + q] = Z_m . (delta_m[k] / 2)  (the projection kernel writes halved increments;
+// P[(n*(L-1) + k)*M*Q + m*Q + q] = Z_m . (delta_m[k] / 2)  (the projection kernel writes halved increments;
 // the factor 2 is restored here). A thread owns V consecutive components of one sequence (V = 4: 16-byte
 // loads; the threads of a sequence then read whole rows of P, and consecutive levels and time steps
 // continue the same stream); B time steps are loaded per batch so that B*M loads are in flight per
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void trp_scan_kernel(const float *__restrict__
 #pragma unroll
         for (int i = 0; i < V; ++i) A[m][i] = 0.f;
     const int64_t T = L - 1, MQ = (int64_t)M * Q;
-    const float *p = P + n * L * MQ + q;
+    const float *p = P + n * T * MQ + q;
     for (int64_t k = 0; k < T; k += B) {
         vec v[B][kMaxLevels];
 #pragma unroll
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void trp_pieces_kernel(float *P, int64_t n_seq
     const int64_t T = L - 1, k0 = (v - n * pieces) * steps, k1 = min(k0 + steps, T);
     constexpr auto at = [](int a, int l) { return a * M - a * (a - 1) / 2 + l - a; };
     const int64_t MQ = (int64_t)M * Q;
-    float *p = P + n * L * MQ + (g - v * Q);
+    float *p = P + n * T * MQ + (g - v * Q);
     float A[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) A[i] = 0.f;
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(64) void trp_join_kernel(const float *__restrict__ 
     const int q = (int)(g - n * Q);
     constexpr auto at = [](int a, int l) { return a * M - a * (a - 1) / 2 + l - a; };
     const int64_t MQ = (int64_t)M * Q, stride = steps * MQ;
-    const float *p = P + n * L * MQ + q;
+    const float *p = P + n * (L - 1) * MQ + q;
     float A[M], B[kAhead][NA];
 #pragma unroll
     for (int m = 0; m < M; ++m) A[m] = p[(int64_t)m * Q];
@@ -170,8 +170,8 @@ TrpCut trp_cut(int64_t N, int64_t L, int M, int Q)
     if (want > T / 32) want = T / 32;
     for (; want >= 4; --want) {                      // (three passes over fewer pieces gain nothing)
         const int64_t steps = (T + want - 1) / want, pieces = (T + steps - 1) / steps;
-        // the last piece, too, has to hold its sums, (M+1)/2 rows of P (the row past the last step is part of P)
-        if (2 * (L - (pieces - 1) * steps) >= M + 1) return {(int)pieces, steps};
+        // the last piece, too, has to hold its sums, (M+1)/2 rows of P
+        if (2 * (T - (pieces - 1) * steps) >= M + 1) return {(int)pieces, steps};
     }
     return {1, T};
 }

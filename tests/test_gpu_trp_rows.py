@@ -1,0 +1,29 @@
+"""RFSF-TRP keeps one row per increment: rows of increments close up behind a sequence's last point. Sequences of every length around
+the 32 rows of a tile and the 255 rows of a workgroup's range, in all three projection kernels."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2501_07145_amd as rfsf
+from tests.parity import FP32_BLOCK_TOL, block_errors
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("L", [2, 3, 5, 31, 32, 33, 34, 64, 65, 255, 256, 257])
+@pytest.mark.parametrize("d,bf16", [(3, False), (66, False), (3, True)])
+def test_rows_close_up_behind_every_sequence(oracle, L, d, bf16):
+    N, M, F, Q = 2 + 600 // L, 3, 20, 24
+    rng = np.random.default_rng(L)
+    X = np.cumsum(rng.standard_normal((N, L, d)) / math.sqrt(L), axis=1).astype(np.float32)
+    W = rng.standard_normal((M, d, F)).astype(np.float32)
+    if bf16:                                                 # operands that the rounding leaves as they are
+        X = (np.round(X * 64) / 64).astype(np.float32)
+        W = (np.round(W * 16) / 16).astype(np.float32)
+    Z = rng.standard_normal((M, Q, 2 * F)).astype(np.float32)
+    ls = float(np.float32(2.0 if bf16 else math.sqrt(d)))
+    got = rfsf.rfsf_trp_features(*(torch.from_numpy(a).cuda() for a in (X, W, Z)), ls, rff_bf16=bf16).cpu().numpy()
+    want = oracle.trp_features(X, W, Z, ls)
+    assert np.all(block_errors(got, want, M, Q) <= FP32_BLOCK_TOL)
