@@ -1328,7 +1328,9 @@ __global__ __launch_bounds__(64 * NTR)
     // and the stages of the first pass that would only copy are left out. Features of 1000 x 151 points, projection included, us: 300 buckets in
     // 1024 points, three levels, 190 frequencies 503 -> 490, 150 in 512, four 538 -> 499, 150 in 1024, five 667 -> 632; as many buckets as
     // points 829 and 829, 1366 and 1363.
-    constexpr int kFew = !P::kRowed || M < 2 ? 1 : M < 4 ? 2 : 4;
+    // (512 points: not where it costs kernels that spill another six registers, five levels, order 2, as many buckets as points 821 -> 894 us.)
+    constexpr bool kSpills = LOG2D == 9 && (JOINT || (ORDER > 1 && kStream));
+    constexpr int kFew = !P::kRowed || M < 2 || kSpills ? 1 : M < 4 ? 2 : 4;
     const int groups = (Dout + P::G - 1) / P::G;
     const bool few = kFew > 1 && groups <= P::R / kFew;
 
