@@ -53,8 +53,8 @@ __host__ __device__ constexpr size_t solo_lds_bytes(int D, int M, int FPW, int P
 }
 
 // Where the accumulators of a lane fit the registers (solo_waves_per_simd) and the levels fill the wavefront's
-// transforms: largest number of levels for which that holds. Six levels at D = 100 spill 4 to 6 registers, five at D = 200 3 or 4 (11 to
-// 14 and 10 with twiddles read ahead, see solo_reads_ahead), the others none. What is left out: four levels at D = 200 (four of six transforms used, 1000 x 100 points 185 -> 203 us), five at D = 128 (25
+// transforms: largest number of levels for which that holds. Five levels at D = 200 spill 4
+// registers (10 with twiddles read ahead, see solo_reads_ahead), at D = 64 one or two, the others none. What is left out: four levels at D = 200 (four of six transforms used, 1000 x 100 points 185 -> 203 us), five at D = 128 (25
 // spills, split batches 142 -> 147), orders 2 and 3, whose carried values do not fit.
 __host__ __device__ constexpr bool solo_fits(int M, int D, int order)
 {
@@ -64,15 +64,15 @@ __host__ __device__ constexpr bool solo_fits(int M, int D, int order)
 // Wavefronts per SIMD that the registers are bounded for. (D = 256, four levels, 5000 x 100 points 639 us with three, 888 with
 // four and 48 spills; three levels, 1000 x 100, 149 and 123. D = 128, four levels, takes 123 registers.)
 __host__ __device__ constexpr int solo_waves_per_simd(int M, int D) { return (D >= 200 && M >= 4) ? 3 : 4; }
-// Ten-point butterflies read their twiddles ahead where a lane's accumulators leave the registers for it (3000 x 200 points, 3 and 8
-// channels and 12 from memory, ahead and on the spot: D = 100, five levels, 30 registers of accumulators, 442, 444, 423 and 447, 446,
-// 430 us; six, 42 registers, 603, 611, 586 and 561, 579, 518; D = 200, five levels, 60 registers, 1002, 1174, 915 and 966, 1073, 923).
+// Ten-point butterflies (D = 200) read their twiddles ahead where a lane's accumulators leave the registers for it (3000 x 200 points, 3 and
+// 8 channels and 12 from memory, ahead and on the spot, five levels, 60 registers of accumulators, in three passes: 1002, 1174, 915 and 966,
+// 1073, 923 us).
 __host__ __device__ constexpr bool solo_reads_ahead(int M, int D) { return (D / 2 + 64) / 64 * M * (M + 1) < 40; }
 constexpr int kSoloChannels = 8;
+constexpr int kRawBufferWord3 = 0x00020000;   // buffer descriptor, last word: untyped 32-bit data
 __host__ __device__ constexpr int solo_columns(int D) { return D <= 128 ? 1 : 2; }     // frequencies of a lane
 typedef const __attribute__((address_space(1))) float *GlobalFloats;
 typedef const __attribute__((address_space(4))) float *ConstantFloats;      // scalar loads where the address is uniform
-
 // d > 0: the increments are not in memory, the wavefront computes them from points of d channels (Points), a frequency per
 // lane: angles by multiply-adds of the points' channels with the lane's column of W. The channels are the same for all lanes, but
 // a multiply-add with a scalar register takes 4.35 cycles of a SIMD instead of 2.6: they are in vector registers where there is room.
@@ -138,21 +138,31 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
     const float scale = 0.5f / sqrtf((float)F);
     auto point = [&](int64_t t, float (&x)[kChannels]) {
         const PointFloats src = points + (t < Ln ? t : Ln - 1) * d;
-        uint32_t here = 0;
-        if constexpr (kVectorPoints) asm volatile("" : "+v"(here));      // (vector loads of what is the same for all lanes)
+        if constexpr (kVectorPoints) {                       // vector loads of what is the same for all lanes: a uniform base and a lane's offset
+            uint32_t here = 0;
+            asm volatile("" : "+v"(here));
+            const GlobalFloats at = (GlobalFloats)((const __attribute__((address_space(1))) char *)src + here);
 #pragma unroll
-        for (int c = 0; c < d; ++c) x[c] = src[here + c];
+            for (int c = 0; c < d; ++c) x[c] = at[c];
+        } else {
+#pragma unroll
+            for (int c = 0; c < d; ++c) x[c] = src[c];
+        }
     };
+    auto signed_by = [&](uint32_t flip) { return __uint_as_float(__float_as_uint(scale) ^ (flip & 0x80000000u)); };
     auto column = [&](int l, int col, float (&w)[kChannels], float &scale_c, float &scale_s) {
-        const int frequency = lane + 64 * col < F ? lane + 64 * col : F - 1;
-        GlobalFloats src = (GlobalFloats)cut.points.W + (int64_t)l * d * F, flips = (GlobalFloats)cut.points.sign + (int64_t)l * twoF;
-        asm volatile("" : "+s"(src), "+s"(flips));           // (read again in every iteration, not kept in registers)
-        src += frequency;
-        flips += frequency;
+        uint32_t frequency = 4u * (uint32_t)(lane + 64 * col < F ? lane + 64 * col : F - 1);
+        // A scalar base and offset and a lane's own: as 64-bit addresses they are sums of 4.6 cycles of a SIMD each, 70 per iteration with five
+        // channels and levels. (With signs by logic, below, and the masks of the recurrence, features, us: 100 x 1000 points, five channels, five
+        // levels, D = 100 91.3 -> 88.6, 10 x 1e5 653 -> 628, 1000 x 100, eight, four, D = 256 157 -> 149, 2000 x 200, six, three, D = 128 183 ->
+        // 168, three, five, D = 64 190 -> 184, five, three, D = 200 266 -> 253.)
+        const auto rows = __builtin_amdgcn_make_buffer_rsrc((void *)(cut.points.W + (int64_t)l * d * F), 0, 4 * d * F, kRawBufferWord3);
+        const auto flips = __builtin_amdgcn_make_buffer_rsrc((void *)(cut.points.sign + (int64_t)l * twoF), 0, 4 * twoF, kRawBufferWord3);
+        asm volatile("" : "+v"(frequency));                  // (read again in every iteration, not kept in registers)
 #pragma unroll
-        for (int c = 0; c < d; ++c) w[c] = src[c * F];
-        scale_c = flips[0] < 0.f ? -scale : scale;
-        scale_s = flips[F] < 0.f ? -scale : scale;
+        for (int c = 0; c < d; ++c) w[c] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, frequency, 4 * c * F, 0));
+        scale_c = signed_by(__builtin_amdgcn_raw_buffer_load_b32(flips, frequency, 0, 0));
+        scale_s = signed_by(__builtin_amdgcn_raw_buffer_load_b32(flips, frequency, 4 * F, 0));
     };
     auto features = [&](const float (&x)[kChannels], const float (&w)[kChannels], const Quarters &turn, float &s, float &c) {
         float t = x[0] * w[0];
@@ -175,6 +185,8 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    uint32_t packed = lane == 0 ? 0xffffffffu : 0u;          // the lane of both real bins
+    if constexpr (kPack) asm volatile("" : "+v"(packed));
     __builtin_amdgcn_s_setprio(1);
     for (int64_t pair0 = 0; pair0 < pairs; pair0 += SP) {
         if constexpr (d > 0) {
@@ -261,16 +273,19 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
         fft.template run_from_registers<solo_reads_ahead(M, D)>(my_slot, v);
         __builtin_amdgcn_s_setprio(1);
         wave_lds_fence();
-        // separation and recurrence, a bin per lane, pair after pair
+        // separation and recurrence, a bin per lane, pair after pair. (A second step that does not exist is taken out by a mask: selects take
+        // 4.5 cycles of a SIMD, from vcc up to 16, and code of its own for such a pair costs registers, six levels at D = 100 23 spills.)
 #pragma unroll 1
         for (int i = 0; i < SP; ++i) {
             const int64_t p = pair0 + i;
             if (p >= pairs) break;
+            uint32_t both = 2 * p + 1 < T ? 0xffffffffu : 0u;
+            asm volatile("" : "+v"(both));
 #pragma unroll
             for (int b = 0; b < BPT; ++b) {
                 const int f = lane + 64 * b;
                 if (NB % 64 != 0 && f >= NB) continue;
-                const bool pk = kPack && f == 0;
+                const uint32_t pk = kPack && b == 0 ? packed : 0u;
                 const float2 *Z = wave_lds + i * PS;
                 const int fi = P::pad(f), fc = P::pad(f > 0 ? D - f : kPack ? D / 2 : 0);
                 LevelCarry<ORDER> c[M];
@@ -279,7 +294,7 @@ __global__ __launch_bounds__(64 * kSoloWaves) __attribute__((amdgpu_waves_per_eu
                     const float2 z = Z[(size_t)LL * SP * PS + fi], zc = Z[(size_t)LL * SP * PS + fc];
                     level_loop<LL + 1>([&](auto start_tag) {
                         constexpr int a = decltype(start_tag)::value;
-                        level_step<ORDER, LL - a, kPack, true>(z, zc, pk, 2 * p + 1 < T, A[b][acc_index(M, a, LL)], c[a]);
+                        level_step<ORDER, LL - a, kPack, true>(z, zc, pk, both, A[b][acc_index(M, a, LL)], c[a]);
                     });
                 });
             }

@@ -37,6 +37,8 @@
 
 #include "rfsf_internal.h"
 
+#include <type_traits>
+
 namespace rfsf {
 namespace tuned {
 
@@ -504,14 +506,24 @@ __device__ constexpr int read_order(int i)
 // The same for a thread whose float2 are not complex numbers but two independent reals (pk; bins 0 and D/2
 // of a real sequence's transform, which one thread carries in the two halves of its values): the products
 // become componentwise. With pk false these are cmulf and cfmaf, operation for operation.
-__device__ __forceinline__ float2 cmulf_pk(float2 a, float2 b, bool pk)
+// (pk: true or false, or, in a vector register, all bits set or none, which a logic instruction chooses by in 2.7 cycles of a SIMD: a
+// select takes 4.5, from vcc up to 16. In the kernel of a workgroup per sequence, where one wavefront in eight has such a thread, it gains
+// nothing and costs registers: 20 x 4000 points, 512 buckets, four levels 305 -> 323 us.)
+__device__ __forceinline__ float choose(bool pk, float x, float y) { return pk ? x : y; }
+__device__ __forceinline__ float choose(uint32_t pk, float x, float y)
 {
-    const float s = pk ? 0.f : b.y, r = pk ? b.y : b.x;
+    return __uint_as_float(__builtin_amdgcn_bitop3_b32(pk, __float_as_uint(x), __float_as_uint(y), 0xca));
+}
+template <typename Packed>
+__device__ __forceinline__ float2 cmulf_pk(float2 a, float2 b, Packed pk)
+{
+    const float s = choose(pk, 0.f, b.y), r = choose(pk, b.y, b.x);
     return make_float2(fmaf(a.x, b.x, -a.y * s), fmaf(a.x, s, a.y * r));
 }
-__device__ __forceinline__ float2 cfmaf_pk(float2 a, float2 b, float2 c, bool pk)
+template <typename Packed>
+__device__ __forceinline__ float2 cfmaf_pk(float2 a, float2 b, float2 c, Packed pk)
 {
-    const float s = pk ? 0.f : b.y, r = pk ? b.y : b.x;
+    const float s = choose(pk, 0.f, b.y), r = choose(pk, b.y, b.x);
     return make_float2(fmaf(a.x, b.x, fmaf(-a.y, s, c.x)), fmaf(a.x, s, fmaf(a.y, r, c.y)));
 }
 
@@ -904,14 +916,23 @@ __device__ __forceinline__ void level_loop(Fn &&f)
 // the packed one (pk), whose float2 hold bins 0 and D/2 and whose z, zc are Z[0], Z[D/2]. ADDS: level 0, whose A_0 is 1, takes two
 // additions instead of four multiply-adds with one and zero (the kernel of whole sequences is no faster for it: 10000 x 200 points,
 // D = 1024, five levels 10.58 and 10.85 ms).
-template <int ORDER, int LL, bool PK, bool ADDS = false>
-__device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool second_step, float2 &a, LevelCarry<ORDER> &c)
+// second_step: whether the second step exists, or all bits set if it does and none if not, in a vector register.
+__device__ __forceinline__ float2 if_step(bool exists, float2 C) { return exists ? C : make_float2(0.f, 0.f); }
+__device__ __forceinline__ float2 if_step(uint32_t exists, float2 C)
+{
+    return make_float2(__uint_as_float(__float_as_uint(C.x) & exists), __uint_as_float(__float_as_uint(C.y) & exists));
+}
+template <int ORDER, int LL, bool PK, bool ADDS = false, typename Packed, typename Second>
+__device__ __forceinline__ void level_step(float2 z, float2 zc, Packed pk, Second second_step, float2 &a, LevelCarry<ORDER> &c)
 {
     auto mul = [&](float2 x, float2 y) { return PK ? cmulf_pk(x, y, pk) : cmulf(x, y); };
     auto fma = [&](float2 x, float2 y, float2 w) { return PK ? cfmaf_pk(x, y, w, pk) : cfmaf(x, y, w); };
     if constexpr (LL == 0) {
         c.reset();
-        if (PK && pk) c.p0.y = c.p1.y = 1.f;                            // A_0 = 1 in both bins of the packed thread
+        if constexpr (PK) {                                             // A_0 = 1 in both bins of the packed thread
+            if constexpr (!std::is_same_v<Packed, bool>) c.p0.y = c.p1.y = choose(pk, 1.f, 0.f);
+            else if (pk) c.p0.y = c.p1.y = 1.f;
+        }
     }
     // separation of the two real transforms; for the packed thread C = (2 Re z, 2 Re zc), (2 Im z, 2 Im zc):
     // the values the general formulas give at f = 0 and f = D/2
@@ -919,13 +940,16 @@ __device__ __forceinline__ void level_step(float2 z, float2 zc, bool pk, bool se
     // a second step that does not exist (odd number of increments) must contribute
     // exactly nothing; the separation alone would leave rounding noise of the first
     float2 C1 = make_float2(z.y + zc.y, zc.x - z.x);
-    if constexpr (PK) {
+    if constexpr (PK && !std::is_same_v<Packed, bool>) {
+        C0 = make_float2(choose(pk, z.x + z.x, C0.x), choose(pk, zc.x + zc.x, C0.y));
+        C1 = make_float2(choose(pk, z.y + z.y, C1.x), choose(pk, zc.y + zc.y, C1.y));
+    } else if constexpr (PK) {
         if (pk) {
             C0 = make_float2(z.x + z.x, zc.x + zc.x);
             C1 = make_float2(z.y + z.y, zc.y + zc.y);
         }
     }
-    if (!second_step) C1 = make_float2(0.f, 0.f);
+    C1 = if_step(second_step, C1);
     const float2 a_old = a;
     float2 a_mid = ADDS && LL == 0 ? make_float2(a_old.x + C0.x, a_old.y + C0.y) : fma(c.p0, C0, a_old);
     // order >= 2 (a time step may be used up to `order` times in a row, q equal indices weighted
