@@ -5,6 +5,8 @@
 #include "sincos.h"
 #include "sketch_tables.h"
 
+#include <type_traits>
+
 // The increments are written once and read once, by the next kernel, long after they have left the caches:
 // non-temporal stores (measured: the projection kernel of Large 8.2 -> 6.4 ms, Long 3 % faster, Medium unchanged;
 // on Small, which would fit the last-level cache, the producer loses what the consumer gains).
@@ -58,8 +60,9 @@ constexpr int kRowsPerTile = 32;
 // the first block of the lower half, from the previous tile (carry).
 // Row layout (PAIRED = false): increment k = phi(row k+1) - phi(row k) is stored at row k, scalar base +
 // 32-bit lane offset, one predicate per row. `last`: bit r is set if row k of tile row r is a sequence's last point, whose increment
-// into the next sequence is left out; the rows behind it then move up.
-template <typename AngleOf>
+// into the next sequence is left out; the rows behind it then move up. GAPS: there is one. (Tiles of long sequences have none, and the few
+// workgroups of small batches wait for every instruction: 32 x 130 points, 237 frequencies 81 -> 87 us with the places counted in every tile.)
+template <bool GAPS, typename AngleOf>
 __device__ __forceinline__ void sincos_difference_store(
     AngleOf angle, const ScaledCoeffs &coeffs, float &carry_c, float &carry_s, int half, bool f_ok, int nrow,
     int64_t gt, int64_t g0, int64_t rf, int F, float *__restrict__ dphi, int cos_at, int64_t row0, uint32_t last)
@@ -69,6 +72,10 @@ __device__ __forceinline__ void sincos_difference_store(
     // exist; both cases are lane-uniform per row and folded into one predicate per store.
     float *cos_base = dphi + row0 * rf;                   // uniform (gt = 0: row -1 is never stored)
     float *sin_base = cos_base + F;
+    const uint32_t lane_off = (uint32_t)cos_at + (uint32_t)(4 * half) * (uint32_t)rf;
+    // GAPS: this half's rows (bits 8 q + i) without an increment, and where the next one goes
+    const uint32_t mine = GAPS ? last >> (4 * half) : 0;
+    uint32_t place = GAPS ? lane_off - (half ? (uint32_t)__popc(last & 15u) * (uint32_t)rf : 0u) : 0;
     const int first = gt > g0 ? 0 : 1;                          // first tile row whose increment is ours
     float below_c = carry_c, below_s = carry_s;                 // lower half: partner's previous block
 #pragma unroll
@@ -85,16 +92,15 @@ __device__ __forceinline__ void sincos_difference_store(
             const float dc = cs[i] - (i ? cs[i - 1] : up_c);
             const float ds = sn[i] - (i ? sn[i - 1] : up_s);
             const int r = 8 * q + 4 * half + i;
-            // (both halves' places in scalar registers: one select)
-            const int lower = 8 * q + i, upper = lower + 4;
-            const uint32_t at_lower = (uint32_t)(lower - __popc(last & ((1u << lower) - 1u))) * (uint32_t)rf;
-            const uint32_t at_upper = (uint32_t)(upper - __popc(last & ((1u << upper) - 1u))) * (uint32_t)rf;
-            if (f_ok && r >= first && r < nrow && !(last >> r & 1u)) {
-                const uint32_t off = (uint32_t)cos_at + (half ? at_upper : at_lower);
+            const uint32_t gap = GAPS ? (uint32_t)__builtin_amdgcn_sbfe((int)mine, 8 * q + i, 1) : 0u;      // all bits, or none
+            const uint32_t off = GAPS ? place : lane_off + (uint32_t)(8 * q + i) * (uint32_t)rf;
+            if (GAPS) place += (uint32_t)rf & ~gap;
+            if (f_ok && r >= first && r < nrow && !gap) {
                 cos_base[off] = dc;
                 sin_base[off] = ds;
             }
         }
+        if (GAPS) place += (4u - (uint32_t)__popc(mine >> (8 * q + 4) & 15u)) * (uint32_t)rf;      // the other half's rows
     }
     carry_c = below_c;      // row 31 of this tile as seen by the lower half (unused by the upper half)
     carry_s = below_s;
@@ -420,8 +426,12 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
         else {
             uint32_t last;
             const int64_t row0 = tile_place(gt, L, last_rows, last);
-            sincos_difference_store([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, nrow, gt, g0,
+            const auto store = [&](auto gaps_tag) {
+                sincos_difference_store<decltype(gaps_tag)::value>([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, nrow, gt, g0,
                                     rf, F, dphi, m * 2 * F + f, row0, last);
+            };
+            if (last) store(std::true_type{});
+            else store(std::false_type{});
         }
         if (more) put_tile(xs + (cur ^ 1) * (kRowsPerTile * XS));
         __syncthreads();
@@ -552,8 +562,12 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
         else {
             uint32_t last;
             const int64_t row0 = tile_place(gt, L, last_rows, last);
-            sincos_difference_store([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s, half,
+            const auto store = [&](auto gaps_tag) {
+                sincos_difference_store<decltype(gaps_tag)::value>([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s, half,
                                     f_ok, nrow, gt, g0, rf, F, dphi, m * 2 * F + f, row0, last);
+            };
+            if (last) store(std::true_type{});
+            else store(std::false_type{});
         }
         if (more) put_tile(cur ^ 1);
         __syncthreads();
@@ -597,11 +611,18 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     // eight, except that 126 increments measured 7 % faster on 10000 x 200 x 17 -- and 11 % slower on
     // 2000 x 2000 x 32 and 50000 x 64 x 64).
     const int64_t slabs = ((int64_t)M * F + 127) / 128;
+    // Row layout: ranges of one (two) tiles where eight would give fewer than 512 (2048) workgroups (RFSF-TRP's features, 200 projections, and
+    // 197 in the third: 32 x 130 points, 237 frequencies 81 -> 75 us, 1 x 768, 328, 65 -> 50, 875 x 5, 57, 58 -> 46; 7494 x 8, 200, 1888
+    // workgroups of eight tiles, with Gram 712 -> 683).
     int64_t rows_per_block = paired ? 254 : 255;
     if (paired) {
         const int64_t wgs = ((rows - 2) / 254 + 1) * slabs;
         if (wgs < 2048) rows_per_block = 62;
         else if (wgs < 4096) rows_per_block = 126;
+    } else if (matrix_cores) {
+        const int64_t wgs = ((rows - 2) / 255 + 1) * slabs;
+        if (wgs < 512) rows_per_block = 31;
+        else if (wgs < 2048) rows_per_block = 63;
     }
     const int64_t nblk = paired ? (rows - 2) / rows_per_block + 1 : (rows - 1 + rows_per_block - 1) / rows_per_block;
     const float scale = 0.5f / sqrtf((float)F);    // the consumer's two-for-one FFT wants halved increments

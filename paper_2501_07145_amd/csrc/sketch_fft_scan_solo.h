@@ -28,10 +28,10 @@ namespace tuned {
 
 // Bank conflicts. 16 lanes at a time write float2, over 32 banks, at least 6.4 cycles for a wavefront, 32 lanes read, over 64 banks, at
 // least 3.5. The lanes of a transform that write next to each other are few here (4, 5 and 8 for 64, 100 and 128 points), so
-// that several transforms' meet in a bank unless the slots are the right distance apart: solo_stride; and with 100 points the first
-// pass turns its results (MixedPlan). Cycles of a transform's exchanges, gather and separation by that count, before and
-// after: 64 points 598 -> 526, 128 567 -> 499 (256: 517, at best 502). SQ_LDS_BANK_CONFLICT of a launch: 1500 x 200 points, five levels, 32
-// frequencies, 64 points 1.71e7 -> 1.03e7; 1500 x 200, four, 64, 128 2.54e7 -> 1.04e7: some are left.
+// that several transforms' meet in a bank unless the slots are the right distance apart: solo_stride. Cycles of a transform's exchanges, gather
+// and separation by that count, before and after: 64 points 598 -> 526, 128 567 -> 499 (256: 517, at best 502). SQ_LDS_BANK_CONFLICT of a
+// launch: 1500 x 200 points, five levels, 32 frequencies, 64 points 1.71e7 -> 1.03e7; 1500 x 200, four, 64, 128 2.54e7 -> 1.04e7: some are
+// left, and not worth more: distances that count a quarter less for the exchanges of 100 points, and a sixth less for those of 256, gained nothing.
 // Pairs of steps of a wavefront's iteration; 0: the levels do not fit a wavefront.
 __host__ __device__ constexpr int solo_pairs(int M, int FPW) { return FPW / M; }
 __host__ __device__ constexpr size_t solo_lds_with(int M, int FPW, int stride, int NTWL)
