@@ -51,6 +51,9 @@ __device__ __forceinline__ void sincos_scaled(float x, const ScaledCoeffs &k, fl
     c = __uint_as_float(__float_as_uint(cc) ^ ((((unsigned)q + 1u) & 2u) << 30));
 }
 
+// The sign bit decides, of zeros and NaN too: the generic consumer and the kernel that computes its increments itself read no more of a sign.
+__device__ __forceinline__ bool sign_bit(float sign) { return (int)__float_as_uint(sign) < 0; }
+
 constexpr int kRowsPerTile = 32;
 
 // Epilogue shared by the matrix-core kernels: sin/cos of the 16 angles a lane holds (rows
@@ -272,8 +275,8 @@ __global__ __launch_bounds__(256) void rff_increments_valu_pairs(
     const int64_t k_hi = min(k_lo + 253, rows_pad - 1);                // odd: whole pairs
     const float *Wm = W + (int64_t)m * d * F;
     const int64_t pair_floats = (int64_t)M * 4 * F;
-    const float sc = active && sign && sign[(int64_t)m * 2 * F + a] < 0.f ? -scale : scale;
-    const float ss = active && sign && sign[(int64_t)m * 2 * F + F + a] < 0.f ? -scale : scale;
+    const float sc = active && sign && sign_bit(sign[(int64_t)m * 2 * F + a]) ? -scale : scale;
+    const float ss = active && sign && sign_bit(sign[(int64_t)m * 2 * F + F + a]) ? -scale : scale;
     float pc = 0.f, ps = 0.f, hold_c = 0.f, hold_s = 0.f;
     // phi of rows k_lo .. k_hi + 1; increment k = phi(k+1) - phi(k)
     for (int64_t gt = k_lo; gt <= k_hi + 1; gt += kRowsPerTile) {
@@ -360,8 +363,8 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
     const int64_t rf = (int64_t)M * 2 * F;
     bool flip_c = false, flip_s = false;
     if (PAIRED && f_ok) {
-        flip_c = sign[(int64_t)m * 2 * F + f] < 0.f;
-        flip_s = sign[(int64_t)m * 2 * F + F + f] < 0.f;
+        flip_c = sign_bit(sign[(int64_t)m * 2 * F + f]);
+        flip_s = sign_bit(sign[(int64_t)m * 2 * F + F + f]);
     }
     const float wscale = (flip_c != flip_s) ? -inv_lengthscale : inv_lengthscale;
 
@@ -480,8 +483,8 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
     const int64_t rf = (int64_t)M * 2 * F;
     bool flip_c = false, flip_s = false;
     if (PAIRED && f_ok) {
-        flip_c = sign[(int64_t)m * 2 * F + f] < 0.f;
-        flip_s = sign[(int64_t)m * 2 * F + F + f] < 0.f;
+        flip_c = sign_bit(sign[(int64_t)m * 2 * F + f]);
+        flip_s = sign_bit(sign[(int64_t)m * 2 * F + F + f]);
     }
     const float wsign = (flip_c != flip_s) ? -1.0f : 1.0f;     // exact in bf16: the rounding of W is unchanged
 
