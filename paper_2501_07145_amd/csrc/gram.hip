@@ -1110,17 +1110,17 @@ hipError_t launch_small(const GramArgs &g, bool sym, bool flip, int batch, hipSt
 
 hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *PhiY, int64_t Ny,
                        int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, bool rows_add_up, int batch,
-                       int64_t step_x, int64_t step_y, int64_t step_k, int64_t route_rows)
+                       int64_t step_x, int64_t step_y, int64_t step_k, int64_t points)
 {
     if (Nx == 0 || Ny == 0) return hipSuccess;
     const GramArgs g = {PhiX, PhiY, K, Nx, Ny, ncols, ldx, ldy, ldk, step_x, step_y, step_k};
     // K = PhiX PhiX^T: only what lies on or above the diagonal is computed, and written twice
     const bool sym = PhiX == PhiY && Nx == Ny && ldx == ldy && !rows_add_up;
-    const int64_t rows = route_rows ? route_rows : Nx;        // rows by which the kind of tile is chosen
-    const auto count = [&](int64_t edge) {
+    const auto count = [&](int64_t edge, int64_t rows) {
         const int64_t ti = (rows + edge - 1) / edge, tj = (Ny + edge - 1) / edge;
         return (sym ? ti * (ti + 1) / 2 : ti * tj) * batch;
     };
+    const auto rounds_of = [&](int64_t rows) { return (big_tiles(rows, Ny, sym) * batch + 255) / 256; };
     const int64_t few = std::min(Nx, Ny), many = std::max(Nx, Ny);
     if (!rows_add_up && batch == 1 && few <= kFew && thin_pays(few, many, ncols)) return launch_thin(g, stream);
     // Large tiles run one per CU at a time or, faster together, two; with `rounds` = their number over 256, rounded up,
@@ -1131,9 +1131,18 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
     // 606 against 56, 70, 118, 464). Two terms are for calls that three would run in large tiles as well: the small ones add up in four
     // or eight sums, and their error is half that of a large tile's single one (5121 columns 5.0e-7 and 9.4e-7), which
     // 2500, 3000 and 4000 rows, faster as they would be, are not to lose.
-    const int64_t tiles = big_tiles(Nx, Ny, sym), rounds = (big_tiles(rows, Ny, sym) * batch + 255) / 256;
+    // RFSF-TRP's products: large tiles are slower up to 800 tiles of 64 x 64 per round and faster from about 1000 on (features of sequences of two
+    // points, five levels, 200 projections, 200 frequencies, 64 x 64 and large: 2400 sequences 48.8 and 53.7 us, 3200 55.4 and 55.4, 4400 71.8 and
+    // 57.5; 16 frequencies 24.4 and 25.8, 27.8 and 27.9, 34.4 and 30.5; 500 73 and 85, 89 and 87, 121 and 94), but their error is 1.1 (32 columns) to
+    // 1.4 times (400 and 1000) that of the small ones. So only calls of which a row for every point, which these products once
+    // had, would be above the line of the others take them, and of these not those that the rows that there are leave below 800.
     const bool two = ncols >= kTwoTermColumns;
-    const bool large = count(64) > 1340 * rounds && (!two || count(64) * (105 + ncols) > 140000 + rounds * (150000 + 760 * ncols));
+    const auto above_line = [&](int64_t rows) {
+        const int64_t small = count(64, rows), rounds = rounds_of(rows);
+        return small > 1340 * rounds && (!two || small * (105 + ncols) > 140000 + rounds * (150000 + 760 * ncols));
+    };
+    const int64_t tiles = big_tiles(Nx, Ny, sym);
+    const bool large = points ? above_line(points) && count(64, Nx) > 800 * rounds_of(Nx) : above_line(Nx);
     if (large && ldx <= kBigMaxStride && ldy <= kBigMaxStride) {
         if (tiles > 0x7fffffffLL - 8) return hipErrorInvalidValue;
         const bool aligned = ldx % 4 == 0 && ldy % 4 == 0 && step_x % 4 == 0 && step_y % 4 == 0 &&
@@ -1162,9 +1171,9 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
     // clock; sixteen wavefronts or two steps ahead change nothing), here half of what a tile of 32 x 32 does (100 x 100 rows, 5121 columns 41 ->
     // 20 us, 200 x 200, 8191 60 -> 31, 16 x 1000, 5121 33 -> 20, 300 x 300, 361 tiles, 2049 columns and more about the same, 400 x 400, 625 tiles,
     // 18 and 24 with 2049)
-    if (count(16) <= 256) return launch_small<1, 8>(g, sym, rows_add_up, batch, stream);
-    if (count(64) <= 150) return launch_small<2, 8>(g, sym, rows_add_up, batch, stream);
-    if (count(64) <= 256) return launch_small<4, 8>(g, sym, rows_add_up, batch, stream);
+    if (count(16, Nx) <= 256) return launch_small<1, 8>(g, sym, rows_add_up, batch, stream);
+    if (count(64, Nx) <= 150) return launch_small<2, 8>(g, sym, rows_add_up, batch, stream);
+    if (count(64, Nx) <= 256) return launch_small<4, 8>(g, sym, rows_add_up, batch, stream);
     return launch_small<4, 4>(g, sym, rows_add_up, batch, stream);
 }
 

@@ -127,10 +127,10 @@ hipError_t launch_fill_trivial(float *out, int64_t n_seq, int64_t ld_out, int64_
 
 // K[Nx, Ny] = PhiX PhiY^T. `rows_add_up`: the caller sums over rows of K, so that their rounding errors must not
 // share a sign. `batch` > 1: that many products in one launch, the pointers advanced by the steps (floats) from one to
-// the next. `route_rows` > 0: the kind of tile is chosen as for that many rows of PhiX.
+// the next. `points` > 0 (RFSF-TRP): the points that the rows of PhiX, increments, lie between.
 hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *PhiY, int64_t Ny,
                        int64_t ldy, int64_t ncols, float *K, int64_t ldk, hipStream_t stream, bool rows_add_up = false,
-                       int batch = 1, int64_t step_x = 0, int64_t step_y = 0, int64_t step_k = 0, int64_t route_rows = 0);
+                       int batch = 1, int64_t step_x = 0, int64_t step_y = 0, int64_t step_k = 0, int64_t points = 0);
 
 // RFSF-DP-1D features, one fused kernel; d <= 64 and M <= 16 (checked by the API layer). scale_turns: angles in
 // half-turns per unit of X . W, 1 / (pi lengthscale).

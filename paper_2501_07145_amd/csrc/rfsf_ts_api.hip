@@ -693,8 +693,7 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
                                             shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr, nullptr, true) != hipSuccess)
                 return RFSF_E_HIP;
         }
-        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch (in the kind of tile, which decides the order of the
-            // sums, that rows for all points but the chunk's last one take)
+        {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch
             rfsf::ProfileScope scope(rfsf::kTrpProject, stream);
             if (rfsf::launch_gram(dphi, cnt * (shape->L - 1), rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
                                   twoF, (int64_t)Q * twoF, Q, cnt * shape->L - 1) != hipSuccess)

@@ -27,3 +27,18 @@ def test_rows_close_up_behind_every_sequence(oracle, L, d, bf16):
     got = rfsf.rfsf_trp_features(*(torch.from_numpy(a).cuda() for a in (X, W, Z)), ls, rff_bf16=bf16).cpu().numpy()
     want = oracle.trp_features(X, W, Z, ls)
     assert np.all(block_errors(got, want, M, Q) <= FP32_BLOCK_TOL)
+
+
+@pytest.mark.parametrize("N,L,Q", [(16, 3, 200), (40, 2, 200), (300, 2, 200), (400, 2, 200), (700, 2, 200), (2400, 2, 200), (2400, 3, 200), (3000, 2, 72)])
+def test_short_sequences_on_both_sides_of_the_kinds_of_tiles(oracle, N, L, Q):
+    """The products' tiles are chosen by the increments, half as many as points here."""
+    M, F = 5, 64
+    rng = np.random.default_rng(N)
+    X = rng.standard_normal((N, L, 3)).astype(np.float32)
+    W = rng.standard_normal((M, 3, F)).astype(np.float32)
+    Z = rng.standard_normal((M, Q, 2 * F)).astype(np.float32)
+    got = rfsf.rfsf_trp_features(*(torch.from_numpy(a).cuda() for a in (X, W, Z)), 1.7).cpu().numpy()
+    want = oracle.trp_features(X, W, Z, 1.7)
+    levels = min(M, L - 1)                                   # (no more steps than levels: blocks of zeros)
+    assert np.all(block_errors(got, want, M, Q)[:levels] <= FP32_BLOCK_TOL)
+    assert not np.any(got[:, 1 + levels * Q:])
