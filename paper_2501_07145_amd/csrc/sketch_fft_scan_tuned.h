@@ -836,11 +836,22 @@ struct WaveFft {
 // same helps where one wavefront per level gives a CU too few wavefronts for other reasons: D = 1024 and 1000
 // with up to three levels (+3-7 %; four levels: +-1 %), and D = 2048, whose slots let one workgroup per CU
 // be resident whatever its size (up to seven levels: +10-20 %, one level +15 %, two +-0). D = 500 with 5 or 6
-// levels gains 16 %, D = 512 with 5 levels 3 % (with 6: none); D = 256 loses 40 %.
+// levels gains 4 to 16 and 0 to 10 %, D = 512 with 5 levels 4 to 20 % (with 6: none), order 1; D = 256 loses 40 %.
 __host__ __device__ constexpr int transforms_in_flight(int M, int LOG2D) {
     return ((LOG2D == 10 || LOG2D == 1000) && (M <= 3 || M == 5 || M == 6)) || (LOG2D == 2048 && M <= 7) ||
                    (LOG2D == 500 && (M == 5 || M == 6)) || (LOG2D == 9 && M == 5)
                ? 8 : M;
+}
+
+// The kernel for whole sequences of orders 2 and 3 carries values from pair to pair, dealt items one set for every pair of a wavefront: with 500
+// and 512 points (two pairs) that costs it 15 to 46 spills, a wavefront per level 0 to 13. (Features, dealt and per level, us, 1500 x 333 and
+// 400 x 100 points, 7 channels, order 2: 500 points, five levels, 250 frequencies 3613 and 3358, 318 and 256, six 4400 and 3657, 405 and
+// 293; 512, five, 256 2670 and 2628, 249 and 217; order 3 4035 and 3366, 361 and 256, 5025 and 4116, 472 and 331, 3381 and 2668, 319 and
+// 223. With one pair, 1000 and 1024 points, dealt items stay ahead: 1024, five levels, order 2 4543 and 5467, 437 and 442, order 3 5331 and
+// 5505, 501 and 449.)
+__host__ __device__ constexpr int whole_transforms_in_flight(int M, int LOG2D, int order)
+{
+    return order > 1 && (LOG2D == 500 || LOG2D == 9) ? M : transforms_in_flight(M, LOG2D);
 }
 
 typedef const __attribute__((address_space(1))) uint32_t *GlobalWords;   // table words, known to be in global memory

@@ -318,7 +318,7 @@ def test_signature_order_three(oracle, N, L, d, M, F, D):
 @pytest.mark.parametrize("order", [1, 2, 3])
 def test_two_pairs_per_wavefront_dealt_to_eight_wavefronts(oracle, L, order):
     """Transforms of 512 with five levels: the items, here groups of two pairs of one level, go to eight
-    wavefronts in order; the lengths give last groups with one and with two pairs and last iterations with
+    wavefronts in order (order 1; a wavefront per level with orders 2 and 3); the lengths give last groups with one and with two pairs and last iterations with
     different numbers of items. Also as a batch of different lengths."""
     N, d, M, F, D = 4, 3, 5, 40, 512
     inp = _random_case(1200 + L, N, L, d, M, F, D)
