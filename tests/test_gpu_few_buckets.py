@@ -31,3 +31,24 @@ def test_empty_groups_of_buckets_are_left_out(oracle, M, F, D, order, L):
     for m in range(min(M, L - 1) if order == 1 else M):              # (no more steps than levels: blocks of zeros)
         g, w = (a[:, 1 + m * D:1 + (m + 1) * D].astype(np.float64) for a in (got, want))
         assert np.linalg.norm(g - w) <= 1.5e-6 * np.linalg.norm(w), m
+
+
+@pytest.mark.parametrize("M,F,D,order", [
+    (2, 60, 255, 2), (3, 60, 171, 1), (4, 60, 127, 2), (5, 60, 103, 1), (6, 60, 85, 3), (7, 60, 74, 2), (8, 60, 63, 1),      # 512 points
+    (3, 200, 683, 2), (4, 200, 511, 1), (5, 200, 410, 2), (6, 200, 341, 3), (7, 200, 292, 1),                                # 2048
+])
+def test_sequences_cut_in_time(oracle, M, F, D, order):
+    """Pieces of a few sequences, whose kernels leave the empty groups out where that costs them no registers. Increments are 0.14 in size, of which
+    32-bit angles, sines and cosines leave 7e-8 / 0.14, sqrt(m) times that of a product of m; three times that."""
+    N, L = 2, 90
+    rng = np.random.default_rng(D + M)
+    X = np.cumsum(rng.standard_normal((N, L, 9)) * 0.2, axis=1).astype(np.float32)
+    W = rng.standard_normal((M, 9, F)).astype(np.float32)
+    hash_ = rng.integers(0, D, size=(M, 2 * F)).astype(np.int32)
+    hash_[:, 0] = D - 1
+    sign = (2.0 * rng.integers(0, 2, size=(M, 2 * F)) - 1.0).astype(np.float32)
+    got = rfsf.rfsf_ts_features(*(torch.from_numpy(a).cuda() for a in (X, W, hash_, sign)), 3.0, D, order=order).cpu().numpy()
+    want = oracle.features(X, W, hash_, sign, 3.0, D, order=order)
+    for m in range(M):
+        g, w = (a[:, 1 + m * D:1 + (m + 1) * D].astype(np.float64) for a in (got, want))
+        assert np.linalg.norm(g - w) <= 1.5e-6 * np.sqrt(m + 1) * np.linalg.norm(w), m
