@@ -1,5 +1,5 @@
 """RFSF-TRP keeps one row per increment: rows of increments close up behind a sequence's last point. Sequences of every length around
-the 32 rows of a tile and the 255 rows of a workgroup's range, in all three projection kernels."""
+the 32 rows of a tile and the 31, 63 and 255 increments of a workgroup's range, in all three projection kernels."""
 import math
 
 import numpy as np
@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("L", [2, 3, 5, 31, 32, 33, 34, 64, 65, 255, 256, 257])
 @pytest.mark.parametrize("d,bf16", [(3, False), (66, False), (3, True)])
 def test_rows_close_up_behind_every_sequence(oracle, L, d, bf16):
+    """Ranges of 255 increments on the vector units (66 channels), of 31, a tile, on the matrix units, where these batches are small."""
     N, M, F, Q = 2 + 600 // L, 3, 20, 24
     rng = np.random.default_rng(L)
     X = np.cumsum(rng.standard_normal((N, L, d)) / math.sqrt(L), axis=1).astype(np.float32)
@@ -27,6 +28,29 @@ def test_rows_close_up_behind_every_sequence(oracle, L, d, bf16):
     got = rfsf.rfsf_trp_features(*(torch.from_numpy(a).cuda() for a in (X, W, Z)), ls, rff_bf16=bf16).cpu().numpy()
     want = oracle.trp_features(X, W, Z, ls)
     assert np.all(block_errors(got, want, M, Q) <= FP32_BLOCK_TOL)
+
+
+@pytest.mark.parametrize("L", [2, 3, 5, 31, 32, 33, 34, 62, 63, 64, 65, 254, 255, 256, 257])
+@pytest.mark.parametrize("rows", [9 * 255, 33 * 255])
+@pytest.mark.parametrize("bf16", [False, True])
+def test_ranges_of_several_tiles_on_the_matrix_units(oracle, L, rows, bf16):
+    """63 slabs of 128 frequencies: from 9 ranges of 255 increments on (512 workgroups) ranges have 63, two tiles, from 33 on (2048) 255, eight.
+    A row out of its place would move those of all later sequences; some are compared, in the middle and at the end."""
+    M, d, F, Q = 4, 3, 2000, 8
+    N = rows // L + 1
+    rng = np.random.default_rng(L + rows)
+    X = np.cumsum(rng.standard_normal((N, L, d)) / math.sqrt(L), axis=1).astype(np.float32)
+    W = rng.standard_normal((M, d, F)).astype(np.float32)
+    if bf16:                                                 # operands that the rounding leaves as they are
+        X = (np.round(X * 64) / 64).astype(np.float32)
+        W = (np.round(W * 16) / 16).astype(np.float32)
+    Z = rng.standard_normal((M, Q, 2 * F)).astype(np.float32)
+    got = rfsf.rfsf_trp_features(*(torch.from_numpy(a).cuda() for a in (X, W, Z)), 2.0, rff_bf16=bf16).cpu().numpy()
+    assert np.all(np.isfinite(got))
+    few = max(2, 200 // L)
+    sel = np.unique(np.clip(np.r_[0:few, N // 3:N // 3 + few, N // 2:N // 2 + few, N - few:N], 0, N - 1))
+    want = oracle.trp_features(X[sel], W, Z, 2.0)
+    assert np.all(block_errors(got[sel], want, M, Q) <= FP32_BLOCK_TOL)
 
 
 @pytest.mark.parametrize("N,L,Q", [(16, 3, 200), (40, 2, 200), (300, 2, 200), (400, 2, 200), (700, 2, 200), (2400, 2, 200), (2400, 3, 200), (3000, 2, 72)])
