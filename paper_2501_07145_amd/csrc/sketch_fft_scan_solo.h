@@ -53,9 +53,11 @@ __host__ __device__ constexpr size_t solo_lds_bytes(int D, int M, int FPW, int P
 }
 
 // Where the accumulators of a lane fit the registers (solo_waves_per_simd) and the levels fill the wavefront's
-// transforms: largest number of levels for which that holds. Five levels at D = 200 spill 4
-// registers (10 with twiddles read ahead, see solo_reads_ahead), at D = 64 one or two, the others none. What is left out: four levels at D = 200 (four of six transforms used, 1000 x 100 points 185 -> 203 us), five at D = 128 (25
-// spills, split batches 142 -> 147), orders 2 and 3, whose carried values do not fit.
+// transforms: largest number of levels for which that holds. Five levels at D = 200 spill 4 registers, at D = 64 one or two, the others none. What is left out: orders 2
+// and 3, whose carried values do not fit; four levels at D = 200, four of six transforms used (in the other kernels and here, us: 1000 x
+// 100 points, 5 channels, 50 frequencies 103 and 144, 8, 100 176 and 176, 10 x 20000, 8, 100 373 and 404, but 100 x 1000, 8, 100 192 and 157,
+// 3000 x 200, 1, 128 1088 and 745); five at D = 128, which has 6 to 8 spills since W is read by 32-bit offsets (25 before, and split batches
+// took 147 for 142) and would be faster here by now (50 frequencies, 5 channels, 3000 x 200 782 and 464, 100 x 1000 111 and 95).
 __host__ __device__ constexpr bool solo_fits(int M, int D, int order)
 {
     if (order != 1 || M < 2) return false;
@@ -64,9 +66,9 @@ __host__ __device__ constexpr bool solo_fits(int M, int D, int order)
 // Wavefronts per SIMD that the registers are bounded for. (D = 256, four levels, 5000 x 100 points 639 us with three, 888 with
 // four and 48 spills; three levels, 1000 x 100, 149 and 123. D = 128, four levels, takes 123 registers.)
 __host__ __device__ constexpr int solo_waves_per_simd(int M, int D) { return (D >= 200 && M >= 4) ? 3 : 4; }
-// Ten-point butterflies (D = 200) read their twiddles ahead where a lane's accumulators leave the registers for it (3000 x 200 points, 3 and
-// 8 channels and 12 from memory, ahead and on the spot, five levels, 60 registers of accumulators, in three passes: 1002, 1174, 915 and 966,
-// 1073, 923 us).
+// Ten-point butterflies (D = 200) read their twiddles ahead where a lane's accumulators leave the registers for it: two and three levels (12 and
+// 24 registers of accumulators), not five (60; 31 spills instead of 4). 3000 x 200 points, 100 frequencies, 3 and 8 channels, ahead and on the spot,
+// us: two 248 and 251, 263 and 266, three 358 and 363, 381 and 385, five 952 and 822, 1059 and 928.
 __host__ __device__ constexpr bool solo_reads_ahead(int M, int D) { return (D / 2 + 64) / 64 * M * (M + 1) < 40; }
 constexpr int kSoloChannels = 8;
 constexpr int kRawBufferWord3 = 0x00020000;   // buffer descriptor, last word: untyped 32-bit data

@@ -2,7 +2,7 @@
 // transform; Sec. 3.5, eqs. (cs), (ts_def), (ts_rec) with p = 1).
 //
 // Work decomposition (one workgroup per sequence, M wavefronts, wavefront m owns level m; a transform always
-// lives in one wavefront: 16 points per lane up to D = 1024, 32 for D = 2048):
+// lives in one wavefront: 16 points per lane up to D = 1024, 32 for D = 2048, 20 for 100, 200, 500 and 1000):
 //   per iteration every wavefront handles FPW pairs of consecutive time steps of its level:
 //     1. CountSketch as a gather. The signed increments of the 2*FPW time steps arrive in LDS in
 //        their natural order (step 2k -> real part, step 2k+1 -> imaginary part of the float2 of
@@ -18,9 +18,9 @@
 //        ds_add_f32 costs ~190 cycles on this chip), no clearing, and the summation order is
 //        fixed, so results are bit-reproducible.
 //     2. FPW complex FFTs of length D held in the wavefront's LDS slots, G = D/R lanes per
-//        transform with R = 16 points per lane in registers (Stockham passes, radix up to 16 in
-//        registers, one LDS exchange per pass; no workgroup barrier inside the transform unless it
-//        spans two wavefronts),
+//        transform with R points per lane in registers (passes of butterflies in registers with an LDS exchange
+//        between them, which the middle pass of 512 to 2048 points spares: WaveFft; no workgroup barrier
+//        inside the transform),
 //   then, after one barrier, every thread owns a few frequency bins, separates the two real
 //   transforms of each slot, and advances the accumulators A_1..A_M of its bins by the two
 //   time steps (A_m += A_{m-1}(before the step) * C_m, A_0 = 1; with signature order 2 also
@@ -75,11 +75,10 @@ struct Plan {
             case 7: return p == 0 ? 16 : 8;
             case 8: return 16;
             case 9: return p == 1 ? 2 : 16;
-            // three passes: the small radix goes in the middle, where all of a lane's butterflies
-            // share their twiddles (Ns divides G), which keeps the twiddle registers few. D = 512 takes
-            // 16 points per lane and a radix-2 middle pass rather than 32 points per lane and two passes:
-            // half the registers and half the LDS per workgroup doubles the resident workgroups, which
-            // outweighs the extra LDS exchange (measured: 20 % faster)
+            // three passes: the small radix goes in the middle, where its inputs lie in as many rows of lanes and meet
+            // without an exchange (kRowed). D = 512 takes 16 points per lane and a radix-2 middle pass rather than 32 points
+            // per lane and two passes: half the registers and half the LDS per workgroup doubles the resident
+            // workgroups (20 % faster even when the middle pass had an exchange of its own)
             case 10: return p == 1 ? 4 : 16;
             default: return p == 1 ? 8 : 16;    // 11 (32 points per lane)
         }
@@ -89,7 +88,8 @@ struct Plan {
     // the same for every u when Ns divides G
     static constexpr int tw_sets(int p) { return G % Ns(p) == 0 ? 1 : R / radix(p); }
     // The twiddles of a radix-16 pass (8 per set) would cost 16 registers per set; they live in an
-    // LDS table shared by the workgroup instead. Smaller passes keep theirs in registers.
+    // LDS table shared by the workgroup instead. Smaller last passes (64 and 128 points) keep theirs in registers; those of
+    // the middle pass differ from butterfly to butterfly and row to row and follow in the table (kMidTwiddles).
     static constexpr bool tw_in_lds(int p) { return p > 0 && radix(p) >= 16; }
     static constexpr int tw_regs(int p) { return (p == 0 || tw_in_lds(p) || kRowed) ? 0 : tw_sets(p) * twiddles(radix(p)); }
     static constexpr int tw_lds(int p) { return tw_in_lds(p) ? tw_sets(p) * twiddles(radix(p)) * G : 0; }   // float2 entries
@@ -619,7 +619,8 @@ struct WaveFft {
             fill_table<1>(twl_table);
         }
         __syncthreads();
-        if constexpr (!P::kTwoPass) init_pass<0>(lg, roots);
+        if constexpr (P::kRowed) init_pass<P::NP - 1>(lg, roots);        // (where the last pass writes)
+        else if constexpr (!P::kTwoPass) init_pass<0>(lg, roots);
         if constexpr (kRoots) __syncthreads();
     }
 
@@ -650,7 +651,7 @@ struct WaveFft {
                 const int k = j % Ns;
                 wbase[P::wb_off(PI) + u] = P::pad((j - k) * r + k);
             }
-            if constexpr (PI > 0 && !P::tw_in_lds(PI) && !P::kRowed) {
+            if constexpr (PI > 0 && !P::tw_in_lds(PI)) {
                 constexpr int NSETS = P::tw_sets(PI);
 #pragma unroll
                 for (int u = 0; u < NSETS; ++u) {
@@ -689,7 +690,8 @@ struct WaveFft {
         else run_pass<0, AHEAD>(slot, v);
     }
     // 100, 200 and 500 points. Result t of lane l lies at G t + l in between, which the lanes write next to each other and read G apart: 25 and
-    // 5 share no factor with the number of banks.
+    // 5 share no factor with the number of banks, 10 shares two, and the ten lanes of such a transform (200 points) still fall on ten different
+    // ones.
     template <bool AHEAD>
     __device__ __forceinline__ void run_two(float2 *slot, float2 (&v)[P::R]) const
     {
@@ -830,13 +832,15 @@ struct WaveFft {
 // of the same footprint, ~116 registers and 51 KB: 1.7 workgroups = 8.6 wavefronts per CU for 5 wavefronts per
 // workgroup, 15.6 wavefronts for 4 or 8 per workgroup: the dispatcher reserves registers for
 // ceil(wavefronts / 4) wavefronts on every SIMD). For D = 1024 those level counts therefore run 8 wavefronts
-// that take the (pair, level) transforms of the sequence in order, 8 at a time, whatever level they belong to.
-// (Measured against one wavefront per level at 100 steps: D = 1024 +10 % with 5 levels, +23 % with 6, -9 to -15 %
-// with 7; D = 512 +-1 %; D <= 256, where a wavefront carries four or more transforms, 35-60 % slower.) The
+// that take the (pair, level) transforms of the sequence in order, 8 at a time, whatever level they belong to. The
 // same helps where one wavefront per level gives a CU too few wavefronts for other reasons: D = 1024 and 1000
-// with up to three levels (+3-7 %; four levels: +-1 %), and D = 2048, whose slots let one workgroup per CU
-// be resident whatever its size (up to seven levels: +10-20 %, one level +15 %, two +-0). D = 500 with 5 or 6
-// levels gains 4 to 16 and 0 to 10 %, D = 512 with 5 levels 4 to 20 % (with 6: none), order 1; D = 256 loses 40 %.
+// with up to three levels, and D = 2048, whose slots let one workgroup per CU be resident whatever its size.
+// (Features, order 1, how much longer a wavefront per level takes, 1500 x 333 and 400 x 100 points: D = 1024 25 and 7 % with 5 levels, 18
+// and 4 with 6, with 1 to 3 -2 and 24, -1 and 51, 10 and 20, with 4 -2 and 9, with 7 3 and -9; D = 1000 16 and 9 with 5, 26 and 3 with 6, 3 and
+// 16, 28 and 54, 6 and 21 with 1 to 3; D = 500 16 and 4 with 5, 10 and -2 with 6; D = 512 20 and 4 with 5. D = 2048, 600 x 200 points, 0, -4, 18, 6, 16,
+// 11 and 5 with 1 to 7. Below 256 points, where a wavefront carries four or more transforms, dealt items lose: D = 200 2.2 to 3.0 times as
+// long, D = 256 40 %. Left with a wavefront per level though dealt items are ahead at places: D = 512 with 6 levels, 9 and -1, and
+// D = 500 with 3, 4 and 23, 3000 x 60 -3.)
 __host__ __device__ constexpr int transforms_in_flight(int M, int LOG2D) {
     return ((LOG2D == 10 || LOG2D == 1000) && (M <= 3 || M == 5 || M == 6)) || (LOG2D == 2048 && M <= 7) ||
                    (LOG2D == 500 && (M == 5 || M == 6)) || (LOG2D == 9 && M == 5)
