@@ -61,11 +61,12 @@ constexpr int kRowsPerTile = 32;
 // four rows at a time so that stores are spread between the arithmetic. The row above a block comes
 // from the partner half-wavefront (its block q for the upper half, q-1 for the lower half) or, for
 // the first block of the lower half, from the previous tile (carry).
-// Row layout (PAIRED = false): increment k = phi(row k+1) - phi(row k) is stored at row k, scalar base +
-// 32-bit lane offset, one predicate per row. `last`: bit r is set if row k of tile row r is a sequence's last point, whose increment
-// into the next sequence is left out; the rows behind it then move up. GAPS: there is one. (Tiles of long sequences have none, and the few
-// workgroups of small batches wait for every instruction: 32 x 130 points, 237 frequencies 81 -> 87 us with the places counted in every tile.)
-template <bool GAPS, typename AngleOf>
+// Row layout (PAIRED = false): increment k = phi(row k+1) - phi(row k) is stored at row k, scalar base + 32-bit lane offset, one
+// predicate per row. GAPS: bit r of `last` is set if row k of tile row r is a sequence's last point, whose increment into the next
+// sequence is left out; the rows behind it then move up. HELD: without a gap the places of all rows are the same in every tile and
+// may stay in registers, where those leave room (RFSF-TRP's features, 10 x 20000 points, 500 frequencies, 18 and 32 channels 3752 and 3692 us,
+// counted up in every tile 3840 and 3740; 64 channels 186 registers and 114, 200-point sequences, 640 to 1000 workgroups 0.97 of the time).
+template <bool GAPS, bool HELD, typename AngleOf>
 __device__ __forceinline__ void sincos_difference_store(
     AngleOf angle, const ScaledCoeffs &coeffs, float &carry_c, float &carry_s, int half, bool f_ok, int nrow,
     int64_t gt, int64_t g0, int64_t rf, int F, float *__restrict__ dphi, int cos_at, int64_t row0, uint32_t last)
@@ -76,9 +77,10 @@ __device__ __forceinline__ void sincos_difference_store(
     float *cos_base = dphi + row0 * rf;                   // uniform (gt = 0: row -1 is never stored)
     float *sin_base = cos_base + F;
     const uint32_t lane_off = (uint32_t)cos_at + (uint32_t)(4 * half) * (uint32_t)rf;
-    // GAPS: this half's rows (bits 8 q + i) without an increment, and where the next one goes
+    // GAPS: this half's rows (bits 8 q + i) without an increment; where the next increment goes
     const uint32_t mine = GAPS ? last >> (4 * half) : 0;
-    uint32_t place = GAPS ? lane_off - (half ? (uint32_t)__popc(last & 15u) * (uint32_t)rf : 0u) : 0;
+    uint32_t place = GAPS ? lane_off - (half ? (uint32_t)__popc(last & 15u) * (uint32_t)rf : 0u) : lane_off;
+    if (!GAPS && !HELD) asm volatile("" : "+v"(place));
     const int first = gt > g0 ? 0 : 1;                          // first tile row whose increment is ours
     float below_c = carry_c, below_s = carry_s;                 // lower half: partner's previous block
 #pragma unroll
@@ -96,31 +98,30 @@ __device__ __forceinline__ void sincos_difference_store(
             const float ds = sn[i] - (i ? sn[i - 1] : up_s);
             const int r = 8 * q + 4 * half + i;
             const uint32_t gap = GAPS ? (uint32_t)__builtin_amdgcn_sbfe((int)mine, 8 * q + i, 1) : 0u;      // all bits, or none
-            const uint32_t off = GAPS ? place : lane_off + (uint32_t)(8 * q + i) * (uint32_t)rf;
-            if (GAPS) place += (uint32_t)rf & ~gap;
+            const uint32_t off = place;
+            place += GAPS ? (uint32_t)rf & ~gap : (uint32_t)rf;
             if (f_ok && r >= first && r < nrow && !gap) {
                 cos_base[off] = dc;
                 sin_base[off] = ds;
             }
         }
-        if (GAPS) place += (4u - (uint32_t)__popc(mine >> (8 * q + 4) & 15u)) * (uint32_t)rf;      // the other half's rows
+        place += (GAPS ? 4u - (uint32_t)__popc(mine >> (8 * q + 4) & 15u) : 4u) * (uint32_t)rf;      // the other half's rows
     }
     carry_c = below_c;      // row 31 of this tile as seen by the lower half (unused by the upper half)
     carry_s = below_s;
 }
 
-// Where the increment of the first row of the tile at row gt goes in the row layout, and the tile's rows without one (`last` above).
-// last_rows: 0 (rows are kept), or a bit at every multiple of L below 32.
+// Where the increment of the first row of the tile at row gt goes where rows close up, and the tile's rows without one (`last` above).
+// last_rows: a bit at every multiple of L below 32.
 __device__ __forceinline__ int64_t tile_place(int64_t gt, int64_t L, uint32_t last_rows, uint32_t &last)
 {
-    last = 0;
     const int64_t k = gt - 1;
-    if (!last_rows || k < 0) {
-        if (last_rows && L < 32) last = last_rows << L;               // row -1, then the L rows of the first sequence
+    if (k < 0) {
+        last = L < 32 ? last_rows << L : 0;                   // row -1, then the L rows of the first sequence
         return k;
     }
     const uint32_t n = (uint32_t)k / (uint32_t)L, to_last = (uint32_t)L - 1u - ((uint32_t)k - n * (uint32_t)L);    // (the host has checked the rows)
-    if (to_last < 32) last = last_rows << to_last;
+    last = to_last < 32 ? last_rows << to_last : 0;
     return k - n;
 }
 
@@ -340,7 +341,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 // frequency vector (sin(-x) = -sin x, cos(-x) = cos x), flipping the cosine alone is both.
 // With a table job (pair layout, first launch of a call) the first M workgroups build the sketch tables instead: the
 // projection does not need them, and the launch and the two cross-stream waits that a build beside it costs are saved.
-template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 2) padded: channels 2*KSTEPS
+template <int KSTEPS, bool PAIRED, bool STREAM, bool COMPACT>     // ceil(d / 2) padded: channels 2*KSTEPS
 __global__ __launch_bounds__(256) void rff_increments_mfma(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
@@ -436,13 +437,14 @@ __global__ __launch_bounds__(256) void rff_increments_mfma(
             sincos_difference_store_pairs<STREAM>([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, gt, g0,
                                           min(g0 + rows_per_block - 2, rows - 2), 2 * rf, dphi, column);
         else {
-            uint32_t last;
-            const int64_t row0 = tile_place(gt, L, last_rows, last);
+            uint32_t last = 0;
+            const int64_t row0 = COMPACT ? tile_place(gt, L, last_rows, last) : gt - 1;
+            constexpr bool kFewChannels = KSTEPS <= 4;
             const auto store = [&](auto gaps_tag) {
-                sincos_difference_store<decltype(gaps_tag)::value>([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half, f_ok, nrow, gt, g0,
-                                    rf, F, dphi, m * 2 * F + f, row0, last);
+                sincos_difference_store<decltype(gaps_tag)::value, KSTEPS <= 16>([&](int v) { return acc[v]; }, coeffs, carry_c, carry_s, half,
+                                                                                 f_ok, nrow, gt, g0, rf, F, dphi, m * 2 * F + f, row0, last);
             };
-            if (last) store(std::true_type{});
+            if (COMPACT && (!kFewChannels || last)) store(std::bool_constant<COMPACT>{});
             else store(std::false_type{});
         }
         if (more) put_tile(xs + (cur ^ 1) * (kRowsPerTile * XS));
@@ -464,7 +466,7 @@ __device__ __forceinline__ float bf16_value(uint32_t b) { return __uint_as_float
 // W is rounded to bf16; X is split into two bf16 terms, hi = bf16(x) and lo = bf16(x - hi),
 // and both are multiplied with the same W, so that the time difference of the angles does not
 // inherit the 2^-9 rounding of x itself. Same tiling and epilogue as the fp32 kernel.
-template <int KSTEPS, bool PAIRED, bool STREAM>     // ceil(d / 16): channels padded to 16*KSTEPS; PAIRED as in the fp32 kernel
+template <int KSTEPS, bool PAIRED, bool STREAM, bool COMPACT>     // ceil(d / 16): channels padded to 16*KSTEPS; PAIRED as in the fp32 kernel
 __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
     const float *__restrict__ X, const float *__restrict__ W, const float *__restrict__ sign, float inv_lengthscale,
     float scale, int64_t rows, int64_t L, int64_t Lp, int d, int M, int F, int64_t rows_per_block,
@@ -572,13 +574,14 @@ __global__ __launch_bounds__(256) void rff_increments_mfma_bf16(
                                           half, f_ok, gt, g0, min(g0 + rows_per_block - 2, rows - 2), 2 * rf,
                                           dphi, column);
         else {
-            uint32_t last;
-            const int64_t row0 = tile_place(gt, L, last_rows, last);
+            uint32_t last = 0;
+            const int64_t row0 = COMPACT ? tile_place(gt, L, last_rows, last) : gt - 1;
+            constexpr bool kFewChannels = KSTEPS <= 1;
             const auto store = [&](auto gaps_tag) {
-                sincos_difference_store<decltype(gaps_tag)::value>([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s, half,
-                                    f_ok, nrow, gt, g0, rf, F, dphi, m * 2 * F + f, row0, last);
+                sincos_difference_store<decltype(gaps_tag)::value, kFewChannels>([&](int v) { return acc[v] * inv_lengthscale; }, coeffs, carry_c, carry_s, half,
+                                                                                 f_ok, nrow, gt, g0, rf, F, dphi, m * 2 * F + f, row0, last);
             };
-            if (last) store(std::true_type{});
+            if (COMPACT && (!kFewChannels || last)) store(std::bool_constant<COMPACT>{});
             else store(std::false_type{});
         }
         if (more) put_tile(cur ^ 1);
@@ -623,9 +626,12 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     // eight, except that 126 increments measured 7 % faster on 10000 x 200 x 17 -- and 11 % slower on
     // 2000 x 2000 x 32 and 50000 x 64 x 64).
     const int64_t slabs = ((int64_t)M * F + 127) / 128;
-    // Row layout: ranges of one (two) tiles where eight would give fewer than 512 (2048) workgroups (RFSF-TRP's features, 200 projections, and
-    // 197 in the third: 32 x 130 points, 237 frequencies 81 -> 75 us, 1 x 768, 328, 65 -> 50, 875 x 5, 57, 58 -> 46; 7494 x 8, 200, 1888
-    // workgroups of eight tiles, with Gram 712 -> 683).
+    // Row layout: one, two or four tiles while eight would leave too few workgroups; a range costs its columns of W again, more with many channels.
+    // (RFSF-TRP's features, sequences of 20 points, 32 projections, 1140 frequencies of all levels, with one, two, four and eight tiles, by the workgroups
+    // of eight, relative to the best: 2 channels 24 workgroups 1.00, 1.10, 1.28, 1.65, 96 1.04, 1.00, 1.07, 1.28, 256 1.13, 1.09, 1.00, 1.11, 640 1.00,
+    // 1.01, 1.02, 1.05; 64 channels 24 1.00, 1.12, 1.35, 1.81, 96 1.15, 1.00, 1.07, 1.33, 256 1.29, 1.17, 1.00, 1.11, 384 1.26, 1.12, 1.02, 1.00, 1000
+    // 1.34, 1.13, 1.00, 1.00, 3000 1.33, 1.17, 1.04, 1.00; 32 channels 480 1.13, 1.03, 1.00, 1.03, 7494 x 8 points, 2 channels, 200 frequencies and
+    // projections, 1888 workgroups 420, 416, 416, 422 us.)
     int64_t rows_per_block = paired ? 254 : 255;
     if (paired) {
         const int64_t wgs = ((rows - 2) / 254 + 1) * slabs;
@@ -633,8 +639,12 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
         else if (wgs < 4096) rows_per_block = 126;
     } else if (matrix_cores) {
         const int64_t wgs = ((rows - 2) / 255 + 1) * slabs;
-        if (wgs < 512) rows_per_block = 31;
-        else if (wgs < 2048) rows_per_block = 63;
+        const bool few_channels = d <= (bf16 ? 16 : 8), many_channels = d > (bf16 ? 64 : 32);
+        const int64_t load = many_channels ? wgs + wgs / 2 : wgs;
+        if (load < 90) rows_per_block = 31;
+        else if (load < 220) rows_per_block = 63;
+        else if (load < 387) rows_per_block = 127;
+        else if (few_channels && wgs < 2048) rows_per_block = 63;
     }
     const int64_t nblk = paired ? (rows - 2) / rows_per_block + 1 : (rows - 1 + rows_per_block - 1) / rows_per_block;
     const float scale = 0.5f / sqrtf((float)F);    // the consumer's two-for-one FFT wants halved increments
@@ -642,14 +652,15 @@ hipError_t launch_rff_increments(const float *X, const float *W, const float *si
     if (blocks > 0x7fffffffLL) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
     const bool whole_lines = F % 8 == 0;           // 16 bytes per frequency and pair of steps
-#define RFSF_LAUNCH(KERNEL, KS, PAIRED, STREAM, TILE)                                                                \
-    hipLaunchKernelGGL((KERNEL<KS, PAIRED, STREAM>), grid, dim3(256), job.table && table_lds > (TILE) ? table_lds : (TILE), \
+#define RFSF_LAUNCH(KERNEL, KS, PAIRED, STREAM, COMPACT, TILE)                                                       \
+    hipLaunchKernelGGL((KERNEL<KS, PAIRED, STREAM, COMPACT>), grid, dim3(256), job.table && table_lds > (TILE) ? table_lds : (TILE), \
                        stream, X, W, sign, inv_lengthscale, scale, rows, L, Lp, d, M, F, rows_per_block, dphi, lengths, last_rows, job)
 #define RFSF_LAUNCH_MFMA(KERNEL, KS, TILE)                                                                           \
     do {                                                                                                         \
-        if (!paired) RFSF_LAUNCH(KERNEL, KS, false, false, TILE);                                                \
-        else if (whole_lines) RFSF_LAUNCH(KERNEL, KS, true, true, TILE);                                         \
-        else RFSF_LAUNCH(KERNEL, KS, true, false, TILE);                                                         \
+        if (compact) RFSF_LAUNCH(KERNEL, KS, false, false, true, TILE);                                          \
+        else if (!paired) RFSF_LAUNCH(KERNEL, KS, false, false, false, TILE);                                    \
+        else if (whole_lines) RFSF_LAUNCH(KERNEL, KS, true, true, false, TILE);                                  \
+        else RFSF_LAUNCH(KERNEL, KS, true, false, false, TILE);                                                  \
     } while (0)
 #define RFSF_LAUNCH_FP32(KS) RFSF_LAUNCH_MFMA(rff_increments_mfma, KS, sizeof(float) * 2 * kRowsPerTile * ((2 * KS) | 1))
 #define RFSF_LAUNCH_BF16(KS) RFSF_LAUNCH_MFMA(rff_increments_mfma_bf16, KS, sizeof(uint16_t) * 4 * kRowsPerTile * (16 * KS + 8))

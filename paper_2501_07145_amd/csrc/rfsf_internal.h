@@ -137,9 +137,9 @@ hipError_t launch_gram(const float *PhiX, int64_t Nx, int64_t ldx, const float *
 hipError_t launch_dp1d(const float *X, const float *W, const float *bias, float scale_turns, int64_t N,
                        int64_t L, int d, int M, int F, float *out, int64_t ld_out, hipStream_t stream);
 
-// RFSF-TRP second stage: recurrence over time on the projected increments P[n_seq*L][M][Q], which it may overwrite, of n_seq
-// sequences of a batch of N; M <= 16.
-hipError_t launch_trp_scan(float *P, int64_t N, int64_t n_seq, int64_t L, int M, int Q, float *out, int64_t ld_out,
+// RFSF-TRP second stage: recurrence over time on the projected increments P[n_seq*rows][M][Q], which it may overwrite, of n_seq
+// sequences of a batch of N, the first L - 1 of a sequence's rows (L - 1 or L); M <= 16.
+hipError_t launch_trp_scan(float *P, int64_t N, int64_t n_seq, int64_t L, int64_t rows, int M, int Q, float *out, int64_t ld_out,
                            hipStream_t stream);
 
 hipError_t launch_normalize(float *Phi, int64_t N, int64_t ld, int M, int D, hipStream_t stream);

@@ -625,6 +625,11 @@ void trp_per_sequence_bytes(const rfsf_ts_shape *s, size_t *incr, size_t *proj)
     *proj = (size_t)s->L * (size_t)s->M * (size_t)s->D * sizeof(float);
 }
 constexpr size_t kTrpFixed = 3 * kAlign;
+// Sequences of up to this many points leave out the row of their last point, which is no increment: one row in L of the projection, the
+// products and the scan, for counting the places of the rows in the projection; with up to 8 channels (16 as bf16 operands), whose projection leaves
+// room for both ways, all do. (With rows left out and kept, features, us: 7500 x 8 points, 2 channels, 200 frequencies and projections 413 and 464,
+// 2 x 129, 3, 16, 32768 69 and 78, 312 x 64, 18, 228, 400 232 and 233, 200 x 100 244 and 241, 100 x 200 235 and 229.)
+constexpr int64_t kCloseUpPoints = 64;
 // Sequences per launch of the TRP kernels: at most 65535, and 65535 * 64 rows. The kernels count their tiles and threads
 // in grid.x and would take more; the recommended workspace, and what is refused, follow from these numbers.
 int64_t trp_chunk_cap(const rfsf_ts_shape *s)
@@ -685,23 +690,25 @@ extern "C" int rfsf_trp_features(const rfsf_ts_shape *shape, const float *X, con
     const int twoF = 2 * shape->F;
     const int64_t rf = (int64_t)shape->M * twoF, MQ = (int64_t)shape->M * Q;
     const float inv_ls = 1.0f / lengthscale;
+    const bool close_up = shape->L <= kCloseUpPoints || shape->d <= (shape->rff_bf16 != 0 ? 16 : 8);
     for (int64_t n0 = 0; n0 < shape->N; n0 += chunk) {
         const int64_t cnt = shape->N - n0 < chunk ? shape->N - n0 : chunk;
         {
             rfsf::ProfileScope scope(rfsf::kRffIncrements, stream);
             if (rfsf::launch_rff_increments(X + n0 * shape->L * shape->d, W, nullptr, inv_ls, cnt, shape->L, shape->d,
-                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr, nullptr, true) != hipSuccess)
+                                            shape->M, shape->F, shape->rff_bf16 != 0, dphi, stream, nullptr, nullptr, close_up) != hipSuccess)
                 return RFSF_E_HIP;
         }
         {   // P[:, m, :] = dphi[:, m, :] Z_m^T, the levels' products in one launch
             rfsf::ProfileScope scope(rfsf::kTrpProject, stream);
-            if (rfsf::launch_gram(dphi, cnt * (shape->L - 1), rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
-                                  twoF, (int64_t)Q * twoF, Q, cnt * shape->L - 1) != hipSuccess)
+            const int64_t points = cnt * shape->L - 1;       // (the last one has no increment)
+            if (rfsf::launch_gram(dphi, close_up ? points - cnt + 1 : points, rf, Z, Q, twoF, twoF, P, MQ, stream, true, shape->M,
+                                  twoF, (int64_t)Q * twoF, Q, points) != hipSuccess)
                 return RFSF_E_HIP;
         }
         {
             rfsf::ProfileScope scope(rfsf::kTrpScan, stream);
-            if (rfsf::launch_trp_scan(P, shape->N, cnt, shape->L, shape->M, Q, out + n0 * shape->ld_out, shape->ld_out,
+            if (rfsf::launch_trp_scan(P, shape->N, cnt, shape->L, close_up ? shape->L - 1 : shape->L, shape->M, Q, out + n0 * shape->ld_out, shape->ld_out,
                                       stream) != hipSuccess)
                 return RFSF_E_HIP;
         }

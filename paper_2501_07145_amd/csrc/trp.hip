@@ -21,13 +21,13 @@ template <> struct Vec<4> { typedef floatv4 type; };
 __device__ __forceinline__ float lane_of(float v, int) { return v; }
 __device__ __forceinline__ float lane_of(floatv4 v, int i) { return v[i]; }
 
-// P[(n*(L-1) + k)*M*Q + m*Q + q] = Z_m . (delta_m[k] / 2)  (the projection kernel writes halved increments;
+// P[(n*rows + k)*M*Q + m*Q + q] = Z_m . (delta_m[k] / 2)  (the projection kernel writes halved increments;
 // the factor 2 is restored here). A thread owns V consecutive components of one sequence (V = 4: 16-byte
 // loads; the threads of a sequence then read whole rows of P, and consecutive levels and time steps
 // continue the same stream); B time steps are loaded per batch so that B*M loads are in flight per
 // thread. The last, partial batch loads clamped rows and skips their updates.
 template <int kMaxLevels, int B, int V>
-__global__ __launch_bounds__(256) void trp_scan_kernel(const float *__restrict__ P, int64_t n_seq, int64_t L, int M,
+__global__ __launch_bounds__(256) void trp_scan_kernel(const float *__restrict__ P, int64_t n_seq, int64_t L, int64_t rows, int M,
                                                        int Q, float *__restrict__ out, int64_t ld_out, float scale)
 {
     typedef typename Vec<V>::type vec;
@@ -44,7 +44,7 @@ __global__ __launch_bounds__(256) void trp_scan_kernel(const float *__restrict__
 #pragma unroll
         for (int i = 0; i < V; ++i) A[m][i] = 0.f;
     const int64_t T = L - 1, MQ = (int64_t)M * Q;
-    const float *p = P + n * T * MQ + q;
+    const float *p = P + n * rows * MQ + q;
     for (int64_t k = 0; k < T; k += B) {
         vec v[B][kMaxLevels];
 #pragma unroll
@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void trp_scan_kernel(const float *__restrict__
 // runs the recurrence for every first level at once (A^{(a..l)}, all a <= l) and leaves the sums in its own column of
 // the rows it has read: the piece's part of P, seen as [steps * M][Q], takes M(M+1)/2 of them per component.
 template <int M, int B>
-__global__ __launch_bounds__(256) void trp_pieces_kernel(float *P, int64_t n_seq, int64_t L, int Q, int pieces, int64_t steps)
+__global__ __launch_bounds__(256) void trp_pieces_kernel(float *P, int64_t n_seq, int64_t L, int64_t rows, int Q, int pieces, int64_t steps)
 {
     constexpr int NA = M * (M + 1) / 2;
     const int64_t g = (int64_t)blockIdx.x * 256 + threadIdx.x, v = g / Q, n = v / pieces;
@@ -86,7 +86,7 @@ __global__ __launch_bounds__(256) void trp_pieces_kernel(float *P, int64_t n_seq
     const int64_t T = L - 1, k0 = (v - n * pieces) * steps, k1 = min(k0 + steps, T);
     constexpr auto at = [](int a, int l) { return a * M - a * (a - 1) / 2 + l - a; };
     const int64_t MQ = (int64_t)M * Q;
-    float *p = P + n * T * MQ + (g - v * Q);
+    float *p = P + n * rows * MQ + (g - v * Q);
     float A[NA];
 #pragma unroll
     for (int i = 0; i < NA; ++i) A[i] = 0.f;
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(256) void trp_pieces_kernel(float *P, int64_t n_seq
 // The pieces of a sequence from left to right (A^{(1..l)}(xy) = A^{(1..l)}(x) + A^{(1..l)}(y) + sum over j of
 // A^{(1..j)}(x) A^{(j+1..l)}(y)), one thread per component; the numbers of the next kAhead pieces are in flight.
 template <int M>
-__global__ __launch_bounds__(64) void trp_join_kernel(const float *__restrict__ P, int64_t n_seq, int64_t L, int Q, int pieces,
+__global__ __launch_bounds__(64) void trp_join_kernel(const float *__restrict__ P, int64_t n_seq, int64_t rows, int Q, int pieces,
                                                       int64_t steps, float *__restrict__ out, int64_t ld_out, float scale)
 {
     constexpr int NA = M * (M + 1) / 2, kAhead = 4;
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(64) void trp_join_kernel(const float *__restrict__ 
     const int q = (int)(g - n * Q);
     constexpr auto at = [](int a, int l) { return a * M - a * (a - 1) / 2 + l - a; };
     const int64_t MQ = (int64_t)M * Q, stride = steps * MQ;
-    const float *p = P + n * (L - 1) * MQ + q;
+    const float *p = P + n * rows * MQ + q;
     float A[M], B[kAhead][NA];
 #pragma unroll
     for (int m = 0; m < M; ++m) A[m] = p[(int64_t)m * Q];
@@ -178,7 +178,7 @@ TrpCut trp_cut(int64_t N, int64_t L, int M, int Q)
 
 }  // namespace
 
-hipError_t launch_trp_scan(float *P, int64_t N, int64_t n_seq, int64_t L, int M, int Q, float *out, int64_t ld_out,
+hipError_t launch_trp_scan(float *P, int64_t N, int64_t n_seq, int64_t L, int64_t rows, int M, int Q, float *out, int64_t ld_out,
                            hipStream_t stream)
 {
     if (n_seq == 0) return hipSuccess;
@@ -191,8 +191,8 @@ hipError_t launch_trp_scan(float *P, int64_t N, int64_t n_seq, int64_t L, int M,
 #define RFSF_TRP_PIECES_CASE(LEVELS)                                                                          \
     case LEVELS:                                                                                              \
         hipLaunchKernelGGL((trp_pieces_kernel<LEVELS, (64 / LEVELS > 16 ? 16 : 64 / LEVELS)>), dim3((unsigned)piece_blocks), \
-                           dim3(256), 0, stream, P, n_seq, L, Q, cut.pieces, cut.steps);                      \
-        hipLaunchKernelGGL(trp_join_kernel<LEVELS>, dim3((unsigned)join_blocks), dim3(64), 0, stream, P, n_seq, L, Q, \
+                           dim3(256), 0, stream, P, n_seq, L, rows, Q, cut.pieces, cut.steps);                \
+        hipLaunchKernelGGL(trp_join_kernel<LEVELS>, dim3((unsigned)join_blocks), dim3(64), 0, stream, P, n_seq, rows, Q, \
                            cut.pieces, cut.steps, out, ld_out, scale);                                        \
         break
             RFSF_TRP_PIECES_CASE(1);
@@ -214,7 +214,7 @@ hipError_t launch_trp_scan(float *P, int64_t N, int64_t n_seq, int64_t L, int M,
     if (blocks > 2147483647) return hipErrorInvalidValue;
     const dim3 grid((unsigned)blocks);
 #define RFSF_LAUNCH_TRP_SCAN(LEVELS, STEPS, WIDTH)                                                            \
-    hipLaunchKernelGGL((trp_scan_kernel<LEVELS, STEPS, WIDTH>), grid, dim3(256), 0, stream, P, n_seq, L, M, Q, out,   \
+    hipLaunchKernelGGL((trp_scan_kernel<LEVELS, STEPS, WIDTH>), grid, dim3(256), 0, stream, P, n_seq, L, rows, M, Q, out,   \
                        ld_out, scale)
     // up to eight levels have kernels of their own (no loads for levels that do not exist); the batch length
     // keeps about 24 loads of 16 bytes, or 64 of 4 bytes, in flight per thread

@@ -1,5 +1,5 @@
 """RFSF-TRP keeps one row per increment: rows of increments close up behind a sequence's last point. Sequences of every length around
-the 32 rows of a tile and the 31, 63 and 255 increments of a workgroup's range, in all three projection kernels."""
+the 32 rows of a tile and the 31, 63, 127 and 255 increments of a workgroup's range, in all three projection kernels."""
 import math
 
 import numpy as np
@@ -31,10 +31,11 @@ def test_rows_close_up_behind_every_sequence(oracle, L, d, bf16):
 
 
 @pytest.mark.parametrize("L", [2, 3, 5, 31, 32, 33, 34, 62, 63, 64, 65, 254, 255, 256, 257])
-@pytest.mark.parametrize("rows", [9 * 255, 33 * 255])
+@pytest.mark.parametrize("rows", [2 * 255, 5 * 255, 9 * 255, 33 * 255])
 @pytest.mark.parametrize("bf16", [False, True])
 def test_ranges_of_several_tiles_on_the_matrix_units(oracle, L, rows, bf16):
-    """63 slabs of 128 frequencies: from 9 ranges of 255 increments on (512 workgroups) ranges have 63, two tiles, from 33 on (2048) 255, eight.
+    """63 slabs of 128 frequencies: 2 ranges of 255 increments (126 to 189 workgroups) are taken 63 at a time, two tiles, 5 (315, 378) 127, 9 (567,
+    630) 63 again and 33 (2079 and more) as they are, eight tiles.
     A row out of its place would move those of all later sequences; some are compared, in the middle and at the end."""
     M, d, F, Q = 4, 3, 2000, 8
     N = rows // L + 1
@@ -66,3 +67,21 @@ def test_short_sequences_on_both_sides_of_the_kinds_of_tiles(oracle, N, L, Q):
     levels = min(M, L - 1)                                   # (no more steps than levels: blocks of zeros)
     assert np.all(block_errors(got, want, M, Q)[:levels] <= FP32_BLOCK_TOL)
     assert not np.any(got[:, 1 + levels * Q:])
+
+
+@pytest.mark.parametrize("L", [64, 65])
+@pytest.mark.parametrize("d,bf16", [(8, False), (9, False), (40, False), (66, False), (16, True), (100, True)])
+def test_rows_are_kept_from_65_points_and_9_channels_on(oracle, L, d, bf16):
+    """Whole sequences, and 3 of 200 and more points in pieces, whose sums take the place of their rows."""
+    M, F, Q = 5, 30, 36
+    rng = np.random.default_rng(L + d)
+    for N, points in ((150, L), (3, 3 * L + 8)):
+        X = np.cumsum(rng.standard_normal((N, points, d)) / math.sqrt(points), axis=1).astype(np.float32)
+        W = rng.standard_normal((M, d, F)).astype(np.float32)
+        if bf16:
+            X = (np.round(X * 64) / 64).astype(np.float32)
+            W = (np.round(W * 16) / 16).astype(np.float32)
+        Z = rng.standard_normal((M, Q, 2 * F)).astype(np.float32)
+        got = rfsf.rfsf_trp_features(*(torch.from_numpy(a).cuda() for a in (X, W, Z)), math.sqrt(d), rff_bf16=bf16).cpu().numpy()
+        want = oracle.trp_features(X, W, Z, math.sqrt(d))
+        assert np.all(block_errors(got, want, M, Q) <= FP32_BLOCK_TOL)
