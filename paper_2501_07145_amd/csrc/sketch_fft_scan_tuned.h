@@ -49,7 +49,7 @@ __host__ __device__ constexpr int pad(int e) { return e + (e >> 4); }
 // Twiddles of a butterfly of r points behind the first pass (twiddle_entry).
 __host__ __device__ constexpr int twiddles(int r) { return (r & (r - 1)) == 0 ? r / 2 : r - 1; }
 
-template <int LOG2D_, int LOG2R_ = 4>
+template <int LOG2D_, int LOG2R_ = 4, bool ROWED = (LOG2D_ >= 9 && LOG2D_ <= 11)>
 struct Plan {
     static constexpr int LOG2D = LOG2D_;
     static constexpr int D = 1 << LOG2D;
@@ -61,7 +61,7 @@ struct Plan {
     static constexpr int FPW = 64 / G;          // transforms per wavefront
     static constexpr int GF = G;                // entries per fold round
     // Lanes of a transform in rows of 16 (ROWS of them): the middle pass meets in registers (WaveFft::run_rows)
-    static constexpr bool kRowed = LOG2D >= 9 && LOG2D <= 11, kTwoPass = false;
+    static constexpr bool kRowed = ROWED, kTwoPass = false;
     static constexpr int ROWS = G / 16, MID = kRowed ? ROWS * (R / 16) : 1;
     static constexpr int kMidTwiddles = kRowed ? 16 * (MID / 2) : 0;     // float2: 16 / ROWS butterflies of a lane, ROWS rows
     static constexpr int PD = D + D / 16;       // padded transform length in float2
@@ -174,6 +174,12 @@ template <> struct Plan<1000> : ThreePassPlan<1000> {};
 // 2048 points in one wavefront: 32 points per lane (twice the registers, half the resident wavefronts, no barrier
 // inside the transform). Selected as Plan<2048>.
 template <> struct Plan<2048> : Plan<11, 5> {};
+// The plan of a kernel. Sequences cut in time with two levels and 512 points keep the exchange of the middle pass (features, us, rows that meet in
+// registers and exchange: 135 x 2000 points, lengths of their own, 96 frequencies 553 and 539, order 2 582 and 549, 256 752 and 729, 10 x 5000, 96,
+// order 2 114 and 109, 256 141 and 140, 35 x 3000, 256 220 and 223; whole sequences 600 x 100, 96 109 and 103, 3000 x 60, 96 183 and 193, 256 310
+// and 318).
+template <int LOG2D, int M, bool JOINT> struct KernelPlan : Plan<LOG2D> {};
+template <> struct KernelPlan<9, 2, true> : Plan<9, 4, false> {};
 
 // Geometry of one LDS slot (float2 units): [0, ZS) data -- the staging area uses [0, 2F), the transform [0, PD) --,
 // [ZS] a float2 that is always zero (source of buckets without a first or second coordinate). A direct load deposits
@@ -1199,7 +1205,7 @@ __global__ __launch_bounds__(64 * NTR)
     const float *__restrict__ dphi, const uint32_t *__restrict__ table, int64_t L,
     const int64_t *__restrict__ lengths, int F, int Dout, float *__restrict__ out, int64_t ld_out, TimeCut cut)
 {
-    using P = Plan<LOG2D>;
+    using P = KernelPlan<LOG2D, M, JOINT>;
     // kStream: the workgroup's NTR transforms of an iteration are the next NTR (pair group, level) items of the
     // sequence in that order, so a wavefront changes level from iteration to iteration and an iteration
     // may end in the middle of a pair; otherwise transform w of the workgroup is always level w.
