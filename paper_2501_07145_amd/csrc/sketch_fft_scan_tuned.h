@@ -1373,12 +1373,13 @@ __global__ __launch_bounds__(64 * NTR)
     // and the stages of the first pass that would only copy are left out. Features of 1000 x 151 points, projection included, us: 300 buckets in
     // 1024 points, three levels, 190 frequencies 503 -> 490, 150 in 512, four 538 -> 499, 150 in 1024, five 667 -> 632; as many buckets as
     // points 829 and 829, 1366 and 1363.
-    // Sequences cut in time, 512 and 2048 points, four to six levels: without it, whose branch costs kernels that spill up to another 18 registers
-    // (with and without, us, 200 frequencies: 512 points, 100 x 200 points, five levels, order 2 183 and 155, 101 buckets 177 and 169, six 219 and
-    // 202, order 3 310 and 281, 85 buckets 277 and 263; 600 frequencies: 2048 points, 60 x 200, four, order 2 253 and 229, five, order 1 351 and
-    // 294, 400 buckets 401 and 364, six 405 and 320, 300 buckets 463 and 402. But 512 points, three levels, 160 buckets 69.8 and 72.6, eight, 63
-    // 204 and 214; 2048 points, three, 600 buckets 151 and 155, seven, 280 979 and 1038, eight, 240 1103 and 1157.)
-    constexpr bool kSpills = JOINT && M >= 4 && M <= 6 && (LOG2D == 9 || LOG2D == 2048);
+    // Sequences cut in time, 512 points with four to six levels, 2048 with five and six and with four in order 2: without it, whose branch costs
+    // kernels that spill up to another 18 registers (with and without, us, 200 frequencies: 512 points, 100 x 200 points, five levels, order 2 183 and
+    // 155, 101 buckets 177 and 169, six 219 and 202, order 3 310 and 281, 85 buckets 277 and 263; 600 frequencies: 2048 points, 60 x 200, five, order 1
+    // 351 and 294, 400 buckets 401 and 364, six 405 and 320, 300 buckets 463 and 402, four, order 2 253 and 229, 320 buckets 208 and 212. But 512
+    // points, three levels, 160 buckets 69.8 and 72.6, eight, 63 204 and 214; 2048 points, three, 600 buckets 151 and 155, four, order 1 206 and 205,
+    // 320 buckets 285 and 312, order 3 263 and 257, 320 buckets 304 and 316, seven, 280 979 and 1038, eight, 240 1103 and 1157.)
+    constexpr bool kSpills = JOINT && ((LOG2D == 9 && M >= 4 && M <= 6) || (LOG2D == 2048 && (M == 5 || M == 6 || (M == 4 && ORDER == 2))));
     constexpr int kFew = !P::kRowed || M < 2 || kSpills ? 1 : M < 4 ? 2 : 4;
     const int groups = (Dout + P::G - 1) / P::G;
     const bool few = kFew > 1 && groups <= P::R / kFew;
