@@ -85,3 +85,17 @@ def test_rows_are_kept_from_65_points_and_9_channels_on(oracle, L, d, bf16):
         got = rfsf.rfsf_trp_features(*(torch.from_numpy(a).cuda() for a in (X, W, Z)), math.sqrt(d), rff_bf16=bf16).cpu().numpy()
         want = oracle.trp_features(X, W, Z, math.sqrt(d))
         assert np.all(block_errors(got, want, M, Q) <= FP32_BLOCK_TOL)
+
+
+@pytest.mark.parametrize("N,L,d", [(6, 70, 9), (1, 300, 20), (40, 64, 9), (5, 66, 70)])
+def test_rows_that_are_kept_hold_nothing_of_the_workspace(N, L, d):
+    """Steps from one sequence into the next are computed from the points where rows are kept; the batch's last row is in no product."""
+    M, F, Q = 3, 12, 20
+    rng = np.random.default_rng(N + L)
+    X, W, Z = (torch.from_numpy(rng.standard_normal(s).astype(np.float32)).cuda() for s in ((N, L, d), (M, d, F), (M, Q, 2 * F)))
+    ws = torch.zeros(rfsf.rfsf_trp_workspace_bytes(N, L, d, M, F, Q)[0] // 4 * 4, dtype=torch.uint8, device="cuda")
+    want = rfsf.rfsf_trp_features(X, W, Z, math.sqrt(d), workspace=ws).clone()
+    ws.view(torch.float32).fill_(float("inf"))
+    got = rfsf.rfsf_trp_features(X, W, Z, math.sqrt(d), workspace=ws)
+    assert torch.equal(got, want)
+    assert not bool(torch.isnan(ws.view(torch.float32)).any())
