@@ -174,12 +174,28 @@ template <> struct Plan<1000> : ThreePassPlan<1000> {};
 // 2048 points in one wavefront: 32 points per lane (twice the registers, half the resident wavefronts, no barrier
 // inside the transform). Selected as Plan<2048>.
 template <> struct Plan<2048> : Plan<11, 5> {};
-// The plan of a kernel. Sequences cut in time with two levels and 512 points keep the exchange of the middle pass (features, us, rows that meet in
-// registers and exchange: 135 x 2000 points, lengths of their own, 96 frequencies 553 and 539, order 2 582 and 549, 256 752 and 729, 10 x 5000, 96,
-// order 2 114 and 109, 256 141 and 140, 35 x 3000, 256 220 and 223; whole sequences 600 x 100, 96 109 and 103, 3000 x 60, 96 183 and 193, 256 310
-// and 318).
-template <int LOG2D, int M, bool JOINT> struct KernelPlan : Plan<LOG2D> {};
-template <> struct KernelPlan<9, 2, true> : Plan<9, 4, false> {};
+// Kernels that keep the exchange of the middle pass. Rows that meet in registers are faster in most, 0.94 of the time over all lengths, levels and
+// orders, and spill less; but what the compiler makes of them leaves these slower (features, six shapes each, 60 and 250 frequencies: 3 x 400, 30 x
+// 1000 and 100 x 200 points cut in time, 300 x 60, 700 x 40 and 2500 x 30 whole; geometric mean and largest against the exchange): 512 points cut, two
+// levels 1.03, 1.06; 1024 cut, orders 2 and 3, four levels 1.03 and 1.05, 1.12, five 1.06 and 1.04, 1.07, six 1.05 and 1.03, 1.07; 1024 whole, seven,
+// orders 2 and 3 1.03 and 1.05, 1.11; 2048 whole, seven, order 3 1.26, 1.40; 4096, order 3, four and six 1.07 and 1.19, 1.43, order 1, eight
+// 1.07, 1.09. (Left in rows: 1024 cut, three, orders 2 and 3 1.01, 0.96 to 1.12, five, order 1 1.02; 512 whole, two, 1.00, 0.93 to 1.06; 4096, order
+// 3, five 1.02, 0.96 to 1.17.)
+constexpr bool exchanges(int LOG2D, int M, int ORDER, bool JOINT)
+{
+    switch (LOG2D) {
+        case 9: return JOINT && M == 2;
+        case 10: return ORDER > 1 && (JOINT ? M >= 4 && M <= 6 : M == 7);
+        case 2048: return !JOINT && M == 7 && ORDER == 3;
+        case 12: return ORDER == 3 ? M == 4 || M == 6 : ORDER == 1 && M == 8;
+        default: return false;
+    }
+}
+template <int LOG2D, bool EXCHANGES> struct PlanBy : Plan<LOG2D> {};
+template <> struct PlanBy<9, true> : Plan<9, 4, false> {};
+template <> struct PlanBy<10, true> : Plan<10, 4, false> {};
+template <> struct PlanBy<2048, true> : Plan<11, 5, false> {};
+template <int LOG2D, int M, int ORDER, bool JOINT> using KernelPlan = PlanBy<LOG2D, exchanges(LOG2D, M, ORDER, JOINT)>;
 
 // Geometry of one LDS slot (float2 units): [0, ZS) data -- the staging area uses [0, 2F), the transform [0, PD) --,
 // [ZS] a float2 that is always zero (source of buckets without a first or second coordinate). A direct load deposits
@@ -693,7 +709,7 @@ struct WaveFft {
     {
         if constexpr (P::kRowed) run_rows<FEW>(slot, v, few);
         else if constexpr (P::kTwoPass) run_two<AHEAD>(slot, v);
-        else run_pass<0, AHEAD>(slot, v);
+        else run_pass<0, AHEAD, FEW>(slot, v, few);
     }
     // 100, 200 and 500 points. Result t of lane l lies at G t + l in between, which the lanes write next to each other and read G apart: 25 and
     // 5 share no factor with the number of banks, 10 shares two, and the ten lanes of such a transform (200 points) still fall on ten different
@@ -795,8 +811,8 @@ struct WaveFft {
         transform_fence<P>();
     }
 
-    template <int PI, bool AHEAD = true>
-    __device__ __forceinline__ void run_pass(float2 *slot, float2 (&v)[P::R]) const
+    template <int PI, bool AHEAD = true, int FEW = 1>
+    __device__ __forceinline__ void run_pass(float2 *slot, float2 (&v)[P::R], [[maybe_unused]] bool few = false) const
     {
         if constexpr (PI < P::NP) {
             constexpr int r = P::radix(PI), Ns = P::Ns(PI), NB = P::R / r;
@@ -807,7 +823,8 @@ struct WaveFft {
 #pragma unroll
                 for (int t = 0; t < r; ++t) x[t] = v[u + t * NB];
                 if constexpr (PI == 0) {
-                    dft_plain(x);
+                    if (FEW > 1 && few) dft_plain<FEW>(x);
+                    else dft_plain(x);
                 } else {
                     constexpr int TW = twiddles(r), set = P::tw_sets(PI) == 1 ? 0 : 1;    // multiplier of u below
                     dft<AHEAD>(x, [&](int e) {
@@ -1205,7 +1222,7 @@ __global__ __launch_bounds__(64 * NTR)
     const float *__restrict__ dphi, const uint32_t *__restrict__ table, int64_t L,
     const int64_t *__restrict__ lengths, int F, int Dout, float *__restrict__ out, int64_t ld_out, TimeCut cut)
 {
-    using P = KernelPlan<LOG2D, M, JOINT>;
+    using P = KernelPlan<LOG2D, M, ORDER, JOINT>;
     // kStream: the workgroup's NTR transforms of an iteration are the next NTR (pair group, level) items of the
     // sequence in that order, so a wavefront changes level from iteration to iteration and an iteration
     // may end in the middle of a pair; otherwise transform w of the workgroup is always level w.
@@ -1380,7 +1397,8 @@ __global__ __launch_bounds__(64 * NTR)
     // points, three levels, 160 buckets 69.8 and 72.6, eight, 63 204 and 214; 2048 points, three, 600 buckets 151 and 155, four, order 1 206 and 205,
     // 320 buckets 285 and 312, order 3 263 and 257, 320 buckets 304 and 316, seven, 280 979 and 1038, eight, 240 1103 and 1157.)
     constexpr bool kSpills = JOINT && ((LOG2D == 9 && M >= 4 && M <= 6) || (LOG2D == 2048 && (M == 5 || M == 6 || (M == 4 && ORDER == 2))));
-    constexpr int kFew = !P::kRowed || M < 2 || kSpills ? 1 : M < 4 ? 2 : 4;
+    constexpr bool kRows = P::kRowed || exchanges(LOG2D, M, ORDER, JOINT);       // 512 to 2048 points
+    constexpr int kFew = !kRows || M < 2 || kSpills ? 1 : M < 4 ? 2 : 4;
     const int groups = (Dout + P::G - 1) / P::G;
     const bool few = kFew > 1 && groups <= P::R / kFew;
 

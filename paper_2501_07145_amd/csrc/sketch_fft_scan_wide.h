@@ -43,7 +43,7 @@ __global__ __launch_bounds__(64 * (1 << LOG2S) * NTR) __attribute__((amdgpu_wave
     const float *__restrict__ dphi, const uint32_t *__restrict__ table, int64_t L,
     const int64_t *__restrict__ lengths, int F, int Dout, float *__restrict__ out, int64_t ld_out, TimeCut cut)
 {
-    using P = Plan<10>;                                     // the transform each wavefront runs
+    using P = PlanBy<10, exchanges(10 + LOG2S, M, ORDER, false)>;      // the transform each wavefront runs
     constexpr int S = 1 << LOG2S, DH = 1024, DF = S * DH, NT = 64 * S * NTR;
     constexpr bool kStream = NTR != M;
     constexpr int BPT = (DF / 2) / NT;                      // bins per thread; thread 0 also carries bin DF/2 (packed)

@@ -17,6 +17,8 @@ pytestmark = pytest.mark.gpu
     (5, 40, 103, 1), (5, 40, 205, 1), (5, 40, 410, 2),
     (8, 40, 64 + 1, 1), (8, 200, 128 - 1, 1),
     (4, 1000, 64, 1), (4, 2000, 256, 1), (5, 2000, 512, 1),          # powers of two in longer transforms
+    (7, 40, 146, 2), (7, 40, 146, 3), (7, 40, 292, 3),               # whole sequences whose middle pass has an exchange
+    (4, 40, 1023, 3), (6, 40, 682, 3), (8, 40, 511, 1),              # ... and 4096 points
 ])
 @pytest.mark.parametrize("L", [4, 23])
 def test_empty_groups_of_buckets_are_left_out(oracle, M, F, D, order, L):
@@ -36,6 +38,7 @@ def test_empty_groups_of_buckets_are_left_out(oracle, M, F, D, order, L):
 @pytest.mark.parametrize("M,F,D,order", [
     (2, 60, 255, 2), (3, 60, 171, 1), (4, 60, 127, 2), (5, 60, 103, 1), (6, 60, 85, 3), (7, 60, 74, 2), (8, 60, 63, 1),      # 512 points
     (3, 200, 683, 2), (4, 200, 511, 1), (5, 200, 410, 2), (6, 200, 341, 3), (7, 200, 292, 1),                                # 2048
+    (4, 120, 255, 2), (4, 120, 255, 3), (5, 120, 204, 1), (5, 120, 204, 2), (5, 120, 204, 3), (6, 120, 170, 2), (6, 120, 170, 3),      # 1024
 ])
 def test_sequences_cut_in_time(oracle, M, F, D, order):
     """Pieces of a few sequences, whose kernels leave the empty groups out where that costs them no registers. Increments are 0.14 in size, of which
